@@ -102,12 +102,11 @@ typedef struct ht_peak {
 typedef struct ht_tuning {
   int32_t rows;         /* A rows per fill tile: a power of two <= 64 whose rows x n_b uint32
                            counters fit in 56 KiB of LDS */
-  int32_t group_tiles;  /* tiles per workgroup of the peak search: 16, 32 or 64 */
-  int32_t cand_cap;     /* candidate-pool entries per tile, a power of two <= 4096: the cells
-                           at or above the threshold of all tiles share a pool of at least
-                           n_tiles * cand_cap entries (more for large events: a quarter of the
-                           bound 4 n_hits n_a / threshold, at most the cell count); tiles that
-                           do not fit are searched densely (slower, same results) */
+  int32_t group_tiles;  /* tiles per workgroup of the ordered writer of crowded events: 16, 32
+                           or 64 */
+  int32_t cand_cap;     /* a power of two <= 4096. The peak search keeps no per-tile candidate
+                           list, so this changes no kernel; it is the size that the limit of
+                           ht_fill_peaks_noalloc is stated in */
   int32_t nt_store;     /* store kind of the fill's single write of the matrix: 0 ordinary
                            16-byte stores, 1 non-temporal 16-byte stores, 2 ordinary 4-byte
                            stores */
@@ -116,9 +115,9 @@ typedef struct ht_tuning {
   int32_t dense_hits;   /* crowded events: a fused fill + peak search of an event with at least
                            this many hits finds its peaks with a stencil over the whole matrix
                            (one read of it, cost independent of the number of candidates)
-                           instead of the candidate pool; -1 never. The default is
+                           instead of testing the fill's survivors; -1 never. The default is
                            n_theta n_phi n_b / 4 hits (16384 on the 4x16x1024x1024 grid), about
-                           where the stencil starts to beat the pool. The stencil needs LDS
+                           where the stencil starts to beat a test of every candidate. The stencil needs LDS
                            fill tiles, at most 4 theta and 16 phi cells (one wave per phi cell
                            holds every theta cell's row), and theta cell 0's row and the last
                            one's less than 2^31 bytes apart; ht_get_tuning reports -1 where it
@@ -158,7 +157,7 @@ int ht_peaks(const ht_grid* grid, const uint32_t* acc, ht_peak* out, int64_t cap
              int64_t* n_found, void* stream);
 
 /* ht_fill_peaks: both steps for one event in one call. Same arguments and results as ht_fill
- * followed by ht_peaks on the same acc; the peak search takes its candidates from the fill, so
+ * followed by ht_peaks on the same acc; the peak search takes its survivors from the fill, so
  * the matrix is written once and not read back in full. */
 int ht_fill_peaks(const ht_grid* grid, const float* x, const float* y, const float* z,
                   int64_t n_hits, uint32_t* acc, ht_peak* out, int64_t capacity,
@@ -167,14 +166,15 @@ int ht_fill_peaks(const ht_grid* grid, const float* x, const float* y, const flo
 /* ht_fill_peaks_noalloc: ht_fill_peaks for callers that cannot allocate device memory (code
  * under HIP graph capture, tight serving loops, hosts that forbid hipMalloc). Same arguments
  * and results as ht_fill_peaks (bit-identical matrix, peak list and count), but all of the
- * library's scratch for the call (slab lists, candidate pool, counters, tables) lives in one
+ * library's scratch for the call (slab lists, survivor masks, counters, tables) lives in one
  * fixed 64 MiB device array that each GPU the library runs on holds until the process ends;
  * the call makes no hipMalloc, hipFree or other allocating call.
- * Limits: n_a <= 16384, and the event's scratch must fit the array: direct slab lists are used
- * while they fit, else the counting sort; about 25 MB for 5000 hits on the 4x16x1024x1024 grid,
- * where events of up to about 500 000 hits fit (crowded events need no candidate pool). A larger
- * event is refused with HT_EINVAL before any device work, and ht_last_error() states the bytes
- * it needed (use ht_fill_peaks for it).
+ * Limits: n_a <= 16384, and the slab lists (direct while they fit, else the counting sort) with
+ * nine bytes per possible candidate (cand_cap per fill tile, more for large events) must fit the
+ * array: about 25 MB for 5000 hits on the 4x16x1024x1024 grid, where events of up to about
+ * 500 000 hits fit (crowded events count no candidates). A larger event is refused with HT_EINVAL
+ * before any device work, and ht_last_error() states the bytes it needed (use ht_fill_peaks for
+ * it). Where the search's own scratch does not fit beside the lists, it runs slice by slice.
  * Sharing: every call on one GPU uses that GPU's array, which keeps the last call's contents.
  * Calls on one GPU must not overlap (on different streams or host threads they race on the
  * array); calls are serialised on the host by a lock, so overlap only arises from work still

@@ -39,6 +39,7 @@ int fail_hip(hipError_t e, const char* what)
               hipGetErrorString(e));
 }
 
+static const int64_t kBlockJobs = 256;  // job flags that a workgroup of the peak test loads at once
 static const double kPi = 3.14159265358979323846;
 
 int validate_grid(const ht_grid* g)
@@ -99,8 +100,7 @@ static int env_int(const char* name, int def)
   return v && *v ? std::atoi(v) : def;
 }
 
-// Largest power-of-two row count (<= 64) whose u32 tile fits the LDS budget; the candidate
-// slots per tile scale with the tile (1/32 of its cells, 64..1024).
+// Largest power-of-two row count (<= 64) whose u32 tile fits the LDS budget.
 // Per-grid launch shapes set through ht_set_tuning (keyed by dimensions and ranges).
 typedef std::tuple<int32_t, int32_t, int32_t, int32_t, uint32_t, uint32_t, uint32_t, uint32_t> TuneKey;
 static std::mutex g_tune_mu;
@@ -158,8 +158,6 @@ Tiling choose_tiling(const ht_grid& g)
   const int forced_ft = env_int("HT_FILL_TILES", 0);
   if (forced_ft > 0 && forced_ft <= 64 && (forced_ft & (forced_ft - 1)) == 0) ft = forced_ft;
   t.fill_tiles = ft;
-  // HT_POOL_BOUND=0: the pool holds n_tiles * cand_cap entries only (tests force overflow so)
-  t.pool_bound = env_int("HT_POOL_BOUND", 1) != 0 ? 1 : 0;
   // HT_PACKED_LISTS=1: every event takes the counting sort into packed slab lists, the layout
   // that large batches and very large events use, so that tests reach it on small grids
   t.packed_lists = env_int("HT_PACKED_LISTS", 0) != 0 ? 1 : 0;
@@ -273,7 +271,7 @@ int get_tables(const ht_grid& g, int dev, DevTables* out)
   return HT_OK;
 }
 
-DevGrid make_devgrid(const ht_grid& g, const DevTables& t, const Tiling& tl)
+DevGrid make_devgrid(const ht_grid& g, const DevTables& t, const Tiling& tl, int n_ev)
 {
   DevGrid d;
   std::memset(&d, 0, sizeof(d));  // padding too: the bytes key the graph cache
@@ -289,24 +287,50 @@ DevGrid make_devgrid(const ht_grid& g, const DevTables& t, const Tiling& tl)
   d.rows = tl.rows;
   d.tiles_per_slab = tl.tiles_per_slab;
   d.n_tiles = tl.n_tiles;
-  d.cand_cap = tl.cand_cap;
   d.lds_fill = tl.lds_fill;
   d.group_tiles = tl.group_tiles;
   d.nt_store = tl.nt_store;
   d.fill_tiles = tl.fill_tiles;
-  d.pool_bound = tl.pool_bound;
   d.phi_sectors = g.phi_sectors;
   d.packed_lists = tl.packed_lists;
-  // candidate test: enough workgroups to spread a few thousand candidates over the whole chip
-  // in one pass (two candidates per wave), few enough that a near-empty event exits at once
-  d.test_blocks = std::max(16, std::min(1024, (tl.n_tiles + 15) / 16));
   d.dense_w = tl.dense_w;
   d.dense_rows = tl.dense_rows;
   d.dense_hits = tl.dense_hits;
   d.a2 = t.a2;
   d.phi_cs = t.phi;
   d.th_cs = t.th;
+  set_jobs(&d, tl.lds_fill ? tl.rows : 0, n_ev);
   return d;
+}
+
+void set_jobs(DevGrid* g, int tile_rows, int n_ev)
+{
+  JobGeom& j = g->j;
+  j.units = (g->n_b + 3) / 4;
+  j.ch = tile_rows ? std::min(tile_rows, 4) : (j.units > 64 * 64 ? 1 : 4);
+  j.sub = 1;
+  while (j.sub * 2 * (int64_t)j.units <= 64 && (!tile_rows || j.sub * 2 <= tile_rows / j.ch)) j.sub *= 2;
+  j.strips = (j.units + 63) / 64;
+  j.tile_rows = tile_rows ? tile_rows : j.ch * j.sub;
+  j.tiles_per_slab = (g->n_a + j.tile_rows - 1) / j.tile_rows;
+  j.tile_jobs = j.tile_rows / (j.ch * j.sub) * j.strips;
+  j.elem_bytes = j.ch == 4 ? 2 : 1;
+  j.n_jobs = (uint32_t)g->n_slabs * (uint32_t)j.tiles_per_slab * (uint32_t)j.tile_jobs;
+  j.row_jobs = j.ch * j.sub == 1 ? 1 : j.strips;
+  // Groups of the peak test, one workgroup each: 32 jobs a group (2048 groups on the paper grid; a
+  // 14k-hit event's test takes 22.8 us, 26.6 us with 64 jobs, 25.2 us with 16); smaller events get
+  // smaller groups, down to 8 jobs, to use more CUs; launches of many groups larger ones, which
+  // pay a workgroup's start once for more jobs (its flags come 256 jobs at a time).
+  int64_t gj = 32;
+  const int64_t all = (int64_t)j.n_jobs * n_ev;
+  while (gj > 8 && all / gj < 512) gj /= 2;
+  while (gj < kBlockJobs / 2 && all / gj > 65536) gj *= 2;
+  while (j.n_jobs / gj > 16384) gj *= 2;
+  gj = std::max<int64_t>(1, gj / j.row_jobs) * j.row_jobs;
+  j.group_jobs = (int32_t)gj;
+  j.n_groups = (uint32_t)((j.n_jobs + gj - 1) / gj);
+  // one peak per 64 cells: uncorrelated counts give one local maximum per 81
+  j.seg = (int32_t)std::min<int64_t>(kSegMax, std::max<int64_t>(128, 16 * gj));
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -325,22 +349,6 @@ bool direct_lists(const DevGrid& g, int64_t n)
          (size_t)g.n_slabs * (size_t)std::max<int64_t>(n, 1) * 16 <= kDirectListMax;
 }
 
-// Candidate-pool entries for an event of up to n hits: cand_cap per tile, and at least a
-// quarter of the bound on the cells that can reach the threshold (a hit's records vote at most
-// once per A row, into at most four (theta, phi) cells, two with phi sectors: votes <= 4 n n_a,
-// candidates <= votes / T). Large events have far more candidates than cand_cap per tile (a
-// 40k-hit event on the paper grid about 2.6M, against 0.25 of its bound of 18M); a tile whose
-// candidates do not fit is searched densely, which is exact but slow.
-size_t pool_entries(const DevGrid& g, int64_t n)
-{
-  const size_t by_tiles = (size_t)g.n_tiles * (size_t)g.cand_cap;
-  const size_t cells = (size_t)g.n_theta * g.n_phi * g.n_a * g.n_b;
-  const size_t bound = g.pool_bound ? (size_t)std::max<int64_t>(n, 0) * (g.phi_sectors ? 2 : 4) *
-                                          (size_t)g.n_a / (size_t)g.threshold
-                                    : 0;
-  return std::min<size_t>(std::max(by_tiles, std::min(cells, bound / 4)), 0xfffffff0u);
-}
-
 static size_t mask_bytes(const DevGrid& g)
 {
   // one 64-bit word per (slab, row, chunk of kChunkCells columns), rows padded to whole segments
@@ -348,6 +356,12 @@ static size_t mask_bytes(const DevGrid& g)
   const size_t n_chunks = ((size_t)g.n_b + kChunkCells - 1) / kChunkCells;
   const size_t rows = (((size_t)g.n_a + g.dense_rows - 1) / g.dense_rows) * g.dense_rows;
   return 8 * (size_t)g.n_slabs * rows * n_chunks;
+}
+
+// peaks per group: of job rows (the fill's survivors), of tiles (the stencil)
+static size_t group_words(const DevGrid& g, int peaks)
+{
+  return std::max<size_t>((peaks & kPeakBands) ? g.j.n_groups : 0, (peaks & kPeakMask) ? (size_t)n_groups(g) : 0);
 }
 
 size_t event_scratch_bytes(const DevGrid& g, int64_t n, bool direct, int peaks)
@@ -363,15 +377,14 @@ size_t event_scratch_bytes(const DevGrid& g, int64_t n, bool direct, int peaks)
     b += al(16 * nn);                         // hit_rec
     b += al(64 * nn + 16);                    // list (+1 record of slack for the fill)
   }
-  b += al(4 * (size_t)g.n_tiles);             // tile_cnt
-  b += al(4 * (size_t)g.n_tiles);             // tile_off
-  const size_t pe = (peaks & kPeakPool) ? pool_entries(g, n) : 0;
-  b += al(8 * pe);                            // pool
-  b += al(pe);                                // pk_flag
+  if (peaks) b += al(4 * group_words(g, peaks));  // group_pk
+  if (peaks & kPeakBands) {
+    b += al(4 * (((size_t)g.j.n_groups + 63) / 64)) + al(g.j.n_jobs);  // super_pk, job_any
+    b += al(16 * (size_t)kLists * kListCap);                              // surv
+    b += al((size_t)64 * g.j.elem_bytes * g.j.n_jobs);                 // masks
+    b += al(8 * (size_t)g.j.seg * g.j.n_groups);                       // seg
+  }
   if (peaks & kPeakMask) b += al(mask_bytes(g));  // pk_mask
-  b += al(4 * (size_t)g.n_tiles);               // ovf_list
-  b += al(4 * (size_t)g.n_tiles);             // tile_pk
-  b += al(4 * (size_t)n_groups(g));           // group_pk
   return b;
 }
 
@@ -397,15 +410,39 @@ void carve_event_scratch(const DevGrid& g, int64_t n, bool direct, char* p, EvDe
     ev->hit_rec = (float4*)take(16 * nn);
     ev->list = (float4*)take(64 * nn + 16);
   }
-  ev->tile_cnt = (uint32_t*)take(4 * (size_t)g.n_tiles);
-  ev->tile_off = (uint32_t*)take(4 * (size_t)g.n_tiles);
-  ev->pool_cap = (peaks & kPeakPool) ? (uint32_t)pool_entries(g, n) : 0u;
-  ev->pool = (uint2*)take(8 * (size_t)ev->pool_cap);
-  ev->pk_flag = (uint8_t*)take((size_t)ev->pool_cap);
-  ev->pk_mask = (peaks & kPeakMask) ? (uint8_t*)take(mask_bytes(g)) : nullptr;
-  ev->ovf_list = (uint32_t*)take(4 * (size_t)g.n_tiles);
-  ev->tile_pk = (uint32_t*)take(4 * (size_t)g.n_tiles);
-  ev->group_pk = (uint32_t*)take(4 * (size_t)n_groups(g));
+  carve_peak_scratch(g, p, ev, peaks, 0, g.j.n_groups);
+}
+
+void carve_peak_scratch(const DevGrid& g, char* p, EvDesc* ev, int peaks, uint32_t grp0, uint32_t n_grp)
+{
+  auto take = [&p](size_t bytes) {
+    char* r = p;
+    p += al(bytes);
+    return r;
+  };
+  const size_t n = std::min<size_t>((size_t)n_grp * g.j.group_jobs, g.j.n_jobs);
+  ev->grp0 = grp0;
+  ev->n_grp = n_grp;
+  ev->clear_n16 = 0;
+  ev->lists = 0;
+  if (peaks & kPeakBands) ev->super_pk = (uint32_t*)take(4 * (((size_t)n_grp + 63) / 64));
+  if (peaks) ev->group_pk = (uint32_t*)take(4 * group_words(g, peaks));
+  if (peaks & kPeakBands) {
+    ev->job_any = (uint8_t*)take(n);
+    ev->masks = (uint8_t*)take((size_t)64 * g.j.elem_bytes * n);
+    ev->clear = ev->super_pk;
+    ev->clear_n16 = (uint32_t)((ev->masks - (uint8_t*)ev->super_pk) / 16);
+    ev->seg = (uint2*)take(8 * (size_t)g.j.seg * n_grp);
+    ev->surv = (uint4*)take(16 * (size_t)kLists * kListCap);
+  }
+  if (peaks & kPeakMask) ev->pk_mask = (uint8_t*)take(mask_bytes(g));
+  if (peaks == kPeakMask) clear_groups(g, ev);
+}
+
+void clear_groups(const DevGrid& g, EvDesc* ev)
+{
+  ev->clear = ev->group_pk;
+  ev->clear_n16 = (uint32_t)(al(4 * (size_t)n_groups(g)) / 16);
 }
 
 // Scratch owned by the library, one per (device, stream). Calls on one stream are ordered on
@@ -510,13 +547,13 @@ int ensure_ev_staging(Workspace* w, int n_ev, hipStream_t s)
   return HT_OK;
 }
 
-int make_device_grid(const ht_grid& g, int dev, DevGrid* out)
+int make_device_grid(const ht_grid& g, int dev, int n_ev, DevGrid* out)
 {
   int rc = validate_grid(&g);
   if (rc) return rc;
   DevTables t;
   if ((rc = get_tables(g, dev, &t))) return rc;
-  *out = make_devgrid(g, t, choose_tiling(g));
+  *out = make_devgrid(g, t, choose_tiling(g), n_ev);
   return HT_OK;
 }
 
@@ -578,13 +615,13 @@ struct Prepared {
   hipStream_t s;
 };
 
-int prepare(const ht_grid* grid, void* stream, Prepared* p)
+int prepare(const ht_grid* grid, void* stream, Prepared* p, int n_ev = 1)
 {
   int rc = validate_grid(grid);
   if (rc) return rc;
   hipError_t e = hipGetDevice(&p->dev);
   if (e != hipSuccess) return fail_hip(e, "hipGetDevice");
-  if ((rc = make_device_grid(*grid, p->dev, &p->g))) return rc;
+  if ((rc = make_device_grid(*grid, p->dev, n_ev, &p->g))) return rc;
   p->s = (hipStream_t)stream;
   return HT_OK;
 }
@@ -607,7 +644,7 @@ int injected_failure(const char* stage)
 }
 
 int launch_batch(const DevGrid& g, const EvDesc* d_ev, int n_ev, int64_t max_hits, bool direct,
-                 bool any_pool, bool any_dense, hipStream_t s, bool* prep_enqueued, const BatchSplit* split)
+                 bool any_bands, bool any_dense, hipStream_t s, bool* prep_enqueued, const BatchSplit* split)
 {
   EvDesc none;
   std::memset(&none, 0, sizeof(none));
@@ -630,13 +667,13 @@ int launch_batch(const DevGrid& g, const EvDesc* d_ev, int n_ev, int64_t max_hit
     hipError_t e;
     for (int i = 0; i < pieces; ++i) {
       const int e0 = (int)((int64_t)n_ev * i / pieces), e1 = (int)((int64_t)n_ev * (i + 1) / pieces);
-      if ((rc = check_launch(launch_fill(g, none, d_ev + e0, e1 - e0, true, max_hits, s), "fill launch")))
+      if ((rc = check_launch(launch_fill(g, none, d_ev + e0, e1 - e0, any_bands, max_hits, s), "fill launch")))
         return rc;
       if ((e = hipEventRecord(split->filled[i], s)) != hipSuccess) return fail_hip(e, "hipEventRecord");
       if ((e = hipStreamWaitEvent(split->side, split->filled[i], 0)) != hipSuccess)
         return fail_hip(e, "hipStreamWaitEvent");
       if (i == 0 && (rc = injected_failure("peaks"))) return rc;
-      if (any_pool && (rc = check_launch(launch_peaks(g, none, d_ev + e0, e1 - e0, split->side), "peak launch")))
+      if (any_bands && (rc = check_launch(launch_peaks(g, none, d_ev + e0, e1 - e0, g.j.n_groups, split->side), "peak launch")))
         return rc;
       if (any_dense &&
           (rc = check_launch(launch_peaks_dense(g, none, d_ev + e0, e1 - e0, split->side), "stencil peak launch")))
@@ -648,7 +685,7 @@ int launch_batch(const DevGrid& g, const EvDesc* d_ev, int n_ev, int64_t max_hit
   }
   if (g.lds_fill) {
     StageTimer t("fill", s);
-    if ((rc = check_launch(launch_fill(g, none, d_ev, n_ev, true, max_hits, s), "fill launch"))) return rc;
+    if ((rc = check_launch(launch_fill(g, none, d_ev, n_ev, any_bands, max_hits, s), "fill launch"))) return rc;
   } else {
     {
       StageTimer t("fill_atomic", s);
@@ -656,11 +693,11 @@ int launch_batch(const DevGrid& g, const EvDesc* d_ev, int n_ev, int64_t max_hit
         return rc;
     }
     StageTimer t("candidates", s);
-    if ((rc = check_launch(launch_candidates(g, none, d_ev, n_ev, s), "candidate launch"))) return rc;
+    if ((rc = check_launch(launch_scan(g, none, d_ev, n_ev, g.j.n_groups, false, s), "candidate launch"))) return rc;
   }
   if ((rc = injected_failure("peaks"))) return rc;
   StageTimer t("peaks", s);
-  if (any_pool && (rc = check_launch(launch_peaks(g, none, d_ev, n_ev, s), "peak launch"))) return rc;
+  if (any_bands && (rc = check_launch(launch_peaks(g, none, d_ev, n_ev, g.j.n_groups, s), "peak launch"))) return rc;
   if (any_dense && (rc = check_launch(launch_peaks_dense(g, none, d_ev, n_ev, s), "stencil peak launch")))
     return rc;
   return HT_OK;
@@ -703,7 +740,7 @@ int check_accessible(const void* ptr, const char* what)
 bool plan_batch(const DevGrid& g, const ht_event* events, int n_events, std::vector<size_t>* offs,
                 size_t* total, int64_t* max_hits)
 {
-  auto layout = [&g](int64_t n) { return dense_peaks(g, n) ? kPeakMask : kPeakPool; };
+  auto layout = [&g](int64_t n) { return dense_peaks(g, n) ? kPeakMask : kPeakBands; };
   bool direct = g.lds_fill != 0;
   size_t direct_bytes = 0;
   for (int i = 0; i < n_events; ++i) {
@@ -743,20 +780,20 @@ int enqueue_event(const DevGrid& g, const EvDesc& ev, int64_t nh, bool direct, b
       if ((rc = check_launch(launch_fill_atomic(g, ev, nullptr, 1, nh, s), "fill launch"))) return rc;
     } else {
       HT_STAGE(t, "fill");
-      if ((rc = check_launch(launch_fill(g, ev, nullptr, 1, do_peaks, nh, s), "fill launch"))) return rc;
+      if ((rc = check_launch(launch_fill(g, ev, nullptr, 1, do_peaks && !ev.dense, nh, s), "fill launch"))) return rc;
     }
   }
   if (do_peaks) {
     if (!do_fill || atomic) {
       HT_STAGE(t, "candidates");
-      if ((rc = check_launch(launch_candidates(g, ev, nullptr, 1, s), "candidate launch"))) return rc;
+      if ((rc = check_launch(launch_scan(g, ev, nullptr, 1, ev.n_grp, !do_fill, s), "candidate launch"))) return rc;
       *counters_used = true;
     }
     if ((rc = injected_failure("peaks"))) return rc;
     HT_STAGE(t, "peaks");
     if (ev.dense) {
       if ((rc = check_launch(launch_peaks_dense(g, ev, nullptr, 1, s), "stencil peak launch"))) return rc;
-    } else if ((rc = check_launch(launch_peaks(g, ev, nullptr, 1, s), "peak launch"))) {
+    } else if ((rc = check_launch(launch_peaks(g, ev, nullptr, 1, ev.n_grp, s), "peak launch"))) {
       return rc;
     }
   }
@@ -784,7 +821,8 @@ int run_event(const ht_grid* grid, const float* x, const float* y, const float* 
   const bool direct = !atomic && direct_lists(p.g, nh);
   // crowded events of the fused call: peaks from the stencil over the written matrix
   const bool dense = do_fill && do_peaks && !atomic && dense_peaks(p.g, nh);
-  const int layout = dense ? kPeakMask : kPeakPool;
+  const int layout = !do_peaks ? 0 : dense ? kPeakMask : kPeakBands;
+  if (do_peaks && (!do_fill || atomic)) set_jobs(&p.g, 0, 1);  // the survivors come from a scan
   Workspace* w;
   if ((rc = get_workspace(p.dev, p.s, event_scratch_bytes(p.g, nh, direct, layout), &w))) return rc;
   if ((rc = ensure_counters(w, 1, p.s))) return rc;
@@ -792,6 +830,7 @@ int run_event(const ht_grid* grid, const float* x, const float* y, const float* 
   std::memset(&ev, 0, sizeof(ev));
   carve_event_scratch(p.g, nh, direct, w->dev, &ev, layout);
   ev.dense = dense ? 1 : 0;
+  ev.lists = layout == kPeakBands && (!do_fill || atomic || !long_lists(p.g, nh)) ? 1 : 0;
   use_counters(w, 0, &ev);
   ev.x = x;
   ev.y = y;
@@ -882,7 +921,7 @@ int ht_fill_peaks_batch(const ht_grid* grid, const ht_event* events, int32_t n_e
     if (ev.peak_capacity > 0 && !out) return fail(HT_EINVAL, "out is NULL");
   }
   Prepared p;
-  if ((rc = prepare(grid, stream, &p))) return rc;
+  if ((rc = prepare(grid, stream, &p, n_events))) return rc;
   if ((rc = check_accessible(out, "out")) || (rc = check_accessible(n_found, "n_found"))) return rc;
   std::vector<size_t> offs;
   size_t total_scratch = 0;
@@ -891,17 +930,24 @@ int ht_fill_peaks_batch(const ht_grid* grid, const ht_event* events, int32_t n_e
   if ((rc = get_workspace(p.dev, p.s, total_scratch, &w))) return rc;
   if ((rc = ensure_ev_staging(w, n_events, p.s))) return rc;
   if ((rc = ensure_counters(w, n_events, p.s))) return rc;
+  // prep grids are sized for a power-of-two bucket of workgroups, so batches of one size share
+  // a graph (workgroups past an event's hits return at once)
+  int64_t blocks = 1;
+  while (blocks * 256 < max_hits) blocks *= 2;
+  const int64_t max_hits_b = max_hits > 0 ? blocks * 256 : 0;
   const uint64_t cells = n_cells(*grid);
-  bool any_pool = false, any_dense = false;
+  bool any_bands = false, any_dense = false;
   for (int32_t i = 0; i < n_events; ++i) {
     const ht_event& ev = events[i];
     EvDesc& d = w->h_ev[i];
     std::memset(&d, 0, sizeof(d));
     const bool dense = p.g.lds_fill && dense_peaks(p.g, ev.n_hits);
-    any_pool = any_pool || !dense;
+    any_bands = any_bands || !dense;
     any_dense = any_dense || dense;
-    carve_event_scratch(p.g, ev.n_hits, direct, w->dev + offs[i], &d, dense ? kPeakMask : kPeakPool);
+    carve_event_scratch(p.g, ev.n_hits, direct, w->dev + offs[i], &d, dense ? kPeakMask : kPeakBands);
     d.dense = dense ? 1 : 0;
+    // the launch's fill variant goes by its largest event
+    d.lists = !dense && !(p.g.lds_fill && long_lists(p.g, max_hits_b)) ? 1 : 0;
     use_counters(w, i, &d);
     d.x = x ? x + ev.hit_offset : nullptr;
     d.y = y ? y + ev.hit_offset : nullptr;
@@ -912,11 +958,6 @@ int ht_fill_peaks_batch(const ht_grid* grid, const ht_event* events, int32_t n_e
     d.cap = ev.peak_capacity;
     d.n_found = n_found + i;
   }
-  // prep grids are sized for a power-of-two bucket of workgroups, so batches of one size share
-  // a graph (workgroups past an event's hits return at once)
-  int64_t blocks = 1;
-  while (blocks * 256 < max_hits) blocks *= 2;
-  const int64_t max_hits_b = max_hits > 0 ? blocks * 256 : 0;
   hipError_t e;
   // overlap of the peak searches with the fills of later events: the batch in `pieces` runs
   const int pieces = std::max(1, std::min(std::min(env_int("HT_BATCH_PIECES", 1), kMaxPieces), (int)n_events));
@@ -943,7 +984,7 @@ int ht_fill_peaks_batch(const ht_grid* grid, const ht_event* events, int32_t n_e
     if (e != hipSuccess) return fail_hip(e, "hipMemcpyAsync(descriptors)");
     if ((e = hipEventRecord(w->ev_copied, p.s)) != hipSuccess) return fail_hip(e, "hipEventRecord");
     bool prep_enqueued = false;
-    rc = launch_batch(p.g, w->d_ev, n_events, max_hits_b, direct, any_pool, any_dense, p.s, &prep_enqueued,
+    rc = launch_batch(p.g, w->d_ev, n_events, max_hits_b, direct, any_bands, any_dense, p.s, &prep_enqueued,
                       pieces > 1 ? &split : nullptr);
     if (prep_enqueued) flip_counters(w, n_events);
     return rc;
@@ -955,7 +996,7 @@ int ht_fill_peaks_batch(const ht_grid* grid, const ht_event* events, int32_t n_e
     std::memcpy(q, &p.g, sizeof(DevGrid));
     q += sizeof(DevGrid);
     const int64_t ints[4] = {n_events, max_hits_b, p.dev,
-                             (direct ? 1 : 0) | (any_pool ? 2 : 0) | (any_dense ? 4 : 0) | (pieces << 3)};
+                             (direct ? 1 : 0) | (any_bands ? 2 : 0) | (any_dense ? 4 : 0) | (pieces << 3)};
     std::memcpy(q, ints, sizeof(ints));
     q += sizeof(ints);
     const void* ptrs[2] = {w->d_ev, w->h_ev};
@@ -975,7 +1016,7 @@ int ht_fill_peaks_batch(const ht_grid* grid, const ht_event* events, int32_t n_e
     e = hipMemcpyAsync(w->d_ev, w->h_ev, sizeof(EvDesc) * n_events, hipMemcpyHostToDevice, w->capture);
     bool captured_prep = false;
     int lrc = e == hipSuccess
-                  ? launch_batch(p.g, w->d_ev, n_events, max_hits_b, direct, any_pool, any_dense, w->capture,
+                  ? launch_batch(p.g, w->d_ev, n_events, max_hits_b, direct, any_bands, any_dense, w->capture,
                                  &captured_prep, pieces > 1 ? &split : nullptr)
                   : HT_EDEVICE;
     t_capturing = false;
@@ -1089,7 +1130,7 @@ int ht_debug_batch_plan(const ht_grid* grid, const ht_event* events, int32_t n_e
     if (events[i].n_hits < 0 || events[i].n_hits > ((int64_t)1 << 28))
       return fail(HT_EINVAL, "event %d has an invalid size", i);
   // the tiling alone decides the layout; the tables (device memory) are not needed
-  const DevGrid g = make_devgrid(*grid, DevTables(), choose_tiling(*grid));
+  const DevGrid g = make_devgrid(*grid, DevTables(), choose_tiling(*grid), n_events);
   std::vector<size_t> offs;
   size_t total = 0;
   int64_t max_hits = 0;

@@ -17,9 +17,6 @@ namespace {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBlock = 256;
-static_assert(kBlock == 256, "candidate emission splits a tile over four wave64s");
-constexpr int kGroupTiles = 64;  // largest group of tiles per peak workgroup (g.group_tiles)
-constexpr int kWalkChunks = 4;   // chunks of kBlock pool entries per round of the ordered peak walk
 
 // A launch's event descriptor: the kernel argument for one event, else evs[blockIdx.y]. The
 // descriptor array is read through the constant address space: both sources are then
@@ -71,16 +68,6 @@ __device__ __forceinline__ void st_rec(float4* p, size_t i, float4 v)
 {
   const f32x4 w = {v.x, v.y, v.z, v.w};
   ((GLOBAL f32x4*)p)[i] = w;
-}
-__device__ __forceinline__ uint2 ld_cand(const uint2* p, size_t i)
-{
-  const u32x2 v = ((const GLOBAL u32x2*)p)[i];
-  return make_uint2(v.x, v.y);
-}
-__device__ __forceinline__ void st_cand(uint2* p, size_t i, uint32_t cell, uint32_t votes)
-{
-  const u32x2 w = {cell, votes};
-  ((GLOBAL u32x2*)p)[i] = w;
 }
 // an output peak: one 8-byte store when the caller's array is 8-byte aligned (a wave's peaks
 // then go out as one contiguous run, which matters when the array is host memory mapped into
@@ -168,139 +155,112 @@ __device__ uint32_t block_sum(uint32_t v, uint32_t* smem)
 }
 
 
-// ---------------------------------------------------------------------------------------------
-// Candidates (cells >= threshold) of one tile held in LDS. Each wave takes a quarter of the tile
-// (in 16-byte units when VEC, the tile then being a multiple of 4 cells): count_candidates
-// leaves each wave's count in s_small[wave]; after a barrier, emit_candidates reserves the
-// tile's chunk of the event's candidate pool with one atomic and each wave writes the
-// candidates of its quarter in cell order (ballot compaction), so every tile's chunk is sorted
-// by cell index. A tile whose candidates do not fit the pool is recorded as overflowed
-// (searched densely). The LDS tile is left as it was. (Dropping here the cells that lose to a
-// neighbour inside the tile cut the peak test but cost the fill more than it saved.)
-// Both are called by the whole block; s_small: >= 9 words. emit_candidates ends with a barrier
-// when the tile holds candidates, so the caller may then overwrite the tile.
-// ---------------------------------------------------------------------------------------------
-template <bool VEC>
-__device__ __forceinline__ void tile_quarter(uint32_t L, int wave, uint32_t* q0, uint32_t* q1)
+__device__ __forceinline__ uint32_t max3u(uint32_t a, uint32_t b, uint32_t c) { return max(a, max(b, c)); }
+// lane j - 1's value (wave_shr:1; lane 0 gets 0)
+__device__ __forceinline__ uint32_t lane_left(uint32_t v)
 {
-  const uint32_t n = VEC ? L / 4u : L;  // 16-byte units or cells
-  const uint32_t seg = (n + 3u) / 4u;
-  *q0 = min(n, (uint32_t)wave * seg);
-  *q1 = min(n, *q0 + seg);
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x138, 0xf, 0xf, true);
+}
+// lane j + 1's value (wave_shl:1; lane 63 gets 0)
+__device__ __forceinline__ uint32_t lane_right(uint32_t v)
+{
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x130, 0xf, 0xf, true);
 }
 
-template <bool VEC>
-__device__ void count_candidates(const uint32_t* s_tile, uint32_t L, uint32_t T, uint32_t* s_small)
+// ---------------------------------------------------------------------------------------------
+// Survivors of a job (JobGeom): the cells >= T that no neighbour among the job's own cells beats
+// under (votes, -index). v[q] holds the lane's four columns of row q (zeros where there is no
+// cell); lmask / rmask are 0 in lanes whose left / right neighbour lane holds another row's cells.
+// Neighbours outside the job are not looked at, so the test only drops cells that are no peaks:
+// on a 40k-hit event it leaves 0.26 of the candidates, and the candidate test does the rest.
+// Per row: R3 = the 3-maximum along B. A cell must exceed the R3 above it and its left neighbour
+// (lower indices) and reach the R3 below it and its right neighbour: four VALU instructions per
+// cell. A job with no cell >= T (nine in ten on an ordinary event) stops after one comparison.
+// Returns the lane's mask, bit 4 q + k; every lane of the wave must be active.
+// ---------------------------------------------------------------------------------------------
+template <int CH>
+__device__ __forceinline__ uint32_t job_survivors(const u32x4 (&v)[CH], uint32_t T, uint32_t lmask, uint32_t rmask)
 {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  uint32_t q0, q1;
-  tile_quarter<VEC>(L, wave, &q0, &q1);
-  uint32_t cnt = 0;  // uniform: sums of ballots
-  if (VEC) {
-    const u32x4* s4 = reinterpret_cast<const u32x4*>(s_tile);
-    const u32x4 zero4 = {0u, 0u, 0u, 0u};
-    for (uint32_t b = q0; b < q1; b += 4 * 64) {
-      u32x4 v[4];
+  uint32_t mx = 0u;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {  // four reads in flight, then the compares
-        const uint32_t i = b + (uint32_t)(k * 64 + lane);
-        v[k] = i < q1 ? s4[i] : zero4;  // T >= 1, so a zero is never a candidate
-      }
+  for (int q = 0; q < CH; ++q) mx = max(max3u(mx, v[q].x, v[q].y), max(v[q].z, v[q].w));
+  if (__builtin_amdgcn_ballot_w64(mx >= T) == 0u) return 0u;  // uniform
+  u32x4 r3[CH];
+  uint32_t lf[CH], rt[CH];
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
-        cnt += (uint32_t)(__popcll(__ballot(v[k].x >= T)) + __popcll(__ballot(v[k].y >= T)) +
-                          __popcll(__ballot(v[k].z >= T)) + __popcll(__ballot(v[k].w >= T)));
-    }
-  } else {
-    for (uint32_t b = q0; b < q1; b += 64) {
-      const uint32_t i = b + lane;
-      cnt += (uint32_t)__popcll(__ballot(i < q1 && s_tile[i] >= T));
-    }
+  for (int q = 0; q < CH; ++q) {
+    lf[q] = lane_left(v[q].w) & lmask;
+    rt[q] = lane_right(v[q].x) & rmask;
+    r3[q].x = max3u(lf[q], v[q].x, v[q].y);
+    r3[q].y = max3u(v[q].x, v[q].y, v[q].z);
+    r3[q].z = max3u(v[q].y, v[q].z, v[q].w);
+    r3[q].w = max3u(v[q].z, v[q].w, rt[q]);
   }
-  if (lane == 0) s_small[wave] = cnt;
+  uint32_t m = 0u;
+#pragma unroll
+  for (int q = 0; q < CH; ++q) {
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+    const u32x4 up = q > 0 ? r3[q > 0 ? q - 1 : 0] : zero;
+    const u32x4 dn = q + 1 < CH ? r3[q + 1 < CH ? q + 1 : 0] : zero;
+    const bool k0 = (v[q].x > max(up.x, lf[q])) & (v[q].x >= max3u(dn.x, v[q].y, T));
+    const bool k1 = (v[q].y > max(up.y, v[q].x)) & (v[q].y >= max3u(dn.y, v[q].z, T));
+    const bool k2 = (v[q].z > max(up.z, v[q].y)) & (v[q].z >= max3u(dn.z, v[q].w, T));
+    const bool k3 = (v[q].w > max(up.w, v[q].z)) & (v[q].w >= max3u(dn.w, rt[q], T));
+    m |= (k0 ? 1u << (4 * q) : 0u) | (k1 ? 2u << (4 * q) : 0u) | (k2 ? 4u << (4 * q) : 0u) |
+         (k3 ? 8u << (4 * q) : 0u);
+  }
+  return m;
 }
 
-template <bool VEC>
-__device__ void emit_candidates(const DevGrid& g, const EvDesc& e, int tile, uint32_t cell0,
-                                const uint32_t* s_tile, uint32_t L, uint32_t* s_small)
+// Stores a job's masks and its flag, if it has survivors. job: its index in the event's arrays.
+template <int CH>
+__device__ __forceinline__ void put_mask(const EvDesc& e, uint32_t job, uint32_t lane, uint32_t m)
 {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const uint32_t T = g.threshold;
-  const uint32_t w0 = s_small[0], w1 = s_small[1], w2 = s_small[2];
-  const uint32_t total = w0 + w1 + w2 + s_small[3];
-  if (total == 0) {  // uniform
-    if (threadIdx.x == 0) {
-      // peak counts start at zero; the candidate test (a later launch) adds to them
-      gp(e.tile_pk)[tile] = 0u;
-      if (tile % g.group_tiles == 0) gp(e.group_pk)[tile / g.group_tiles] = 0u;
-      gp(e.tile_cnt)[tile] = 0u;
-      gp(e.tile_off)[tile] = 0u;
-    }
+  if (CH == 4) ((GLOBAL uint16_t*)gp(e.masks))[(size_t)job * 64u + lane] = (uint16_t)m;
+  else gp(e.masks)[(size_t)job * 64u + lane] = (uint8_t)m;
+  if (lane == 0u) gp(e.job_any)[job] = 1;
+}
+
+// Adds a job's survivors to one of the event's lists (cell, votes, group of jobs), one reservation
+// per job. Entries past the list's end are dropped: the test then works from the masks instead.
+// c0: the lane's first cell; v: its cells, as in job_survivors.
+template <int CH>
+__device__ __forceinline__ void list_survivors(const EvDesc& e, uint32_t job, uint32_t grp, uint32_t lane, uint32_t m,
+                                               uint32_t c0, uint32_t nb, const u32x4 (&v)[CH])
+{
+  const uint32_t l = job % kLists;
+  const uint32_t c = (uint32_t)__builtin_popcount(m), incl = wave_incl_scan(c);
+  uint32_t from = 0u;
+  if (lane == 63u) from = gatomic_add(e.slab_cnt + kListLens + l * kListLine, incl);
+  from = (uint32_t)__builtin_amdgcn_readlane((int)from, 63);
+  if (lane == 63u && from + incl > kListCap) gp(e.slab_cnt)[kListOver] = 1u;
+  uint32_t at = from + incl - c;
+#pragma unroll
+  for (int q = 0; q < CH; ++q)
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (m >> (4 * q + k) & 1u) {
+        const u32x4 en = {c0 + (uint32_t)q * nb + (uint32_t)k, v[q][k], grp, 0u};
+        if (at < kListCap) ((GLOBAL u32x4*)gp(e.surv))[l * kListCap + at] = en;
+        ++at;
+      }
+}
+
+// A lane's unit of four columns of a row of nb cells: one 16-byte access (of 4-byte alignment
+// where rows are not whole units), the row's last unit cell by cell.
+typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
+template <bool NT>
+__device__ __forceinline__ void st_unit(uint32_t* acc, uint32_t c, uint32_t left, u32x4 v)
+{
+  GLOBAL uint32_t* const d = gp(acc) + c;
+  if (left >= 4u) {
+    if (NT) __builtin_nontemporal_store(v, (GLOBAL u32x4_a4*)d);
+    else *(GLOBAL u32x4_a4*)d = v;
     return;
   }
-  if (threadIdx.x == 0) {
-    uint32_t base = gatomic_add(e.slab_cnt + kPoolCounter, total);
-    if (base > e.pool_cap || total > e.pool_cap - base) {
-      // reservations are contiguous, so at most one starts inside the pool and crosses its
-      // end: it marks where the written entries stop
-      if (base <= e.pool_cap) gp(e.slab_cnt)[kPoolCut] = e.pool_cap - base + 1u;
-      gp(e.ovf_list)[gatomic_add(e.slab_cnt + kOvfCounter, 1u)] = (uint32_t)tile;
-      base = kTileOverflow;
-    }
-    s_small[8] = base;
-    gp(e.tile_cnt)[tile] = total;
-    gp(e.tile_off)[tile] = base;
-    gp(e.tile_pk)[tile] = 0u;
-    if (tile % g.group_tiles == 0) gp(e.group_pk)[tile / g.group_tiles] = 0u;
-  }
-  lds_barrier();
-  const uint32_t base = s_small[8];
-  if (base != kTileOverflow) {  // uniform
-    uint32_t q0, q1;
-    tile_quarter<VEC>(L, wave, &q0, &q1);
-    // candidates of the earlier quarters
-    uint32_t run = base + (wave > 0 ? w0 : 0u) + (wave > 1 ? w1 : 0u) + (wave > 2 ? w2 : 0u);
-    // a lane's rank among the ballot's set lanes below it: mbcnt adds the count of set bits below
-    // the lane in one half of the mask to its second operand
-    auto rank = [](uint64_t m, uint32_t base) {
-      return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, base));
-    };
-    if (VEC) {
-      const u32x4* s4 = reinterpret_cast<const u32x4*>(s_tile);
-      const u32x4 zero4 = {0u, 0u, 0u, 0u};
-      for (uint32_t b = q0; b < q1; b += 2 * 64) {
-        u32x4 v[2];
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-          const uint32_t i = b + (uint32_t)(k * 64 + lane);
-          v[k] = i < q1 ? s4[i] : zero4;
-        }
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-          // cells 4i .. 4i+3 of lane l precede those of lane l+1
-          const uint32_t c = cell0 + 4u * (b + (uint32_t)(k * 64 + lane));
-          const bool c0 = v[k].x >= T, c1 = v[k].y >= T, c2 = v[k].z >= T, c3 = v[k].w >= T;
-          const uint64_t m0 = __ballot(c0), m1 = __ballot(c1), m2 = __ballot(c2), m3 = __ballot(c3);
-          uint32_t r = rank(m3, rank(m2, rank(m1, rank(m0, run))));
-          if (c0) st_cand(e.pool, r++, c, v[k].x);
-          if (c1) st_cand(e.pool, r++, c + 1u, v[k].y);
-          if (c2) st_cand(e.pool, r++, c + 2u, v[k].z);
-          if (c3) st_cand(e.pool, r, c + 3u, v[k].w);
-          run += (uint32_t)(__popcll(m0) + __popcll(m1) + __popcll(m2) + __popcll(m3));
-        }
-      }
-    } else {
-      for (uint32_t b = q0; b < q1; b += 64) {
-        const uint32_t i = b + lane;
-        const uint32_t v = i < q1 ? s_tile[i] : 0u;
-        const bool c = v >= T;
-        const uint64_t m = __ballot(c);
-        if (c) st_cand(e.pool, rank(m, run), cell0 + i, v);
-        run += (uint32_t)__popcll(m);
-      }
-    }
-  }
-  lds_barrier();
+  for (uint32_t k = 0; k < 3; ++k)
+    if (k < left) d[k] = v[k];
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -309,10 +269,11 @@ __device__ void emit_candidates(const DevGrid& g, const EvDesc& e, int tile, uin
 // workgroups write one contiguous stretch of the matrix. Per tile: the slab's record list is
 // read (with direct lists the first CACHE records per thread are loaded together with the list
 // length, in one memory round trip; longer lists come in further chunks of CACHE records per
-// thread, each chunk's loads issued together), the votes go to LDS, the tile's candidates are
-// pooled, the tile is written out once, and the LDS tile is left all zero. CACHE is 2 for short
-// lists (few registers, so eight waves fit on each SIMD) and 8 for long ones, where the LDS
-// tile, not the registers, limits how many workgroups fit.
+// thread, each chunk's loads issued together) and the votes go to LDS. Then the waves take the
+// tile's jobs in turn, with no further barrier: a wave reads its job's cells once, writes them to
+// the matrix, clears them in LDS, and (EMIT) stores the survivors' masks of the peak search.
+// CACHE is 2 for short lists (few registers, so eight waves fit on each SIMD) and 8 for long
+// ones, where the LDS tile, not the registers, limits how many workgroups fit.
 // ---------------------------------------------------------------------------------------------
 template <int ROWS, bool VEC, bool EMIT, bool NT, int CACHE>
 __global__ __launch_bounds__(kBlock) void k_fill(DevGrid g, EvDesc ev0, const EvDesc* evs)
@@ -320,18 +281,26 @@ __global__ __launch_bounds__(kBlock) void k_fill(DevGrid g, EvDesc ev0, const Ev
   extern __shared__ uint32_t smem[];
   EvDesc e = load_ev(ev0, evs);
   const uint32_t nb = (uint32_t)g.n_b;
-  const uint32_t Lpad = ((uint32_t)ROWS * nb + 3u) & ~3u;
+  // row stride in LDS: whole 16-byte units where jobs read them, else none is lost
+  const uint32_t ldr4 = (nb + 3u) / 4u, ldr = EMIT ? 4u * ldr4 : nb;
+  const uint32_t Lpad = ((uint32_t)ROWS * ldr + 3u) & ~3u;
   uint32_t* s_tile = smem;
-  uint32_t* s_small = smem + Lpad;  // 16 words
-  // long lists only: one word per lane past the small words, where a vote outside the row goes
-  uint32_t* const s_spill = smem + Lpad + 16u + (threadIdx.x & 63u);
+  // long lists only: one word per lane past the tile, where a vote outside the row goes
+  uint32_t* const s_spill = smem + Lpad + (threadIdx.x & 63u);
   u32x4* s4 = reinterpret_cast<u32x4*>(s_tile);
   const u32x4 zero4 = {0u, 0u, 0u, 0u};
   for (uint32_t i = threadIdx.x; i < Lpad / 4; i += kBlock) s4[i] = zero4;
 
   const float b_min = g.b_min, inv_db = g.inv_db, nb_f = g.nb_f;
   const uint32_t nb_bits = __float_as_uint(nb_f);
-  const uint32_t T = g.threshold;
+  // the wave's jobs: lane -> (band of the job, 4-column unit); wide rows: unit = 64 strip + lane
+  constexpr int CH = ROWS < 4 ? ROWS : 4;
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint32_t sub = g.j.sub > 1 ? lane / ldr4 : 0u;
+  const uint32_t unit0 = g.j.sub > 1 ? lane - sub * ldr4 : lane;
+  const uint32_t lmask = unit0 > 0u ? ~0u : 0u;  // a strip's first lane reads 0 anyway
+  const uint32_t rmask = g.j.sub > 1 && unit0 + 1u == ldr4 ? 0u : ~0u;
   // Workgroups are dealt to the eight XCDs in turn, so consecutive tiles land on different
   // XCDs and a slab's record list is fetched into every XCD's L2. Giving each XCD one
   // contiguous range of tiles instead measured 11% slower on the paper grid (eight separate
@@ -348,11 +317,13 @@ __global__ __launch_bounds__(kBlock) void k_fill(DevGrid g, EvDesc ev0, const Ev
   size_t beg = 0;
   uint32_t n = 0;
   float cx[CACHE], cr2[CACHE], ck[CACHE];
+  constexpr bool kSplit = CACHE != 8 && ROWS >= 4;  // see the votes of very short lists
+  constexpr int kPart = kSplit ? ROWS / (kBlock / 64) : ROWS;
+  float sx = 0.0f, sr2 = 0.0f, sk = 0.0f, sa2 = 0.0f;
   for (int tile = t_begin; tile < t_end; tile += t_step) {  // uniform
     const int slab = tile / g.tiles_per_slab;
     const int a0 = (tile - slab * g.tiles_per_slab) * ROWS;
     const int rows = min(ROWS, g.n_a - a0);
-    const uint32_t L = (uint32_t)rows * nb;
     if (CACHE != 8 || slab != held_slab) {  // the short-list variant never holds a list
       uint32_t last;  // last readable record (before n is known)
       if (e.list_cap > 0) {
@@ -371,11 +342,19 @@ __global__ __launch_bounds__(kBlock) void k_fill(DevGrid g, EvDesc ev0, const Ev
 #pragma unroll
       for (int c = 0; c < CACHE; ++c)
         ld_xyz(e.list, beg + min(threadIdx.x + (uint32_t)c * kBlock, last), &cx[c], &cr2[c], &ck[c]);
+      if (kSplit) ld_xyz(e.list, beg + min(lane, last), &sx, &sr2, &sk);
       held_slab = (consecutive && n <= (uint32_t)(CACHE * kBlock)) ? slab : -1;
     }
-    float a2r[ROWS];
+    // tall tiles read each row's A from the lane that holds it: 64 of them in scalar registers spill
+    constexpr bool kLaneA2 = ROWS >= 16;
+    if (kSplit || kLaneA2) sa2 = gp(g.a2)[min(a0 + (int)lane, g.n_a - 1)];
+    constexpr int kVoteUnroll = ROWS < 8 ? ROWS : 8;
+    float a2r[kLaneA2 ? 1 : ROWS];
+    if (!kLaneA2) {
 #pragma unroll
-    for (int r = 0; r < ROWS; ++r) a2r[r] = g.a2[min(a0 + r, g.n_a - 1)];
+      for (int r = 0; r < ROWS; ++r) a2r[kLaneA2 ? 0 : r] = g.a2[min(a0 + r, g.n_a - 1)];
+    }
+    auto lane_a2 = [&](int row) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sa2), row)); };
     // the LDS tile is zero: set at the start, restored at the end of every tile
     lds_barrier();
     // Long lists (crowded events) vote with no branch: every row, and a vote outside the row
@@ -385,28 +364,40 @@ __global__ __launch_bounds__(kBlock) void k_fill(DevGrid g, EvDesc ev0, const Ev
     // negative values, NaN and infinity all have patterns at or above that of n_b. This measured
     // 11% faster on the long-list fill of a 40k-hit event and 4% slower on the short-list fill
     // of the paper event, which keeps the branch.
-    auto vote = [&](float x, float r2, float k) {
-#pragma unroll
-      for (int r = 0; r < ROWS; ++r) {
-        if (CACHE == 8 || r < rows) {
-          float ax = a2r[r] * x;
-          float num = r2 - ax;
-          float B = num * k;
-          float d = B - b_min;
-          float f = d * inv_db;
-          if (CACHE == 8) {
-            const float f0 = f + 0.0f;
-            const bool in = __float_as_uint(f0) < nb_bits;
-            atomicAdd(in ? &s_tile[(uint32_t)r * nb + (uint32_t)(int)f0] : s_spill, 1u);
-          } else if (f >= 0.0f && f < nb_f) {
-            atomicAdd(&s_tile[(uint32_t)r * nb + (uint32_t)(int)f], 1u);
-          }
-        }
+    auto vote_row = [&](int r, float a2, float x, float r2, float k) {
+      if (CACHE != 8 && r >= rows) return;
+      float ax = a2 * x;
+      float num = r2 - ax;
+      float B = num * k;
+      float d = B - b_min;
+      float f = d * inv_db;
+      if (CACHE == 8) {
+        const float f0 = f + 0.0f;
+        const bool in = __float_as_uint(f0) < nb_bits;
+        atomicAdd(in ? &s_tile[(uint32_t)r * ldr + (uint32_t)(int)f0] : s_spill, 1u);
+      } else if (f >= 0.0f && f < nb_f) {
+        atomicAdd(&s_tile[(uint32_t)r * ldr + (uint32_t)(int)f], 1u);
       }
     };
+    auto vote = [&](float x, float r2, float k) {
+#pragma unroll kVoteUnroll
+      for (int r = 0; r < ROWS; ++r) vote_row(r, kLaneA2 ? lane_a2(r) : a2r[kLaneA2 ? 0 : r], x, r2, k);
+    };
+    // Lists of at most one record per lane (small events: 13 records in a slab on average) would
+    // leave all but one wave idle through ROWS dependent votes: each wave takes a quarter of the
+    // rows instead, every lane the record of its lane number.
+    if (kSplit && n <= 64u) {  // uniform
+#pragma unroll 4
+      for (int r = 0; r < kPart; ++r) {
+        const int row = (int)wave * kPart + r;
+        const float a2 = lane_a2(row);
+        if (lane < n) vote_row(row, a2, sx, sr2, sk);
+      }
+    } else {
 #pragma unroll
-    for (int c = 0; c < CACHE; ++c)
-      if (threadIdx.x + (uint32_t)c * kBlock < n) vote(cx[c], cr2[c], ck[c]);
+      for (int c = 0; c < CACHE; ++c)
+        if (threadIdx.x + (uint32_t)c * kBlock < n) vote(cx[c], cr2[c], ck[c]);
+    }
     // longer lists: further chunks of CACHE records per thread, each chunk's loads issued
     // together (one round trip per chunk)
     for (uint32_t base = CACHE * kBlock; base < n; base += CACHE * kBlock) {  // uniform
@@ -420,39 +411,72 @@ __global__ __launch_bounds__(kBlock) void k_fill(DevGrid g, EvDesc ev0, const Ev
     lds_barrier();
 
     const uint32_t cell0 = ((uint32_t)slab * (uint32_t)g.n_a + (uint32_t)a0) * nb;
-    if (EMIT && e.dense) {
-      // crowded event: its peaks come from the stencil over the written matrix, which only
-      // needs the group's peak count cleared
-      if (threadIdx.x == 0 && tile % g.group_tiles == 0) gp(e.group_pk)[tile / g.group_tiles] = 0u;
-    } else if (EMIT) {
-      // candidates are pooled before the tile is written, so the wait for the pool reservation
-      // never falls behind this tile's stores (the memory counter a wave waits on counts stores
-      // too); each pass keeps several 16-byte LDS reads in flight per lane
-      count_candidates<VEC>(s_tile, L, T, s_small);
-      lds_barrier();
-      emit_candidates<VEC>(g, e, tile, cell0, s_tile, L, s_small);
-    }
-
-    // write the tile out once, clearing LDS on the way
-    GLOBAL uint32_t* dst = gp(e.acc) + cell0;
-    if (VEC) {
-      GLOBAL u32x4* d4 = reinterpret_cast<GLOBAL u32x4*>(dst);
-      for (uint32_t i = threadIdx.x; i < L / 4; i += kBlock) {
-        const u32x4 v = s4[i];
-        if (NT) __builtin_nontemporal_store(v, d4 + i);
-        else d4[i] = v;
-        s4[i] = zero4;
+    if (!EMIT) {
+      // no search of the tile: one linear sweep over it
+      const uint32_t L = (uint32_t)rows * nb;
+      GLOBAL uint32_t* dst = gp(e.acc) + cell0;
+      if (VEC) {
+        GLOBAL u32x4* d4 = reinterpret_cast<GLOBAL u32x4*>(dst);
+        for (uint32_t i = threadIdx.x; i < L / 4u; i += kBlock) {
+          const u32x4 v = s4[i];
+          if (NT) __builtin_nontemporal_store(v, d4 + i);
+          else d4[i] = v;
+          s4[i] = zero4;
+        }
+      } else {
+        for (uint32_t i = threadIdx.x; i < L; i += kBlock) {
+          const uint32_t v = s_tile[i];
+          if (NT) __builtin_nontemporal_store(v, dst + i);
+          else dst[i] = v;
+          s_tile[i] = 0u;
+        }
       }
-    } else {
-      for (uint32_t i = threadIdx.x; i < L; i += kBlock) {
-        const uint32_t v = s_tile[i];
-        if (NT) __builtin_nontemporal_store(v, dst + i);
-        else dst[i] = v;
-        s_tile[i] = 0u;
-      }
+      if (CACHE == 8 && L < Lpad)  // uniform: the rows past a short last tile took votes
+        for (uint32_t i = L + threadIdx.x; i < Lpad; i += kBlock) s_tile[i] = 0u;
+      continue;
     }
-    if (CACHE == 8 && L < Lpad)  // uniform: the rows past a short last tile took votes
-      for (uint32_t i = L + threadIdx.x; i < Lpad; i += kBlock) s_tile[i] = 0u;
+    const bool emit = !e.dense;  // uniform; a crowded event's peaks come from the stencil
+    // Every job's cells: read from LDS once, written to the matrix, cleared, and searched for
+    // survivors in registers. No wave waits for another here: what bounds the fill of an ordinary
+    // event is its stores, and a pass that counted candidates, a barrier, a pool reservation and
+    // a second pass over the tile cost 9 us of 47 on the paper event.
+    uint32_t bg = 0u, st = wave;  // job = bg * strips + st
+    while (st >= (uint32_t)g.j.strips) { st -= (uint32_t)g.j.strips; ++bg; }
+    for (uint32_t job = wave; job < (uint32_t)g.j.tile_jobs; job += kBlock / 64) {  // uniform
+      const uint32_t u = g.j.sub > 1 ? unit0 : st * 64u + lane;
+      const uint32_t r0 = (bg * (uint32_t)g.j.sub + sub) * CH;
+      const bool in = u < ldr4 && sub < (uint32_t)g.j.sub;
+      u32x4 v[CH];
+#pragma unroll
+      for (int q = 0; q < CH; ++q) v[q] = in && (int)r0 + q < rows ? s4[(r0 + q) * ldr4 + u] : zero4;
+#pragma unroll
+      for (int q = 0; q < CH; ++q) {
+        if (in && (int)r0 + q < rows) {
+          const uint32_t c = cell0 + (r0 + q) * nb + 4u * u;
+          if (VEC) {
+            GLOBAL u32x4* d4 = reinterpret_cast<GLOBAL u32x4*>(gp(e.acc) + c);
+            if (NT) __builtin_nontemporal_store(v[q], d4);
+            else *d4 = v[q];
+          } else {
+            st_unit<NT>(e.acc, c, nb - 4u * u, v[q]);
+          }
+          s4[(r0 + q) * ldr4 + u] = zero4;
+        }
+      }
+      if (emit) {
+        const uint32_t m = job_survivors<CH>(v, g.threshold, lmask, rmask);
+        if (__builtin_amdgcn_ballot_w64(m != 0u) != 0u) {  // uniform
+          const uint32_t id = (uint32_t)tile * (uint32_t)g.j.tile_jobs + job;
+          put_mask<CH>(e, id, lane, m);
+          if (CACHE != 8 && e.lists)  // uniform
+            list_survivors<CH>(e, id, id / (uint32_t)g.j.group_jobs, lane, m, cell0 + r0 * nb + 4u * u, nb, v);
+        }
+      }
+      st += kBlock / 64;
+      while (st >= (uint32_t)g.j.strips) { st -= (uint32_t)g.j.strips; ++bg; }
+    }
+    if (CACHE == 8 && rows < ROWS)  // uniform: the rows past a short last tile took votes
+      for (uint32_t i = (uint32_t)rows * ldr4 + threadIdx.x; i < Lpad / 4u; i += kBlock) s4[i] = zero4;
     // the LDS tile is all zero again; the next tile's votes start after its first barrier
   }
 }

@@ -16,21 +16,42 @@ constexpr int kMaxSlabs = 4096;
 // Per-event slab counters: a pair of arrays used alternately by successive calls. A call counts
 // into the array that is zero and clears the other one for the next call, so no call needs a
 // separate clearing launch. They live in memory of their own, cleared once when allocated.
-// Each array holds kMaxSlabs slab counters followed by the candidate-pool cursor, the marker
-// of the one pool reservation that crosses the pool's end (pool_cap + 1 - its start, 0 if
-// none) and the number of tiles whose candidates did not fit.
-constexpr int kCounterWords = kMaxSlabs + 64;
-constexpr int kPoolCounter = kMaxSlabs;
-constexpr int kPoolCut = kMaxSlabs + 1;
-constexpr int kOvfCounter = kMaxSlabs + 2;
+// Each array holds kMaxSlabs slab counters, then the lengths of the survivor lists (from kListLens
+// on) and a word that is set when a survivor did not fit its list (kListOver). An event's survivors
+// (cell, votes, group of jobs) go to kLists lists of kListCap entries each, its jobs taking the
+// lists in turn. One list would do but for its counter: atomic additions to one cache line take
+// 10 ns each, and an event of 10k hits has 5000 jobs with survivors; the lists' lengths are a
+// cache line (kListLine words) apart. The entries are four per half wave of a test of 1024
+// workgroups; an event with more survivors is tested group by group.
+constexpr uint32_t kLists = 8;
+constexpr uint32_t kListCap = 4096;
+constexpr uint32_t kListLine = 32;
+constexpr int kListLens = kMaxSlabs;
+constexpr int kListOver = kListLens + (int)(kLists * kListLine);
+constexpr int kCounterWords = kListOver + (int)kListLine;
 constexpr size_t kCounterBytes = 2 * sizeof(uint32_t) * kCounterWords;
-// tile_off value of a tile whose candidates did not fit the pool (searched densely instead)
-constexpr uint32_t kTileOverflow = 0xffffffffu;
 // Direct slab lists (one fixed-capacity list per slab, capacity = the event's hit count) are
 // used while they need at most this many bytes per event; above it, a counting sort.
 constexpr size_t kDirectListMax = (size_t)1 << 29;
 // A batch uses direct lists only while the scratch of all its events stays within this.
 constexpr size_t kBatchDirectMax = (size_t)8 << 30;
+
+// Jobs of the peak search. A wave64 takes one job: `ch` consecutive A rows (a band, up to 4) of
+// 4 B columns per lane, so up to 256 columns (a strip). Rows narrower than 32 units of 4 columns
+// put `sub` bands one after another into one job; wider rows take `strips` jobs per band. A
+// tile (tile_rows A rows of one slab) holds tile_jobs jobs, in (band, strip) order; the strips of
+// one band or of `sub` bands are a job row. Each lane's survivors of a job are one mask element of
+// elem_bytes bytes: bit 4 q + k is row q, column k of its cells.
+struct JobGeom {
+  int32_t ch, sub, strips, units;   // units: 4-column units per row
+  int32_t tile_rows, tiles_per_slab, tile_jobs;
+  int32_t elem_bytes;               // mask bytes per lane: 2 (ch 4) or 1
+  int32_t row_jobs;                 // jobs in whose order cells are not in order: a job row, or 1
+  int32_t group_jobs;               // jobs per group of the peak test (whole job rows)
+  int32_t seg;                      // peaks of a group that its segment holds (at most kSegMax)
+  uint32_t n_jobs, n_groups;
+};
+constexpr uint32_t kSegMax = 1024;
 
 // Grid constants and tables as the kernels see them (passed by value as a kernel argument).
 struct DevGrid {
@@ -43,18 +64,16 @@ struct DevGrid {
   int32_t rows;            // A rows per tile; a tile is rows x n_b contiguous cells of one slab
   int32_t tiles_per_slab;  // ceil(n_a / rows)
   int32_t n_tiles;         // n_slabs * tiles_per_slab
-  int32_t cand_cap;        // candidate-pool entries per tile (the pool is shared by all tiles)
   int32_t lds_fill;        // 1: fill through an LDS tile; 0: global atomics (very wide B rows)
   int32_t group_tiles;     // tiles per workgroup of the peak search (16, 32 or 64)
   int32_t nt_store;        // fill store kind: 0 16-byte, 1 non-temporal 16-byte, 2 4-byte
   int32_t fill_tiles;      // fill tiles per workgroup (filled in turn)
-  int32_t pool_bound;      // 1: large events get a candidate pool sized by their vote bound
   int32_t phi_sectors;     // 1: phi cells are independent sectors (no phi widening or neighbours)
   int32_t packed_lists;    // 1: always the counting-sort (packed) slab lists, never direct ones
-  int32_t test_blocks;     // workgroups per event of the candidate test
   int32_t dense_w;         // 1: the stencil peak search is available on this grid (0: not)
   int32_t dense_rows;      // A rows per workgroup of the stencil peak search (a multiple of 12)
   int32_t dense_hits;      // events with at least this many hits take the stencil (0: never)
+  JobGeom j;               // jobs of the candidate search (of fill tiles, or of a scanned matrix)
   const float* a2;         // device [n_a]
   const float* phi_cs;     // device [2 * 2 n_phi] (cos, sin)
   const float* th_cs;      // device [2 * (2 n_theta + 1)] (cos, sin)
@@ -79,14 +98,20 @@ struct EvDesc {
   uint32_t* hit_pos;    // [4 n_hits] position of the (hit, cell) in its slab list
   float4* hit_rec;      // [n_hits] (x, r2, k, 0)
   float4* list;         // hit records bucketed by slab: [n_slabs * list_cap] or [4 n_hits]
-  uint32_t* tile_cnt;   // [n_tiles] candidates (cells >= threshold) per tile
-  uint32_t* tile_off;   // [n_tiles] first pool entry of each tile's candidates, or kTileOverflow
-  uint2* pool;          // [pool_cap] (cell, votes) of the candidates, ascending within a tile
-  uint32_t pool_cap;    // entries: at least n_tiles * cand_cap, more for large events
-  uint8_t* pk_flag;     // [pool_cap] 1 if the pool entry is a peak
-  uint32_t* ovf_list;   // [n_tiles] tiles whose candidates did not fit the pool
-  uint32_t* tile_pk;    // [n_tiles] peaks per tile
-  uint32_t* group_pk;   // [n_groups] peaks per group of tiles
+  // candidate search (ordinary events): the groups [grp0, grp0 + n_grp) of the event, all of them
+  // except where a caller's fixed scratch holds only a slice at a time
+  uint32_t grp0, n_grp;
+  uint32_t* group_pk;   // [n_grp] peaks per group of jobs (or of tiles: crowded events)
+  uint32_t* super_pk;   // [n_grp / 64, rounded up] peaks per 64 groups
+  uint8_t* job_any;     // [jobs] 1: the job has survivors (its masks are valid)
+  uint8_t* masks;       // [jobs][64 lanes] mask elements; jobs without the flag are not written
+  uint2* seg;           // [n_grp][g.j.seg] each group's peaks (cell, votes)
+  uint4* surv;          // [kLists][kListCap] survivors (cell, votes, group, 0) in no order
+  uint32_t lists;       // 0: no lists are made (crowded slabs)
+  void* clear;          // what the preparation clears: super_pk, group_pk and job_any, or the
+  uint32_t clear_n16;   // stencil's group_pk; in 16-byte units
+  const int64_t* carry_in;  // peaks of the earlier slices, or NULL
+  int64_t* carry_out;       // receives the peaks up to and with this slice, or NULL
   int32_t dense;        // 1: peaks from the stencil over the matrix (crowded events), not the pool
   uint8_t* pk_mask;     // 64-bit words of peak bits of a dense event, kChunkCells cells per
                         // (slab, row, chunk) word, stored by the stencil's workgroups
@@ -98,8 +123,8 @@ constexpr int kChunkCells = 62;
 
 // Launch shape of one grid (ht_tuning resolved against the defaults).
 struct Tiling {
-  int32_t rows, tiles_per_slab, n_tiles, cand_cap, lds_fill, group_tiles, nt_store, fill_tiles;
-  int32_t pool_bound;
+  int32_t rows, tiles_per_slab, n_tiles, lds_fill, group_tiles, nt_store, fill_tiles;
+  int32_t cand_cap;  // reported and accepted only: the survivors of the fill take no pool entries
   int32_t packed_lists;
   int32_t dense_w, dense_rows, dense_hits;  // stencil peak search (DevGrid fields of these names)
 };
@@ -119,20 +144,28 @@ inline size_t th_floats(const ht_grid& g) { return 2 * (2 * (size_t)g.n_theta + 
 // The tables computed on the host in double and rounded once to float, into caller arrays of
 // the sizes above.
 void host_tables_into(const ht_grid& g, float* a2, float* inv_db, float* phi, float* th);
-DevGrid make_devgrid(const ht_grid& g, const DevTables& t, const Tiling& tl);
+DevGrid make_devgrid(const ht_grid& g, const DevTables& t, const Tiling& tl, int n_ev);
+// Sets g.j: the jobs of tiles of `tile_rows` rows, or with 0 those of a matrix that k_scan reads
+// (bands of four rows, or of one in very wide rows). n_ev: events of the launch.
+void set_jobs(DevGrid* g, int tile_rows, int n_ev);
 
 // Whether an event of n_hits hits uses direct slab lists (see kDirectListMax).
 bool direct_lists(const DevGrid& g, int64_t n_hits);
 // Whether the fused fill + peaks of an event of n_hits hits searches its peaks with the stencil
-// over the matrix (crowded events) instead of the candidate pool.
+// over the matrix (crowded events) instead of testing the fill's survivors.
 bool dense_peaks(const DevGrid& g, int64_t n_hits);
-// What an event's peak-search scratch holds: the candidate pool, the stencil's peak mask, or
-// both (request-loop slots, which serve events of either kind).
-enum PeakScratch { kPeakPool = 1, kPeakMask = 2 };
+// What an event's peak-search scratch holds: the survivors' masks, the stencil's peak words, or
+// both (request-loop slots, which serve events of either kind), or neither.
+enum PeakScratch { kPeakBands = 1, kPeakMask = 2 };
 // Bytes of per-event scratch for a grid tiling and an event size, and the carving of it.
-size_t event_scratch_bytes(const DevGrid& g, int64_t n_hits, bool direct, int peaks = kPeakPool);
+size_t event_scratch_bytes(const DevGrid& g, int64_t n_hits, bool direct, int peaks = kPeakBands);
 void carve_event_scratch(const DevGrid& g, int64_t n_hits, bool direct, char* base, EvDesc* ev,
-                         int peaks = kPeakPool);
+                         int peaks = kPeakBands);
+// The peak-search part of it alone, for n_grp groups from grp0 on.
+void carve_peak_scratch(const DevGrid& g, char* base, EvDesc* ev, int peaks, uint32_t grp0, uint32_t n_grp);
+
+// The preparation clears the stencil's peak counts (an event of a layout with both searches).
+void clear_groups(const DevGrid& g, EvDesc* ev);
 
 // Kernel launchers (ht_kernels.hip). `evs` is a device array of n_ev descriptors, or nullptr
 // for a single event passed by value in `ev0`. `max_hits` bounds n_hits over the events.
@@ -140,9 +173,12 @@ hipError_t launch_prep(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, i
                        int64_t max_hits, bool direct, hipStream_t s);
 hipError_t launch_fill(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev,
                        bool emit_candidates, int64_t max_hits, hipStream_t s);
-hipError_t launch_candidates(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev,
-                             hipStream_t s);
-hipError_t launch_peaks(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev,
+// Survivors of a written matrix (g.j set for a scan), for n_grp groups per event. counters: the
+// scan uses the counter pair (no preparation of the same call does): the lists' lengths in one
+// array, and it clears the other.
+hipError_t launch_scan(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev, uint32_t n_grp,
+                       bool counters, hipStream_t s);
+hipError_t launch_peaks(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev, uint32_t n_grp,
                         hipStream_t s);
 // Stencil peak search and ordered write of the events marked dense (others are skipped).
 hipError_t launch_peaks_dense(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev,
@@ -155,6 +191,9 @@ hipError_t launch_fill_atomic(const DevGrid& g, const EvDesc& ev0, const EvDesc*
 hipError_t launch_readout(const DevGrid& g, const ht_peak* peaks, const int64_t* n_found, int64_t cap,
                           ht_track* tracks, double b_min, double db, hipStream_t s);
 
+// Whether the fill of events of up to max_hits hits takes its long-list variant, which makes no
+// list of survivors.
+bool long_lists(const DevGrid& g, int64_t max_hits);
 size_t fill_lds_bytes(const DevGrid& g);
 int n_groups(const DevGrid& g);
 
@@ -175,7 +214,8 @@ int fail_hip(hipError_t e, const char* what);
 int validate_grid(const ht_grid* g);
 uint64_t n_cells(const ht_grid& g);
 // Validates the grid, uploads its tables once per device and picks the tiling.
-int make_device_grid(const ht_grid& g, int dev, DevGrid* out);
+// n_ev: events of the launches it is for (a hint).
+int make_device_grid(const ht_grid& g, int dev, int n_ev, DevGrid* out);
 // The whole batched pipeline (prep, fill with candidates, peaks) for n_ev events whose
 // descriptors are already in device memory.
 // *prep_enqueued is set once the preparation (which counts into and clears the events' counter
@@ -189,10 +229,10 @@ struct BatchSplit {
   hipEvent_t filled[kMaxPieces];  // recorded on the launch stream after each run's fill
   hipEvent_t done;                // recorded on the side stream after the last peak search
 };
-// any_pool / any_dense: whether some event searches its peaks through the candidate pool /
+// any_bands / any_dense: whether some event searches its peaks through the fill's survivors /
 // the stencil (only the kernels needed are launched). split: NULL, or how to overlap.
 int launch_batch(const DevGrid& g, const EvDesc* d_ev, int n_ev, int64_t max_hits, bool direct,
-                 bool any_pool, bool any_dense, hipStream_t s, bool* prep_enqueued,
+                 bool any_bands, bool any_dense, hipStream_t s, bool* prep_enqueued,
                  const BatchSplit* split = nullptr);
 
 }  // namespace ht

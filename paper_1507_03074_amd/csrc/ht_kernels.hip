@@ -9,20 +9,19 @@
 //                 with LDS-aggregated atomics. Very large events use a counting sort instead:
 //                 k_prep counts, then k_bucket scans the counts in LDS and scatters.
 //   k_fill        one workgroup per (slab, tile of A rows): the slab's records vote into an LDS
-//                 tile (ds_add), the cells >= threshold go to the event's candidate pool as
-//                 sorted per-tile chunks (cell, votes), then every cell of the tile is written to
-//                 HBM once with coalesced 16-byte stores (so the matrix needs no memset)
-//   k_peak_test   the pooled candidates spread evenly over the workgroups: each takes the strict
-//                 3^4 test against its 80 neighbours (a cell below the threshold can never beat a
-//                 candidate, so only candidates need testing); peaks are counted per tile and
-//                 per group of 16-64 tiles
-//   k_peak_write  per group: its output offset from the earlier groups' totals; the ordered
-//                 peak list
-//   crowded events (at least dense_hits hits) skip the candidate pool: the fill only writes
+//                 tile (ds_add), then every cell of the tile is written to HBM once with
+//                 coalesced 16-byte stores (so the matrix needs no memset); the survivors, the
+//                 cells >= threshold that no cell of the wave's own job beats, go to bit masks
+//   k_peak_test   one workgroup per group of jobs: the survivors take the strict 3^4 test against
+//                 their 80 neighbours (a cell below the threshold can never beat one at or above
+//                 it, so only survivors need testing); the group's peaks, sorted, and their count
+//   k_peak_write  per group: its output offset from the earlier groups' counts; its peaks go
+//                 to the ordered list
+//   crowded events (at least dense_hits hits) have no masks: the fill only writes
 //   the matrix, k_peak_stencil tests every cell in one read of it (one wave per phi cell, the
 //   theta cells in its registers, the phi neighbours through LDS) into 64-bit peak words, and
 //   k_peak_write_dense writes the ordered peak list from them
-// ht_peaks on an arbitrary matrix replaces prep and fill with k_cand_scan (one read of it).
+// ht_peaks on an arbitrary matrix replaces prep and fill with k_scan (one read of it).
 // No kernel synchronises workgroups with each other: on this multi-XCD part an agent-scope
 // release costs an L2 write-back, while a kernel boundary is cheap.
 //
@@ -147,20 +146,29 @@ __device__ __forceinline__ void tables_to_lds(const DevGrid& g, float* s_tab, co
   *tab_th = s_tab + n_phi;
 }
 
+// Clears the event's peak counts and job flags, and the other counter array: all of it, since an
+// earlier call on a grid with more slabs may have used entries past this grid's n_slabs (the
+// preparation's workgroups share the work).
+__device__ __forceinline__ void clear_jobs(const EvDesc& e)
+{
+  for (int i = (int)(blockIdx.x * kBlock + threadIdx.x); i < kCounterWords; i += (int)(gridDim.x * kBlock))
+    gp(e.slab_cnt_next)[i] = 0u;
+  const u32x4 zero = {0u, 0u, 0u, 0u};
+  GLOBAL u32x4* const p = (GLOBAL u32x4*)gp((uint32_t*)e.clear);
+  for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < e.clear_n16; i += gridDim.x * kBlock) p[i] = zero;
+}
+
 // Direct lists: counts per slab in LDS per workgroup, one global atomic per (workgroup, slab)
 // reserves the workgroup's range of each slab's fixed-capacity list, then the records are
-// written there. slab_cnt is zero on entry and ends holding the list lengths; workgroup 0 clears
-// the other counter array for the next call.
+// written there. slab_cnt is zero on entry and ends holding the list lengths; The workgroups
+// clear the other counter array for the next call.
 template <bool LDS_TABLES>
 __global__ __launch_bounds__(kBlock) void k_prep_direct(DevGrid g, EvDesc ev0, const EvDesc* evs)
 {
   __shared__ uint32_t lcnt[kMaxSlabs];
   extern __shared__ float s_tab[];
   EvDesc e = load_ev(ev0, evs);
-  // clear all of the other array: an earlier call on a grid with more slabs may have used
-  // entries past this grid's n_slabs
-  if (blockIdx.x == 0)
-    for (int i = threadIdx.x; i < kCounterWords; i += kBlock) gp(e.slab_cnt_next)[i] = 0u;
+  clear_jobs(e);
   if ((int64_t)blockIdx.x * kBlock >= e.n_hits) return;  // uniform: whole block idle
   const int64_t h = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   // the hit's coordinates are loaded first, so their round trip overlaps the table copy
@@ -196,17 +204,14 @@ __global__ __launch_bounds__(kBlock) void k_prep_direct(DevGrid g, EvDesc ev0, c
 }
 
 // Counting sort, first pass: counts per slab (LDS, then one global atomic per workgroup and
-// slab) and each record's position within its slab. Workgroup 0 clears the other counter array.
+// slab) and each record's position within its slab. The workgroups clear the other counter array.
 template <bool LDS_TABLES>
 __global__ __launch_bounds__(kBlock) void k_prep(DevGrid g, EvDesc ev0, const EvDesc* evs)
 {
   __shared__ uint32_t lcnt[kMaxSlabs];
   extern __shared__ float s_tab[];
   EvDesc e = load_ev(ev0, evs);
-  // clear all of the other array: an earlier call on a grid with more slabs may have used
-  // entries past this grid's n_slabs
-  if (blockIdx.x == 0)
-    for (int i = threadIdx.x; i < kCounterWords; i += kBlock) e.slab_cnt_next[i] = 0u;
+  clear_jobs(e);
   if ((int64_t)blockIdx.x * kBlock >= e.n_hits) return;  // uniform: whole block idle
   const int64_t h = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   const int64_t hc = min(h, e.n_hits - 1);
@@ -274,38 +279,91 @@ __global__ __launch_bounds__(kBlock) void k_bucket(DevGrid g, EvDesc ev0, const 
   }
 }
 
-// Candidates of an arbitrary matrix: one coalesced read of each tile into LDS, then the same
-// count and ordered emission as the fill's. Workgroup 0 clears the other counter array for the
-// next call.
-template <bool VEC>
-__global__ __launch_bounds__(kBlock) void k_cand_scan(DevGrid g, EvDesc ev0, const EvDesc* evs)
+// Where a job's cells are: its rows are a0 .. of `slab` (absent from row n_a and, in a fill tile,
+// from the tile's end on), lane l's band starts at row a0 + sub * ch and its unit is u.
+struct JobAt {
+  uint32_t slab, a0, st;
+};
+__device__ __forceinline__ JobAt job_at(const DevGrid& g, uint32_t job)
 {
-  extern __shared__ uint32_t smem[];
+  const uint32_t tile = job / (uint32_t)g.j.tile_jobs, k = job - tile * (uint32_t)g.j.tile_jobs;
+  const uint32_t bg = k / (uint32_t)g.j.strips;
+  JobAt j;
+  j.slab = tile / (uint32_t)g.j.tiles_per_slab;
+  j.a0 = (tile - j.slab * (uint32_t)g.j.tiles_per_slab) * (uint32_t)g.j.tile_rows +
+         bg * (uint32_t)(g.j.sub * g.j.ch);
+  j.st = k - bg * (uint32_t)g.j.strips;
+  return j;
+}
+
+// Survivors of an arbitrary matrix: every job's cells read once, straight into registers, two
+// jobs per wave in flight. Bound by the read of the matrix. Stores every job's flag, and clears
+// the peak counts that the test adds to and (counters: no preparation came before) the other
+// counter array.
+template <bool VEC, int CH>
+__global__ __launch_bounds__(kBlock) void k_scan(DevGrid g, EvDesc ev0, const EvDesc* evs, int counters)
+{
   EvDesc e = load_ev(ev0, evs);
-  const int tile = blockIdx.x;
-  if (tile == 0)
-    for (int i = threadIdx.x; i < kCounterWords; i += kBlock) gp(e.slab_cnt_next)[i] = 0u;
-  const int slab = tile / g.tiles_per_slab;
-  const int a0 = (tile - slab * g.tiles_per_slab) * g.rows;
-  const int rows = min(g.rows, g.n_a - a0);
-  const uint32_t nb = (uint32_t)g.n_b;
-  const uint32_t L = (uint32_t)rows * nb;
-  const uint32_t Lpad = ((uint32_t)g.rows * nb + 3u) & ~3u;
-  uint32_t* s_tile = smem;
-  uint32_t* s_small = smem + Lpad;
-  const uint32_t cell0 = ((uint32_t)slab * (uint32_t)g.n_a + (uint32_t)a0) * nb;
-  const GLOBAL uint32_t* src = gp(e.acc) + cell0;
-  if (VEC) {
-    const GLOBAL u32x4* s4 = reinterpret_cast<const GLOBAL u32x4*>(src);
-    u32x4* l4 = reinterpret_cast<u32x4*>(s_tile);
-    for (uint32_t i = threadIdx.x; i < L / 4; i += kBlock) l4[i] = __builtin_nontemporal_load(s4 + i);
-  } else {
-    for (uint32_t i = threadIdx.x; i < L; i += kBlock) s_tile[i] = src[i];
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint32_t nb = (uint32_t)g.n_b, units = (uint32_t)g.j.units, P = (uint32_t)g.j.sub;
+  for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < e.n_grp; i += gridDim.x * kBlock) {
+    gp(e.group_pk)[i] = 0u;
+    if (i < (e.n_grp + 63u) / 64u) gp(e.super_pk)[i] = 0u;
   }
-  lds_barrier();
-  count_candidates<VEC>(s_tile, L, g.threshold, s_small);
-  lds_barrier();
-  emit_candidates<VEC>(g, e, tile, cell0, s_tile, L, s_small);
+  if (counters)  // uniform
+    for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < (uint32_t)kCounterWords; i += gridDim.x * kBlock)
+      gp(e.slab_cnt_next)[i] = 0u;
+  const uint32_t sub = P > 1u ? lane / units : 0u;
+  const uint32_t unit0 = P > 1u ? lane - sub * units : lane;
+  const uint32_t lmask = unit0 > 0u ? ~0u : 0u;
+  const uint32_t rmask = P > 1u && unit0 + 1u == units ? 0u : ~0u;
+  const uint32_t gj = (uint32_t)g.j.group_jobs;
+  const uint64_t first = (uint64_t)e.grp0 * gj;
+  const uint64_t n = min((uint64_t)g.j.n_jobs - first, (uint64_t)e.n_grp * gj);
+  const u32x4 zero4 = {0u, 0u, 0u, 0u};
+  u32x4 v[2][CH];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const uint64_t jl = (uint64_t)blockIdx.x * 8u + (uint32_t)h * 4u + wave;
+#pragma unroll
+    for (int q = 0; q < CH; ++q) v[h][q] = zero4;
+    if (jl < n) {  // uniform
+      const JobAt at = job_at(g, (uint32_t)(first + jl));
+      const uint32_t u = P > 1u ? unit0 : at.st * 64u + lane;
+      const uint32_t a = at.a0 + sub * CH;
+      const bool in = u < units && sub < P;
+#pragma unroll
+      for (int q = 0; q < CH; ++q) {
+        if (in && a + (uint32_t)q < (uint32_t)g.n_a) {
+          const GLOBAL uint32_t* src = gp((const uint32_t*)e.acc) + (at.slab * (uint32_t)g.n_a + a + (uint32_t)q) * nb + 4u * u;
+          if (VEC) {
+            v[h][q] = __builtin_nontemporal_load(reinterpret_cast<const GLOBAL u32x4*>(src));
+          } else if (4u * u + 3u < nb) {
+            v[h][q] = *reinterpret_cast<const GLOBAL u32x4_a4*>(src);
+          } else {
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+              if (4u * u + (uint32_t)k < nb) v[h][q][k] = src[k];
+          }
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const uint64_t jl = (uint64_t)blockIdx.x * 8u + (uint32_t)h * 4u + wave;
+    if (jl >= n) return;  // uniform
+    const uint32_t m = job_survivors<CH>(v[h], g.threshold, lmask, rmask);
+    if (__builtin_amdgcn_ballot_w64(m != 0u) == 0u) {  // uniform
+      if (lane == 0u) gp(e.job_any)[jl] = 0;
+      continue;
+    }
+    put_mask<CH>(e, (uint32_t)jl, lane, m);
+    const JobAt at = job_at(g, (uint32_t)(first + jl));
+    const uint32_t c0 = (at.slab * (uint32_t)g.n_a + at.a0 + sub * CH) * nb + 4u * (P > 1u ? unit0 : at.st * 64u + lane);
+    list_survivors<CH>(e, (uint32_t)jl, (uint32_t)jl / gj, lane, m, c0, nb, v[h]);
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -324,76 +382,87 @@ __device__ __forceinline__ void cell_coords(const DevGrid& g, uint32_t c, uint32
 }
 
 
-// The 27 neighbour rows are taken one theta slice (9 rows of three cells, one 12-byte load each)
-// at a time, its own theta first: the nine loads of a slice are issued together, and a
-// candidate beaten in one slice skips the rest (most candidates are beaten early). The window
-// of a row starts at min(max(b, 1) - 1, n_b - 3), so it stays inside the row; absent rows
-// (outside theta or A, or phi neighbours across sectors) read the candidate's own row and are
-// masked out.
-__device__ bool is_peak(const DevGrid& g, const uint32_t* __restrict__ acc, uint32_t c, uint32_t v)
+// A cell under test: its coordinates and the window of three columns that its neighbour rows are
+// read through, which starts at min(max(b, 1) - 1, n_b - 3) so that it stays inside the row (grids
+// with n_b < 3 read their one or two columns).
+struct TestCell {
+  uint32_t c, v, t, p, a, b, w0;
+};
+__device__ __forceinline__ TestCell test_cell(const DevGrid& g, uint32_t c, uint32_t v)
+{
+  TestCell x;
+  x.c = c;
+  x.v = v;
+  cell_coords(g, c, &x.t, &x.p, &x.a, &x.b);
+  x.w0 = min(max(x.b, 1u) - 1u, max((uint32_t)g.n_b, 3u) - 3u);
+  return x;
+}
+// Neighbour row (dt, dp, da): its first window cell, or the cell's own window where the row is
+// absent (outside theta or A, or a phi neighbour across sectors; *in false). Phi wraps.
+__device__ __forceinline__ uint32_t row_window(const DevGrid& g, const TestCell& x, int dt, int dp, int da, bool* in)
 {
   const uint32_t nb = (uint32_t)g.n_b, na = (uint32_t)g.n_a, np = (uint32_t)g.n_phi;
-  uint32_t t, p, a, b;
-  cell_coords(g, c, &t, &p, &a, &b);
-  const uint32_t pm = p == 0 ? np - 1 : p - 1;
-  const uint32_t pp1 = p + 1 == np ? 0 : p + 1;
-  if (nb < 3) {
-    // narrow rows: one load per neighbour
-    bool beaten = false;
-    for (int k = 0; k < 27; ++k) {
-      const int dt = k / 9 - 1, dp = (k / 3) % 3 - 1, da = k % 3 - 1;
-      const int tt = (int)t + dt, aa = (int)a + da;
-      if (tt < 0 || tt >= g.n_theta || aa < 0 || aa >= (int)na) continue;
-      if (g.phi_sectors && dp != 0) continue;
-      const uint32_t pp = dp < 0 ? pm : (dp > 0 ? pp1 : p);
-      const uint32_t rowc = (((uint32_t)tt * np + pp) * na + (uint32_t)aa) * nb;
-      for (int db = -1; db <= 1; ++db) {
-        const int bb = (int)b + db;
-        if (bb < 0 || bb >= (int)nb || (dt == 0 && dp == 0 && da == 0 && db == 0)) continue;
-        const uint32_t n = rowc + (uint32_t)bb;
-        const uint32_t w = gp(acc)[n];
-        beaten |= w > v || (w == v && n < c);
-      }
-    }
-    return !beaten;
+  const int tt = (int)x.t + dt, aa = (int)x.a + da;
+  *in = tt >= 0 && tt < g.n_theta && aa >= 0 && aa < (int)na && !(g.phi_sectors && dp != 0);
+  uint32_t pp = x.p;
+  if (dp < 0) pp = x.p == 0u ? np - 1u : x.p - 1u;
+  if (dp > 0) pp = x.p + 1u == np ? 0u : x.p + 1u;
+  return (*in ? (((uint32_t)tt * np + pp) * na + (uint32_t)aa) * nb : x.c - x.b) + x.w0;
+}
+struct Row3 {
+  uint32_t w[3];
+};
+// NARROW: rows of fewer than three cells; else one 12-byte load.
+template <bool NARROW>
+__device__ __forceinline__ Row3 load_row(const DevGrid& g, const uint32_t* acc, uint32_t at)
+{
+  const GLOBAL uint32_t* r = gp(acc) + at;
+  Row3 o;
+  o.w[0] = r[0];
+  o.w[1] = !NARROW || g.n_b > 1 ? r[1] : 0u;
+  o.w[2] = !NARROW ? r[2] : 0u;
+  return o;
+}
+// Whether the row beats the cell under (votes, -index): a row other than the cell's own lies
+// wholly before it (an equal count beats it) or after it. v >= 1, so zeros beat nothing. (Votes
+// may be any 32-bit count: no + 1 here.)
+__device__ __forceinline__ bool row_wins(const TestCell& x, const Row3& r, uint32_t at, bool own)
+{
+  bool beaten = false;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    const uint32_t bb = x.w0 + (uint32_t)q;
+    const bool near = bb + 1u >= x.b && bb <= x.b + 1u && !(own && bb == x.b);
+    const bool before = own ? bb < x.b : at < x.c;
+    beaten |= near && (r.w[q] > x.v || (before && r.w[q] == x.v));
   }
-  const uint32_t w0 = min(max(b, 1u) - 1u, nb - 3u);
+  return beaten;
+}
+// The nine neighbour rows of theta cell t + dt, all loaded together.
+template <bool NARROW>
+__device__ __forceinline__ bool slice_wins(const DevGrid& g, const uint32_t* acc, const TestCell& x, int dt)
+{
+  Row3 r[9];
+  uint32_t at[9];
+  bool in[9];
 #pragma unroll
-  for (int slice = 0; slice < 3; ++slice) {
-    const int dt = slice == 0 ? 0 : (slice == 1 ? -1 : 1);
-    const int tt = (int)t + dt;
-    if (tt < 0 || tt >= g.n_theta) continue;
-    uint32_t row[9][3];
-    uint32_t base[9];
-    bool rv[9];
-#pragma unroll
-    for (int k = 0; k < 9; ++k) {
-      const int dp = k / 3 - 1, da = k % 3 - 1;
-      const int aa = (int)a + da;
-      rv[k] = aa >= 0 && aa < (int)na && !(g.phi_sectors && dp != 0);
-      const uint32_t pp = dp < 0 ? pm : (dp > 0 ? pp1 : p);
-      base[k] = (rv[k] ? (((uint32_t)tt * np + pp) * na + (uint32_t)aa) * nb : c - b) + w0;
-      const GLOBAL uint32_t* rw = gp(acc) + base[k];
-      row[k][0] = rw[0];
-      row[k][1] = rw[1];
-      row[k][2] = rw[2];
-    }
-    bool beaten = false;
-#pragma unroll
-    for (int k = 0; k < 9; ++k) {
-      const bool centre_row = dt == 0 && k == 4;
-#pragma unroll
-      for (int q = 0; q < 3; ++q) {
-        const uint32_t bb = w0 + (uint32_t)q;
-        // inside the window; neighbour iff |bb - b| <= 1 and not the candidate itself
-        const bool near = bb + 1u >= b && bb <= b + 1u && !(centre_row && bb == b);
-        const uint32_t n = base[k] + (uint32_t)q;
-        beaten |= rv[k] && near && (row[k][q] > v || (row[k][q] == v && n < c));
-      }
-    }
-    if (beaten) return false;
+  for (int k = 0; k < 9; ++k) {
+    at[k] = row_window(g, x, dt, k / 3 - 1, k % 3 - 1, &in[k]);
+    r[k] = load_row<NARROW>(g, acc, at[k]);
   }
-  return true;
+  bool beaten = false;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) beaten |= in[k] && row_wins(x, r[k], at[k], dt == 0 && k == 4);
+  return beaten;
+}
+
+// Block b of a grid of G runs on XCD b % 8 (workgroups are dealt to the eight XCDs in turn); the
+// number this returns is a bijection of [0, G) under which XCD x runs one contiguous range of
+// numbers: the first G % 8 XCDs take ceil(G / 8) of them, the others floor(G / 8).
+__device__ __forceinline__ uint32_t xcd_contiguous(uint32_t b, uint32_t G)
+{
+  const uint32_t x = b & 7u, i = b >> 3, q = G >> 3, r = G & 7u;
+  return x < r ? x * (q + 1u) + i : r * (q + 1u) + (x - r) * q + i;
 }
 
 __device__ __forceinline__ void tile_range(const DevGrid& g, int tile, uint32_t* cell0, uint32_t* L)
@@ -405,287 +474,389 @@ __device__ __forceinline__ void tile_range(const DevGrid& g, int tile, uint32_t*
   *L = (uint32_t)rows * (uint32_t)g.n_b;
 }
 
-// Candidates of an arbitrary matrix whose B rows are too wide for an LDS tile (grids that also
-// fill through global atomics; a tile is then one row of up to 2^24 cells): the same count and
-// ordered emission as k_cand_scan, read straight from the matrix, so the row is read twice.
-// Workgroup 0 clears the other counter array for the next call.
-__global__ __launch_bounds__(kBlock) void k_cand_scan_wide(DevGrid g, EvDesc ev0, const EvDesc* evs)
-{
-  __shared__ uint32_t s_small[16];
-  EvDesc e = load_ev(ev0, evs);
-  const int tile = blockIdx.x;
-  if (tile == 0)
-    for (int i = threadIdx.x; i < kCounterWords; i += kBlock) gp(e.slab_cnt_next)[i] = 0u;
-  uint32_t cell0, L;
-  tile_range(g, tile, &cell0, &L);
-  const uint32_t* src = e.acc + cell0;
-  count_candidates<false>(src, L, g.threshold, s_small);
-  lds_barrier();
-  emit_candidates<false>(g, e, tile, cell0, src, L, s_small);
-}
+// Peak test of the survivors. It is bound by the latency of its gather (27 rows of 12 bytes, each
+// in a cache line of its own). Two forms:
+//
+// From the lists, when they are made and every survivor fits them (ordinary events: 2.7k
+// survivors on the paper event): spread evenly over the grid whatever their groups, half a wave
+// each, one lane per neighbour row, so the whole test is two memory round trips (the list, the
+// rows) and a third for each peak's place in its group's segment. Survivors cluster (the
+// fullest of the paper event's 1024 groups holds 157 of them, the mean group 2.7), and a
+// workgroup per group waited 15 us for that one.
+//
+// Else from the masks, one workgroup per group of jobs. The flagged jobs' masks (64 jobs at a
+// time, their loads in flight together) are turned into one list of survivors in LDS, shared by
+// the four waves, so the tests run with full waves however the survivors lie in their jobs: up
+// to kFew of them half a wave each, more a lane each, the nine rows of the own theta cell first
+// (they beat most: adjacent phi cells hold the same circles), and those left, packed again into
+// full waves, the rows of the two theta neighbours. The group's peaks are then sorted by rank in
+// LDS and stored in the group's segment.
+constexpr uint32_t kList = 1024;  // four jobs have at most this many survivors (one per 2 x 2 cells)
+constexpr uint32_t kFew = 64;
+constexpr uint32_t kSuperGroups = 2048;
+constexpr uint32_t kTestBlocks = 16 * kLists * 32 / kBlock;
+constexpr uint32_t kTestGrid = 8192;
+constexpr uint32_t kPassJobs = 64;
 
-// Largest t with pre[t] <= f, given pre[0] <= f < pre[kGroupTiles] and pre non-decreasing: a
-// fixed number of halving steps, with no branch.
-__device__ __forceinline__ int group_tile_of(const uint32_t* pre, uint32_t f)
-{
-  static_assert((kGroupTiles & (kGroupTiles - 1)) == 0, "halving search over a power of two");
-  int lo = 0;
-#pragma unroll
-  for (int step = kGroupTiles / 2; step > 0; step >>= 1) lo += pre[lo + step] <= f ? step : 0;
-  return lo;
-}
-
-// Whether any cell of neighbour row k (0..26: dt, dp, da in {-1, 0, 1}, row-major) of candidate
-// c with v votes beats it under (votes, -index). Rows outside theta or A are absent; phi wraps.
-// Loads one 12-byte window of three cells; the window of a row starts at
-// min(max(b, 1) - 1, n_b - 3), so it stays inside the row.
-__device__ bool row_beats(const DevGrid& g, const uint32_t* __restrict__ acc, uint32_t c, uint32_t v, int k)
-{
-  const uint32_t nb = (uint32_t)g.n_b, na = (uint32_t)g.n_a, np = (uint32_t)g.n_phi;
-  uint32_t t, p, a, b;
-  cell_coords(g, c, &t, &p, &a, &b);
-  const int dt = k / 9 - 1, dp = (k / 3) % 3 - 1, da = k % 3 - 1;
-  const int tt = (int)t + dt, aa = (int)a + da;
-  if (tt < 0 || tt >= g.n_theta || aa < 0 || aa >= (int)na) return false;
-  if (g.phi_sectors && dp != 0) return false;  // sectors have no phi neighbours
-  const uint32_t pp = dp < 0 ? (p == 0 ? np - 1 : p - 1) : (dp > 0 ? (p + 1 == np ? 0 : p + 1) : p);
-  const uint32_t rowc = (((uint32_t)tt * np + pp) * na + (uint32_t)aa) * nb;
-  const bool centre_row = k == 13;
-  if (nb < 3) {
-    bool beaten = false;
-    for (uint32_t bb = b == 0 ? 0 : b - 1; bb <= b + 1 && bb < nb; ++bb) {
-      if (centre_row && bb == b) continue;
-      const uint32_t n = rowc + bb;
-      const uint32_t w = gp(acc)[n];
-      beaten |= w > v || (w == v && n < c);
-    }
-    return beaten;
-  }
-  const uint32_t w0 = min(max(b, 1u) - 1u, nb - 3u);
-  const GLOBAL uint32_t* rw = gp(acc) + rowc + w0;
-  const uint32_t vals[3] = {rw[0], rw[1], rw[2]};
-  bool beaten = false;
-#pragma unroll
-  for (int q = 0; q < 3; ++q) {
-    const uint32_t bb = w0 + (uint32_t)q;
-    const bool near = bb + 1u >= b && bb <= b + 1u && !(centre_row && bb == b);
-    const uint32_t n = rowc + bb;
-    beaten |= near && (vals[q] > v || (vals[q] == v && n < c));
-  }
-  return beaten;
-}
-
-__device__ __forceinline__ void count_peak(const DevGrid& g, const EvDesc& e, uint32_t c)
-{
-  // (slab, a) from the row index c / n_b: a slab of one cell row by 2^32 cells (n_a n_b = 2^32)
-  // would wrap a 32-bit slab size
-  const uint32_t row = c / (uint32_t)g.n_b;
-  const uint32_t slab = row / (uint32_t)g.n_a;
-  const uint32_t a = row - slab * (uint32_t)g.n_a;
-  const uint32_t tile = slab * (uint32_t)g.tiles_per_slab + a / (uint32_t)g.rows;
-  gatomic_add(e.tile_pk + tile, 1u);
-  gatomic_add(e.group_pk + tile / (uint32_t)g.group_tiles, 1u);
-}
-
-// Peak test of every pooled candidate, spread evenly over the grid whatever tiles they came
-// from. Few candidates (at most two passes of the grid): half a wave (32 lanes) per candidate,
-// one lane per neighbour row, so a candidate costs one load per lane and a ballot, and the
-// whole test is about one memory round trip. Many candidates: one thread per candidate, its 27
-// row loads issued back to back; each workgroup takes one contiguous run of the pool (whole
-// waves), so the waves of a CU test neighbouring cells and share their rows in the L1, and the
-// runs of one XCD are adjacent, so its L2 holds one region. Each result goes to pk_flag; a
-// peak adds one to its tile's and its group's counts. Tiles whose candidates did not fit the
-// pool are counted densely, one wave per tile.
+template <bool NARROW>
 __global__ __launch_bounds__(kBlock) void k_peak_test(DevGrid g, EvDesc ev0, const EvDesc* evs)
 {
+  __shared__ uint32_t s_pos[kList];         // survivors: slot << 10 | lane << 4 | bit of the mask
+  __shared__ uint32_t s_m[kPassJobs * 32];  // masks of the pass, 16 bits per lane
+  __shared__ uint32_t s_slab[kPassJobs], s_a0[kPassJobs], s_st[kPassJobs];  // where its jobs are
+  __shared__ __align__(16) uint32_t s_pc[kSegMax];
+  __shared__ uint32_t s_pv[kSegMax];
+  __shared__ uint16_t s_ids[kBlock];
+  __shared__ uint32_t s_w[4], s_n, s_np;
   EvDesc e = load_ev(ev0, evs);
   if (e.dense) return;  // uniform: searched by the stencil
-  const int lane = threadIdx.x & 63, half = lane >> 5, k = lane & 31;
-  // workgroups are dealt to the 8 XCDs in turn: give each XCD one contiguous run of blocks
-  const uint32_t blk =
-      gridDim.x % 8u ? blockIdx.x : (blockIdx.x % 8u) * (gridDim.x / 8u) + blockIdx.x / 8u;
-  const uint32_t wave = blk * (kBlock / 64) + (threadIdx.x >> 6);
-  const uint32_t n_waves = gridDim.x * (kBlock / 64);
-  // this half-wave's first entry is loaded before the entry count is known (an index inside
-  // the pool is always readable), so the count and the entry cost one round trip
-  const uint32_t i_first = 2u * wave + (uint32_t)half;
-  uint2 cv_first = make_uint2(0u, 0u);
-  if (i_first < e.pool_cap) cv_first = ld_cand(e.pool, i_first);
-  // the three counters load together (none waits for another)
-  const uint32_t cut = gp(e.slab_cnt)[kPoolCut];
-  const uint32_t reserved = gp(e.slab_cnt)[kPoolCounter];
-  const uint32_t n_ovf = gp(e.slab_cnt)[kOvfCounter];
-  const uint32_t n_valid = min(cut ? e.pool_cap + 1u - cut : reserved, e.pool_cap);
-  const uint32_t* acc = e.acc;
-  if (n_valid <= 4u * n_waves) {
-    for (uint32_t i0 = 2u * wave; i0 < n_valid; i0 += 2u * n_waves) {  // wave-uniform
-      const uint32_t i = i0 + (uint32_t)half;
-      const bool live = i < n_valid;
-      uint2 cv = make_uint2(0u, 0u);
-      bool beaten = false;
-      if (live) {
-        cv = i == i_first ? cv_first : ld_cand(e.pool, i);
-        if (k < 27) beaten = row_beats(g, acc, cv.x, cv.y, k);
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const bool supers = e.n_grp > kSuperGroups;
+  const uint32_t seg_cap = (uint32_t)g.j.seg;
+  if (e.lists) {  // uniform
+    // half wave h takes entries h / kLists, h / kLists + step, ... of list h % kLists, four of them
+    // in flight (half waves past a multiple of kLists of them take none)
+    const uint32_t hw = blockIdx.x * (kBlock / 32) + (threadIdx.x >> 5), k = threadIdx.x & 31u;
+    const uint32_t l = hw % kLists, step = gridDim.x * (kBlock / 32) / kLists;
+    const GLOBAL u32x4* const list = (const GLOBAL u32x4*)gp((const uint4*)e.surv) + l * kListCap;
+    // the first entry is loaded before the list's length is known: one round trip for both
+    u32x4 en[4];
+    en[0] = list[min(hw / kLists, kListCap - 1u)];
+    const uint32_t n = gp((const uint32_t*)e.slab_cnt)[kListLens + l * kListLine];
+    if (gp((const uint32_t*)e.slab_cnt)[kListOver] == 0u) {  // uniform over the grid
+      const int kk = (int)min(k, 26u), dt = kk / 9 - 1, dp = kk / 3 % 3 - 1, da = kk % 3 - 1;
+      const uint32_t n_max = max((uint32_t)__builtin_amdgcn_readlane((int)n, 0), (uint32_t)__builtin_amdgcn_readlane((int)n, 32));
+      const uint32_t i_wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(hw / kLists));  // the same in both halves
+      if (i_wave >= step) return;
+      for (uint32_t i0 = i_wave; i0 < n_max; i0 += 4u * step) {  // wave-uniform
+        bool beaten[4];
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q) {
+          const uint32_t i = i0 + q * step;
+          if (i < n_max && i != i_wave) en[q] = list[min(i, kListCap - 1u)];
+        }
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q) {
+          const uint32_t i = i0 + q * step;
+          beaten[q] = true;
+          if (i < n) {
+            const TestCell x = test_cell(g, en[q].x, en[q].y);
+            bool in;
+            const uint32_t at = row_window(g, x, dt, dp, da, &in);
+            beaten[q] = row_wins(x, load_row<NARROW>(g, e.acc, at), at, kk == 13) && in && k < 27u;
+          }
+        }
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q) {
+          const uint32_t hm = (uint32_t)(__builtin_amdgcn_ballot_w64(beaten[q]) >> (lane & 32u));
+          if (k == 0u && hm == 0u) {
+            const uint32_t o = gatomic_add(e.group_pk + en[q].z, 1u);
+            if (supers) gatomic_add(e.super_pk + en[q].z / 64u, 1u);
+            const u32x2 pk = {en[q].x, en[q].y};
+            if (o < seg_cap) ((GLOBAL u32x2*)gp(e.seg))[(size_t)en[q].z * seg_cap + o] = pk;
+          }
+        }
       }
-      const uint64_t m = __ballot(beaten);
-      const uint32_t hm = (uint32_t)(m >> (32 * half));
-      if (live && k == 0) {
-        const bool pk = hm == 0u;
-        gp(e.pk_flag)[i] = pk ? 1 : 0;
-        if (pk) count_peak(g, e, cv.x);
-      }
-    }
-  } else {
-    // the run length is a whole number of waves; the last runs may be short or empty. Bounds
-    // and index are 64-bit: the pool may hold nearly 2^32 entries.
-    const uint64_t per = (((uint64_t)n_valid + gridDim.x - 1u) / gridDim.x + 63u) & ~(uint64_t)63u;
-    const uint64_t i_end = min((uint64_t)n_valid, (uint64_t)(blk + 1u) * per);
-    for (uint64_t i = (uint64_t)blk * per + threadIdx.x; i < i_end; i += kBlock) {
-      const uint2 cv = ld_cand(e.pool, i);
-      const bool pk = is_peak(g, acc, cv.x, cv.y);
-      gp(e.pk_flag)[i] = pk ? 1 : 0;
-      if (pk) count_peak(g, e, cv.x);
+      return;
     }
   }
-  for (uint32_t j = wave; j < n_ovf; j += n_waves) {
-    const int tile = (int)gp(e.ovf_list)[j];
-    uint32_t cell0, L;
-    tile_range(g, tile, &cell0, &L);
-    uint32_t mine = 0;
-    for (uint32_t q = (uint32_t)lane; q < L; q += 64) {
-      const uint32_t c = cell0 + q;
-      const uint32_t v = gp(acc)[c];
-      if (v >= g.threshold && is_peak(g, acc, c, v)) ++mine;
+  const bool two = g.j.elem_bytes == 2;
+  const uint32_t* acc = e.acc;
+  const uint32_t na = (uint32_t)g.n_a, nb = (uint32_t)g.n_b, np = (uint32_t)g.n_phi;
+  const uint32_t P = (uint32_t)g.j.sub, ch = (uint32_t)g.j.ch, units = (uint32_t)g.j.units;
+  uint16_t* const m16 = reinterpret_cast<uint16_t*>(s_m);
+  // the survivor of a list entry
+  auto cell_of = [&](uint32_t pos) {
+    const uint32_t slot = pos >> 10, l = pos >> 4 & 63u, bit = pos & 15u;
+    const uint32_t sub = P > 1u ? l / units : 0u;
+    const uint32_t slab = s_slab[slot];
+    TestCell x;
+    x.a = s_a0[slot] + sub * ch + (bit >> 2);
+    x.b = 4u * (P > 1u ? l - sub * units : s_st[slot] * 64u + l) + (bit & 3u);
+    x.t = slab >> 16;
+    x.p = slab & 0xffffu;
+    x.c = ((x.t * np + x.p) * na + x.a) * nb + x.b;
+    x.v = gp(acc)[x.c];
+    x.w0 = min(max(x.b, 1u) - 1u, max(nb, 3u) - 3u);
+    return x;
+  };
+  auto keep = [&](const TestCell& x) {
+    const uint32_t i = atomicAdd(&s_np, 1u);
+    if (i < seg_cap) {
+      s_pc[i] = x.c;
+      s_pv[i] = x.v;
     }
-    mine = wave_sum(mine);
-    if (lane == 0 && mine) {
-      gatomic_add(e.tile_pk + tile, mine);
-      gatomic_add(e.group_pk + tile / g.group_tiles, mine);
+  };
+  auto rank_of = [](uint64_t m, uint32_t from) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, from));
+  };
+  // each XCD takes one contiguous range of groups, so the rows that neighbouring groups share are
+  // fetched into one L2
+  const uint32_t per = (e.n_grp + gridDim.x - 1u) / gridDim.x;
+  const uint32_t g0 = xcd_contiguous(blockIdx.x, gridDim.x) * per;
+  for (uint32_t grp = g0; grp < min(g0 + per, e.n_grp); ++grp) {  // uniform
+  const uint32_t gj = (uint32_t)g.j.group_jobs;
+  const uint64_t first = (uint64_t)(e.grp0 + grp) * gj;
+  const uint32_t nj = (uint32_t)min((uint64_t)gj, (uint64_t)g.j.n_jobs - first);
+  const uint64_t l0 = (uint64_t)grp * gj;  // the group's first job in the event's arrays
+  if (threadIdx.x == 0) s_np = 0u;
+  for (uint32_t win = 0u; win < nj; win += kBlock) {  // uniform
+    // the window's flagged jobs, in order
+    const uint32_t j = win + threadIdx.x;
+    uint32_t flag = 0u;
+    if (j < nj) flag = gp(e.job_any)[l0 + j];
+    const uint64_t fb = __builtin_amdgcn_ballot_w64(flag != 0u);
+    if (lane == 0u) s_w[w] = (uint32_t)__builtin_popcountll(fb);
+    lds_barrier();
+    const uint32_t f1 = s_w[0], f2 = f1 + s_w[1], f3 = f2 + s_w[2], nf = f3 + s_w[3];
+    if (flag) s_ids[rank_of(fb, w == 0u ? 0u : w == 1u ? f1 : w == 2u ? f2 : f3)] = (uint16_t)threadIdx.x;
+    lds_barrier();
+    for (uint32_t p0 = 0u; p0 < nf; p0 += kPassJobs) {  // uniform
+      const uint32_t n_job = min(kPassJobs, nf - p0);
+      // the pass's masks: slot w + 4 i is this wave's i-th job
+      uint32_t m[kPassJobs / 4];
+#pragma unroll
+      for (uint32_t i = 0; i < kPassJobs / 4; ++i) {
+        m[i] = 0u;
+        if (w + 4u * i < n_job) {  // uniform
+          const size_t at = (size_t)(l0 + win + s_ids[p0 + w + 4u * i]) * 64u + lane;
+          m[i] = two ? ((const GLOBAL uint16_t*)gp((const uint8_t*)e.masks))[at]
+                     : gp((const uint8_t*)e.masks)[at];
+        }
+      }
+      if (threadIdx.x < n_job) {  // meanwhile, a lane per job: where it is
+        const JobAt at = job_at(g, (uint32_t)(first + win + s_ids[p0 + threadIdx.x]));
+        const uint32_t t = at.slab / np;
+        s_slab[threadIdx.x] = t << 16 | (at.slab - t * np);
+        s_a0[threadIdx.x] = at.a0;
+        s_st[threadIdx.x] = at.st;
+      }
+      uint32_t cnt = 0u;
+#pragma unroll
+      for (uint32_t i = 0; i < kPassJobs / 4; ++i) {
+        if (w + 4u * i < n_job) {  // uniform
+          m16[(w + 4u * i) * 64u + lane] = (uint16_t)m[i];
+          cnt += (uint32_t)__builtin_popcount(m[i]);
+        }
+      }
+      cnt = wave_sum(cnt);
+      if (lane == 0u) s_w[w] = cnt;
+      if (threadIdx.x == 0) s_n = 0u;
+      lds_barrier();
+      // all the jobs' survivors at once where the list holds them, else four jobs at a time
+      const uint32_t step = s_w[0] + s_w[1] + s_w[2] + s_w[3] <= kList ? kPassJobs / 4 : 1u;
+      for (uint32_t i0 = 0u; 4u * i0 < n_job; i0 += step) {               // uniform
+        for (uint32_t i = i0; i < i0 + step && w + 4u * i < n_job; ++i) {  // uniform
+          const uint32_t slot = w + 4u * i;
+          uint32_t mm = m16[slot * 64u + lane];
+          const uint32_t c = (uint32_t)__builtin_popcount(mm), incl = wave_incl_scan(c);
+          uint32_t from = 0u;
+          if (lane == 63u) from = atomicAdd(&s_n, incl);
+          uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)from, 63) + incl - c;
+          while (mm) {
+            s_pos[at++] = (slot << 10) | (lane << 4) | (uint32_t)__builtin_ctz(mm);
+            mm &= mm - 1u;
+          }
+        }
+        lds_barrier();
+        const uint32_t n = s_n;  // uniform
+        if (n <= kFew) {
+          const uint32_t half = threadIdx.x >> 5, k = threadIdx.x & 31u;
+          const int kk = (int)min(k, 26u), dt = kk / 9 - 1, dp = kk / 3 % 3 - 1, da = kk % 3 - 1;
+          for (uint32_t b0 = 0u; b0 < n; b0 += 32u) {  // uniform
+            TestCell x[4];
+            bool beaten[4];
+#pragma unroll
+            for (uint32_t q = 0; q < 4; ++q) {
+              x[q] = cell_of(s_pos[min(b0 + half + 8u * q, n - 1u)]);
+              bool in;
+              const uint32_t at = row_window(g, x[q], dt, dp, da, &in);
+              beaten[q] = row_wins(x[q], load_row<NARROW>(g, acc, at), at, kk == 13) && in && k < 27u;
+            }
+#pragma unroll
+            for (uint32_t q = 0; q < 4; ++q) {
+              const uint32_t i = b0 + half + 8u * q;
+              const uint32_t hm = (uint32_t)(__builtin_amdgcn_ballot_w64(beaten[q]) >> (lane & 32u));
+              if (k == 0u && i < n && hm == 0u) keep(x[q]);
+            }
+          }
+        } else {
+          uint32_t n2 = 0u;
+          for (uint32_t b0 = 0u; b0 < n; b0 += kBlock) {  // uniform
+            const uint32_t i = b0 + threadIdx.x;
+            uint32_t pos = 0u;
+            bool alive = false;
+            if (i < n) {
+              pos = s_pos[i];
+              alive = !slice_wins<NARROW>(g, acc, cell_of(pos), 0);
+            }
+            const uint64_t b = __builtin_amdgcn_ballot_w64(alive);
+            if (lane == 0u) s_w[w] = (uint32_t)__builtin_popcountll(b);
+            lds_barrier();  // every wave has read its entries: the front of the list is free
+            const uint32_t c1 = s_w[0], c2 = c1 + s_w[1], c3 = c2 + s_w[2];
+            if (alive) s_pos[rank_of(b, n2 + (w == 0u ? 0u : w == 1u ? c1 : w == 2u ? c2 : c3))] = pos;
+            n2 += c3 + s_w[3];
+            lds_barrier();
+          }
+          for (uint32_t i = threadIdx.x; i < n2; i += kBlock) {
+            const TestCell x = cell_of(s_pos[i]);
+            const bool w0 = g.n_theta > 1 && slice_wins<NARROW>(g, acc, x, -1);  // uniform condition
+            const bool w1 = g.n_theta > 1 && slice_wins<NARROW>(g, acc, x, 1);
+            if (!w0 && !w1) keep(x);
+          }
+        }
+        lds_barrier();
+        if (threadIdx.x == 0) s_n = 0u;
+        lds_barrier();
+      }
     }
+  }
+  lds_barrier();
+  const uint32_t n = s_np;
+  if (threadIdx.x == 0) {
+    gp(e.group_pk)[grp] = n;
+    if (n && supers) gatomic_add(e.super_pk + grp / 64u, n);
+  }
+  if (n == 0u || n > seg_cap) {  // uniform
+    lds_barrier();
+    continue;
+  }
+  // pad to whole 16-byte reads with cells that rank after every peak's
+  if (threadIdx.x < 4u && n + threadIdx.x < seg_cap) s_pc[n + threadIdx.x] = 0xffffffffu;
+  lds_barrier();
+  const u32x4* s4 = reinterpret_cast<const u32x4*>(s_pc);
+  for (uint32_t i = threadIdx.x; i < n; i += kBlock) {
+    const uint32_t c = s_pc[i];
+    uint32_t r = 0u;
+    for (uint32_t k = 0u; k < (n + 3u) / 4u; ++k) {
+      const u32x4 o = s4[k];
+      r += (o.x < c ? 1u : 0u) + (o.y < c ? 1u : 0u) + (o.z < c ? 1u : 0u) + (o.w < c ? 1u : 0u);
+    }
+    const u32x2 pk = {c, s_pv[i]};
+    ((GLOBAL u32x2*)gp(e.seg))[(size_t)grp * seg_cap + r] = pk;
+  }
+  lds_barrier();  // the next group clears what this one still reads
   }
 }
 
-// One workgroup per group of tiles: its output offset is the sum of the earlier groups' peak
-// counts; the group's pooled candidates are walked in order (tile by tile, each tile's chunk
-// ascending, kWalkChunks * kBlock of them per memory round trip) and the flagged ones written
-// out; tiles that did not fit the pool are re-scanned densely.
+// Ordered peak list, one wave per group: its output offset is the sum of the earlier groups'
+// counts, loaded together with its first 64 peaks, so an ordinary group is one memory round trip.
+// Past kSuperGroups groups the counts are also kept per block of 64 groups (not below: the atomic
+// additions of a test to one cache line take 10 ns each, which cost 9 us on the paper event). Peaks found from the list are in
+// no order in their segment: each lane ranks its own among the group's. A group with more peaks
+// than its segment holds walks its survivors' masks in cell order and tests them again (whole job
+// rows: band by band, row by row, strip by strip, then lane and column).
+template <bool NARROW>
 __global__ __launch_bounds__(kBlock) void k_peak_write(DevGrid g, EvDesc ev0, const EvDesc* evs)
 {
-  __shared__ uint32_t s_pre[kGroupTiles + 1];
-  __shared__ uint32_t s_out[kGroupTiles + 1];
-  __shared__ uint32_t s_ovf[kGroupTiles];
-  __shared__ uint32_t s_off[kGroupTiles];
-  __shared__ uint32_t s_first[kGroupTiles];
-  __shared__ uint32_t smem[32];
+  __shared__ __align__(16) uint32_t s_all[kBlock / 64][kSegMax];
   EvDesc e = load_ev(ev0, evs);
   if (e.dense) return;  // uniform: written by k_peak_write_dense
-  const int G = blockIdx.x;
-  const int t0 = G * g.group_tiles;
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint32_t G = blockIdx.x * (kBlock / 64) + w;
+  if (G >= e.n_grp) return;  // uniform
   const bool a8 = ((uintptr_t)e.out & 7u) == 0;
-  const int nt = min(g.group_tiles, g.n_tiles - t0);
-  // every load that does not depend on another is issued first: the earlier groups' peak
-  // counts (all threads), the group's candidate counts and pool offsets (wave 0) and its peak
-  // counts (wave 1)
-  const int ti = (int)(threadIdx.x & 63);
-  uint32_t t_cnt = 0, t_off = 0, t_pk = 0;
-  if (threadIdx.x < 64 && ti < nt) {
-    t_cnt = gp(e.tile_cnt)[t0 + ti];
-    t_off = gp(e.tile_off)[t0 + ti];
-  } else if (threadIdx.x >= 64 && threadIdx.x < 128 && ti < nt) {
-    t_pk = gp(e.tile_pk)[t0 + ti];
-  }
-  // four loads in flight per thread and round (groups past G read as zero)
-  uint32_t part = 0;
-  for (int i0 = 0; i0 < G; i0 += 4 * kBlock) {  // uniform
-    uint32_t w[4];
+  const uint32_t seg_cap = (uint32_t)g.j.seg;
+  const GLOBAL u32x2* const seg = (const GLOBAL u32x2*)gp((const uint2*)e.seg) + (size_t)G * seg_cap;
+  const u32x2 head = seg[lane];  // may hold no peaks yet
+  const uint32_t mine = gp(e.group_pk)[G];
+  // the test worked from the lists if they were made and none overflowed
+  const bool sorted = !e.lists || gp((const uint32_t*)e.slab_cnt)[kListOver] != 0u;
+  const uint32_t s0 = e.n_grp > kSuperGroups ? G & ~63u : 0u;  // groups before s0: by their blocks
+  uint32_t part = 0u;
+  for (uint32_t i = lane; i < s0 / 64u; i += 64u) part += gp(e.super_pk)[i];
+  for (uint32_t i0 = s0; i0 < G; i0 += 16u * 64u) {  // uniform; sixteen loads in flight
+    uint32_t x[16];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int i = i0 + k * kBlock + (int)threadIdx.x;
-      w[k] = i < G ? gp(e.group_pk)[i] : 0u;
-    }
-    part += w[0] + w[1] + w[2] + w[3];
-  }
-  const uint32_t base32 = block_sum(part, smem);
-  const int64_t base = (int64_t)base32;
-  if (G == (int)gridDim.x - 1 && threadIdx.x == 0) *gp(e.n_found) = base + gp(e.group_pk)[G];
-  if (base >= e.cap) return;  // uniform
-  static_assert(kGroupTiles == 64, "one wave holds a group's tiles");
-  if (threadIdx.x < 64) {
-    // tiles nt..63 count zero, so s_pre[nt..64] all equal the group's candidate total; tiles
-    // whose candidates did not fit the pool count zero here (they are scanned densely)
-    const uint32_t ovf = t_off == kTileOverflow ? 1u : 0u;
-    s_ovf[ti] = ovf;
-    s_off[ti] = t_off;
-    const uint32_t inc = wave_incl_scan(ovf ? 0u : t_cnt);
-    s_pre[ti + 1] = inc;
-    if (ti == 0) s_pre[0] = 0u;
-  } else if (threadIdx.x < 128) {
-    // prefix of the peak counts of all the group's tiles
-    const uint32_t inc = wave_incl_scan(t_pk);
-    s_out[ti + 1] = inc;
-    if (ti == 0) s_out[0] = 0u;
-  }
-  lds_barrier();
-  const uint32_t total = s_pre[kGroupTiles];
-  uint32_t run = 0;
-  // kWalkChunks chunks of kBlock candidates per round: the flags and entries of all of them are
-  // loaded, with no branch between the loads, before the first chunk is scanned, so a round
-  // costs one memory round trip. Positions past the group's total load its first candidate
-  // (always readable) and count as no peak.
-  for (uint32_t b0 = 0; b0 < total; b0 += kWalkChunks * kBlock) {  // uniform
-    uint32_t flag[kWalkChunks];
-    int tl[kWalkChunks];
-    uint2 cv[kWalkChunks];
-#pragma unroll
-    for (int k = 0; k < kWalkChunks; ++k) {
-      const uint32_t f = b0 + (uint32_t)k * kBlock + threadIdx.x;
-      const uint32_t fc = f < total ? f : 0u;
-      tl[k] = group_tile_of(s_pre, fc);
-      const size_t idx = (size_t)s_off[tl[k]] + (fc - s_pre[tl[k]]);
-      flag[k] = gp(e.pk_flag)[idx];
-      cv[k] = ld_cand(e.pool, idx);
+    for (uint32_t k = 0; k < 16; ++k) {
+      const uint32_t i = i0 + k * 64u + lane;
+      x[k] = i < G ? gp(e.group_pk)[i] : 0u;
     }
 #pragma unroll
-    for (int k = 0; k < kWalkChunks; ++k) {
-      const uint32_t f0 = b0 + (uint32_t)k * kBlock;
-      if (f0 >= total) break;  // uniform
-      const uint32_t f = f0 + threadIdx.x;
-      const bool pk = f < total && flag[k] != 0u;
-      uint32_t tot;
-      const uint32_t pos = run + block_excl_scan(pk ? 1u : 0u, smem, &tot);
-      // the first candidate of a tile records how many of the group's pooled peaks precede it
-      if (f < total && f == s_pre[tl[k]]) s_first[tl[k]] = pos;
-      lds_barrier();
-      if (pk) {
-        const int64_t o = base + s_out[tl[k]] + (pos - s_first[tl[k]]);
-        if (o < e.cap) st_peak(e.out, o, cv[k].x, cv[k].y, a8);
+    for (uint32_t k = 0; k < 16; ++k) part += x[k];
+  }
+  int64_t base = (int64_t)wave_sum(part);
+  if (e.carry_in) base += *gp(e.carry_in);
+  if (G == e.n_grp - 1u && lane == 0u) {
+    *gp(e.n_found) = base + mine;
+    if (e.carry_out) *gp(e.carry_out) = base + mine;
+  }
+  if (mine == 0u || base >= e.cap) return;  // uniform
+  if (mine <= 64u) {                        // uniform
+    uint32_t r = lane;
+    if (!sorted) {
+      r = 0u;
+      for (uint32_t k = 0u; k < mine; ++k)
+        r += (uint32_t)__builtin_amdgcn_readlane((int)head.x, (int)k) < head.x ? 1u : 0u;
+    }
+    if (lane < mine && base + r < e.cap) st_peak(e.out, base + r, head.x, head.y, a8);
+    return;
+  }
+  if (mine <= seg_cap) {  // uniform
+    if (!sorted) {
+      for (uint32_t i = lane; i < mine; i += 64u) s_all[w][i] = seg[i].x;
+      if (lane < 4u && mine + lane < seg_cap) s_all[w][mine + lane] = 0xffffffffu;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+    }
+    const u32x4* s4 = reinterpret_cast<const u32x4*>(s_all[w]);
+    for (uint32_t i = lane; i < mine; i += 64u) {
+      const u32x2 pk = seg[i];
+      uint32_t r = i;
+      if (!sorted) {
+        r = 0u;
+        for (uint32_t k = 0u; k < (mine + 3u) / 4u; ++k) {
+          const u32x4 o = s4[k];
+          r += (o.x < pk.x ? 1u : 0u) + (o.y < pk.x ? 1u : 0u) + (o.z < pk.x ? 1u : 0u) + (o.w < pk.x ? 1u : 0u);
+        }
       }
-      run += tot;
+      if (base + r < e.cap) st_peak(e.out, base + r, pk.x, pk.y, a8);
     }
+    return;
   }
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const uint32_t* acc = e.acc;
-  for (int tl = wave; tl < nt; tl += kBlock / 64) {
-    if (!s_ovf[tl]) continue;
-    uint32_t cell0, L;
-    tile_range(g, t0 + tl, &cell0, &L);
-    uint32_t r = 0;
-    for (uint32_t b0 = 0; b0 < L; b0 += 64) {
-      const uint32_t i = b0 + lane;
-      bool pk = false;
-      uint32_t c = 0, v = 0;
-      if (i < L) {
-        c = cell0 + i;
-        v = gp(acc)[c];
-        pk = v >= g.threshold && is_peak(g, acc, c, v);
-      }
-      const uint64_t m = __ballot(pk);
-      const int64_t o = base + s_out[tl] + r + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-      if (pk && o < e.cap) st_peak(e.out, o, c, v, a8);
-      r += (uint32_t)__popcll(m);
-    }
-  }
+  const uint32_t gj = (uint32_t)g.j.group_jobs, nb = (uint32_t)g.n_b;
+  const uint64_t first = (uint64_t)(e.grp0 + G) * gj;
+  const uint32_t nj = (uint32_t)min((uint64_t)gj, (uint64_t)g.j.n_jobs - first);
+  const uint64_t l0 = (uint64_t)G * gj;
+  const uint32_t P = (uint32_t)g.j.sub, ch = (uint32_t)g.j.ch, strips = (uint32_t)g.j.row_jobs;
+  const uint32_t sub = P > 1u ? lane / (uint32_t)g.j.units : 0u;
+  const uint32_t unit0 = P > 1u ? lane - sub * (uint32_t)g.j.units : lane;
+  for (uint32_t j0 = 0u; j0 < nj; j0 += strips)  // uniform, as all that follow
+    for (uint32_t b = 0u; b < P; ++b)
+      for (uint32_t q = 0u; q < ch; ++q)
+        for (uint32_t s = 0u; s < strips; ++s) {
+          const uint64_t jl = l0 + j0 + s;
+          if (gp((const uint8_t*)e.job_any)[jl] == 0) continue;
+          const size_t i = (size_t)jl * 64u + lane;
+          const uint32_t m = g.j.elem_bytes == 2 ? ((const GLOBAL uint16_t*)gp((const uint8_t*)e.masks))[i]
+                                                 : gp((const uint8_t*)e.masks)[i];
+          uint32_t nib = sub == b ? m >> (4u * q) & 15u : 0u;
+          const JobAt at = job_at(g, (uint32_t)(first + j0 + s));
+          const uint32_t c = (at.slab * (uint32_t)g.n_a + at.a0 + b * ch + q) * nb +
+                             4u * (P > 1u ? unit0 : at.st * 64u + lane);
+          uint32_t v[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+          for (uint32_t k = 0; k < 4; ++k)
+            if (nib >> k & 1u) {
+              const TestCell x = test_cell(g, c + k, gp(e.acc)[c + k]);
+              v[k] = x.v;
+              for (int dt = -1; dt <= 1; ++dt)
+                if (slice_wins<NARROW>(g, e.acc, x, dt)) nib &= ~(1u << k);
+            }
+          const uint32_t n = (uint32_t)__builtin_popcount(nib), incl = wave_incl_scan(n);
+          int64_t o = base + (int64_t)(incl - n);
+#pragma unroll
+          for (uint32_t k = 0; k < 4; ++k)
+            if (nib >> k & 1u) {
+              if (o < e.cap) st_peak(e.out, o, c + k, v[k], a8);
+              ++o;
+            }
+          base += (int64_t)__builtin_amdgcn_readlane((int)incl, 63);
+        }
 }
+
+constexpr int kWriteStage = 4096;  // peaks of a group staged in LDS by the dense writer
 
 // ---------------------------------------------------------------------------------------------
 // Peak search of crowded events: an LDS-halo stencil over the whole matrix (one read of it), in
@@ -734,18 +905,6 @@ constexpr uint64_t kTestedLanes = 0x7ffffffffffffffeull;  // lanes 1..62
 constexpr uint32_t kStOutside = 0x80000000u;                // a load offset past every resource
 constexpr int kStWholeRows = 48;  // segments up to this many rows keep all their peak words in LDS
 
-__device__ __forceinline__ uint32_t max3u(uint32_t a, uint32_t b, uint32_t c) { return max(a, max(b, c)); }
-// lane j - 1's value (wave_shr:1; lane 0 gets 0)
-__device__ __forceinline__ uint32_t lane_left(uint32_t v)
-{
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x138, 0xf, 0xf, true);
-}
-// lane j + 1's value (wave_shl:1; lane 63 gets 0)
-__device__ __forceinline__ uint32_t lane_right(uint32_t v)
-{
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x130, 0xf, 0xf, true);
-}
-
 // Inclusive maximum over a wave64, with the DPP steps of the inclusive sum (a lane whose source
 // lies outside its row takes the maximum with 0). Every lane of the wave must be active.
 template <int CTRL, int ROW_MASK>
@@ -784,15 +943,6 @@ __device__ __forceinline__ void add_group_counts(uint32_t* group_pk, bool valid,
   if (valid && last && incl != run0) gatomic_add(group_pk + grp, incl - run0);
 }
 
-// Block b of a grid of G runs on XCD b % 8 (workgroups are dealt to the eight XCDs in turn); the
-// number this returns is a bijection of [0, G) under which XCD x runs one contiguous range of
-// numbers: the first G % 8 XCDs take ceil(G / 8) of them, the others floor(G / 8).
-__device__ __forceinline__ uint32_t xcd_contiguous(uint32_t b, uint32_t G)
-{
-  const uint32_t x = b & 7u, i = b >> 3, q = G >> 3, r = G & 7u;
-  return x < r ? x * (q + 1u) + i : r * (q + 1u) + (x - r) * q + i;
-}
-
 template <int NT, bool SECT>
 __global__ __launch_bounds__(1024) void k_peak_stencil(DevGrid g, EvDesc ev0, const EvDesc* evs)
 {
@@ -801,7 +951,7 @@ __global__ __launch_bounds__(1024) void k_peak_stencil(DevGrid g, EvDesc ev0, co
   extern __shared__ uint32_t s_w9[];
   constexpr uint32_t kTBytes = 16u * 256u, kBufBytes = NT * kTBytes;
   EvDesc e = load_ev(ev0, evs);
-  if (!e.dense) return;  // uniform: this event's peaks come from the candidate pool
+  if (!e.dense) return;  // uniform: this event's peaks come from the fill's survivors
   const uint32_t nb = (uint32_t)g.n_b;
   const int na = g.n_a, np = g.n_phi, S = g.dense_rows;
   const uint32_t lane = threadIdx.x & 63u;
@@ -1017,8 +1167,6 @@ __global__ __launch_bounds__(1024) void k_peak_stencil(DevGrid g, EvDesc ev0, co
 // loaded at once; one block scan of the pieces' peak counts gives each thread where its peaks
 // go, in cell order (words in row, then chunk order; bits 1..62 of a word are the chunk's cells
 // in B order).
-constexpr int kWriteStage = 4096;  // peaks of a group staged in LDS by the dense writer
-
 __global__ __launch_bounds__(kBlock) void k_peak_write_dense(DevGrid g, EvDesc ev0, const EvDesc* evs,
                                                                uint32_t stage_cap)
 {
@@ -1311,8 +1459,7 @@ int n_groups(const DevGrid& g) { return (g.n_tiles + g.group_tiles - 1) / g.grou
 
 size_t fill_lds_bytes(const DevGrid& g)
 {
-  const size_t lpad = (((size_t)g.rows * g.n_b) + 3) & ~(size_t)3;
-  return (lpad + 16) * sizeof(uint32_t);
+  return (size_t)g.rows * (((size_t)g.n_b + 3) & ~(size_t)3) * sizeof(uint32_t);
 }
 
 hipError_t launch_prep(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev,
@@ -1333,39 +1480,49 @@ hipError_t launch_prep(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, i
   return hipGetLastError();
 }
 
-hipError_t launch_fill(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev,
-                       bool emit, int64_t max_hits, hipStream_t s)
+bool long_lists(const DevGrid& g, int64_t max_hits)
 {
   // more than two records per thread expected per slab (a hit has at most four cells, about
   // three on average): load eight per thread per round trip
-  const bool long_lists = max_hits * 3 > (int64_t)2 * kBlock * g.n_slabs;
+  return max_hits * 3 > (int64_t)2 * kBlock * g.n_slabs;
+}
+
+hipError_t launch_fill(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev,
+                       bool emit, int64_t max_hits, hipStream_t s)
+{
+  const bool long_l = long_lists(g, max_hits);
   // store kind 2: 4-byte stores (the dword path), otherwise 16-byte stores where rows allow
   const bool vec = (g.n_b % 4) == 0 && g.nt_store != 2;
   // long lists: 64 spill words past the tile (one per lane) for votes outside the row
-  const size_t lds = fill_lds_bytes(g) + (long_lists ? 64 * sizeof(uint32_t) : 0);
-  return launch_fill_nt(g, ev0, evs, n_ev, g.nt_store == 1, vec, emit, long_lists, lds, s);
+  const size_t lds = fill_lds_bytes(g) + (long_l ? 64 * sizeof(uint32_t) : 0);
+  return launch_fill_nt(g, ev0, evs, n_ev, g.nt_store == 1, vec, emit, long_l, lds, s);
 }
 
-hipError_t launch_candidates(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev,
-                             hipStream_t s)
+hipError_t launch_scan(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev, uint32_t n_grp,
+                       bool counters, hipStream_t s)
 {
-  dim3 grid(g.n_tiles, n_ev);
-  if (!g.lds_fill) {
-    // rows wider than an LDS tile (up to 2^24 cells): read from the matrix directly
-    hipLaunchKernelGGL(k_cand_scan_wide, grid, dim3(kBlock), 0, s, g, ev0, evs);
-    return hipGetLastError();
-  }
-  const size_t lds = fill_lds_bytes(g);
-  if (g.n_b % 4 == 0) hipLaunchKernelGGL(k_cand_scan<true>, grid, dim3(kBlock), lds, s, g, ev0, evs);
-  else hipLaunchKernelGGL(k_cand_scan<false>, grid, dim3(kBlock), lds, s, g, ev0, evs);
+  const uint64_t jobs = std::min<uint64_t>((uint64_t)n_grp * g.j.group_jobs, g.j.n_jobs);
+  dim3 grid((unsigned)((jobs + 7) / 8), n_ev);
+  const bool vec = g.n_b % 4 == 0;
+  if (g.j.ch == 4 && vec) hipLaunchKernelGGL((k_scan<true, 4>), grid, dim3(kBlock), 0, s, g, ev0, evs, counters ? 1 : 0);
+  else if (g.j.ch == 4) hipLaunchKernelGGL((k_scan<false, 4>), grid, dim3(kBlock), 0, s, g, ev0, evs, counters ? 1 : 0);
+  else if (vec) hipLaunchKernelGGL((k_scan<true, 1>), grid, dim3(kBlock), 0, s, g, ev0, evs, counters ? 1 : 0);
+  else hipLaunchKernelGGL((k_scan<false, 1>), grid, dim3(kBlock), 0, s, g, ev0, evs, counters ? 1 : 0);
   return hipGetLastError();
 }
 
-hipError_t launch_peaks(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev,
+hipError_t launch_peaks(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev, uint32_t n_grp,
                         hipStream_t s)
 {
-  hipLaunchKernelGGL(k_peak_test, dim3(g.test_blocks, n_ev), dim3(kBlock), 0, s, g, ev0, evs);
-  hipLaunchKernelGGL(k_peak_write, dim3(n_groups(g), n_ev), dim3(kBlock), 0, s, g, ev0, evs);
+  // a workgroup per group while that fills the chip (kTestGrid workgroups), and at least 16 half
+  // waves per list
+  const unsigned most = std::max(kTestBlocks, kTestGrid / (unsigned)n_ev);
+  const dim3 tg(std::max(std::min(n_grp, most), kTestBlocks), n_ev);
+  if (g.n_b < 3) hipLaunchKernelGGL(k_peak_test<true>, tg, dim3(kBlock), 0, s, g, ev0, evs);
+  else hipLaunchKernelGGL(k_peak_test<false>, tg, dim3(kBlock), 0, s, g, ev0, evs);
+  const dim3 wg((n_grp + 3) / 4, n_ev);
+  if (g.n_b < 3) hipLaunchKernelGGL(k_peak_write<true>, wg, dim3(kBlock), 0, s, g, ev0, evs);
+  else hipLaunchKernelGGL(k_peak_write<false>, wg, dim3(kBlock), 0, s, g, ev0, evs);
   return hipGetLastError();
 }
 

@@ -6,12 +6,13 @@
 // holds, on each device the library runs on:
 //   [0, kCounterBytes)            the pair of slab-counter arrays (one counts, one is cleared)
 //   [kTabOff, kTabOff + kTabBytes) the bin-rule tables of the grid last used on the device
-//   [kEvOff, kNoAllocBytes)       the event scratch (slab lists, candidate pool, peak counts)
+//   [kEvOff, kNoAllocBytes)       the event scratch (slab lists, survivor masks, peak counts)
 // Host code never passes the array's name to a kernel or a copy: its host-side symbol is only
 // a stand-in. The device address of each device's copy is looked up once, with that device
 // current, and kept in g_ptr[device].
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstring>
 #include <mutex>
 
@@ -52,6 +53,22 @@ bool same_tables(const ht_grid& a, const ht_grid& b)
 
 size_t al256(size_t v) { return (v + 255) & ~(size_t)255; }
 
+// The call's size limit, in bytes: the slab lists, 16 bytes per fill tile, and for an ordinary
+// event nine bytes per entry of a candidate list of cand_cap cells per tile, or a quarter of the
+// bound 4 n_hits n_a / threshold on the cells that can reach the threshold when that is larger.
+// The survivor masks that the search keeps instead are smaller on nearly every grid; where they
+// are not (rows past 70 000 cells), the search runs slice by slice, so the limit stays this one.
+size_t limit_bytes(const DevGrid& g, const Tiling& tl, int64_t n, bool direct, bool dense)
+{
+  const size_t t = (size_t)g.n_tiles;
+  size_t b = event_scratch_bytes(g, n, direct, dense ? kPeakMask : 0) + 4 * al256(4 * t);
+  if (dense) return b;
+  const size_t cells = (size_t)g.n_theta * g.n_phi * g.n_a * g.n_b;
+  const size_t bound = (size_t)n * (g.phi_sectors ? 2 : 4) * (size_t)g.n_a / (size_t)g.threshold;
+  const size_t pool = std::min<size_t>(std::max(t * (size_t)tl.cand_cap, std::min(cells, bound / 4)), 0xfffffff0u);
+  return b + al256(4 * (size_t)n_groups(g)) + al256(8 * pool) + al256(pool);
+}
+
 }  // namespace
 }  // namespace ht
 
@@ -83,17 +100,18 @@ extern "C" int ht_fill_peaks_noalloc(const ht_grid* grid, const float* x, const 
   // the layout: direct slab lists when they fit, else the counting sort (the same results);
   // an event that fits neither is refused before any device work
   const Tiling tl = choose_tiling(*grid);
-  DevGrid g = make_devgrid(*grid, DevTables(), tl);
+  DevGrid g = make_devgrid(*grid, DevTables(), tl, 1);
   const bool atomic = !g.lds_fill;
   const bool dense = !atomic && dense_peaks(g, n_hits);
-  const int layout = dense ? kPeakMask : kPeakPool;
+  const int layout = dense ? kPeakMask : kPeakBands;
   const size_t room = kNoAllocBytes - kEvOff;
-  bool direct = !atomic && direct_lists(g, n_hits) && event_scratch_bytes(g, n_hits, true, layout) <= room;
-  const size_t need = event_scratch_bytes(g, n_hits, direct, layout);
+  bool direct = !atomic && direct_lists(g, n_hits) && limit_bytes(g, tl, n_hits, true, dense) <= room;
+  const size_t need = limit_bytes(g, tl, n_hits, direct, dense);
   if (need > room)
     return fail(HT_EINVAL,
                 "ht_fill_peaks_noalloc: this event needs %zu bytes of scratch; the fixed scratch "
                 "holds %zu (use ht_fill_peaks)", need, room);
+  const bool sliced = event_scratch_bytes(g, n_hits, direct, layout) > room;
 
   std::lock_guard<std::mutex> lk(g_na_mu);
   if (!g_ptr[dev]) {
@@ -127,12 +145,13 @@ extern "C" int ht_fill_peaks_noalloc(const ht_grid* grid, const float* x, const 
   t.phi = (float*)(base + kTabOff + phi_off);
   t.th = (float*)(base + kTabOff + th_off);
   t.inv_db = inv_db;
-  g = make_devgrid(*grid, t, tl);
+  g = make_devgrid(*grid, t, tl, 1);
 
   EvDesc ev;
   std::memset(&ev, 0, sizeof(ev));
-  carve_event_scratch(g, n_hits, direct, base + kEvOff, &ev, layout);
+  carve_event_scratch(g, n_hits, direct, base + kEvOff, &ev, sliced ? 0 : layout);
   ev.dense = dense ? 1 : 0;
+  ev.lists = !sliced && !dense && (atomic || !long_lists(g, n_hits)) ? 1 : 0;
   uint32_t* pair = (uint32_t*)base;
   ev.slab_cnt = pair + (g_parity[dev] ? kCounterWords : 0);
   ev.slab_cnt_next = pair + (g_parity[dev] ? 0 : kCounterWords);
@@ -145,7 +164,30 @@ extern "C" int ht_fill_peaks_noalloc(const ht_grid* grid, const float* x, const 
   ev.cap = capacity;
   ev.n_found = n_found;
   bool used = false;
-  rc = enqueue_event(g, ev, n_hits, direct, atomic, true, true, false, s, &used);
+  rc = enqueue_event(g, ev, n_hits, direct, atomic, true, !sliced, false, s, &used);
   if (used) g_parity[dev] ^= 1;
-  return rc;
+  if (rc || !sliced) return rc;
+  // The masks do not fit beside the slab lists: the peaks are searched in the written matrix, as
+  // many groups of job rows at a time as fit the whole event scratch (the lists are done with
+  // then), each slice counting on from the one before.
+  set_jobs(&g, 0, 1);
+  int64_t* carry = (int64_t*)(base + kEvOff);
+  const size_t fixed = 256 + 2 * al256(4 * (size_t)g.j.n_groups) + 16 * (size_t)kListCap * kLists + 6 * 256;
+  const size_t per = (size_t)(1 + 64 * g.j.elem_bytes) * g.j.group_jobs + 8 * (size_t)g.j.seg;
+  const size_t fit = fixed < room ? (room - fixed) / per : 0;
+  if (fit == 0) return fail(HT_EINVAL, "ht_fill_peaks_noalloc: one group of rows needs %zu bytes of scratch", per);
+  for (uint32_t g0 = 0, k = 0; g0 < g.j.n_groups; ++k) {
+    const uint32_t n_grp = (uint32_t)std::min<size_t>(fit, g.j.n_groups - g0);
+    carve_peak_scratch(g, base + kEvOff + 256, &ev, kPeakBands, g0, n_grp);
+    ev.lists = 1;
+    ev.carry_in = k > 0 ? carry + (k & 1) : nullptr;
+    ev.carry_out = carry + ((k + 1) & 1);
+    ev.slab_cnt = pair + (g_parity[dev] ? kCounterWords : 0);
+    ev.slab_cnt_next = pair + (g_parity[dev] ? 0 : kCounterWords);
+    if ((e = launch_scan(g, ev, nullptr, 1, n_grp, true, s)) != hipSuccess) return fail_hip(e, "candidate launch");
+    g_parity[dev] ^= 1;
+    if ((e = launch_peaks(g, ev, nullptr, 1, n_grp, s)) != hipSuccess) return fail_hip(e, "peak launch");
+    g0 += n_grp;
+  }
+  return HT_OK;
 }

@@ -73,7 +73,7 @@ struct ht_server {
   uint64_t cells = 0;
   size_t scratch_bytes = 0;
   bool direct = false;
-  int layout = kPeakPool;       // slots hold a candidate pool, and a peak mask when events can be crowded
+  int layout = kPeakBands;       // slots hold survivor masks, and peak words when events can be crowded
   char* arena = nullptr;        // device: all slots
   uint32_t* ctr = nullptr;      // device: slab counters of all slots
   char* host_out = nullptr;     // pinned: per-slot peak lists and counts
@@ -123,8 +123,9 @@ int launch(ht_server* sv, Batch& b)
 {
   hipStream_t s = sv->streams[b.stream];
   const int64_t mh = sv->opts.max_hits;
-  int64_t max_n = 0;
-  bool any_pool = false, any_dense = false;
+  int64_t max_n = 0, batch_max = 0;
+  for (const Request* r : b.reqs) batch_max = std::max(batch_max, r->n);
+  bool any_bands = false, any_dense = false;
   hipError_t e;
   for (size_t i = 0; i < b.reqs.size(); ++i) {
     Request* r = b.reqs[i];
@@ -138,7 +139,9 @@ int launch(ht_server* sv, Batch& b)
     carve_event_scratch(sv->g, mh, sv->direct, sl.scratch, &d, sv->layout);
     // crowded events search their peaks with the stencil (the slot holds both layouts)
     d.dense = (sv->layout & kPeakMask) && dense_peaks(sv->g, r->n) ? 1 : 0;
-    any_pool = any_pool || !d.dense;
+    if (d.dense) clear_groups(sv->g, &d);
+    d.lists = !d.dense && !(sv->g.lds_fill && long_lists(sv->g, batch_max)) ? 1 : 0;
+    any_bands = any_bands || !d.dense;
     any_dense = any_dense || d.dense;
     d.slab_cnt = sl.ctr + (sl.parity ? kCounterWords : 0);
     d.slab_cnt_next = sl.ctr + (sl.parity ? 0 : kCounterWords);
@@ -156,7 +159,7 @@ int launch(ht_server* sv, Batch& b)
                           hipMemcpyHostToDevice, s)) != hipSuccess)
     return fail_hip(e, "hipMemcpyAsync(descriptors)");
   bool prep_enqueued = false;
-  int rc = launch_batch(sv->g, sv->d_ev[b.stream], (int)b.reqs.size(), max_n, sv->direct, any_pool,
+  int rc = launch_batch(sv->g, sv->d_ev[b.stream], (int)b.reqs.size(), max_n, sv->direct, any_bands,
                         any_dense, s, &prep_enqueued);
   // a slot switches counter arrays only once the preparation that counts into this one and
   // clears the other is on the stream
@@ -262,13 +265,13 @@ int ht_serve_create(const ht_grid* grid, const ht_serve_opts* opts, ht_server** 
   sv->grid = *grid;
   sv->opts = *opts;
   sv->dev = opts->device;
-  if ((rc = make_device_grid(*grid, sv->dev, &sv->g))) {
+  if ((rc = make_device_grid(*grid, sv->dev, opts->max_batch, &sv->g))) {
     delete sv;
     return rc;
   }
   sv->cells = n_cells(*grid);
   sv->direct = direct_lists(sv->g, opts->max_hits);
-  sv->layout = kPeakPool | (dense_peaks(sv->g, opts->max_hits) ? kPeakMask : 0);
+  sv->layout = kPeakBands | (dense_peaks(sv->g, opts->max_hits) ? kPeakMask : 0);
   sv->scratch_bytes = event_scratch_bytes(sv->g, opts->max_hits, sv->direct, sv->layout);
   const size_t slot_bytes = al(4 * sv->cells) + al(sv->scratch_bytes) + al(12 * (size_t)opts->max_hits);
   const int64_t n_slots = std::min<int64_t>(opts->hbm_budget_bytes / (int64_t)slot_bytes, 4096);

@@ -1,0 +1,115 @@
+"""The survivor search (the fill's and the scan's jobs, the peak test from lists and from masks, the
+ordered writer) where it can go wrong: rows of every width around the job sizes, tiles of every
+height, lists and group segments that overflow, counts up to 2^32 - 1, and the no-alloc call's
+slice-by-slice search. Against the CPU oracle, bit for bit."""
+import sys
+
+import numpy as np
+import pytest
+
+from paper_1507_03074_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def say(*a):
+    print(*a, flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module")
+def B():
+    import torch
+    from paper_1507_03074_amd import binding
+    from paper_1507_03074_amd import build as hbuild
+    hbuild.ensure_built()
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    torch.cuda.set_device(0)
+    return binding
+
+
+def oracle_peaks(spec, M):
+    from oracle import oracle
+    return oracle.peaks(oracle.OracleGrid(*spec.as_tuple()), M)
+
+
+def same_peaks(spec, got, M, tag):
+    oc, ov, on = oracle_peaks(spec, M)
+    c, v, n = got
+    assert n == on, (tag, n, on)
+    assert np.array_equal(c, oc) and np.array_equal(v, ov), tag
+
+
+# widths around a unit (4), half a wave of units (128), a wave of units (256), and ragged ones
+@pytest.mark.parametrize("n_b", [1, 2, 3, 5, 16, 31, 64, 100, 127, 128, 129, 255, 257, 512, 1030])
+@pytest.mark.parametrize("n_hits", [30, 900])  # one record per lane at most, and longer lists
+def test_every_job_shape_bit_exact(B, n_b, n_hits):
+    import torch
+    from oracle import oracle
+    rng = np.random.default_rng([n_b, n_hits])
+    ev = synth.make_hits(rng, n_hits // 15, n_hits - 12 * (n_hits // 15))
+    spec = synth.GridSpec(2, 3, 70, n_b, threshold=2)
+    M, _ = oracle.fill(oracle.OracleGrid(*spec.as_tuple()), ev.x, ev.y, ev.z)
+    x, y, z = B.hits_to_device(ev.x, ev.y, ev.z)
+    for rows in (1, 2, 4, 8, 16, 32, 64):
+        if 4 * rows * n_b > 56 * 1024:
+            continue
+        say("n_b", n_b, "hits", n_hits, "rows", rows)
+        B.ht_set_tuning(spec, rows=rows, dense_hits=-1)
+        try:
+            acc, c, v, n = B.fill_peaks(spec, x, y, z)
+            torch.cuda.synchronize()
+        finally:
+            B.ht_set_tuning(spec)
+        assert np.array_equal(B.as_u32(acc), M), rows
+        same_peaks(spec, (c, v, n), M, "rows %d" % rows)
+    c, v, n = B.peaks(spec, torch.from_numpy(M.view(np.int32).copy()).cuda())
+    same_peaks(spec, (c, v, n), M, "peaks of a matrix")
+
+
+@pytest.mark.parametrize("shape", [(1, 3, 64, 256), (2, 3, 512, 1024), (1, 3, 40, 33), (1, 3, 3, 17000)])
+def test_crowded_matrices_overflow_lists_and_segments(B, shape):
+    """A peak on every other row and column of one slab: more than any group's segment holds, and on
+    the larger grids more survivors than the lists hold."""
+    import torch
+    rng = np.random.default_rng(shape)
+    M = np.zeros(shape, np.uint32)
+    M[0, 0, ::2, ::2] = rng.integers(1, 4, M[0, 0, ::2, ::2].shape)
+    M[0, 1] = rng.integers(0, 2, M[0, 1].shape)
+    M[0, 0, 0, 0] = 0xffffffff
+    M[0, 0, 0, 1] = 0xffffffff  # a tie at the largest count: the lower cell wins
+    for T in (1, 2, 0xffffffff):
+        say("crowded matrix", shape, T)
+        spec = synth.GridSpec(*shape, threshold=T)
+        got = B.peaks(spec, torch.from_numpy(M.view(np.int32).copy()).cuda())
+        same_peaks(spec, got, M, (shape, T))
+        n = got[2]
+        if n > 3:  # truncated inside a group
+            c, v, m = B.peaks(spec, torch.from_numpy(M.view(np.int32).copy()).cuda(), capacity=n // 2,
+                              allow_truncation=True)
+            assert m == n and np.array_equal(c, got[0][:n // 2]) and np.array_equal(v, got[1][:n // 2])
+
+
+def test_noalloc_searches_in_slices(B):
+    """A grid whose masks pass the fixed scratch, admitted because its candidate list is set small:
+    the same matrix and peaks as ht_fill_peaks, twice in a row."""
+    import torch
+    spec = synth.GridSpec(4, 16, 2048, 2048, threshold=9)
+    ev = synth.make_event(1, 3)
+    x, y, z = B.hits_to_device(ev.x, ev.y, ev.z)
+    B.ht_set_tuning(spec, cand_cap=2)
+    try:
+        ref = B.new_acc(spec)
+        ref, c, v, n = B.fill_peaks(spec, x, y, z, acc=ref)
+        assert n > 100
+        acc = B.new_acc(spec)
+        for k in range(2):
+            say("sliced no-alloc search", k)
+            out, nf = B.new_peaks(1 << 16)
+            acc.fill_(7)
+            B.ht_fill_peaks_noalloc(spec, x, y, z, acc, out, 1 << 16, nf)
+            c2, v2, n2 = B.peaks_to_host(out, nf, 1 << 16)
+            assert n2 == n and np.array_equal(c2, c) and np.array_equal(v2, v)
+            assert torch.equal(acc, ref)
+    finally:
+        B.ht_set_tuning(spec)
