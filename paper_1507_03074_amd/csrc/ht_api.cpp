@@ -293,6 +293,10 @@ DevGrid make_devgrid(const ht_grid& g, const DevTables& t, const Tiling& tl, int
   d.fill_tiles = tl.fill_tiles;
   d.phi_sectors = g.phi_sectors;
   d.packed_lists = tl.packed_lists;
+  // |A2| <= 2^60 and a hit's |x| < 2^64 (r2 is finite): A2 x is finite, r2 - A2 x no NaN; 1/(2y) is
+  // finite and not 0, so B is no NaN; and neither is (B - b_min) inv_db while inv_db is finite
+  d.finite_votes = std::max(std::fabs((double)g.a_min), std::fabs((double)g.a_max)) <= std::ldexp(1.0, 59) &&
+                   std::isfinite((float)((double)g.n_b / ((double)g.b_max - (double)g.b_min))) ? 1 : 0;
   d.dense_w = tl.dense_w;
   d.dense_rows = tl.dense_rows;
   d.dense_hits = tl.dense_hits;

@@ -17,6 +17,7 @@ namespace {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBlock = 256;
+constexpr int kSpill = 64;  // spill words per row of a long-list fill tile
 
 // A launch's event descriptor: the kernel argument for one event, else evs[blockIdx.y]. The
 // descriptor array is read through the constant address space: both sources are then
@@ -246,9 +247,21 @@ __device__ __forceinline__ void list_survivors(const EvDesc& e, uint32_t job, ui
       }
 }
 
+// floor(f) as a signed integer, saturated (v_cvt_flr_i32_f32; a NaN gives 0)
+__device__ __forceinline__ int32_t floor_i32(float f)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+  int32_t r;
+  asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(r) : "v"(f));
+  return r;
+#else
+  return (int32_t)f;  // the host pass only parses device functions
+#endif
+}
+
+typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
 // A lane's unit of four columns of a row of nb cells: one 16-byte access (of 4-byte alignment
 // where rows are not whole units), the row's last unit cell by cell.
-typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
 template <bool NT>
 __device__ __forceinline__ void st_unit(uint32_t* acc, uint32_t c, uint32_t left, u32x4 v)
 {
@@ -272,27 +285,30 @@ __device__ __forceinline__ void st_unit(uint32_t* acc, uint32_t c, uint32_t left
 // thread, each chunk's loads issued together) and the votes go to LDS. Then the waves take the
 // tile's jobs in turn, with no further barrier: a wave reads its job's cells once, writes them to
 // the matrix, clears them in LDS, and (EMIT) stores the survivors' masks of the peak search.
-// CACHE is 2 for short lists (few registers, so eight waves fit on each SIMD) and 8 for long
-// ones, where the LDS tile, not the registers, limits how many workgroups fit.
+// Short lists: 256 threads, two records per thread and round trip. LONG lists: 512 threads and
+// four records each, so that the 32 KiB tile, of which a CU holds four, has 32 waves to vote, not
+// 16.
 // ---------------------------------------------------------------------------------------------
-template <int ROWS, bool VEC, bool EMIT, bool NT, int CACHE>
-__global__ __launch_bounds__(kBlock) void k_fill(DevGrid g, EvDesc ev0, const EvDesc* evs)
+template <int ROWS, bool VEC, bool EMIT, bool NT, bool LONG>
+__global__ __launch_bounds__(LONG ? 2 * kBlock : kBlock, LONG || ROWS <= 4 ? 8 : 1) void k_fill(DevGrid g, EvDesc ev0, const EvDesc* evs)
 {
+  constexpr int kThreads = LONG ? 2 * kBlock : kBlock;
+  constexpr int CACHE = LONG ? 4 : 2;
   extern __shared__ uint32_t smem[];
   EvDesc e = load_ev(ev0, evs);
   const uint32_t nb = (uint32_t)g.n_b;
-  // row stride in LDS: whole 16-byte units where jobs read them, else none is lost
-  const uint32_t ldr4 = (nb + 3u) / 4u, ldr = EMIT ? 4u * ldr4 : nb;
+  // row stride in LDS: whole 16-byte units where jobs read them; long lists: then kSpill words
+  // that take the votes outside the row, the lane's own from word n_b + lane on
+  const uint32_t ldr4 = (nb + 3u) / 4u, ldr = LONG ? 4u * ldr4 + (uint32_t)kSpill : EMIT ? 4u * ldr4 : nb;
+  const uint32_t ldr4s = ldr / 4u;
   const uint32_t Lpad = ((uint32_t)ROWS * ldr + 3u) & ~3u;
   uint32_t* s_tile = smem;
-  // long lists only: one word per lane past the tile, where a vote outside the row goes
-  uint32_t* const s_spill = smem + Lpad + (threadIdx.x & 63u);
   u32x4* s4 = reinterpret_cast<u32x4*>(s_tile);
   const u32x4 zero4 = {0u, 0u, 0u, 0u};
-  for (uint32_t i = threadIdx.x; i < Lpad / 4; i += kBlock) s4[i] = zero4;
+  for (uint32_t i = threadIdx.x; i < Lpad / 4; i += kThreads) s4[i] = zero4;
 
   const float b_min = g.b_min, inv_db = g.inv_db, nb_f = g.nb_f;
-  const uint32_t nb_bits = __float_as_uint(nb_f);
+  const uint32_t spill = nb + (threadIdx.x & 63u);  // long lists
   // the wave's jobs: lane -> (band of the job, 4-column unit); wide rows: unit = 64 strip + lane
   constexpr int CH = ROWS < 4 ? ROWS : 4;
   const uint32_t lane = threadIdx.x & 63u;
@@ -309,7 +325,7 @@ __global__ __launch_bounds__(kBlock) void k_fill(DevGrid g, EvDesc ev0, const Ev
   // With long lists and several tiles per workgroup, a workgroup instead fills consecutive
   // tiles, the A rows of one slab in turn, and keeps the slab's records in registers from one
   // tile to the next when they all fit (no list load after the first tile).
-  const bool consecutive = CACHE == 8 && g.fill_tiles > 1;  // uniform
+  const bool consecutive = LONG && g.fill_tiles > 1;  // uniform
   const int t_begin = consecutive ? (int)blockIdx.x * g.fill_tiles : (int)blockIdx.x;
   const int t_end = consecutive ? min(t_begin + g.fill_tiles, g.n_tiles) : g.n_tiles;
   const int t_step = consecutive ? 1 : (int)gridDim.x;
@@ -317,14 +333,14 @@ __global__ __launch_bounds__(kBlock) void k_fill(DevGrid g, EvDesc ev0, const Ev
   size_t beg = 0;
   uint32_t n = 0;
   float cx[CACHE], cr2[CACHE], ck[CACHE];
-  constexpr bool kSplit = CACHE != 8 && ROWS >= 4;  // see the votes of very short lists
-  constexpr int kPart = kSplit ? ROWS / (kBlock / 64) : ROWS;
+  constexpr bool kSplit = !LONG && ROWS >= 4;  // see the votes of very short lists
+  constexpr int kPart = kSplit ? ROWS / (kThreads / 64) : ROWS;
   float sx = 0.0f, sr2 = 0.0f, sk = 0.0f, sa2 = 0.0f;
   for (int tile = t_begin; tile < t_end; tile += t_step) {  // uniform
     const int slab = tile / g.tiles_per_slab;
     const int a0 = (tile - slab * g.tiles_per_slab) * ROWS;
     const int rows = min(ROWS, g.n_a - a0);
-    if (CACHE != 8 || slab != held_slab) {  // the short-list variant never holds a list
+    if (!LONG || slab != held_slab) {  // the short-list variant never holds a list
       uint32_t last;  // last readable record (before n is known)
       if (e.list_cap > 0) {
         beg = (size_t)slab * (size_t)e.list_cap;
@@ -341,9 +357,9 @@ __global__ __launch_bounds__(kBlock) void k_fill(DevGrid g, EvDesc ev0, const Ev
       // the registers the votes read, and the loads overlap the list-length load
 #pragma unroll
       for (int c = 0; c < CACHE; ++c)
-        ld_xyz(e.list, beg + min(threadIdx.x + (uint32_t)c * kBlock, last), &cx[c], &cr2[c], &ck[c]);
+        ld_xyz(e.list, beg + min(threadIdx.x + (uint32_t)c * (uint32_t)kThreads, last), &cx[c], &cr2[c], &ck[c]);
       if (kSplit) ld_xyz(e.list, beg + min(lane, last), &sx, &sr2, &sk);
-      held_slab = (consecutive && n <= (uint32_t)(CACHE * kBlock)) ? slab : -1;
+      held_slab = (consecutive && n <= (uint32_t)(CACHE * (uint32_t)kThreads)) ? slab : -1;
     }
     // tall tiles read each row's A from the lane that holds it: 64 of them in scalar registers spill
     constexpr bool kLaneA2 = ROWS >= 16;
@@ -357,24 +373,23 @@ __global__ __launch_bounds__(kBlock) void k_fill(DevGrid g, EvDesc ev0, const Ev
     auto lane_a2 = [&](int row) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sa2), row)); };
     // the LDS tile is zero: set at the start, restored at the end of every tile
     lds_barrier();
-    // Long lists (crowded events) vote with no branch: every row, and a vote outside the row
-    // adds to the lane's spill word instead (rows past a short last tile are cleared after it).
-    // In range means 0 <= f < n_b: adding +0 turns -0 into +0 and leaves every other value as
-    // it is, and the bit patterns of non-negative binary32 values order as the values do, while
-    // negative values, NaN and infinity all have patterns at or above that of n_b. This measured
-    // 11% faster on the long-list fill of a 40k-hit event and 4% slower on the short-list fill
-    // of the paper event, which keeps the branch.
+    // Long lists (crowded events) vote with no branch: every row (rows past a short last tile are
+    // cleared after it), and a vote outside the row goes to the spill words past it. floor(f) as a
+    // signed integer, taken as unsigned and held at n_b + lane, is f's bin where 0 <= f < n_b, and
+    // a spill word elsewhere: negative values floor to at least 2^31, large ones and infinities
+    // saturate. (f is no NaN: launch_fill's rule and the preparation see to that. -0 floors to 0,
+    // its bin.) That is eight VALU instructions per vote. Comparing bit patterns and selecting a
+    // spill word past the tile took ten, and branches slowed a 40k-hit event's fill by 11%; the
+    // short-list fill of the paper event is 4% faster with the branch and keeps it.
     auto vote_row = [&](int r, float a2, float x, float r2, float k) {
-      if (CACHE != 8 && r >= rows) return;
+      if (!LONG && r >= rows) return;
       float ax = a2 * x;
       float num = r2 - ax;
       float B = num * k;
       float d = B - b_min;
       float f = d * inv_db;
-      if (CACHE == 8) {
-        const float f0 = f + 0.0f;
-        const bool in = __float_as_uint(f0) < nb_bits;
-        atomicAdd(in ? &s_tile[(uint32_t)r * ldr + (uint32_t)(int)f0] : s_spill, 1u);
+      if (LONG) {
+        atomicAdd(&s_tile[(uint32_t)r * ldr + min((uint32_t)floor_i32(f), spill)], 1u);
       } else if (f >= 0.0f && f < nb_f) {
         atomicAdd(&s_tile[(uint32_t)r * ldr + (uint32_t)(int)f], 1u);
       }
@@ -396,59 +411,57 @@ __global__ __launch_bounds__(kBlock) void k_fill(DevGrid g, EvDesc ev0, const Ev
     } else {
 #pragma unroll
       for (int c = 0; c < CACHE; ++c)
-        if (threadIdx.x + (uint32_t)c * kBlock < n) vote(cx[c], cr2[c], ck[c]);
+        if (threadIdx.x + (uint32_t)c * (uint32_t)kThreads < n) vote(cx[c], cr2[c], ck[c]);
     }
     // longer lists: further chunks of CACHE records per thread, each chunk's loads issued
     // together (one round trip per chunk)
-    for (uint32_t base = CACHE * kBlock; base < n; base += CACHE * kBlock) {  // uniform
+    for (uint32_t base = CACHE * (uint32_t)kThreads; base < n; base += CACHE * (uint32_t)kThreads) {  // uniform
 #pragma unroll
       for (int c = 0; c < CACHE; ++c)
-        ld_xyz(e.list, beg + min(base + threadIdx.x + (uint32_t)c * kBlock, n - 1u), &cx[c], &cr2[c], &ck[c]);
+        ld_xyz(e.list, beg + min(base + threadIdx.x + (uint32_t)c * (uint32_t)kThreads, n - 1u), &cx[c], &cr2[c], &ck[c]);
 #pragma unroll
       for (int c = 0; c < CACHE; ++c)
-        if (base + threadIdx.x + (uint32_t)c * kBlock < n) vote(cx[c], cr2[c], ck[c]);
+        if (base + threadIdx.x + (uint32_t)c * (uint32_t)kThreads < n) vote(cx[c], cr2[c], ck[c]);
     }
     lds_barrier();
 
     const uint32_t cell0 = ((uint32_t)slab * (uint32_t)g.n_a + (uint32_t)a0) * nb;
-    if (!EMIT) {
+    if (!EMIT && !LONG) {
       // no search of the tile: one linear sweep over it
       const uint32_t L = (uint32_t)rows * nb;
       GLOBAL uint32_t* dst = gp(e.acc) + cell0;
       if (VEC) {
         GLOBAL u32x4* d4 = reinterpret_cast<GLOBAL u32x4*>(dst);
-        for (uint32_t i = threadIdx.x; i < L / 4u; i += kBlock) {
+        for (uint32_t i = threadIdx.x; i < L / 4u; i += kThreads) {
           const u32x4 v = s4[i];
           if (NT) __builtin_nontemporal_store(v, d4 + i);
           else d4[i] = v;
           s4[i] = zero4;
         }
       } else {
-        for (uint32_t i = threadIdx.x; i < L; i += kBlock) {
+        for (uint32_t i = threadIdx.x; i < L; i += kThreads) {
           const uint32_t v = s_tile[i];
           if (NT) __builtin_nontemporal_store(v, dst + i);
           else dst[i] = v;
           s_tile[i] = 0u;
         }
       }
-      if (CACHE == 8 && L < Lpad)  // uniform: the rows past a short last tile took votes
-        for (uint32_t i = L + threadIdx.x; i < Lpad; i += kBlock) s_tile[i] = 0u;
       continue;
     }
-    const bool emit = !e.dense;  // uniform; a crowded event's peaks come from the stencil
+    const bool emit = EMIT && !e.dense;  // uniform; a crowded event's peaks come from the stencil
     // Every job's cells: read from LDS once, written to the matrix, cleared, and searched for
     // survivors in registers. No wave waits for another here: what bounds the fill of an ordinary
     // event is its stores, and a pass that counted candidates, a barrier, a pool reservation and
     // a second pass over the tile cost 9 us of 47 on the paper event.
     uint32_t bg = 0u, st = wave;  // job = bg * strips + st
     while (st >= (uint32_t)g.j.strips) { st -= (uint32_t)g.j.strips; ++bg; }
-    for (uint32_t job = wave; job < (uint32_t)g.j.tile_jobs; job += kBlock / 64) {  // uniform
+    for (uint32_t job = wave; job < (uint32_t)g.j.tile_jobs; job += kThreads / 64) {  // uniform
       const uint32_t u = g.j.sub > 1 ? unit0 : st * 64u + lane;
       const uint32_t r0 = (bg * (uint32_t)g.j.sub + sub) * CH;
       const bool in = u < ldr4 && sub < (uint32_t)g.j.sub;
       u32x4 v[CH];
 #pragma unroll
-      for (int q = 0; q < CH; ++q) v[q] = in && (int)r0 + q < rows ? s4[(r0 + q) * ldr4 + u] : zero4;
+      for (int q = 0; q < CH; ++q) v[q] = in && (int)r0 + q < rows ? s4[(r0 + q) * ldr4s + u] : zero4;
 #pragma unroll
       for (int q = 0; q < CH; ++q) {
         if (in && (int)r0 + q < rows) {
@@ -460,7 +473,7 @@ __global__ __launch_bounds__(kBlock) void k_fill(DevGrid g, EvDesc ev0, const Ev
           } else {
             st_unit<NT>(e.acc, c, nb - 4u * u, v[q]);
           }
-          s4[(r0 + q) * ldr4 + u] = zero4;
+          s4[(r0 + q) * ldr4s + u] = zero4;
         }
       }
       if (emit) {
@@ -468,30 +481,30 @@ __global__ __launch_bounds__(kBlock) void k_fill(DevGrid g, EvDesc ev0, const Ev
         if (__builtin_amdgcn_ballot_w64(m != 0u) != 0u) {  // uniform
           const uint32_t id = (uint32_t)tile * (uint32_t)g.j.tile_jobs + job;
           put_mask<CH>(e, id, lane, m);
-          if (CACHE != 8 && e.lists)  // uniform
+          if (!LONG && e.lists)  // uniform
             list_survivors<CH>(e, id, id / (uint32_t)g.j.group_jobs, lane, m, cell0 + r0 * nb + 4u * u, nb, v);
         }
       }
-      st += kBlock / 64;
+      st += kThreads / 64;
       while (st >= (uint32_t)g.j.strips) { st -= (uint32_t)g.j.strips; ++bg; }
     }
-    if (CACHE == 8 && rows < ROWS)  // uniform: the rows past a short last tile took votes
-      for (uint32_t i = (uint32_t)rows * ldr4 + threadIdx.x; i < Lpad / 4u; i += kBlock) s4[i] = zero4;
+    if (LONG && rows < ROWS)  // uniform: the rows past a short last tile took votes
+      for (uint32_t i = (uint32_t)rows * ldr4s + threadIdx.x; i < Lpad / 4u; i += kThreads) s4[i] = zero4;
     // the LDS tile is all zero again; the next tile's votes start after its first barrier
   }
 }
 
-template <int ROWS, bool NT, int CACHE>
-hipError_t launch_fill_cache(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev,
+template <int ROWS, bool NT, bool LONG>
+hipError_t launch_fill_form(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev,
                              bool vec, bool emit, size_t lds, hipStream_t s)
 {
   dim3 grid((g.n_tiles + g.fill_tiles - 1) / g.fill_tiles, n_ev);  // interleaved tiles
   if (vec) {
-    if (emit) hipLaunchKernelGGL((k_fill<ROWS, true, true, NT, CACHE>), grid, dim3(kBlock), lds, s, g, ev0, evs);
-    else hipLaunchKernelGGL((k_fill<ROWS, true, false, NT, CACHE>), grid, dim3(kBlock), lds, s, g, ev0, evs);
+    if (emit) hipLaunchKernelGGL((k_fill<ROWS, true, true, NT, LONG>), grid, dim3(LONG ? 2 * kBlock : kBlock), lds, s, g, ev0, evs);
+    else hipLaunchKernelGGL((k_fill<ROWS, true, false, NT, LONG>), grid, dim3(LONG ? 2 * kBlock : kBlock), lds, s, g, ev0, evs);
   } else {
-    if (emit) hipLaunchKernelGGL((k_fill<ROWS, false, true, NT, CACHE>), grid, dim3(kBlock), lds, s, g, ev0, evs);
-    else hipLaunchKernelGGL((k_fill<ROWS, false, false, NT, CACHE>), grid, dim3(kBlock), lds, s, g, ev0, evs);
+    if (emit) hipLaunchKernelGGL((k_fill<ROWS, false, true, NT, LONG>), grid, dim3(LONG ? 2 * kBlock : kBlock), lds, s, g, ev0, evs);
+    else hipLaunchKernelGGL((k_fill<ROWS, false, false, NT, LONG>), grid, dim3(LONG ? 2 * kBlock : kBlock), lds, s, g, ev0, evs);
   }
   return hipGetLastError();
 }
@@ -501,8 +514,8 @@ hipError_t launch_fill_rows(const DevGrid& g, const EvDesc& ev0, const EvDesc* e
                             bool vec, bool emit, bool long_lists, size_t lds, hipStream_t s)
 {
   // long-list variant only where tiles are narrow enough for it to matter (rows <= 8)
-  if (ROWS <= 8 && long_lists) return launch_fill_cache<ROWS, NT, 8>(g, ev0, evs, n_ev, vec, emit, lds, s);
-  return launch_fill_cache<ROWS, NT, 2>(g, ev0, evs, n_ev, vec, emit, lds, s);
+  if (ROWS <= 8 && long_lists) return launch_fill_form<ROWS, NT, true>(g, ev0, evs, n_ev, vec, emit, lds, s);
+  return launch_fill_form<ROWS, NT, false>(g, ev0, evs, n_ev, vec, emit, lds, s);
 }
 }  // namespace
 

@@ -70,6 +70,7 @@ struct DevGrid {
   int32_t fill_tiles;      // fill tiles per workgroup (filled in turn)
   int32_t phi_sectors;     // 1: phi cells are independent sectors (no phi widening or neighbours)
   int32_t packed_lists;    // 1: always the counting-sort (packed) slab lists, never direct ones
+  int32_t finite_votes;    // 1: no vote of a hit with finite 1/(2y) is NaN (bounded A, finite inv_db)
   int32_t dense_w;         // 1: the stencil peak search is available on this grid (0: not)
   int32_t dense_rows;      // A rows per workgroup of the stencil peak search (a multiple of 12)
   int32_t dense_hits;      // events with at least this many hits take the stencil (0: never)
@@ -194,7 +195,7 @@ hipError_t launch_readout(const DevGrid& g, const ht_peak* peaks, const int64_t*
 // Whether the fill of events of up to max_hits hits takes its long-list variant, which makes no
 // list of survivors.
 bool long_lists(const DevGrid& g, int64_t max_hits);
-size_t fill_lds_bytes(const DevGrid& g);
+size_t fill_lds_bytes(const DevGrid& g, bool long_l);
 int n_groups(const DevGrid& g);
 
 // Host helpers (ht_api.cpp).

@@ -183,6 +183,7 @@ __global__ __launch_bounds__(kBlock) void k_prep_direct(DevGrid g, EvDesc ev0, c
   uint32_t local[4] = {0u, 0u, 0u, 0u};
   if (h < e.n_hits) {
     p = prep_hit(g, tab_phi, tab_th, hx, hy, hz);
+    if (isinf(p.k)) p.n = 0;  // (2y subnormal) every B is infinite or NaN: it has no votes
     // constant indices keep p.slab and local in registers (a runtime index would put them in
     // scratch memory)
 #pragma unroll
@@ -225,6 +226,7 @@ __global__ __launch_bounds__(kBlock) void k_prep(DevGrid g, EvDesc ev0, const Ev
   uint32_t local[4] = {0u, 0u, 0u, 0u};
   if (h < e.n_hits) {
     p = prep_hit(g, tab_phi, tab_th, hx, hy, hz);
+    if (isinf(p.k)) p.n = 0;  // (2y subnormal) every B is infinite or NaN: it has no votes
     e.hit_rec[h] = make_float4(p.x, p.r2, p.k, 0.0f);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -1457,9 +1459,9 @@ hipError_t launch_fill_nt(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs
 
 int n_groups(const DevGrid& g) { return (g.n_tiles + g.group_tiles - 1) / g.group_tiles; }
 
-size_t fill_lds_bytes(const DevGrid& g)
+size_t fill_lds_bytes(const DevGrid& g, bool long_l)
 {
-  return (size_t)g.rows * (((size_t)g.n_b + 3) & ~(size_t)3) * sizeof(uint32_t);
+  return (size_t)g.rows * ((((size_t)g.n_b + 3) & ~(size_t)3) + (long_l ? kSpill : 0)) * sizeof(uint32_t);
 }
 
 hipError_t launch_prep(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev,
@@ -1482,9 +1484,10 @@ hipError_t launch_prep(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, i
 
 bool long_lists(const DevGrid& g, int64_t max_hits)
 {
-  // more than two records per thread expected per slab (a hit has at most four cells, about
-  // three on average): load eight per thread per round trip
-  return max_hits * 3 > (int64_t)2 * kBlock * g.n_slabs;
+  // more than two records per thread of the short-list fill expected per slab (a hit has at most
+  // four cells, about three on average), in tiles narrow enough for it to matter; and votes that
+  // are never NaN, which the long-list fill cannot tell from bin 0
+  return g.rows <= 8 && g.finite_votes && max_hits * 3 > (int64_t)2 * kBlock * g.n_slabs;
 }
 
 hipError_t launch_fill(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev,
@@ -1493,8 +1496,7 @@ hipError_t launch_fill(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, i
   const bool long_l = long_lists(g, max_hits);
   // store kind 2: 4-byte stores (the dword path), otherwise 16-byte stores where rows allow
   const bool vec = (g.n_b % 4) == 0 && g.nt_store != 2;
-  // long lists: 64 spill words past the tile (one per lane) for votes outside the row
-  const size_t lds = fill_lds_bytes(g) + (long_l ? 64 * sizeof(uint32_t) : 0);
+  const size_t lds = fill_lds_bytes(g, long_l);
   return launch_fill_nt(g, ev0, evs, n_ev, g.nt_store == 1, vec, emit, long_l, lds, s);
 }
 

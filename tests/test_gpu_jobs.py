@@ -113,3 +113,30 @@ def test_noalloc_searches_in_slices(B):
             assert torch.equal(acc, ref)
     finally:
         B.ht_set_tuning(spec)
+
+
+@pytest.mark.parametrize("ranges", [(-2000.0, 2000.0), (-1e18, 1e18), (-3e38, 3e38), (0.0, 1.5e-45), (-1e-30, 3e-30)])
+@pytest.mark.parametrize("rows", [2, 8])
+def test_long_lists_with_extreme_hits_bit_exact(B, ranges, rows):
+    """Votes that overflow, vanish or would be NaN (1/(2y) infinite, A x infinite, an infinite bin
+    scale) through the long-list fill, and on grids that it leaves to the other one."""
+    import torch
+    from oracle import oracle
+    lo, hi = ranges
+    spec = synth.GridSpec(1, 3, 21, 64, a_min=lo, a_max=hi, b_min=lo, b_max=hi, threshold=2)
+    rng = np.random.default_rng(7)
+    n = 3000  # three slabs: more than the 512 records each that make a long list
+    scale = rng.choice([1.0, 1e3, 1e-3, 1e18, 1e-18, 1e-25, 3e-39, 1e-42], (2, n))
+    x, y = (rng.uniform(-1, 1, (2, n)) * scale).astype(np.float32)
+    x[::17] = 0.0
+    z = rng.uniform(-2000, 2000, n).astype(np.float32)
+    say("ranges", ranges, "rows", rows)
+    M, _ = oracle.fill(oracle.OracleGrid(*spec.as_tuple()), x, y, z)
+    B.ht_set_tuning(spec, rows=rows, dense_hits=-1)
+    try:
+        acc, c, v, k = B.fill_peaks(spec, *B.hits_to_device(x, y, z))
+        torch.cuda.synchronize()
+    finally:
+        B.ht_set_tuning(spec)
+    assert np.array_equal(B.as_u32(acc), M)
+    same_peaks(spec, (c, v, k), M, ranges)
