@@ -492,7 +492,8 @@ __device__ __forceinline__ void tile_range(const DevGrid& g, int tile, uint32_t*
 // to kFew of them half a wave each, more a lane each, the nine rows of the own theta cell first
 // (they beat most: adjacent phi cells hold the same circles), and those left, packed again into
 // full waves, the rows of the two theta neighbours. The group's peaks are then sorted by rank in
-// LDS and stored in the group's segment.
+// LDS and stored in the group's segment; the masks are written back as the peaks' masks, for
+// groups whose peaks do not fit it.
 constexpr uint32_t kList = 1024;  // four jobs have at most this many survivors (one per 2 x 2 cells)
 constexpr uint32_t kFew = 64;
 constexpr uint32_t kSuperGroups = 2048;
@@ -583,7 +584,8 @@ __global__ __launch_bounds__(kBlock) void k_peak_test(DevGrid g, EvDesc ev0, con
     x.w0 = min(max(x.b, 1u) - 1u, max(nb, 3u) - 3u);
     return x;
   };
-  auto keep = [&](const TestCell& x) {
+  auto keep = [&](uint32_t pos, const TestCell& x) {
+    atomicOr(&s_m[pos >> 5], 1u << (pos & 31u));
     const uint32_t i = atomicAdd(&s_np, 1u);
     if (i < seg_cap) {
       s_pc[i] = x.c;
@@ -652,6 +654,7 @@ __global__ __launch_bounds__(kBlock) void k_peak_test(DevGrid g, EvDesc ev0, con
         for (uint32_t i = i0; i < i0 + step && w + 4u * i < n_job; ++i) {  // uniform
           const uint32_t slot = w + 4u * i;
           uint32_t mm = m16[slot * 64u + lane];
+          m16[slot * 64u + lane] = 0;
           const uint32_t c = (uint32_t)__builtin_popcount(mm), incl = wave_incl_scan(c);
           uint32_t from = 0u;
           if (lane == 63u) from = atomicAdd(&s_n, incl);
@@ -680,7 +683,7 @@ __global__ __launch_bounds__(kBlock) void k_peak_test(DevGrid g, EvDesc ev0, con
             for (uint32_t q = 0; q < 4; ++q) {
               const uint32_t i = b0 + half + 8u * q;
               const uint32_t hm = (uint32_t)(__builtin_amdgcn_ballot_w64(beaten[q]) >> (lane & 32u));
-              if (k == 0u && i < n && hm == 0u) keep(x[q]);
+              if (k == 0u && i < n && hm == 0u) keep(s_pos[i], x[q]);
             }
           }
         } else {
@@ -702,15 +705,23 @@ __global__ __launch_bounds__(kBlock) void k_peak_test(DevGrid g, EvDesc ev0, con
             lds_barrier();
           }
           for (uint32_t i = threadIdx.x; i < n2; i += kBlock) {
-            const TestCell x = cell_of(s_pos[i]);
+            const uint32_t pos = s_pos[i];
+            const TestCell x = cell_of(pos);
             const bool w0 = g.n_theta > 1 && slice_wins<NARROW>(g, acc, x, -1);  // uniform condition
             const bool w1 = g.n_theta > 1 && slice_wins<NARROW>(g, acc, x, 1);
-            if (!w0 && !w1) keep(x);
+            if (!w0 && !w1) keep(pos, x);
           }
         }
         lds_barrier();
         if (threadIdx.x == 0) s_n = 0u;
         lds_barrier();
+      }
+      for (uint32_t i = 0u; i < kPassJobs / 4 && w + 4u * i < n_job; ++i) {  // uniform: the peaks' masks
+        const uint32_t slot = w + 4u * i;
+        const size_t at = (size_t)(l0 + win + s_ids[p0 + slot]) * 64u + lane;
+        const uint32_t mm = m16[slot * 64u + lane];
+        if (two) ((GLOBAL uint16_t*)gp(e.masks))[at] = (uint16_t)mm;
+        else gp(e.masks)[at] = (uint8_t)mm;
       }
     }
   }
@@ -743,43 +754,56 @@ __global__ __launch_bounds__(kBlock) void k_peak_test(DevGrid g, EvDesc ev0, con
 }
 
 // Ordered peak list, one wave per group: its output offset is the sum of the earlier groups'
-// counts, loaded together with its first 64 peaks, so an ordinary group is one memory round trip.
-// Past kSuperGroups groups the counts are also kept per block of 64 groups (not below: the atomic
-// additions of a test to one cache line take 10 ns each, which cost 9 us on the paper event). Peaks found from the list are in
-// no order in their segment: each lane ranks its own among the group's. A group with more peaks
-// than its segment holds walks its survivors' masks in cell order and tests them again (whole job
-// rows: band by band, row by row, strip by strip, then lane and column).
+// counts (a workgroup's four waves share it: with 2048 groups a wave of its own took 6.2 us, four
+// together 4.7), loaded together with its first 64 peaks, so an ordinary group is one memory
+// round trip. Past kSuperGroups groups the counts are also kept per block of 64 groups (not
+// below: the atomic additions of a test to one cache line take 10 ns each, which cost 9 us on the
+// paper event). Peaks found from the lists are in no order in their segment: each lane ranks its
+// own among the group's. A group with more peaks than its segment holds is listed from its masks
+// in LDS, in cell order (whole job rows: band by band, row by row, strip by strip, then lane and
+// column), up to eight jobs' masks in flight; masks that the lists replaced still hold survivors,
+// which are tested again.
 template <bool NARROW>
 __global__ __launch_bounds__(kBlock) void k_peak_write(DevGrid g, EvDesc ev0, const EvDesc* evs)
 {
   __shared__ __align__(16) uint32_t s_all[kBlock / 64][kSegMax];
+  __shared__ uint16_t s_m[kBlock / 64][8 * 64];
+  __shared__ uint32_t s_sum[kBlock / 64];
   EvDesc e = load_ev(ev0, evs);
   if (e.dense) return;  // uniform: written by k_peak_write_dense
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const uint32_t G = blockIdx.x * (kBlock / 64) + w;
-  if (G >= e.n_grp) return;  // uniform
   const bool a8 = ((uintptr_t)e.out & 7u) == 0;
   const uint32_t seg_cap = (uint32_t)g.j.seg;
-  const GLOBAL u32x2* const seg = (const GLOBAL u32x2*)gp((const uint2*)e.seg) + (size_t)G * seg_cap;
+  const bool live = G < e.n_grp;  // uniform in a wave
+  const uint32_t Gl = live ? G : 0u;
+  const GLOBAL u32x2* const seg = (const GLOBAL u32x2*)gp((const uint2*)e.seg) + (size_t)Gl * seg_cap;
   const u32x2 head = seg[lane];  // may hold no peaks yet
-  const uint32_t mine = gp(e.group_pk)[G];
   // the test worked from the lists if they were made and none overflowed
   const bool sorted = !e.lists || gp((const uint32_t*)e.slab_cnt)[kListOver] != 0u;
-  const uint32_t s0 = e.n_grp > kSuperGroups ? G & ~63u : 0u;  // groups before s0: by their blocks
+  const uint32_t G0 = blockIdx.x * (kBlock / 64);                      // the workgroup's first group
+  const uint32_t s0 = e.n_grp > kSuperGroups ? G0 & ~63u : 0u;         // groups before s0: by their blocks
+  const uint32_t own = G0 + lane < e.n_grp && lane < kBlock / 64 ? gp(e.group_pk)[G0 + lane] : 0u;
   uint32_t part = 0u;
-  for (uint32_t i = lane; i < s0 / 64u; i += 64u) part += gp(e.super_pk)[i];
-  for (uint32_t i0 = s0; i0 < G; i0 += 16u * 64u) {  // uniform; sixteen loads in flight
-    uint32_t x[16];
+  for (uint32_t i = threadIdx.x; i < s0 / 64u; i += kBlock) part += gp(e.super_pk)[i];
+  for (uint32_t i0 = s0; i0 < G0; i0 += 8u * kBlock) {  // uniform; eight loads in flight
+    uint32_t x[8];
 #pragma unroll
-    for (uint32_t k = 0; k < 16; ++k) {
-      const uint32_t i = i0 + k * 64u + lane;
-      x[k] = i < G ? gp(e.group_pk)[i] : 0u;
+    for (uint32_t k = 0; k < 8; ++k) {
+      const uint32_t i = i0 + k * kBlock + threadIdx.x;
+      x[k] = i < G0 ? gp(e.group_pk)[i] : 0u;
     }
 #pragma unroll
-    for (uint32_t k = 0; k < 16; ++k) part += x[k];
+    for (uint32_t k = 0; k < 8; ++k) part += x[k];
   }
-  int64_t base = (int64_t)wave_sum(part);
+  part = wave_sum(part);
+  if (lane == 0u) s_sum[w] = part;
+  lds_barrier();
+  if (!live) return;
+  const uint32_t mine = (uint32_t)__builtin_amdgcn_readlane((int)own, (int)w);
+  int64_t base = (int64_t)(s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3]);
+  for (uint32_t k = 0; k < w; ++k) base += (uint32_t)__builtin_amdgcn_readlane((int)own, (int)k);
   if (e.carry_in) base += *gp(e.carry_in);
   if (G == e.n_grp - 1u && lane == 0u) {
     *gp(e.n_found) = base + mine;
@@ -824,38 +848,63 @@ __global__ __launch_bounds__(kBlock) void k_peak_write(DevGrid g, EvDesc ev0, co
   const uint32_t P = (uint32_t)g.j.sub, ch = (uint32_t)g.j.ch, strips = (uint32_t)g.j.row_jobs;
   const uint32_t sub = P > 1u ? lane / (uint32_t)g.j.units : 0u;
   const uint32_t unit0 = P > 1u ? lane - sub * (uint32_t)g.j.units : lane;
-  for (uint32_t j0 = 0u; j0 < nj; j0 += strips)  // uniform, as all that follow
-    for (uint32_t b = 0u; b < P; ++b)
+  uint32_t n = 0u;  // cells listed in s_all[w]
+  auto flush = [&]() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+#pragma unroll 1
+    for (uint32_t i0 = 0u; i0 < n; i0 += 64u) {  // uniform
+      bool pk = i0 + lane < n;
+      const uint32_t c = s_all[w][min(i0 + lane, n - 1u)];
+      const uint32_t v = gp((const uint32_t*)e.acc)[c];
+      if (!sorted) {  // uniform
+        const TestCell x = test_cell(g, c, v);
+#pragma unroll 1
+        for (int dt = -1; dt <= 1; ++dt)
+          if (pk) pk = !slice_wins<NARROW>(g, e.acc, x, dt);
+      }
+      const uint64_t b = __builtin_amdgcn_ballot_w64(pk);
+      const int64_t o = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
+      if (pk && o < e.cap) st_peak(e.out, o, c, v, a8);
+      base += (int64_t)__builtin_popcountll(b);
+    }
+    n = 0u;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+  };
+  auto mask_of = [&](uint32_t j) -> uint32_t {  // job j of the group; 0 without survivors
+    const size_t i = (size_t)(l0 + j) * 64u + lane;
+    const uint32_t m = g.j.elem_bytes == 2 ? ((const GLOBAL uint16_t*)gp((const uint8_t*)e.masks))[i]
+                                           : gp((const uint8_t*)e.masks)[i];
+    return gp((const uint8_t*)e.job_any)[l0 + j] ? m : 0u;
+  };
+  auto list = [&](uint32_t j, uint32_t nib, uint32_t row) {  // a lane's columns of one row of job j
+    if (__builtin_amdgcn_ballot_w64(nib != 0u) == 0ull) return;  // uniform
+    const JobAt at = job_at(g, (uint32_t)(first + j));
+    const uint32_t c = (at.slab * (uint32_t)g.n_a + at.a0 + row) * nb + 4u * (P > 1u ? unit0 : at.st * 64u + lane);
+    const uint32_t k = (uint32_t)__builtin_popcount(nib), incl = wave_incl_scan(k);
+    uint32_t i = n + incl - k;
+    for (; nib; nib &= nib - 1u) s_all[w][i++] = c + (uint32_t)__builtin_ctz(nib);
+    n += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+    if (n > kSegMax - 128u) flush();  // uniform; a row of a job has at most 128 survivors
+  };
+  if (strips <= 8u) {  // uniform, as all that follow
+    const uint32_t rows = 8u / strips;  // job rows at a time
+    for (uint32_t j0 = 0u; j0 < nj; j0 += rows * strips) {
+      const uint32_t jobs = min(rows * strips, nj - j0);
+#pragma unroll
+      for (uint32_t s = 0; s < 8; ++s) s_m[w][s * 64u + lane] = s < jobs ? (uint16_t)mask_of(j0 + s) : (uint16_t)0;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+      for (uint32_t r = 0u; r < jobs; r += strips)
+        for (uint32_t b = 0u; b < P; ++b)
+          for (uint32_t q = 0u; q < ch; ++q)
+            for (uint32_t s = 0u; s < strips; ++s)
+              list(j0 + r + s, sub == b ? s_m[w][(r + s) * 64u + lane] >> (4u * q) & 15u : 0u, b * ch + q);
+    }
+  } else {  // wide rows: one band per job row
+    for (uint32_t j0 = 0u; j0 < nj; j0 += strips)
       for (uint32_t q = 0u; q < ch; ++q)
-        for (uint32_t s = 0u; s < strips; ++s) {
-          const uint64_t jl = l0 + j0 + s;
-          if (gp((const uint8_t*)e.job_any)[jl] == 0) continue;
-          const size_t i = (size_t)jl * 64u + lane;
-          const uint32_t m = g.j.elem_bytes == 2 ? ((const GLOBAL uint16_t*)gp((const uint8_t*)e.masks))[i]
-                                                 : gp((const uint8_t*)e.masks)[i];
-          uint32_t nib = sub == b ? m >> (4u * q) & 15u : 0u;
-          const JobAt at = job_at(g, (uint32_t)(first + j0 + s));
-          const uint32_t c = (at.slab * (uint32_t)g.n_a + at.a0 + b * ch + q) * nb +
-                             4u * (P > 1u ? unit0 : at.st * 64u + lane);
-          uint32_t v[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-          for (uint32_t k = 0; k < 4; ++k)
-            if (nib >> k & 1u) {
-              const TestCell x = test_cell(g, c + k, gp(e.acc)[c + k]);
-              v[k] = x.v;
-              for (int dt = -1; dt <= 1; ++dt)
-                if (slice_wins<NARROW>(g, e.acc, x, dt)) nib &= ~(1u << k);
-            }
-          const uint32_t n = (uint32_t)__builtin_popcount(nib), incl = wave_incl_scan(n);
-          int64_t o = base + (int64_t)(incl - n);
-#pragma unroll
-          for (uint32_t k = 0; k < 4; ++k)
-            if (nib >> k & 1u) {
-              if (o < e.cap) st_peak(e.out, o, c + k, v[k], a8);
-              ++o;
-            }
-          base += (int64_t)__builtin_amdgcn_readlane((int)incl, 63);
-        }
+        for (uint32_t s = 0u; s < strips; ++s) list(j0 + s, mask_of(j0 + s) >> (4u * q) & 15u, q);
+  }
+  flush();
 }
 
 constexpr int kWriteStage = 4096;  // peaks of a group staged in LDS by the dense writer
