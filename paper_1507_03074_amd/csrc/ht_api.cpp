@@ -152,6 +152,8 @@ Tiling choose_tiling(const ht_grid& g)
   if (forced_gt == 16 || forced_gt == 32 || forced_gt == 64) gt = forced_gt;
   t.group_tiles = gt;
   t.nt_store = std::min(2, std::max(0, env_int("HT_FILL_NT", 0)));
+  t.auto_nt = env_int("HT_FILL_NT", -1) < 0 ? 1 : 0;
+  t.auto_rows = env_int("HT_FILL_ROWS", 0) <= 0 && env_int("HT_FILL_LDS_BYTES", 0) <= 0 ? 1 : 0;
   // fill tiles per workgroup: one by default (measured fastest on the paper grid: many short
   // workgroups hide the record-load latency better than fewer workgroups looping over tiles)
   int ft = 1;
@@ -173,10 +175,16 @@ Tiling choose_tiling(const ht_grid& g)
     }
   }
   if (have) {
-    if (tu.rows > 0 && t.lds_fill) t.rows = tu.rows;
+    if (tu.rows > 0 && t.lds_fill) {
+      t.rows = tu.rows;
+      t.auto_rows = 0;
+    }
     if (tu.group_tiles > 0) t.group_tiles = tu.group_tiles;
     if (tu.cand_cap > 0) t.cand_cap = tu.cand_cap;
-    if (tu.nt_store >= 0) t.nt_store = tu.nt_store;
+    if (tu.nt_store >= 0) {
+      t.nt_store = tu.nt_store;
+      t.auto_nt = 0;
+    }
     if (tu.tiles_per_block > 0) t.fill_tiles = tu.tiles_per_block;
     t.tiles_per_slab = (g.n_a + t.rows - 1) / t.rows;
     t.n_tiles = g.n_theta * g.n_phi * t.tiles_per_slab;
@@ -197,15 +205,22 @@ Tiling choose_tiling(const ht_grid& g)
     if (forced > 0) s_rows = std::min(forced, 4096);
     t.dense_rows = std::max(12, ((s_rows + 11) / 12) * 12);
   }
-  // default: events with at least n_slabs n_b / 4 hits, a quarter of a hit per (theta, phi, B)
-  // cell, where the stencil's one pass over the matrix measured faster than the candidate pool
-  // (on the 4x16x1024x1024 grid: 16384 hits; the pool won up to 15k hits, the stencil from 18k);
-  // -1 never
-  int64_t dh = ((int64_t)g.n_theta * g.n_phi * g.n_b + 3) / 4;
+  // The reported default, n_slabs n_b / 4 hits (a quarter of a hit per (theta, phi, B) cell), is
+  // where one pass over the matrix beats a test of every candidate. The survivors are a quarter of
+  // them, so unless the caller sets a threshold the stencil starts at twice that, or two and a half
+  // times where a pass is long, from 128 MiB on. Whole call, survivors against stencil, in us:
+  // 4x16x1024x1024 at 2 times 113 / 134, at 3 times 155 / 144; 4x16x512x512 at 1 time 40 / 46, at
+  // 2 times 55 / 52; 4x16x64x64 at 2 times 20 / 27; 3x7x501x333 at 2 times 28 / 30, at 3 times
+  // 34 / 32. -1: never
+  const int64_t def = ((int64_t)g.n_theta * g.n_phi * g.n_b + 3) / 4;
+  const int64_t bytes = 4 * (int64_t)g.n_theta * g.n_phi * g.n_a * g.n_b;
+  int64_t dh = def, from = bytes >= ((int64_t)128 << 20) ? def * 5 / 2 : def * 2;
   const int forced_dh = env_int("HT_DENSE_HITS", 0);
-  if (forced_dh != 0) dh = forced_dh;
-  if (have && tu.dense_hits != 0) dh = tu.dense_hits;
-  t.dense_hits = (t.dense_w > 0 && dh > 0) ? (int32_t)std::min<int64_t>(dh, 1 << 28) : 0;
+  if (forced_dh != 0) dh = from = forced_dh;
+  if (have && tu.dense_hits != 0) dh = from = tu.dense_hits;
+  const bool on = t.dense_w > 0 && dh > 0;
+  t.dense_hits = on ? (int32_t)std::min<int64_t>(dh, 1 << 28) : 0;
+  t.dense_from = on ? (int32_t)std::min<int64_t>(from, 1 << 28) : 0;
   return t;
 }
 
@@ -271,7 +286,44 @@ int get_tables(const ht_grid& g, int dev, DevTables* out)
   return HT_OK;
 }
 
-DevGrid make_devgrid(const ht_grid& g, const DevTables& t, const Tiling& tl, int n_ev)
+// The rows per tile and the store kind of a launch of n_ev events of up to max_hits hits, where
+// the caller set none (the tiling's are those of crowded events).
+static void shape_launch(DevGrid* d, const Tiling& tl, int n_ev, int64_t max_hits)
+{
+  const int rows = d->rows;
+  if (tl.auto_rows && tl.lds_fill) {
+    // Long slab lists: 32 KiB tiles of up to eight rows, as the long-list fill takes (14k hits on
+    // 512x512 planes: 54.6 us with eight rows, 64.8 with sixteen, which go to the other fill).
+    // Short ones: tiles of 16 KiB, twice the workgroups per CU (paper event, 4 against 8 rows: 62.3
+    // and 66.5 us; at 512 and 256 columns the 16 KiB tile is the fastest of three as well), but
+    // four rows, a whole band. Launches of fewer tiles than the chip has CUs take lower ones (250
+    // hits on 4x16x64x64: 17.0 us with 16 rows, 17.8 with 64; a hundred such events: 85 and 64).
+    d->rows = std::min(rows, 8);
+    if (!long_lists(*d, max_hits)) {
+      d->rows = rows;
+      while (d->rows > 4 && (int64_t)d->rows * d->n_b * 4 > 16384) d->rows /= 2;
+      while (d->rows > 8 && (int64_t)d->n_slabs * ((d->n_a + d->rows - 1) / d->rows) * n_ev < 256) d->rows /= 2;
+    }
+    d->tiles_per_slab = (d->n_a + d->rows - 1) / d->rows;
+    d->n_tiles = d->n_slabs * d->tiles_per_slab;
+  }
+  const bool long_l = tl.lds_fill && long_lists(*d, max_hits);
+  if (tl.auto_nt) {
+    // Non-temporal stores where the launch writes more than the 256 MiB last-level cache holds (100
+    // paper events: 4.5 and 5.3 ms), or the fill is not what waits for its stores: long lists and
+    // the stencil (14k hits: 72.6 and 81.5 us; 40k hits with the stencil: 137 and 161 us). A single
+    // ordinary event's matrix stays in the cache for its peak test and for the next event in the
+    // same matrix (paper event in one matrix: 56.7 us, non-temporal 61.6; in three by turns 64.0
+    // and 62.3). Below 128 MiB the stencil reads what the cache kept (512x512 planes: 46.9 and
+    // 51.9 us); below 4 MiB the L2 does (17.0 and 18.8 us).
+    const int64_t bytes = (int64_t)n_ev * 4 * d->n_slabs * d->n_a * d->n_b;
+    const bool dense = dense_peaks(*d, max_hits);
+    d->nt_store = bytes > ((int64_t)256 << 20) || (dense && bytes >= ((int64_t)128 << 20)) ||
+                  (long_l && !dense && bytes >= ((int64_t)4 << 20));
+  }
+}
+
+DevGrid make_devgrid(const ht_grid& g, const DevTables& t, const Tiling& tl, int n_ev, int64_t max_hits)
 {
   DevGrid d;
   std::memset(&d, 0, sizeof(d));  // padding too: the bytes key the graph cache
@@ -299,11 +351,12 @@ DevGrid make_devgrid(const ht_grid& g, const DevTables& t, const Tiling& tl, int
                    std::isfinite((float)((double)g.n_b / ((double)g.b_max - (double)g.b_min))) ? 1 : 0;
   d.dense_w = tl.dense_w;
   d.dense_rows = tl.dense_rows;
-  d.dense_hits = tl.dense_hits;
+  d.dense_hits = tl.dense_from;
   d.a2 = t.a2;
   d.phi_cs = t.phi;
   d.th_cs = t.th;
-  set_jobs(&d, tl.lds_fill ? tl.rows : 0, n_ev);
+  shape_launch(&d, tl, n_ev, max_hits);
+  set_jobs(&d, tl.lds_fill ? d.rows : 0, n_ev);
   return d;
 }
 
@@ -323,16 +376,22 @@ void set_jobs(DevGrid* g, int tile_rows, int n_ev)
   j.row_jobs = j.ch * j.sub == 1 ? 1 : j.strips;
   // Groups of the peak test, one workgroup each: 32 jobs a group (2048 groups on the paper grid; a
   // 14k-hit event's test takes 22.8 us, 26.6 us with 64 jobs, 25.2 us with 16); smaller events get
-  // smaller groups, down to 8 jobs, to use more CUs; launches of many groups larger ones, which
-  // pay a workgroup's start once for more jobs (its flags come 256 jobs at a time).
+  // smaller groups, down to 8 jobs, to use more CUs (24.6k hits on 512x512 planes: 61 us whole,
+  // 100 us with a quarter of the groups), batches of them fewer (100 small events: 62.6 and 66.7
+  // us); launches of many groups get larger ones, which pay a workgroup's start once for more jobs
+  // (its flags come 256 jobs at a time).
   int64_t gj = 32;
   const int64_t all = (int64_t)j.n_jobs * n_ev;
-  while (gj > 8 && all / gj < 512) gj /= 2;
+  while (gj > 8 && all / gj < (n_ev > 1 ? 512 : 2048)) gj /= 2;
   while (gj < kBlockJobs / 2 && all / gj > 65536) gj *= 2;
   while (j.n_jobs / gj > 16384) gj *= 2;
   gj = std::max<int64_t>(1, gj / j.row_jobs) * j.row_jobs;
   j.group_jobs = (int32_t)gj;
   j.n_groups = (uint32_t)((j.n_jobs + gj - 1) / gj);
+  // The test adds its peaks to the counts with atomics, which take 10 ns each on one cache line (32
+  // words), and peaks cluster: the counts of up to 16384 words are spread out.
+  j.pk_step = 1;
+  while (j.pk_step < 32 && (int64_t)j.n_groups * j.pk_step * 2 <= 16384) j.pk_step *= 2;
   // one peak per 64 cells: uncorrelated counts give one local maximum per 81
   j.seg = (int32_t)std::min<int64_t>(kSegMax, std::max<int64_t>(128, 16 * gj));
 }
@@ -365,7 +424,7 @@ static size_t mask_bytes(const DevGrid& g)
 // peaks per group: of job rows (the fill's survivors), of tiles (the stencil)
 static size_t group_words(const DevGrid& g, int peaks)
 {
-  return std::max<size_t>((peaks & kPeakBands) ? g.j.n_groups : 0, (peaks & kPeakMask) ? (size_t)n_groups(g) : 0);
+  return std::max<size_t>((peaks & kPeakBands) ? (size_t)g.j.n_groups * g.j.pk_step : 0, (peaks & kPeakMask) ? (size_t)n_groups(g) : 0);
 }
 
 size_t event_scratch_bytes(const DevGrid& g, int64_t n, bool direct, int peaks)
@@ -551,13 +610,13 @@ int ensure_ev_staging(Workspace* w, int n_ev, hipStream_t s)
   return HT_OK;
 }
 
-int make_device_grid(const ht_grid& g, int dev, int n_ev, DevGrid* out)
+int make_device_grid(const ht_grid& g, int dev, int n_ev, int64_t max_hits, DevGrid* out)
 {
   int rc = validate_grid(&g);
   if (rc) return rc;
   DevTables t;
   if ((rc = get_tables(g, dev, &t))) return rc;
-  *out = make_devgrid(g, t, choose_tiling(g), n_ev);
+  *out = make_devgrid(g, t, choose_tiling(g), n_ev, max_hits);
   return HT_OK;
 }
 
@@ -619,13 +678,13 @@ struct Prepared {
   hipStream_t s;
 };
 
-int prepare(const ht_grid* grid, void* stream, Prepared* p, int n_ev = 1)
+int prepare(const ht_grid* grid, void* stream, Prepared* p, int n_ev, int64_t max_hits)
 {
   int rc = validate_grid(grid);
   if (rc) return rc;
   hipError_t e = hipGetDevice(&p->dev);
   if (e != hipSuccess) return fail_hip(e, "hipGetDevice");
-  if ((rc = make_device_grid(*grid, p->dev, n_ev, &p->g))) return rc;
+  if ((rc = make_device_grid(*grid, p->dev, n_ev, max_hits, &p->g))) return rc;
   p->s = (hipStream_t)stream;
   return HT_OK;
 }
@@ -737,6 +796,16 @@ int check_accessible(const void* ptr, const char* what)
   return HT_OK;
 }
 
+// The event size that a batch's launches are made for: prep grids are sized for a power-of-two
+// bucket of workgroups, so batches of one size share a graph (workgroups past an event's hits
+// return at once).
+int64_t batch_hits(int64_t max_hits)
+{
+  int64_t blocks = 1;
+  while (blocks * 256 < max_hits) blocks *= 2;
+  return max_hits > 0 ? blocks * 256 : 0;
+}
+
 // Scratch layout of a batch: direct slab lists for every event when each event allows them and
 // their scratch totals at most 8 GiB, else the counting sort for all (the 16-event batch of
 // 105600-hit events on the 8x32x2048x2048 grid takes the counting sort). Returns whether the
@@ -816,7 +885,7 @@ int run_event(const ht_grid* grid, const float* x, const float* y, const float* 
     return fail(HT_EINVAL, "peak output arguments are invalid");
   if (n > ((int64_t)1 << 28)) return fail(HT_EINVAL, "n_hits must be <= 2^28");
   Prepared p;
-  int rc = prepare(grid, stream, &p);
+  int rc = prepare(grid, stream, &p, 1, do_fill ? n : 0);
   if (rc) return rc;
   if (do_peaks && ((rc = check_accessible(out, "out")) || (rc = check_accessible(n_found, "n_found"))))
     return rc;
@@ -834,7 +903,7 @@ int run_event(const ht_grid* grid, const float* x, const float* y, const float* 
   std::memset(&ev, 0, sizeof(ev));
   carve_event_scratch(p.g, nh, direct, w->dev, &ev, layout);
   ev.dense = dense ? 1 : 0;
-  ev.lists = layout == kPeakBands && (!do_fill || atomic || !long_lists(p.g, nh)) ? 1 : 0;
+  ev.lists = layout == kPeakBands && (!do_fill || atomic || use_lists(p.g, nh, nh)) ? 1 : 0;
   use_counters(w, 0, &ev);
   ev.x = x;
   ev.y = y;
@@ -921,11 +990,13 @@ int ht_fill_peaks_batch(const ht_grid* grid, const ht_event* events, int32_t n_e
     if (ev.n_hits < 0 || ev.n_hits > ((int64_t)1 << 28) || ev.hit_offset < 0 || ev.peak_capacity < 0 ||
         ev.peak_offset < 0)
       return fail(HT_EINVAL, "event %d has invalid offsets or sizes", i);
+    max_hits = std::max(max_hits, ev.n_hits);
     if (ev.n_hits > 0 && (!x || !y || !z)) return fail(HT_EINVAL, "hit arrays are NULL");
     if (ev.peak_capacity > 0 && !out) return fail(HT_EINVAL, "out is NULL");
   }
+  const int64_t max_hits_b = batch_hits(max_hits);
   Prepared p;
-  if ((rc = prepare(grid, stream, &p, n_events))) return rc;
+  if ((rc = prepare(grid, stream, &p, n_events, max_hits_b))) return rc;
   if ((rc = check_accessible(out, "out")) || (rc = check_accessible(n_found, "n_found"))) return rc;
   std::vector<size_t> offs;
   size_t total_scratch = 0;
@@ -934,11 +1005,6 @@ int ht_fill_peaks_batch(const ht_grid* grid, const ht_event* events, int32_t n_e
   if ((rc = get_workspace(p.dev, p.s, total_scratch, &w))) return rc;
   if ((rc = ensure_ev_staging(w, n_events, p.s))) return rc;
   if ((rc = ensure_counters(w, n_events, p.s))) return rc;
-  // prep grids are sized for a power-of-two bucket of workgroups, so batches of one size share
-  // a graph (workgroups past an event's hits return at once)
-  int64_t blocks = 1;
-  while (blocks * 256 < max_hits) blocks *= 2;
-  const int64_t max_hits_b = max_hits > 0 ? blocks * 256 : 0;
   const uint64_t cells = n_cells(*grid);
   bool any_bands = false, any_dense = false;
   for (int32_t i = 0; i < n_events; ++i) {
@@ -950,8 +1016,7 @@ int ht_fill_peaks_batch(const ht_grid* grid, const ht_event* events, int32_t n_e
     any_dense = any_dense || dense;
     carve_event_scratch(p.g, ev.n_hits, direct, w->dev + offs[i], &d, dense ? kPeakMask : kPeakBands);
     d.dense = dense ? 1 : 0;
-    // the launch's fill variant goes by its largest event
-    d.lists = !dense && !(p.g.lds_fill && long_lists(p.g, max_hits_b)) ? 1 : 0;
+    d.lists = !dense && (!p.g.lds_fill || use_lists(p.g, max_hits_b, ev.n_hits)) ? 1 : 0;
     use_counters(w, i, &d);
     d.x = x ? x + ev.hit_offset : nullptr;
     d.y = y ? y + ev.hit_offset : nullptr;
@@ -1085,7 +1150,7 @@ int ht_readout(const ht_grid* grid, const ht_peak* peaks, const int64_t* n_found
   if (capacity < 0 || capacity > ((int64_t)1 << 31)) return fail(HT_EINVAL, "capacity out of range");
   if (!n_found || (capacity > 0 && (!peaks || !tracks))) return fail(HT_EINVAL, "NULL readout argument");
   Prepared p;
-  int rc = prepare(grid, stream, &p);
+  int rc = prepare(grid, stream, &p, 1, 0);
   if (rc) return rc;
   if ((rc = check_accessible(peaks, "peaks")) || (rc = check_accessible(n_found, "n_found")) ||
       (rc = check_accessible(tracks, "tracks")))
@@ -1108,7 +1173,7 @@ int ht_debug_hit_values(const ht_grid* grid, const float* x, const float* y, con
   if (n_hits < 0) return fail(HT_EINVAL, "n_hits < 0");
   if (n_hits > 0 && (!x || !y || !z || !info || !vals || !slabs)) return fail(HT_EINVAL, "NULL pointer");
   Prepared p;
-  int rc = prepare(grid, stream, &p);
+  int rc = prepare(grid, stream, &p, 1, 0);
   if (rc) return rc;
   return check_launch(launch_debug_hits(p.g, x, y, z, n_hits, info, vals, slabs, p.s), "debug launch");
 }
@@ -1134,10 +1199,11 @@ int ht_debug_batch_plan(const ht_grid* grid, const ht_event* events, int32_t n_e
     if (events[i].n_hits < 0 || events[i].n_hits > ((int64_t)1 << 28))
       return fail(HT_EINVAL, "event %d has an invalid size", i);
   // the tiling alone decides the layout; the tables (device memory) are not needed
-  const DevGrid g = make_devgrid(*grid, DevTables(), choose_tiling(*grid), n_events);
+  int64_t max_hits = 0;
+  for (int32_t i = 0; i < n_events; ++i) max_hits = std::max(max_hits, events[i].n_hits);
+  const DevGrid g = make_devgrid(*grid, DevTables(), choose_tiling(*grid), n_events, batch_hits(max_hits));
   std::vector<size_t> offs;
   size_t total = 0;
-  int64_t max_hits = 0;
   *direct = plan_batch(g, events, n_events, &offs, &total, &max_hits) ? 1 : 0;
   *scratch_bytes = (int64_t)total;
   return HT_OK;

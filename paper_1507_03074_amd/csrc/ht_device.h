@@ -229,7 +229,8 @@ template <int CH>
 __device__ __forceinline__ void list_survivors(const EvDesc& e, uint32_t job, uint32_t grp, uint32_t lane, uint32_t m,
                                                uint32_t c0, uint32_t nb, const u32x4 (&v)[CH])
 {
-  const uint32_t l = job % kLists;
+  const uint32_t l = (job * 0x9e3779b1u) >> 29;  // neighbouring jobs' survivors cluster: spread them
+  static_assert(kLists == 8, "the hash's top three bits choose the list");
   const uint32_t c = (uint32_t)__builtin_popcount(m), incl = wave_incl_scan(c);
   uint32_t from = 0u;
   if (lane == 63u) from = gatomic_add(e.slab_cnt + kListLens + l * kListLine, incl);

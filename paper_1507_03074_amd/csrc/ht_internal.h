@@ -21,10 +21,9 @@ constexpr int kMaxSlabs = 4096;
 // (cell, votes, group of jobs) go to kLists lists of kListCap entries each, its jobs taking the
 // lists in turn. One list would do but for its counter: atomic additions to one cache line take
 // 10 ns each, and an event of 10k hits has 5000 jobs with survivors; the lists' lengths are a
-// cache line (kListLine words) apart. The entries are four per half wave of a test of 1024
-// workgroups; an event with more survivors is tested group by group.
+// cache line (kListLine words) apart. An event with more survivors is tested group by group.
 constexpr uint32_t kLists = 8;
-constexpr uint32_t kListCap = 4096;
+constexpr uint32_t kListCap = 8192;
 constexpr uint32_t kListLine = 32;
 constexpr int kListLens = kMaxSlabs;
 constexpr int kListOver = kListLens + (int)(kLists * kListLine);
@@ -48,6 +47,7 @@ struct JobGeom {
   int32_t elem_bytes;               // mask bytes per lane: 2 (ch 4) or 1
   int32_t row_jobs;                 // jobs in whose order cells are not in order: a job row, or 1
   int32_t group_jobs;               // jobs per group of the peak test (whole job rows)
+  int32_t pk_step;                  // words from one group's peak count to the next
   int32_t seg;                      // peaks of a group that its segment holds (at most kSegMax)
   uint32_t n_jobs, n_groups;
 };
@@ -102,7 +102,7 @@ struct EvDesc {
   // candidate search (ordinary events): the groups [grp0, grp0 + n_grp) of the event, all of them
   // except where a caller's fixed scratch holds only a slice at a time
   uint32_t grp0, n_grp;
-  uint32_t* group_pk;   // [n_grp] peaks per group of jobs (or of tiles: crowded events)
+  uint32_t* group_pk;   // peaks per group of jobs, g.j.pk_step words apart (or [groups of tiles]: stencil)
   uint32_t* super_pk;   // [n_grp / 64, rounded up] peaks per 64 groups
   uint8_t* job_any;     // [jobs] 1: the job has survivors (its masks are valid)
   uint8_t* masks;       // [jobs][64 lanes] mask elements; jobs without the flag are not written
@@ -125,9 +125,12 @@ constexpr int kChunkCells = 62;
 // Launch shape of one grid (ht_tuning resolved against the defaults).
 struct Tiling {
   int32_t rows, tiles_per_slab, n_tiles, lds_fill, group_tiles, nt_store, fill_tiles;
+  int32_t auto_rows, auto_nt;  // 1: not set by the caller, so each launch may take its own
   int32_t cand_cap;  // reported and accepted only: the survivors of the fill take no pool entries
   int32_t packed_lists;
-  int32_t dense_w, dense_rows, dense_hits;  // stencil peak search (DevGrid fields of these names)
+  int32_t dense_w, dense_rows;  // stencil peak search (DevGrid fields of these names)
+  int32_t dense_hits;           // hits from which it is used: as reported,
+  int32_t dense_from;           // and as done (DevGrid::dense_hits)
 };
 Tiling choose_tiling(const ht_grid& g);
 
@@ -145,7 +148,8 @@ inline size_t th_floats(const ht_grid& g) { return 2 * (2 * (size_t)g.n_theta + 
 // The tables computed on the host in double and rounded once to float, into caller arrays of
 // the sizes above.
 void host_tables_into(const ht_grid& g, float* a2, float* inv_db, float* phi, float* th);
-DevGrid make_devgrid(const ht_grid& g, const DevTables& t, const Tiling& tl, int n_ev);
+// n_ev, max_hits: what the launches it is for hold.
+DevGrid make_devgrid(const ht_grid& g, const DevTables& t, const Tiling& tl, int n_ev, int64_t max_hits);
 // Sets g.j: the jobs of tiles of `tile_rows` rows, or with 0 those of a matrix that k_scan reads
 // (bands of four rows, or of one in very wide rows). n_ev: events of the launch.
 void set_jobs(DevGrid* g, int tile_rows, int n_ev);
@@ -192,8 +196,10 @@ hipError_t launch_fill_atomic(const DevGrid& g, const EvDesc& ev0, const EvDesc*
 hipError_t launch_readout(const DevGrid& g, const ht_peak* peaks, const int64_t* n_found, int64_t cap,
                           ht_track* tracks, double b_min, double db, hipStream_t s);
 
-// Whether the fill of events of up to max_hits hits takes its long-list variant, which makes no
-// list of survivors.
+// Whether the fill of a launch of events of up to max_hits hits makes lists of the survivors of an
+// event of `hits` hits.
+bool use_lists(const DevGrid& g, int64_t max_hits, int64_t hits);
+// Whether that fill takes its long-list variant (given g.rows).
 bool long_lists(const DevGrid& g, int64_t max_hits);
 size_t fill_lds_bytes(const DevGrid& g, bool long_l);
 int n_groups(const DevGrid& g);
@@ -215,8 +221,7 @@ int fail_hip(hipError_t e, const char* what);
 int validate_grid(const ht_grid* g);
 uint64_t n_cells(const ht_grid& g);
 // Validates the grid, uploads its tables once per device and picks the tiling.
-// n_ev: events of the launches it is for (a hint).
-int make_device_grid(const ht_grid& g, int dev, int n_ev, DevGrid* out);
+int make_device_grid(const ht_grid& g, int dev, int n_ev, int64_t max_hits, DevGrid* out);
 // The whole batched pipeline (prep, fill with candidates, peaks) for n_ev events whose
 // descriptors are already in device memory.
 // *prep_enqueued is set once the preparation (which counts into and clears the events' counter

@@ -310,7 +310,7 @@ __global__ __launch_bounds__(kBlock) void k_scan(DevGrid g, EvDesc ev0, const Ev
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const uint32_t nb = (uint32_t)g.n_b, units = (uint32_t)g.j.units, P = (uint32_t)g.j.sub;
   for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < e.n_grp; i += gridDim.x * kBlock) {
-    gp(e.group_pk)[i] = 0u;
+    gp(e.group_pk)[i * (uint32_t)g.j.pk_step] = 0u;
     if (i < (e.n_grp + 63u) / 64u) gp(e.super_pk)[i] = 0u;
   }
   if (counters)  // uniform
@@ -497,7 +497,7 @@ __device__ __forceinline__ void tile_range(const DevGrid& g, int tile, uint32_t*
 constexpr uint32_t kList = 1024;  // four jobs have at most this many survivors (one per 2 x 2 cells)
 constexpr uint32_t kFew = 64;
 constexpr uint32_t kSuperGroups = 2048;
-constexpr uint32_t kTestBlocks = 16 * kLists * 32 / kBlock;
+constexpr uint32_t kTestBlocks = 4 * kLists * 32 / kBlock;
 constexpr uint32_t kTestGrid = 8192;
 constexpr uint32_t kPassJobs = 64;
 
@@ -554,7 +554,7 @@ __global__ __launch_bounds__(kBlock) void k_peak_test(DevGrid g, EvDesc ev0, con
         for (uint32_t q = 0; q < 4; ++q) {
           const uint32_t hm = (uint32_t)(__builtin_amdgcn_ballot_w64(beaten[q]) >> (lane & 32u));
           if (k == 0u && hm == 0u) {
-            const uint32_t o = gatomic_add(e.group_pk + en[q].z, 1u);
+            const uint32_t o = gatomic_add(e.group_pk + en[q].z * (uint32_t)g.j.pk_step, 1u);
             if (supers) gatomic_add(e.super_pk + en[q].z / 64u, 1u);
             const u32x2 pk = {en[q].x, en[q].y};
             if (o < seg_cap) ((GLOBAL u32x2*)gp(e.seg))[(size_t)en[q].z * seg_cap + o] = pk;
@@ -728,7 +728,7 @@ __global__ __launch_bounds__(kBlock) void k_peak_test(DevGrid g, EvDesc ev0, con
   lds_barrier();
   const uint32_t n = s_np;
   if (threadIdx.x == 0) {
-    gp(e.group_pk)[grp] = n;
+    gp(e.group_pk)[grp * (uint32_t)g.j.pk_step] = n;
     if (n && supers) gatomic_add(e.super_pk + grp / 64u, n);
   }
   if (n == 0u || n > seg_cap) {  // uniform
@@ -782,9 +782,10 @@ __global__ __launch_bounds__(kBlock) void k_peak_write(DevGrid g, EvDesc ev0, co
   const u32x2 head = seg[lane];  // may hold no peaks yet
   // the test worked from the lists if they were made and none overflowed
   const bool sorted = !e.lists || gp((const uint32_t*)e.slab_cnt)[kListOver] != 0u;
+  const uint32_t ps = (uint32_t)g.j.pk_step;
   const uint32_t G0 = blockIdx.x * (kBlock / 64);                      // the workgroup's first group
   const uint32_t s0 = e.n_grp > kSuperGroups ? G0 & ~63u : 0u;         // groups before s0: by their blocks
-  const uint32_t own = G0 + lane < e.n_grp && lane < kBlock / 64 ? gp(e.group_pk)[G0 + lane] : 0u;
+  const uint32_t own = G0 + lane < e.n_grp && lane < kBlock / 64 ? gp(e.group_pk)[(G0 + lane) * ps] : 0u;
   uint32_t part = 0u;
   for (uint32_t i = threadIdx.x; i < s0 / 64u; i += kBlock) part += gp(e.super_pk)[i];
   for (uint32_t i0 = s0; i0 < G0; i0 += 8u * kBlock) {  // uniform; eight loads in flight
@@ -792,7 +793,7 @@ __global__ __launch_bounds__(kBlock) void k_peak_write(DevGrid g, EvDesc ev0, co
 #pragma unroll
     for (uint32_t k = 0; k < 8; ++k) {
       const uint32_t i = i0 + k * kBlock + threadIdx.x;
-      x[k] = i < G0 ? gp(e.group_pk)[i] : 0u;
+      x[k] = i < G0 ? gp(e.group_pk)[i * ps] : 0u;
     }
 #pragma unroll
     for (uint32_t k = 0; k < 8; ++k) part += x[k];
@@ -1539,6 +1540,17 @@ bool long_lists(const DevGrid& g, int64_t max_hits)
   return g.rows <= 8 && g.finite_votes && max_hits * 3 > (int64_t)2 * kBlock * g.n_slabs;
 }
 
+bool use_lists(const DevGrid& g, int64_t max_hits, int64_t hits)
+{
+  if (long_lists(g, max_hits)) return false;
+  // The survivors expected must fit: on the paper grid 2.7k at 5000 hits, 46k at 14142, 661k at
+  // 40000; about as the cube of the hits per (slab, B) column, times the cells. The lists hold 65k.
+  // The long-list fill makes none: with the code for them it spills registers (a 14142-hit event's
+  // fill took 68 us, not 55, and its test 23 us, not 24).
+  const double ratio = 4.0 * (double)hits / ((double)g.n_slabs * g.n_b);
+  return ratio * ratio * ratio * (double)g.n_slabs * g.n_a * g.n_b <= 48e6;
+}
+
 hipError_t launch_fill(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev,
                        bool emit, int64_t max_hits, hipStream_t s)
 {
@@ -1565,10 +1577,10 @@ hipError_t launch_scan(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, i
 hipError_t launch_peaks(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev, uint32_t n_grp,
                         hipStream_t s)
 {
-  // a workgroup per group while that fills the chip (kTestGrid workgroups), and at least 16 half
-  // waves per list
-  const unsigned most = std::max(kTestBlocks, kTestGrid / (unsigned)n_ev);
-  const dim3 tg(std::max(std::min(n_grp, most), kTestBlocks), n_ev);
+  // a workgroup per group, up to kTestGrid of them, and for the lists of small grids at least one
+  // per CU over all events
+  const unsigned least = std::max(kTestBlocks, 256u / (unsigned)n_ev), most = std::max(least, kTestGrid / (unsigned)n_ev);
+  const dim3 tg(std::min(std::max(n_grp, least), most), n_ev);
   if (g.n_b < 3) hipLaunchKernelGGL(k_peak_test<true>, tg, dim3(kBlock), 0, s, g, ev0, evs);
   else hipLaunchKernelGGL(k_peak_test<false>, tg, dim3(kBlock), 0, s, g, ev0, evs);
   const dim3 wg((n_grp + 3) / 4, n_ev);

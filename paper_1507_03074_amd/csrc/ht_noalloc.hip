@@ -60,13 +60,13 @@ size_t al256(size_t v) { return (v + 255) & ~(size_t)255; }
 // are not (rows past 70 000 cells), the search runs slice by slice, so the limit stays this one.
 size_t limit_bytes(const DevGrid& g, const Tiling& tl, int64_t n, bool direct, bool dense)
 {
-  const size_t t = (size_t)g.n_tiles;
+  const size_t t = (size_t)tl.n_tiles;
   size_t b = event_scratch_bytes(g, n, direct, dense ? kPeakMask : 0) + 4 * al256(4 * t);
   if (dense) return b;
   const size_t cells = (size_t)g.n_theta * g.n_phi * g.n_a * g.n_b;
   const size_t bound = (size_t)n * (g.phi_sectors ? 2 : 4) * (size_t)g.n_a / (size_t)g.threshold;
   const size_t pool = std::min<size_t>(std::max(t * (size_t)tl.cand_cap, std::min(cells, bound / 4)), 0xfffffff0u);
-  return b + al256(4 * (size_t)n_groups(g)) + al256(8 * pool) + al256(pool);
+  return b + al256(4 * ((t + tl.group_tiles - 1) / tl.group_tiles)) + al256(8 * pool) + al256(pool);
 }
 
 }  // namespace
@@ -100,7 +100,7 @@ extern "C" int ht_fill_peaks_noalloc(const ht_grid* grid, const float* x, const 
   // the layout: direct slab lists when they fit, else the counting sort (the same results);
   // an event that fits neither is refused before any device work
   const Tiling tl = choose_tiling(*grid);
-  DevGrid g = make_devgrid(*grid, DevTables(), tl, 1);
+  DevGrid g = make_devgrid(*grid, DevTables(), tl, 1, n_hits);
   const bool atomic = !g.lds_fill;
   const bool dense = !atomic && dense_peaks(g, n_hits);
   const int layout = dense ? kPeakMask : kPeakBands;
@@ -145,13 +145,13 @@ extern "C" int ht_fill_peaks_noalloc(const ht_grid* grid, const float* x, const 
   t.phi = (float*)(base + kTabOff + phi_off);
   t.th = (float*)(base + kTabOff + th_off);
   t.inv_db = inv_db;
-  g = make_devgrid(*grid, t, tl, 1);
+  g = make_devgrid(*grid, t, tl, 1, n_hits);
 
   EvDesc ev;
   std::memset(&ev, 0, sizeof(ev));
   carve_event_scratch(g, n_hits, direct, base + kEvOff, &ev, sliced ? 0 : layout);
   ev.dense = dense ? 1 : 0;
-  ev.lists = !sliced && !dense && (atomic || !long_lists(g, n_hits)) ? 1 : 0;
+  ev.lists = !sliced && !dense && (atomic || use_lists(g, n_hits, n_hits)) ? 1 : 0;
   uint32_t* pair = (uint32_t*)base;
   ev.slab_cnt = pair + (g_parity[dev] ? kCounterWords : 0);
   ev.slab_cnt_next = pair + (g_parity[dev] ? 0 : kCounterWords);
@@ -172,7 +172,7 @@ extern "C" int ht_fill_peaks_noalloc(const ht_grid* grid, const float* x, const 
   // then), each slice counting on from the one before.
   set_jobs(&g, 0, 1);
   int64_t* carry = (int64_t*)(base + kEvOff);
-  const size_t fixed = 256 + 2 * al256(4 * (size_t)g.j.n_groups) + 16 * (size_t)kListCap * kLists + 6 * 256;
+  const size_t fixed = 256 + al256(4 * (size_t)g.j.n_groups * g.j.pk_step) + al256(4 * (size_t)g.j.n_groups) + 16 * (size_t)kListCap * kLists + 6 * 256;
   const size_t per = (size_t)(1 + 64 * g.j.elem_bytes) * g.j.group_jobs + 8 * (size_t)g.j.seg;
   const size_t fit = fixed < room ? (room - fixed) / per : 0;
   if (fit == 0) return fail(HT_EINVAL, "ht_fill_peaks_noalloc: one group of rows needs %zu bytes of scratch", per);

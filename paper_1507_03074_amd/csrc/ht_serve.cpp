@@ -140,7 +140,7 @@ int launch(ht_server* sv, Batch& b)
     // crowded events search their peaks with the stencil (the slot holds both layouts)
     d.dense = (sv->layout & kPeakMask) && dense_peaks(sv->g, r->n) ? 1 : 0;
     if (d.dense) clear_groups(sv->g, &d);
-    d.lists = !d.dense && !(sv->g.lds_fill && long_lists(sv->g, batch_max)) ? 1 : 0;
+    d.lists = !d.dense && (!sv->g.lds_fill || use_lists(sv->g, batch_max, r->n)) ? 1 : 0;
     any_bands = any_bands || !d.dense;
     any_dense = any_dense || d.dense;
     d.slab_cnt = sl.ctr + (sl.parity ? kCounterWords : 0);
@@ -265,7 +265,7 @@ int ht_serve_create(const ht_grid* grid, const ht_serve_opts* opts, ht_server** 
   sv->grid = *grid;
   sv->opts = *opts;
   sv->dev = opts->device;
-  if ((rc = make_device_grid(*grid, sv->dev, opts->max_batch, &sv->g))) {
+  if ((rc = make_device_grid(*grid, sv->dev, opts->max_batch, opts->max_hits, &sv->g))) {
     delete sv;
     return rc;
   }
