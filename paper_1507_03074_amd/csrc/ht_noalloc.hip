@@ -41,6 +41,7 @@ char* g_ptr[kNoAllocMaxDevices];          // device address of each device's scr
 uint8_t g_parity[kNoAllocMaxDevices];     // which counter array the next call counts into
 bool g_tab_valid[kNoAllocMaxDevices];     // the table region holds the tables of g_tab_grid
 ht_grid g_tab_grid[kNoAllocMaxDevices];
+float g_inv_db[kNoAllocMaxDevices];       // and their 1 / (width of a B bin)
 // host staging of the tables (a fixed array, so no host allocation either)
 float g_tab_host[kTabBytes / 4];
 
@@ -129,11 +130,10 @@ extern "C" int ht_fill_peaks_noalloc(const ht_grid* grid, const float* x, const 
   const size_t phi_off = al256(4 * a2_floats(*grid));
   const size_t th_off = phi_off + al256(4 * phi_floats(*grid));
   const size_t tab_bytes = th_off + 4 * th_floats(*grid);
-  float inv_db = 0.0f;
-  host_tables_into(*grid, g_tab_host + a2_off / 4, &inv_db, g_tab_host + phi_off / 4,
-                   g_tab_host + th_off / 4);
   if (!g_tab_valid[dev] || !same_tables(g_tab_grid[dev], *grid)) {
     g_tab_valid[dev] = false;
+    host_tables_into(*grid, g_tab_host + a2_off / 4, &g_inv_db[dev], g_tab_host + phi_off / 4,
+                     g_tab_host + th_off / 4);
     if ((e = hipMemcpyAsync(base + kTabOff, g_tab_host, tab_bytes, hipMemcpyHostToDevice, s)) != hipSuccess)
       return fail_hip(e, "hipMemcpyAsync(tables)");
     if ((e = hipStreamSynchronize(s)) != hipSuccess) return fail_hip(e, "hipStreamSynchronize(tables)");
@@ -144,7 +144,7 @@ extern "C" int ht_fill_peaks_noalloc(const ht_grid* grid, const float* x, const 
   t.a2 = (float*)(base + kTabOff + a2_off);
   t.phi = (float*)(base + kTabOff + phi_off);
   t.th = (float*)(base + kTabOff + th_off);
-  t.inv_db = inv_db;
+  t.inv_db = g_inv_db[dev];
   g = make_devgrid(*grid, t, tl, 1, n_hits);
 
   EvDesc ev;
