@@ -463,6 +463,15 @@ __global__ __launch_bounds__(LONG ? 2 * kBlock : kBlock, LONG || ROWS <= 4 ? 8 :
       u32x4 v[CH];
 #pragma unroll
       for (int q = 0; q < CH; ++q) v[q] = in && (int)r0 + q < rows ? s4[(r0 + q) * ldr4s + u] : zero4;
+      if (LONG && !VEC) {  // the first spill words complete a ragged row's last unit: they are no cells
+        const uint32_t left = nb - 4u * u;
+#pragma unroll
+        for (int q = 0; q < CH; ++q) {
+          v[q].y = left > 1u ? v[q].y : 0u;
+          v[q].z = left > 2u ? v[q].z : 0u;
+          v[q].w = left > 3u ? v[q].w : 0u;
+        }
+      }
 #pragma unroll
       for (int q = 0; q < CH; ++q) {
         if (in && (int)r0 + q < rows) {

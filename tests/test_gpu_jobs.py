@@ -140,3 +140,27 @@ def test_long_lists_with_extreme_hits_bit_exact(B, ranges, rows):
         B.ht_set_tuning(spec)
     assert np.array_equal(B.as_u32(acc), M)
     same_peaks(spec, (c, v, k), M, ranges)
+
+
+@pytest.mark.parametrize("n_b", [33, 66, 131, 333, 1030])
+def test_long_lists_with_ragged_rows(B, n_b):
+    """Votes outside the row of the long-list fill are counted in words past it: with rows that are
+    not whole units of four columns, none of these is a cell of the survivor search."""
+    import torch
+    from oracle import oracle
+    rng = np.random.default_rng(n_b)
+    spec = synth.GridSpec(1, 3, 21, n_b, b_min=-300.0, b_max=300.0, threshold=4)  # many votes outside
+    for n in (520, 1500, 4000):
+        say("n_b", n_b, "hits", n)
+        ev = synth.make_hits(rng, n // 14, n - 12 * (n // 14))
+        M, _ = oracle.fill(oracle.OracleGrid(*spec.as_tuple()), ev.x, ev.y, ev.z)
+        x, y, z = B.hits_to_device(ev.x, ev.y, ev.z)
+        for rows in (1, 4, 8):
+            B.ht_set_tuning(spec, rows=rows, dense_hits=-1)
+            try:
+                acc, c, v, found = B.fill_peaks(spec, x, y, z)
+                torch.cuda.synchronize()
+            finally:
+                B.ht_set_tuning(spec)
+            assert np.array_equal(B.as_u32(acc), M), rows
+            same_peaks(spec, (c, v, found), M, "rows %d" % rows)
