@@ -713,6 +713,18 @@ int launch_batch(const DevGrid& g, const EvDesc* d_ev, int n_ev, int64_t max_hit
   std::memset(&none, 0, sizeof(none));
   int rc;
   *prep_enqueued = false;
+  const int pieces = split && g.lds_fill ? std::min(split->pieces, n_ev) : 1;
+  if (!any_dense && pieces == 1 && tiny_launch(g, n_ev, max_hits)) {
+    if ((rc = injected_failure("prep")) || (rc = injected_failure("fill"))) return rc;
+    {
+      StageTimer t("fill", s);
+      if ((rc = check_launch(launch_tiny_fill(g, none, d_ev, n_ev, s), "fill launch"))) return rc;
+      *prep_enqueued = true;
+    }
+    if ((rc = injected_failure("peaks"))) return rc;
+    StageTimer t("peaks", s);
+    return check_launch(launch_few_peaks(g, none, d_ev, n_ev, s), "peak launch");
+  }
   {
     StageTimer t("prep", s);
     if ((rc = injected_failure("prep")) ||
@@ -721,7 +733,6 @@ int launch_batch(const DevGrid& g, const EvDesc* d_ev, int n_ev, int64_t max_hit
     *prep_enqueued = true;
   }
   if ((rc = injected_failure("fill"))) return rc;
-  const int pieces = split && g.lds_fill ? std::min(split->pieces, n_ev) : 1;
   if (pieces > 1) {
     // The batch in `pieces` runs of consecutive events: the fill of run i + 1 (on s) overlaps
     // the peak search of run i (on the side stream, after an event recorded when run i's fill
@@ -760,6 +771,8 @@ int launch_batch(const DevGrid& g, const EvDesc* d_ev, int n_ev, int64_t max_hit
   }
   if ((rc = injected_failure("peaks"))) return rc;
   StageTimer t("peaks", s);
+  if (!any_dense && g.lds_fill && few_cells(g, max_hits) && use_lists(g, max_hits, max_hits))
+    return check_launch(launch_few_peaks(g, none, d_ev, n_ev, s), "peak launch");
   if (any_bands && (rc = check_launch(launch_peaks(g, none, d_ev, n_ev, g.j.n_groups, s), "peak launch"))) return rc;
   if (any_dense && (rc = check_launch(launch_peaks_dense(g, none, d_ev, n_ev, s), "stencil peak launch")))
     return rc;
@@ -839,6 +852,17 @@ int enqueue_event(const DevGrid& g, const EvDesc& ev, int64_t nh, bool direct, b
 #define HT_STAGE(var, name) StageTimer var(timed ? name : nullptr, s)
   int rc;
   *counters_used = false;
+  if (do_fill && do_peaks && !atomic && !ev.dense && tiny_launch(g, 1, nh)) {
+    if ((rc = injected_failure("prep")) || (rc = injected_failure("fill"))) return rc;
+    {
+      HT_STAGE(t, "fill");
+      if ((rc = check_launch(launch_tiny_fill(g, ev, nullptr, 1, s), "fill launch"))) return rc;
+      *counters_used = true;
+    }
+    if ((rc = injected_failure("peaks"))) return rc;
+    HT_STAGE(t, "peaks");
+    return check_launch(launch_few_peaks(g, ev, nullptr, 1, s), "peak launch");
+  }
   if (do_fill) {
     {
       HT_STAGE(t, "prep");
@@ -866,6 +890,8 @@ int enqueue_event(const DevGrid& g, const EvDesc& ev, int64_t nh, bool direct, b
     HT_STAGE(t, "peaks");
     if (ev.dense) {
       if ((rc = check_launch(launch_peaks_dense(g, ev, nullptr, 1, s), "stencil peak launch"))) return rc;
+    } else if (do_fill && !atomic && ev.lists && few_cells(g, nh)) {
+      if ((rc = check_launch(launch_few_peaks(g, ev, nullptr, 1, s), "peak launch"))) return rc;
     } else if ((rc = check_launch(launch_peaks(g, ev, nullptr, 1, ev.n_grp, s), "peak launch"))) {
       return rc;
     }

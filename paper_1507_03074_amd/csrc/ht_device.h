@@ -277,6 +277,58 @@ __device__ __forceinline__ void st_unit(uint32_t* acc, uint32_t c, uint32_t left
     if (k < left) d[k] = v[k];
 }
 
+// Sweeps a filled LDS tile, each wave its jobs in turn: every job's cells are read from LDS once,
+// written to the matrix, cleared, and given to on_job (job of the tile, the lane's first cell, its
+// cells by row; called by every lane of the wave) to be searched for survivors in registers. No
+// wave waits for another here: what bounds the fill of an ordinary event is its stores, and a
+// pass that counted candidates, a barrier, a pool reservation and a second pass over the tile cost
+// 9 us of 47 on the paper event.
+// ldr4s: 16-byte units of an LDS row; ldr4: those of them that hold cells; sub, unit0: the lane's
+// band and unit (of its strip) in a job. SPILL: words past a row's cells may hold counts.
+template <int CH, bool VEC, bool NT, bool SPILL, int WAVES, typename F>
+__device__ __forceinline__ void sweep_jobs(const DevGrid& g, uint32_t* acc, u32x4* s4, uint32_t ldr4s, uint32_t ldr4,
+                                           uint32_t nb, uint32_t cell0, int rows, uint32_t wave, uint32_t lane,
+                                           uint32_t sub, uint32_t unit0, F on_job)
+{
+  const u32x4 zero4 = {0u, 0u, 0u, 0u};
+  uint32_t bg = 0u, st = wave;  // job = bg * strips + st
+  while (st >= (uint32_t)g.j.strips) { st -= (uint32_t)g.j.strips; ++bg; }
+  for (uint32_t job = wave; job < (uint32_t)g.j.tile_jobs; job += WAVES) {  // uniform
+    const uint32_t u = g.j.sub > 1 ? unit0 : st * 64u + lane;
+    const uint32_t r0 = (bg * (uint32_t)g.j.sub + sub) * CH;
+    const bool in = u < ldr4 && sub < (uint32_t)g.j.sub;
+    u32x4 v[CH];
+#pragma unroll
+    for (int q = 0; q < CH; ++q) v[q] = in && (int)r0 + q < rows ? s4[(r0 + q) * ldr4s + u] : zero4;
+    if (SPILL && !VEC) {  // the first spill words complete a ragged row's last unit: they are no cells
+      const uint32_t left = nb - 4u * u;
+#pragma unroll
+      for (int q = 0; q < CH; ++q) {
+        v[q].y = left > 1u ? v[q].y : 0u;
+        v[q].z = left > 2u ? v[q].z : 0u;
+        v[q].w = left > 3u ? v[q].w : 0u;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < CH; ++q) {
+      if (in && (int)r0 + q < rows) {
+        const uint32_t c = cell0 + (r0 + q) * nb + 4u * u;
+        if (VEC) {
+          GLOBAL u32x4* d4 = reinterpret_cast<GLOBAL u32x4*>(gp(acc) + c);
+          if (NT) __builtin_nontemporal_store(v[q], d4);
+          else *d4 = v[q];
+        } else {
+          st_unit<NT>(acc, c, nb - 4u * u, v[q]);
+        }
+        s4[(r0 + q) * ldr4s + u] = zero4;
+      }
+    }
+    on_job(job, cell0 + r0 * nb + 4u * u, v);
+    st += WAVES;
+    while (st >= (uint32_t)g.j.strips) { st -= (uint32_t)g.j.strips; ++bg; }
+  }
+}
+
 // ---------------------------------------------------------------------------------------------
 // Fill through an LDS tile of ROWS x n_b counters. The grid holds ceil(n_tiles / fill_tiles)
 // workgroups; workgroup w fills tiles w, w + G, w + 2G, ... (G workgroups), so at any moment the
@@ -450,54 +502,16 @@ __global__ __launch_bounds__(LONG ? 2 * kBlock : kBlock, LONG || ROWS <= 4 ? 8 :
       continue;
     }
     const bool emit = EMIT && !e.dense;  // uniform; a crowded event's peaks come from the stencil
-    // Every job's cells: read from LDS once, written to the matrix, cleared, and searched for
-    // survivors in registers. No wave waits for another here: what bounds the fill of an ordinary
-    // event is its stores, and a pass that counted candidates, a barrier, a pool reservation and
-    // a second pass over the tile cost 9 us of 47 on the paper event.
-    uint32_t bg = 0u, st = wave;  // job = bg * strips + st
-    while (st >= (uint32_t)g.j.strips) { st -= (uint32_t)g.j.strips; ++bg; }
-    for (uint32_t job = wave; job < (uint32_t)g.j.tile_jobs; job += kThreads / 64) {  // uniform
-      const uint32_t u = g.j.sub > 1 ? unit0 : st * 64u + lane;
-      const uint32_t r0 = (bg * (uint32_t)g.j.sub + sub) * CH;
-      const bool in = u < ldr4 && sub < (uint32_t)g.j.sub;
-      u32x4 v[CH];
-#pragma unroll
-      for (int q = 0; q < CH; ++q) v[q] = in && (int)r0 + q < rows ? s4[(r0 + q) * ldr4s + u] : zero4;
-      if (LONG && !VEC) {  // the first spill words complete a ragged row's last unit: they are no cells
-        const uint32_t left = nb - 4u * u;
-#pragma unroll
-        for (int q = 0; q < CH; ++q) {
-          v[q].y = left > 1u ? v[q].y : 0u;
-          v[q].z = left > 2u ? v[q].z : 0u;
-          v[q].w = left > 3u ? v[q].w : 0u;
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < CH; ++q) {
-        if (in && (int)r0 + q < rows) {
-          const uint32_t c = cell0 + (r0 + q) * nb + 4u * u;
-          if (VEC) {
-            GLOBAL u32x4* d4 = reinterpret_cast<GLOBAL u32x4*>(gp(e.acc) + c);
-            if (NT) __builtin_nontemporal_store(v[q], d4);
-            else *d4 = v[q];
-          } else {
-            st_unit<NT>(e.acc, c, nb - 4u * u, v[q]);
-          }
-          s4[(r0 + q) * ldr4s + u] = zero4;
-        }
-      }
-      if (emit) {
-        const uint32_t m = job_survivors<CH>(v, g.threshold, lmask, rmask);
-        if (__builtin_amdgcn_ballot_w64(m != 0u) != 0u) {  // uniform
-          const uint32_t id = (uint32_t)tile * (uint32_t)g.j.tile_jobs + job;
-          put_mask<CH>(e, id, lane, m);
-          if (!LONG && e.lists)  // uniform
-            list_survivors<CH>(e, id, id / (uint32_t)g.j.group_jobs, lane, m, cell0 + r0 * nb + 4u * u, nb, v);
-        }
-      }
-      st += kThreads / 64;
-      while (st >= (uint32_t)g.j.strips) { st -= (uint32_t)g.j.strips; ++bg; }
-    }
+    sweep_jobs<CH, VEC, NT, LONG, kThreads / 64>(g, e.acc, s4, ldr4s, ldr4, nb, cell0, rows, wave, lane, sub, unit0,
+                                           [&](uint32_t job, uint32_t c0, const u32x4 (&v)[CH]) {
+      if (!emit) return;
+      const uint32_t m = job_survivors<CH>(v, g.threshold, lmask, rmask);
+      if (__builtin_amdgcn_ballot_w64(m != 0u) == 0u) return;  // uniform
+      const uint32_t id = (uint32_t)tile * (uint32_t)g.j.tile_jobs + job;
+      put_mask<CH>(e, id, lane, m);
+      if (!LONG && e.lists)  // uniform
+        list_survivors<CH>(e, id, id / (uint32_t)g.j.group_jobs, lane, m, c0, nb, v);
+    });
     if (LONG && rows < ROWS)  // uniform: the rows past a short last tile took votes
       for (uint32_t i = (uint32_t)rows * ldr4s + threadIdx.x; i < Lpad / 4u; i += kThreads) s4[i] = zero4;
     // the LDS tile is all zero again; the next tile's votes start after its first barrier

@@ -52,6 +52,10 @@ struct JobGeom {
   uint32_t n_jobs, n_groups;
 };
 constexpr uint32_t kSegMax = 1024;
+// Few peaks: at most this many cells can reach the threshold (each of the lists holds as many).
+constexpr uint32_t kFewCells = 8192;
+static_assert(kFewCells <= kListCap, "no list overflows where so few cells reach the threshold");
+constexpr int kTinyHits = 1024;  // of an event that takes two launches (tiny_launch)
 
 // Grid constants and tables as the kernels see them (passed by value as a kernel argument).
 struct DevGrid {
@@ -188,6 +192,14 @@ hipError_t launch_peaks(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, 
 // Stencil peak search and ordered write of the events marked dense (others are skipped).
 hipError_t launch_peaks_dense(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev,
                               hipStream_t s);
+// Peak search of filled events with survivor lists whose grid and hits leave at most kFewCells cells
+// at the threshold (few_cells): one launch.
+bool few_cells(const DevGrid& g, int64_t max_hits);
+hipError_t launch_few_peaks(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev, hipStream_t s);
+// Launches of tiny events (g.j set for fill tiles, few cells): whether these are, and their fill with
+// the preparation in it (it uses the counter pair).
+bool tiny_launch(const DevGrid& g, int n_ev, int64_t max_hits);
+hipError_t launch_tiny_fill(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev, hipStream_t s);
 // Plain fill: zero the matrix, then one global atomicAdd per vote (reference path and the
 // fallback for B rows too wide for an LDS tile).
 hipError_t launch_fill_atomic(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev,

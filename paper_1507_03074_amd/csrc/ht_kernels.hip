@@ -21,6 +21,8 @@
 //   the matrix, k_peak_stencil tests every cell in one read of it (one wave per phi cell, the
 //   theta cells in its registers, the phi neighbours through LDS) into 64-bit peak words, and
 //   k_peak_write_dense writes the ordered peak list from them
+//   k_few_peaks   both of these in one workgroup per event, where few cells can be peaks
+//   k_tiny_fill   the preparation and the fill in one launch, for the smallest events
 // ht_peaks on an arbitrary matrix replaces prep and fill with k_scan (one read of it).
 // No kernel synchronises workgroups with each other: on this multi-XCD part an agent-scope
 // release costs an L2 write-back, while a kernel boundary is cheap.
@@ -277,6 +279,93 @@ __global__ __launch_bounds__(kBlock) void k_bucket(DevGrid g, EvDesc ev0, const 
     if (s < 0) break;
     e.list[s_off[s] + e.hit_pos[4 * h + q]] = rec;
   }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Tiny events (tiny_launch: up to 1024 hits, 1024 tiles). Their calls were bound by the launches,
+// four of them, of which each takes the host 2 us and the device 3 to 5: now two, 15.6 and 9.6 us
+// for 250 hits on 4x16x64x64.
+//
+// The fill: every workgroup prepares all of the event's hits itself (170 instructions per thread
+// and 256 hits, less than a round trip to a list), and keeps the records of its own slab in LDS;
+// each wave then votes a quarter of the rows. Survivors go to the lists only.
+// ---------------------------------------------------------------------------------------------
+template <bool VEC, bool NT>
+__global__ __launch_bounds__(kBlock) void k_tiny_fill(DevGrid g, EvDesc ev0, const EvDesc* evs)
+{
+  extern __shared__ uint32_t smem[];
+  __shared__ float s_x[kTinyHits], s_r2[kTinyHits], s_k[kTinyHits];
+  __shared__ uint32_t s_n;
+  EvDesc e = load_ev(ev0, evs);
+  const uint32_t nb = (uint32_t)g.n_b, ldr4 = (nb + 3u) / 4u, ldr = 4u * ldr4;
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint32_t tile_words = (uint32_t)g.rows * ldr;
+  u32x4* const s4 = reinterpret_cast<u32x4*>(smem);
+  const u32x4 zero4 = {0u, 0u, 0u, 0u};
+  const int n_hits = (int)e.n_hits;
+  // the first hits are loaded before anything else
+  const int h0 = min((int)threadIdx.x, n_hits - 1);
+  float hx = 0.0f, hy = 0.0f, hz = 0.0f;
+  if (n_hits > 0) {  // uniform
+    hx = gp(e.x)[h0];
+    hy = gp(e.y)[h0];
+    hz = gp(e.z)[h0];
+  }
+  const float *tab_phi, *tab_th;
+  tables_to_lds<true>(g, reinterpret_cast<float*>(smem) + tile_words, &tab_phi, &tab_th);
+  for (uint32_t i = threadIdx.x; i < tile_words / 4u; i += kBlock) s4[i] = zero4;
+  if (threadIdx.x == 0) s_n = 0u;
+  for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < (uint32_t)kCounterWords; i += gridDim.x * kBlock)
+    gp(e.slab_cnt_next)[i] = 0u;
+  const int slab = (int)blockIdx.x / g.tiles_per_slab;
+  const int a0 = ((int)blockIdx.x - slab * g.tiles_per_slab) * g.rows;
+  const int rows = min(g.rows, g.n_a - a0);
+  lds_barrier();
+  for (int h = 0; h < n_hits; h += kBlock) {  // uniform
+    if (h > 0) {
+      const int i = min(h + (int)threadIdx.x, n_hits - 1);
+      hx = gp(e.x)[i];
+      hy = gp(e.y)[i];
+      hz = gp(e.z)[i];
+    }
+    const HitPrep p = prep_hit(g, tab_phi, tab_th, hx, hy, hz);
+    bool mine = false;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) mine |= q < p.n && p.slab[q] == slab;  // its cells are distinct
+    if (mine && h + (int)threadIdx.x < n_hits) {
+      const uint32_t i = atomicAdd(&s_n, 1u);
+      s_x[i] = p.x;
+      s_r2[i] = p.r2;
+      s_k[i] = p.k;
+    }
+  }
+  lds_barrier();
+  const uint32_t n = s_n;
+  for (uint32_t i0 = 0u; i0 < n; i0 += 64u) {  // uniform
+    const uint32_t i = min(i0 + lane, n - 1u);
+    const float x = s_x[i], r2 = s_r2[i], k = s_k[i];
+#pragma unroll 4
+    for (int r = (int)wave; r < rows; r += kBlock / 64) {
+      const float ax = g.a2[a0 + r] * x;
+      const float num = r2 - ax;
+      const float Bv = num * k;
+      const float d = Bv - g.b_min;
+      const float f = d * g.inv_db;
+      if (i0 + lane < n && f >= 0.0f && f < g.nb_f) atomicAdd(&smem[(uint32_t)r * ldr + (uint32_t)(int)f], 1u);
+    }
+  }
+  lds_barrier();
+  const uint32_t sub = g.j.sub > 1 ? lane / ldr4 : 0u;
+  const uint32_t unit0 = g.j.sub > 1 ? lane - sub * ldr4 : lane;
+  const uint32_t lmask = unit0 > 0u ? ~0u : 0u, rmask = g.j.sub > 1 && unit0 + 1u == ldr4 ? 0u : ~0u;
+  const uint32_t cell0 = ((uint32_t)slab * (uint32_t)g.n_a + (uint32_t)a0) * nb;
+  sweep_jobs<4, VEC, NT, false, kBlock / 64>(g, e.acc, s4, ldr4, ldr4, nb, cell0, rows, wave, lane, sub, unit0,
+                                      [&](uint32_t job, uint32_t c0, const u32x4 (&v)[4]) {
+    const uint32_t m = job_survivors<4>(v, g.threshold, lmask, rmask);
+    if (__builtin_amdgcn_ballot_w64(m != 0u) == 0u) return;  // uniform
+    list_survivors<4>(e, blockIdx.x * (uint32_t)g.j.tile_jobs + job, 0u, lane, m, c0, nb, v);
+  });
 }
 
 // Where a job's cells are: its rows are a0 .. of `slab` (absent from row n_a and, in a fill tile,
@@ -748,6 +837,75 @@ __global__ __launch_bounds__(kBlock) void k_peak_test(DevGrid g, EvDesc ev0, con
     ((GLOBAL u32x2*)gp(e.seg))[(size_t)grp * seg_cap + r] = pk;
   }
   lds_barrier();  // the next group clears what this one still reads
+  }
+}
+
+// Peaks of an event of which at most kFewCells cells reach the threshold, one workgroup: its
+// survivors half a wave each, one lane per neighbour row, four in flight; the peaks wait in LDS,
+// and each is written at its rank. Bound by its three memory round trips (the lists, the rows, the
+// stores), where the test and the ordered write are two launches of two each.
+template <bool NARROW>
+__global__ __launch_bounds__(1024) void k_few_peaks(DevGrid g, EvDesc ev0, const EvDesc* evs)
+{
+  __shared__ __align__(16) uint32_t s_c[kFewCells + 4];
+  __shared__ uint16_t s_v[kFewCells];  // votes: at most kTinyHits
+  __shared__ uint32_t s_n;
+  EvDesc e = load_ev(ev0, evs);
+  const bool a8 = ((uintptr_t)e.out & 7u) == 0;
+  const uint32_t lane = threadIdx.x & 63u, hw = threadIdx.x >> 5, k = threadIdx.x & 31u;
+  constexpr uint32_t kStep = 1024 / 32 / kLists;  // half waves per list
+  const uint32_t l = hw % kLists;
+  const GLOBAL u32x4* const list = (const GLOBAL u32x4*)gp((const uint4*)e.surv) + l * kListCap;
+  if (threadIdx.x == 0) s_n = 0u;
+  u32x4 en[4];
+#pragma unroll
+  for (uint32_t q = 0; q < 4; ++q) en[q] = list[hw / kLists + q * kStep];  // before their number is known
+  const uint32_t n = gp((const uint32_t*)e.slab_cnt)[kListLens + l * kListLine];
+  const int kk = (int)min(k, 26u), dt = kk / 9 - 1, dp = kk / 3 % 3 - 1, da = kk % 3 - 1;
+  const uint32_t n_max = max((uint32_t)__builtin_amdgcn_readlane((int)n, 0), (uint32_t)__builtin_amdgcn_readlane((int)n, 32));
+  const uint32_t i_wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(hw / kLists));  // the same in both halves
+  lds_barrier();
+  for (uint32_t i0 = i_wave; i0 < n_max; i0 += 4u * kStep) {  // wave-uniform
+    bool beaten[4];
+#pragma unroll
+    for (uint32_t q = 0; q < 4; ++q) {
+      const uint32_t i = i0 + q * kStep;
+      if (i0 != i_wave && i < n_max) en[q] = list[min(i, kListCap - 1u)];
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < 4; ++q) {
+      beaten[q] = true;
+      if (i0 + q * kStep < n) {
+        const TestCell x = test_cell(g, en[q].x, en[q].y);
+        bool in;
+        const uint32_t at = row_window(g, x, dt, dp, da, &in);
+        beaten[q] = row_wins(x, load_row<NARROW>(g, e.acc, at), at, kk == 13) && in && k < 27u;
+      }
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < 4; ++q) {
+      const uint32_t hm = (uint32_t)(__builtin_amdgcn_ballot_w64(beaten[q]) >> (lane & 32u));
+      if (k == 0u && hm == 0u) {
+        const uint32_t o = atomicAdd(&s_n, 1u);
+        s_c[o] = en[q].x;
+        s_v[o] = (uint16_t)en[q].y;
+      }
+    }
+  }
+  lds_barrier();
+  const uint32_t np = s_n;
+  if (threadIdx.x == 0) *gp(e.n_found) = (int64_t)np;
+  if (threadIdx.x < 4u) s_c[np + threadIdx.x] = 0xffffffffu;  // whole 16-byte reads
+  lds_barrier();
+  const u32x4* s4 = reinterpret_cast<const u32x4*>(s_c);
+  for (uint32_t i = threadIdx.x; i < np; i += 1024u) {
+    const uint32_t c = s_c[i];
+    uint32_t r = 0u;
+    for (uint32_t j = 0u; j < (np + 3u) / 4u; ++j) {
+      const u32x4 o = s4[j];
+      r += (o.x < c ? 1u : 0u) + (o.y < c ? 1u : 0u) + (o.z < c ? 1u : 0u) + (o.w < c ? 1u : 0u);
+    }
+    if ((int64_t)r < e.cap) st_peak(e.out, r, c, s_v[i], a8);
   }
 }
 
@@ -1557,6 +1715,49 @@ hipError_t launch_fill(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, i
   const bool vec = (g.n_b % 4) == 0 && g.nt_store != 2;
   const size_t lds = fill_lds_bytes(g, long_l);
   return launch_fill_nt(g, ev0, evs, n_ev, g.nt_store == 1, vec, emit, long_l, lds, s);
+}
+
+// the tile and the boundary tables
+static size_t tiny_lds_bytes(const DevGrid& g)
+{
+  return fill_lds_bytes(g, false) + (size_t)(4 * g.n_phi + 2 * (2 * g.n_theta + 1)) * sizeof(float);
+}
+
+bool few_cells(const DevGrid& g, int64_t max_hits)
+{
+  // A hit votes once per A row and cell, so hits * cells * n_a / threshold cells reach the threshold
+  // at most. (The counts have 16 bits in the kernel.)
+  return max_hits <= 65535 && max_hits * (g.phi_sectors ? 2 : 4) * g.n_a / (int64_t)g.threshold <= kFewCells;
+}
+
+bool tiny_launch(const DevGrid& g, int n_ev, int64_t max_hits)
+{
+  // Every workgroup prepares every hit, so the hits fit its LDS, and there are no more workgroups
+  // than the chip holds at once. 250 hits on 4x16x64x64 (256 workgroups): 15.6 us a call in four
+  // launches, 9.6 in two; on 256x256 planes (1024): 16.5 and 13.4; 200 on 512x512 (4096): 24.8 and
+  // 33.9; batches of 16 of the first (1024) 38.0 and 36.9 us, of 32 (2048) 41.7 and 44.7, of 100
+  // 60 and 84.
+  if (!g.lds_fill || g.packed_lists || g.j.ch != 4 || max_hits > kTinyHits || !few_cells(g, max_hits)) return false;
+  return (int64_t)g.n_tiles * n_ev <= 1024 && tiny_lds_bytes(g) + 12 * kTinyHits + 64 <= 65536;
+}
+
+hipError_t launch_tiny_fill(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev, hipStream_t s)
+{
+  const size_t lds = tiny_lds_bytes(g);
+  const dim3 grid(g.n_tiles, n_ev);
+  const bool vec = g.n_b % 4 == 0 && g.nt_store != 2, nt = g.nt_store == 1;
+  if (vec && nt) hipLaunchKernelGGL((k_tiny_fill<true, true>), grid, dim3(kBlock), lds, s, g, ev0, evs);
+  else if (vec) hipLaunchKernelGGL((k_tiny_fill<true, false>), grid, dim3(kBlock), lds, s, g, ev0, evs);
+  else if (nt) hipLaunchKernelGGL((k_tiny_fill<false, true>), grid, dim3(kBlock), lds, s, g, ev0, evs);
+  else hipLaunchKernelGGL((k_tiny_fill<false, false>), grid, dim3(kBlock), lds, s, g, ev0, evs);
+  return hipGetLastError();
+}
+
+hipError_t launch_few_peaks(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev, hipStream_t s)
+{
+  if (g.n_b < 3) hipLaunchKernelGGL(k_few_peaks<true>, dim3(1, n_ev), dim3(1024), 0, s, g, ev0, evs);
+  else hipLaunchKernelGGL(k_few_peaks<false>, dim3(1, n_ev), dim3(1024), 0, s, g, ev0, evs);
+  return hipGetLastError();
 }
 
 hipError_t launch_scan(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev, uint32_t n_grp,

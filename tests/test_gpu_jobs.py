@@ -164,3 +164,41 @@ def test_long_lists_with_ragged_rows(B, n_b):
                 B.ht_set_tuning(spec)
             assert np.array_equal(B.as_u32(acc), M), rows
             same_peaks(spec, (c, v, found), M, "rows %d" % rows)
+
+
+# (cells per axis, threshold) on either side of the two-launch rule's bounds: hits up to 1024, and
+# hits * cells per hit * n_a / threshold up to 8192; rows of a unit and less, and past a wave's units
+@pytest.mark.parametrize("n_a,n_b,threshold", [(64, 64, 32), (64, 64, 31), (64, 1, 40), (63, 2, 40), (33, 3, 17),
+                                               (20, 5, 10), (64, 33, 33), (40, 300, 20), (5, 1030, 3), (4, 16, 1)])
+@pytest.mark.parametrize("sectors", [False, True])
+def test_tiny_events_in_two_launches(B, n_a, n_b, threshold, sectors):
+    import torch
+    from oracle import oracle
+    rng = np.random.default_rng([n_a, n_b, threshold, sectors])
+    spec = synth.GridSpec(2, 3, n_a, n_b, threshold=threshold, phi_sectors=sectors)
+    og = oracle.OracleGrid(*spec.as_tuple())
+    evs, want = [], []
+    for n in (0, 1, 63, 257, 512, 1023, 1024, 1025):
+        say("hits", n)
+        ev = synth.make_hits(rng, n // 14, n - 12 * (n // 14))
+        x, y, z = (np.array(a[:n], dtype=np.float32) for a in (ev.x, ev.y, ev.z))
+        if n > 60:  # many alike (their cells hold large counts), refused ones and extremes among the others
+            x[n // 3:], y[n // 3:], z[n // 3:] = x[0], y[0], z[0]
+            x[1], y[2], z[3], y[4], y[5] = np.nan, 0.0, np.inf, 1e-40, -1e-30
+        M, _ = oracle.fill(og, x, y, z)
+        evs.append((x, y, z))
+        want.append(M)
+        dev = B.hits_to_device(x, y, z)
+        acc, c, v, found = B.fill_peaks(spec, *dev)
+        torch.cuda.synchronize()
+        assert np.array_equal(B.as_u32(acc), M), n
+        same_peaks(spec, (c, v, found), M, "hits %d" % n)
+        if found > 1:  # a short list: its first peaks and the full count
+            acc, c2, v2, found2 = B.fill_peaks(spec, *dev, capacity=found - 1, allow_truncation=True)
+            assert found2 == found and np.array_equal(c2, c[:-1]) and np.array_equal(v2, v[:-1]), n
+    for evs, want in ((evs[:-1], want[:-1]), (evs, want)):
+        for k in range(3):  # a captured batch and its replays
+            res = B.fill_peaks_batch(spec, evs)
+            for i, M in enumerate(want):
+                assert np.array_equal(B.as_u32(res.acc[i]), M), (k, i)
+                same_peaks(spec, res.peaks[i], M, "event %d" % i)
