@@ -223,9 +223,9 @@ typedef struct ht_event {
 } ht_event;
 
 /* ht_fill_peaks_batch: both steps for n_events independent events of uneven sizes. The stages
- * (prep, fill, peak search) each run as one launch over the whole batch; the sequence, with the
- * upload of the event descriptors, is captured once per batch shape into a HIP graph and
- * replayed, so a batch costs one graph launch on the host.
+ * (prep, fill, peak search) each run as one launch over the whole batch, after one that fetches
+ * the event descriptors. HT_BATCH_GRAPH=1 in the environment captures the sequence once per batch
+ * shape into a HIP graph and replays that.
  * events: HOST ht_event[n_events] (copied before the call returns).
  * x, y, z: device float arrays holding all events' hits.
  * acc: device uint32[n_events * cells]; event e's matrix is acc + e*cells, fully overwritten.

@@ -516,10 +516,14 @@ struct Workspace {
   uint32_t* ctr = nullptr;  // zeroed slab counter pairs, kCounterBytes per event slot
   int ctr_events = 0;
   std::vector<uint8_t> parity;  // which array of each pair the next call counts into
-  EvDesc* h_ev = nullptr;   // pinned staging of batch descriptors
+  // Pinned staging of batch descriptors, two by turns: a call writes its own while the batch
+  // before it is still running (its launches then follow without a gap), and waits only for the
+  // one before that. Their copy on the device is fetched in stream order, so it needs no second.
+  EvDesc* h_ev[2] = {};
+  hipEvent_t ev_read[2] = {};  // the launches that read each staging are done
+  int turn = 0;
   EvDesc* d_ev = nullptr;
   int ev_cap = 0;
-  hipEvent_t ev_copied = nullptr;
   hipStream_t capture = nullptr;  // private stream used only to capture batch graphs
   hipStream_t side = nullptr;     // side stream of split batches (eager launches)
   hipStream_t capture_side = nullptr;  // side stream of split batches under capture
@@ -583,29 +587,30 @@ void use_counters(Workspace* w, int i, EvDesc* d)
 
 void flip_counters(Workspace* w, int n) { for (int i = 0; i < n; ++i) w->parity[i] ^= 1; }
 
+// Makes w->h_ev[w->turn] free for n_ev descriptors of a new call.
 int ensure_ev_staging(Workspace* w, int n_ev, hipStream_t s)
 {
+  w->turn ^= 1;
+  hipError_t e;
   if (n_ev <= w->ev_cap) {
-    if (w->ev_copied) {
-      hipError_t e = hipEventSynchronize(w->ev_copied);
-      if (e != hipSuccess) return fail_hip(e, "hipEventSynchronize");
-    }
+    if ((e = hipEventSynchronize(w->ev_read[w->turn])) != hipSuccess) return fail_hip(e, "hipEventSynchronize");
     return HT_OK;
   }
-  hipError_t e = hipStreamSynchronize(s);
-  if (e != hipSuccess) return fail_hip(e, "hipStreamSynchronize");
-  if (w->h_ev) (void)hipHostFree(w->h_ev);
+  if ((e = hipStreamSynchronize(s)) != hipSuccess) return fail_hip(e, "hipStreamSynchronize");
   if (w->d_ev) (void)hipFree(w->d_ev);
-  w->h_ev = nullptr;
   w->d_ev = nullptr;
   w->ev_cap = 0;
   int cap = std::max(n_ev, 16);
-  if ((e = hipHostMalloc((void**)&w->h_ev, sizeof(EvDesc) * cap, hipHostMallocDefault)) != hipSuccess)
-    return fail_hip(e, "hipHostMalloc(descriptors)");
+  for (int k = 0; k < 2; ++k) {
+    if (w->h_ev[k]) (void)hipHostFree(w->h_ev[k]);
+    w->h_ev[k] = nullptr;
+    if ((e = hipHostMalloc((void**)&w->h_ev[k], sizeof(EvDesc) * cap, hipHostMallocDefault)) != hipSuccess)
+      return fail_hip(e, "hipHostMalloc(descriptors)");
+    if (!w->ev_read[k] && (e = hipEventCreateWithFlags(&w->ev_read[k], hipEventDisableTiming)) != hipSuccess)
+      return fail_hip(e, "hipEventCreate");
+  }
   if ((e = hipMalloc((void**)&w->d_ev, sizeof(EvDesc) * cap)) != hipSuccess)
     return fail_hip(e, "hipMalloc(descriptors)");
-  if (!w->ev_copied && (e = hipEventCreateWithFlags(&w->ev_copied, hipEventDisableTiming)) != hipSuccess)
-    return fail_hip(e, "hipEventCreate");
   w->ev_cap = cap;
   return HT_OK;
 }
@@ -1031,11 +1036,12 @@ int ht_fill_peaks_batch(const ht_grid* grid, const ht_event* events, int32_t n_e
   if ((rc = get_workspace(p.dev, p.s, total_scratch, &w))) return rc;
   if ((rc = ensure_ev_staging(w, n_events, p.s))) return rc;
   if ((rc = ensure_counters(w, n_events, p.s))) return rc;
+  EvDesc* const h_ev = w->h_ev[w->turn];
   const uint64_t cells = n_cells(*grid);
   bool any_bands = false, any_dense = false;
   for (int32_t i = 0; i < n_events; ++i) {
     const ht_event& ev = events[i];
-    EvDesc& d = w->h_ev[i];
+    EvDesc& d = h_ev[i];
     std::memset(&d, 0, sizeof(d));
     const bool dense = p.g.lds_fill && dense_peaks(p.g, ev.n_hits);
     any_bands = any_bands || !dense;
@@ -1059,7 +1065,18 @@ int ht_fill_peaks_batch(const ht_grid* grid, const ht_event* events, int32_t n_e
   BatchSplit split;
   std::memset(&split, 0, sizeof(split));
   split.pieces = pieces;
-  const bool graph_mode = env_int("HT_BATCH_GRAPH", 1) != 0;
+  // The launches go to the stream one by one: five kernels cost the host what one graph launch
+  // costs, and a graph starts 8 us after the work before it (100 events of 250 hits: 44.7 us a
+  // batch, 52.8 as a graph; 100 paper events 4457 and 4465). HT_BATCH_GRAPH=1 captures the batch
+  // once per shape and replays it; so does a caller's stream under capture, as the descriptors
+  // are staged anew on each call.
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  const int graph_env = env_int("HT_BATCH_GRAPH", -1);
+  if (graph_env < 0 && hipStreamIsCapturing(p.s, &cap) != hipSuccess) {  // the default stream beside a capture
+    (void)hipGetLastError();
+    cap = hipStreamCaptureStatusActive;
+  }
+  const bool graph_mode = graph_env < 0 ? cap != hipStreamCaptureStatusNone : graph_env != 0;
   if (pieces > 1) {
     hipStream_t& side = graph_mode ? w->capture_side : w->side;
     if (!side && (e = hipStreamCreateWithFlags(&side, hipStreamNonBlocking)) != hipSuccess)
@@ -1075,9 +1092,8 @@ int ht_fill_peaks_batch(const ht_grid* grid, const ht_event* events, int32_t n_e
   // arrays only once this call's preparation (which counts into these and clears those) is on
   // the stream; a call that fails before that leaves the counters as they were.
   if (!graph_mode) {
-    e = hipMemcpyAsync(w->d_ev, w->h_ev, sizeof(EvDesc) * n_events, hipMemcpyHostToDevice, p.s);
-    if (e != hipSuccess) return fail_hip(e, "hipMemcpyAsync(descriptors)");
-    if ((e = hipEventRecord(w->ev_copied, p.s)) != hipSuccess) return fail_hip(e, "hipEventRecord");
+    if ((e = launch_fetch(w->d_ev, h_ev, n_events, p.s)) != hipSuccess) return fail_hip(e, "descriptor launch");
+    if ((e = hipEventRecord(w->ev_read[w->turn], p.s)) != hipSuccess) return fail_hip(e, "hipEventRecord");
     bool prep_enqueued = false;
     rc = launch_batch(p.g, w->d_ev, n_events, max_hits_b, direct, any_bands, any_dense, p.s, &prep_enqueued,
                       pieces > 1 ? &split : nullptr);
@@ -1094,7 +1110,7 @@ int ht_fill_peaks_batch(const ht_grid* grid, const ht_event* events, int32_t n_e
                              (direct ? 1 : 0) | (any_bands ? 2 : 0) | (any_dense ? 4 : 0) | (pieces << 3)};
     std::memcpy(q, ints, sizeof(ints));
     q += sizeof(ints);
-    const void* ptrs[2] = {w->d_ev, w->h_ev};
+    const void* ptrs[2] = {w->d_ev, h_ev};
     std::memcpy(q, ptrs, sizeof(ptrs));
   }
   hipGraphExec_t exec = nullptr;
@@ -1108,7 +1124,7 @@ int ht_fill_peaks_batch(const ht_grid* grid, const ht_event* events, int32_t n_e
     if ((e = hipStreamBeginCapture(w->capture, hipStreamCaptureModeThreadLocal)) != hipSuccess)
       return fail_hip(e, "hipStreamBeginCapture");
     t_capturing = true;
-    e = hipMemcpyAsync(w->d_ev, w->h_ev, sizeof(EvDesc) * n_events, hipMemcpyHostToDevice, w->capture);
+    e = launch_fetch(w->d_ev, h_ev, n_events, w->capture);
     bool captured_prep = false;
     int lrc = e == hipSuccess
                   ? launch_batch(p.g, w->d_ev, n_events, max_hits_b, direct, any_bands, any_dense, w->capture,
@@ -1117,7 +1133,7 @@ int ht_fill_peaks_batch(const ht_grid* grid, const ht_event* events, int32_t n_e
     t_capturing = false;
     hipGraph_t graph = nullptr;
     hipError_t e2 = hipStreamEndCapture(w->capture, &graph);
-    if (e != hipSuccess) return fail_hip(e, "hipMemcpyAsync(descriptors, capture)");
+    if (e != hipSuccess) return fail_hip(e, "descriptor launch (capture)");
     if (lrc != HT_OK) {
       if (graph) (void)hipGraphDestroy(graph);
       return lrc;
@@ -1126,7 +1142,11 @@ int ht_fill_peaks_batch(const ht_grid* grid, const ht_event* events, int32_t n_e
     e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
     (void)hipGraphDestroy(graph);
     if (e != hipSuccess) return fail_hip(e, "hipGraphInstantiate");
-    if (w->graphs.size() >= 16) {
+    if (w->graphs.size() >= 32) {  // two per batch shape; the oldest may still be running
+      if ((e = hipStreamSynchronize(p.s)) != hipSuccess) {
+        (void)hipGraphExecDestroy(exec);
+        return fail_hip(e, "hipStreamSynchronize");
+      }
       (void)hipGraphExecDestroy(w->graphs.front().exec);
       w->graphs.erase(w->graphs.begin());
     }
@@ -1137,7 +1157,7 @@ int ht_fill_peaks_batch(const ht_grid* grid, const ht_event* events, int32_t n_e
     if ((e = hipGraphLaunch(exec, p.s)) != hipSuccess) return fail_hip(e, "hipGraphLaunch");
   }
   flip_counters(w, n_events);
-  if ((e = hipEventRecord(w->ev_copied, p.s)) != hipSuccess) return fail_hip(e, "hipEventRecord");
+  if ((e = hipEventRecord(w->ev_read[w->turn], p.s)) != hipSuccess) return fail_hip(e, "hipEventRecord");
   return HT_OK;
 }
 

@@ -178,6 +178,9 @@ void clear_groups(const DevGrid& g, EvDesc* ev);
 
 // Kernel launchers (ht_kernels.hip). `evs` is a device array of n_ev descriptors, or nullptr
 // for a single event passed by value in `ev0`. `max_hits` bounds n_hits over the events.
+// launch_fetch copies the descriptors to `evs` from pinned host memory, which has to stay as it is
+// until the launch is done.
+hipError_t launch_fetch(EvDesc* evs, const EvDesc* host, int n_ev, hipStream_t s);
 hipError_t launch_prep(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev,
                        int64_t max_hits, bool direct, hipStream_t s);
 hipError_t launch_fill(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev,

@@ -158,6 +158,14 @@ __device__ __forceinline__ void clear_jobs(const EvDesc& e)
   for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < e.clear_n16; i += gridDim.x * kBlock) p[i] = zero;
 }
 
+// A batch's descriptors, fetched from pinned host memory by a kernel like the others: a copy command
+// is a 3 us kernel too, and 4 us pass after it before the next kernel starts.
+__global__ __launch_bounds__(kBlock) void k_fetch(u32x2* to, const u32x2* from, uint32_t n)
+{
+  const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
+  if (i < n) ((GLOBAL u32x2*)to)[i] = ((const GLOBAL u32x2*)from)[i];
+}
+
 // Direct lists: counts per slab in LDS per workgroup, one global atomic per (workgroup, slab)
 // reserves the workgroup's range of each slab's fixed-capacity list, then the records are
 // written there. slab_cnt is zero on entry and ends holding the list lengths; The workgroups
@@ -1668,6 +1676,14 @@ int n_groups(const DevGrid& g) { return (g.n_tiles + g.group_tiles - 1) / g.grou
 size_t fill_lds_bytes(const DevGrid& g, bool long_l)
 {
   return (size_t)g.rows * ((((size_t)g.n_b + 3) & ~(size_t)3) + (long_l ? kSpill : 0)) * sizeof(uint32_t);
+}
+
+hipError_t launch_fetch(EvDesc* evs, const EvDesc* host, int n_ev, hipStream_t s)
+{
+  static_assert(sizeof(EvDesc) % sizeof(u32x2) == 0 && alignof(EvDesc) == alignof(u32x2), "whole 8-byte words");
+  const uint32_t n = (uint32_t)n_ev * (uint32_t)(sizeof(EvDesc) / sizeof(u32x2));
+  hipLaunchKernelGGL(k_fetch, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, s, (u32x2*)evs, (const u32x2*)host, n);
+  return hipGetLastError();
 }
 
 hipError_t launch_prep(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev,

@@ -155,9 +155,8 @@ int launch(ht_server* sv, Batch& b)
     d.n_found = sl.d_nfound;
     max_n = std::max(max_n, r->n);
   }
-  if ((e = hipMemcpyAsync(sv->d_ev[b.stream], sv->h_ev[b.stream], sizeof(EvDesc) * b.reqs.size(),
-                          hipMemcpyHostToDevice, s)) != hipSuccess)
-    return fail_hip(e, "hipMemcpyAsync(descriptors)");
+  if ((e = launch_fetch(sv->d_ev[b.stream], sv->h_ev[b.stream], (int)b.reqs.size(), s)) != hipSuccess)
+    return fail_hip(e, "descriptor launch");
   bool prep_enqueued = false;
   int rc = launch_batch(sv->g, sv->d_ev[b.stream], (int)b.reqs.size(), max_n, sv->direct, any_bands,
                         any_dense, s, &prep_enqueued);

@@ -171,7 +171,7 @@ def test_long_lists_with_ragged_rows(B, n_b):
 @pytest.mark.parametrize("n_a,n_b,threshold", [(64, 64, 32), (64, 64, 31), (64, 1, 40), (63, 2, 40), (33, 3, 17),
                                                (20, 5, 10), (64, 33, 33), (40, 300, 20), (5, 1030, 3), (4, 16, 1)])
 @pytest.mark.parametrize("sectors", [False, True])
-def test_tiny_events_in_two_launches(B, n_a, n_b, threshold, sectors):
+def test_tiny_events_in_two_launches(B, monkeypatch, n_a, n_b, threshold, sectors):
     import torch
     from oracle import oracle
     rng = np.random.default_rng([n_a, n_b, threshold, sectors])
@@ -197,7 +197,8 @@ def test_tiny_events_in_two_launches(B, n_a, n_b, threshold, sectors):
             acc, c2, v2, found2 = B.fill_peaks(spec, *dev, capacity=found - 1, allow_truncation=True)
             assert found2 == found and np.array_equal(c2, c[:-1]) and np.array_equal(v2, v[:-1]), n
     for evs, want in ((evs[:-1], want[:-1]), (evs, want)):
-        for k in range(3):  # a captured batch and its replays
+        for k in range(6):  # by turns launched and as a captured graph, replayed
+            monkeypatch.setenv("HT_BATCH_GRAPH", str(k % 2))
             res = B.fill_peaks_batch(spec, evs)
             for i, M in enumerate(want):
                 assert np.array_equal(B.as_u32(res.acc[i]), M), (k, i)
