@@ -203,3 +203,32 @@ def test_tiny_events_in_two_launches(B, monkeypatch, n_a, n_b, threshold, sector
             for i, M in enumerate(want):
                 assert np.array_equal(B.as_u32(res.acc[i]), M), (k, i)
                 same_peaks(spec, res.peaks[i], M, "event %d" % i)
+
+
+@pytest.mark.parametrize("shape", [(3, 11, 96, 260), (1, 3, 7, 2000), (8, 32, 40, 64), (2, 3, 300, 33), (5, 1, 64, 1030)])
+def test_mask_groups_are_all_searched(B, shape):
+    """Every group of the mask search is taken by exactly one workgroup, whatever the number of
+    slabs and groups, in single events and batches."""
+    import torch
+    from oracle import oracle
+    rng = np.random.default_rng(shape)
+    spec = synth.GridSpec(*shape, threshold=3, phi_sectors=shape[1] < 3)
+    og = oracle.OracleGrid(*spec.as_tuple())
+    evs, want = [], []
+    for n in (20000, 21000, 700):
+        ev = synth.make_hits(rng, n // 14, n - 12 * (n // 14))
+        evs.append((ev.x, ev.y, ev.z))
+        want.append(oracle.fill(og, *evs[-1])[0])
+    B.ht_set_tuning(spec, rows=4, dense_hits=-1)
+    try:
+        for events in (evs, evs * 4):
+            say(shape, "events", len(events))
+            res = B.fill_peaks_batch(spec, events)
+            for i in range(len(events)):
+                assert np.array_equal(B.as_u32(res.acc[i]), want[i % 3]), i
+                same_peaks(spec, res.peaks[i], want[i % 3], "event %d" % i)
+        for h, M in zip(evs, want):
+            acc, c, v, n = B.fill_peaks(spec, *B.hits_to_device(*h))
+            same_peaks(spec, (c, v, n), M, "one event")
+    finally:
+        B.ht_set_tuning(spec)
