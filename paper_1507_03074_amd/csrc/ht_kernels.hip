@@ -535,22 +535,46 @@ __device__ __forceinline__ bool row_wins(const TestCell& x, const Row3& r, uint3
   }
   return beaten;
 }
-// The nine neighbour rows of theta cell t + dt, all loaded together.
-template <bool NARROW>
-__device__ __forceinline__ bool slice_wins(const DevGrid& g, const uint32_t* acc, const TestCell& x, int dt)
+// The nine neighbour rows of theta cell t + DT: whether one beats the cell, one cell per lane. With
+// every lane at it, this is bound by the lines and the instructions of its rows. So three rows are
+// in flight at a time, those of one phi cell (the nearest lines first), and a lane stops at the first
+// that beats it; rows lie at constant distances (row_window takes three products for each); and a
+// row counts by the maximum of its near columns, which beats the cell above v, or above v - 1 where
+// the row lies before the cell. (With sectors the rows of the other phi cells are the same ones
+// again: a branch around them costs the other grids 3%.) The test of a 40k-hit event takes 54 us; with the nine rows together
+// 64 (whatever the occupancy, from three to eight waves), with two rows of either side first 65.
+template <bool NARROW, int DT>
+__device__ __forceinline__ bool slice_wins(const DevGrid& g, const uint32_t* acc, const TestCell& x)
 {
-  Row3 r[9];
-  uint32_t at[9];
-  bool in[9];
+  const uint32_t nb = (uint32_t)g.n_b, np = (uint32_t)g.n_phi, S = (uint32_t)g.n_a * nb;
+  if (DT < 0 ? x.t == 0u : DT > 0 && x.t + 1u == (uint32_t)g.n_theta) return false;
+  const uint32_t at0 = x.c - x.b + x.w0 + (uint32_t)DT * np * S;
+  const bool first = x.b == 0u, last = x.b + 1u == nb;  // the window's third or first column is not near
+  const uint32_t before = x.v - 1u;                     // x.v >= 1
+  // the rows at A - 1 and A + 1; where there is none, the one at A again
+  const uint32_t up = x.a > 0u ? 0u - nb : 0u, down = x.a + 1u < (uint32_t)g.n_a ? nb : 0u;
 #pragma unroll
-  for (int k = 0; k < 9; ++k) {
-    at[k] = row_window(g, x, dt, k / 3 - 1, k % 3 - 1, &in[k]);
-    r[k] = load_row<NARROW>(g, acc, at[k]);
+  for (int q = 0; q < 3; ++q) {  // phi cells p, p - 1, p + 1
+    const bool wraps = q == 1 ? x.p == 0u : x.p + 1u == np;
+    const uint32_t at = at0 + (q == 0 || g.phi_sectors ? 0u : q == 1 ? (wraps ? (np - 1u) * S : 0u - S) : (wraps ? 0u - (np - 1u) * S : S));
+    Row3 r[3] = {load_row<NARROW>(g, acc, at + up), load_row<NARROW>(g, acc, at), load_row<NARROW>(g, acc, at + down)};
+    // whole rows: the compiler would load a column that an edge drops by itself, and later
+#pragma unroll
+    for (int k = 0; k < 3; ++k) asm volatile("" : "+v"(r[k].w[0]), "+v"(r[k].w[1]), "+v"(r[k].w[2]));
+    uint32_t m[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      m[k] = max(max(!NARROW && last ? 0u : r[k].w[0], r[k].w[1]), first ? 0u : r[k].w[2]);
+    if (DT == 0 && q == 0) {  // of the own row, the columns beside the cell
+      const uint32_t left = first ? 0u : !NARROW && last ? r[1].w[1] : r[1].w[0];
+      const uint32_t right = last ? 0u : first ? r[1].w[1] : r[1].w[2];
+      if (max(left, up ? m[0] : 0u) > before || max(right, down ? m[2] : 0u) > x.v) return true;
+    } else {
+      const bool lies_before = DT < 0 || (DT == 0 && (q == 1) != wraps);
+      if (max(max(m[0], m[1]), m[2]) > (lies_before ? before : x.v) && !(DT == 0 && g.phi_sectors)) return true;
+    }
   }
-  bool beaten = false;
-#pragma unroll
-  for (int k = 0; k < 9; ++k) beaten |= in[k] && row_wins(x, r[k], at[k], dt == 0 && k == 4);
-  return beaten;
+  return false;
 }
 
 // Block b of a grid of G runs on XCD b % 8 (workgroups are dealt to the eight XCDs in turn); the
@@ -700,159 +724,157 @@ __global__ __launch_bounds__(kBlock) void k_peak_test(DevGrid g, EvDesc ev0, con
   const uint32_t piece = min((e.n_grp + 7u) / 8u, 4u * max(1u, e.n_grp / (uint32_t)g.n_slabs));
   const uint32_t rounds = (e.n_grp + 8u * piece - 1u) / (8u * piece);
   for (uint32_t sl = blockIdx.x; sl < rounds * 8u * piece; sl += gridDim.x) {  // uniform
-  const uint32_t round = (sl >> 3) / piece;
-  const uint32_t grp = (round * 8u + (((sl & 7u) - round) & 7u)) * piece + ((sl >> 3) - round * piece);
-  if (grp >= e.n_grp) continue;
-  const uint32_t gj = (uint32_t)g.j.group_jobs;
-  const uint64_t first = (uint64_t)(e.grp0 + grp) * gj;
-  const uint32_t nj = (uint32_t)min((uint64_t)gj, (uint64_t)g.j.n_jobs - first);
-  const uint64_t l0 = (uint64_t)grp * gj;  // the group's first job in the event's arrays
-  if (threadIdx.x == 0) s_np = 0u;
-  for (uint32_t win = 0u; win < nj; win += kBlock) {  // uniform
-    // the window's flagged jobs, in order
-    const uint32_t j = win + threadIdx.x;
-    uint32_t flag = 0u;
-    if (j < nj) flag = gp(e.job_any)[l0 + j];
-    const uint64_t fb = __builtin_amdgcn_ballot_w64(flag != 0u);
-    if (lane == 0u) s_w[w] = (uint32_t)__builtin_popcountll(fb);
-    lds_barrier();
-    const uint32_t f1 = s_w[0], f2 = f1 + s_w[1], f3 = f2 + s_w[2], nf = f3 + s_w[3];
-    if (flag) s_ids[rank_of(fb, w == 0u ? 0u : w == 1u ? f1 : w == 2u ? f2 : f3)] = (uint16_t)threadIdx.x;
-    lds_barrier();
-    for (uint32_t p0 = 0u; p0 < nf; p0 += kPassJobs) {  // uniform
-      const uint32_t n_job = min(kPassJobs, nf - p0);
-      // the pass's masks: slot w + 4 i is this wave's i-th job
-      uint32_t m[kPassJobs / 4];
-#pragma unroll
-      for (uint32_t i = 0; i < kPassJobs / 4; ++i) {
-        m[i] = 0u;
-        if (w + 4u * i < n_job) {  // uniform
-          const size_t at = (size_t)(l0 + win + s_ids[p0 + w + 4u * i]) * 64u + lane;
-          m[i] = two ? ((const GLOBAL uint16_t*)gp((const uint8_t*)e.masks))[at]
-                     : gp((const uint8_t*)e.masks)[at];
-        }
-      }
-      if (threadIdx.x < n_job) {  // meanwhile, a lane per job: where it is
-        const JobAt at = job_at(g, (uint32_t)(first + win + s_ids[p0 + threadIdx.x]));
-        const uint32_t t = at.slab / np;
-        s_slab[threadIdx.x] = t << 16 | (at.slab - t * np);
-        s_a0[threadIdx.x] = at.a0;
-        s_st[threadIdx.x] = at.st;
-      }
-      uint32_t cnt = 0u;
-#pragma unroll
-      for (uint32_t i = 0; i < kPassJobs / 4; ++i) {
-        if (w + 4u * i < n_job) {  // uniform
-          m16[(w + 4u * i) * 64u + lane] = (uint16_t)m[i];
-          cnt += (uint32_t)__builtin_popcount(m[i]);
-        }
-      }
-      cnt = wave_sum(cnt);
-      if (lane == 0u) s_w[w] = cnt;
-      if (threadIdx.x == 0) s_n = 0u;
+    const uint32_t round = (sl >> 3) / piece;
+    const uint32_t grp = (round * 8u + (((sl & 7u) - round) & 7u)) * piece + ((sl >> 3) - round * piece);
+    if (grp >= e.n_grp) continue;
+    const uint32_t gj = (uint32_t)g.j.group_jobs;
+    const uint64_t first = (uint64_t)(e.grp0 + grp) * gj;
+    const uint32_t nj = (uint32_t)min((uint64_t)gj, (uint64_t)g.j.n_jobs - first);
+    const uint64_t l0 = (uint64_t)grp * gj;  // the group's first job in the event's arrays
+    if (threadIdx.x == 0) s_np = 0u;
+    for (uint32_t win = 0u; win < nj; win += kBlock) {  // uniform
+      // the window's flagged jobs, in order
+      const uint32_t j = win + threadIdx.x;
+      uint32_t flag = 0u;
+      if (j < nj) flag = gp(e.job_any)[l0 + j];
+      const uint64_t fb = __builtin_amdgcn_ballot_w64(flag != 0u);
+      if (lane == 0u) s_w[w] = (uint32_t)__builtin_popcountll(fb);
       lds_barrier();
-      // all the jobs' survivors at once where the list holds them, else four jobs at a time
-      const uint32_t step = s_w[0] + s_w[1] + s_w[2] + s_w[3] <= kList ? kPassJobs / 4 : 1u;
-      for (uint32_t i0 = 0u; 4u * i0 < n_job; i0 += step) {               // uniform
-        for (uint32_t i = i0; i < i0 + step && w + 4u * i < n_job; ++i) {  // uniform
-          const uint32_t slot = w + 4u * i;
-          uint32_t mm = m16[slot * 64u + lane];
-          m16[slot * 64u + lane] = 0;
-          const uint32_t c = (uint32_t)__builtin_popcount(mm), incl = wave_incl_scan(c);
-          uint32_t from = 0u;
-          if (lane == 63u) from = atomicAdd(&s_n, incl);
-          uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)from, 63) + incl - c;
-          while (mm) {
-            s_pos[at++] = (slot << 10) | (lane << 4) | (uint32_t)__builtin_ctz(mm);
-            mm &= mm - 1u;
+      const uint32_t f1 = s_w[0], f2 = f1 + s_w[1], f3 = f2 + s_w[2], nf = f3 + s_w[3];
+      if (flag) s_ids[rank_of(fb, w == 0u ? 0u : w == 1u ? f1 : w == 2u ? f2 : f3)] = (uint16_t)threadIdx.x;
+      lds_barrier();
+      for (uint32_t p0 = 0u; p0 < nf; p0 += kPassJobs) {  // uniform
+        const uint32_t n_job = min(kPassJobs, nf - p0);
+        // the pass's masks: slot w + 4 i is this wave's i-th job
+        uint32_t m[kPassJobs / 4];
+#pragma unroll
+        for (uint32_t i = 0; i < kPassJobs / 4; ++i) {
+          m[i] = 0u;
+          if (w + 4u * i < n_job) {  // uniform
+            const size_t at = (size_t)(l0 + win + s_ids[p0 + w + 4u * i]) * 64u + lane;
+            m[i] = two ? ((const GLOBAL uint16_t*)gp((const uint8_t*)e.masks))[at]
+                       : gp((const uint8_t*)e.masks)[at];
           }
         }
-        lds_barrier();
-        const uint32_t n = s_n;  // uniform
-        if (n <= kFew) {
-          const uint32_t half = threadIdx.x >> 5, k = threadIdx.x & 31u;
-          const int kk = (int)min(k, 26u), dt = kk / 9 - 1, dp = kk / 3 % 3 - 1, da = kk % 3 - 1;
-          for (uint32_t b0 = 0u; b0 < n; b0 += 32u) {  // uniform
-            TestCell x[4];
-            bool beaten[4];
+        if (threadIdx.x < n_job) {  // meanwhile, a lane per job: where it is
+          const JobAt at = job_at(g, (uint32_t)(first + win + s_ids[p0 + threadIdx.x]));
+          const uint32_t t = at.slab / np;
+          s_slab[threadIdx.x] = t << 16 | (at.slab - t * np);
+          s_a0[threadIdx.x] = at.a0;
+          s_st[threadIdx.x] = at.st;
+        }
+        uint32_t cnt = 0u;
 #pragma unroll
-            for (uint32_t q = 0; q < 4; ++q) {
-              x[q] = cell_of(s_pos[min(b0 + half + 8u * q, n - 1u)]);
-              bool in;
-              const uint32_t at = row_window(g, x[q], dt, dp, da, &in);
-              beaten[q] = row_wins(x[q], load_row<NARROW>(g, acc, at), at, kk == 13) && in && k < 27u;
-            }
-#pragma unroll
-            for (uint32_t q = 0; q < 4; ++q) {
-              const uint32_t i = b0 + half + 8u * q;
-              const uint32_t hm = (uint32_t)(__builtin_amdgcn_ballot_w64(beaten[q]) >> (lane & 32u));
-              if (k == 0u && i < n && hm == 0u) keep(s_pos[i], x[q]);
-            }
-          }
-        } else {
-          uint32_t n2 = 0u;
-          for (uint32_t b0 = 0u; b0 < n; b0 += kBlock) {  // uniform
-            const uint32_t i = b0 + threadIdx.x;
-            uint32_t pos = 0u;
-            bool alive = false;
-            if (i < n) {
-              pos = s_pos[i];
-              alive = !slice_wins<NARROW>(g, acc, cell_of(pos), 0);
-            }
-            const uint64_t b = __builtin_amdgcn_ballot_w64(alive);
-            if (lane == 0u) s_w[w] = (uint32_t)__builtin_popcountll(b);
-            lds_barrier();  // every wave has read its entries: the front of the list is free
-            const uint32_t c1 = s_w[0], c2 = c1 + s_w[1], c3 = c2 + s_w[2];
-            if (alive) s_pos[rank_of(b, n2 + (w == 0u ? 0u : w == 1u ? c1 : w == 2u ? c2 : c3))] = pos;
-            n2 += c3 + s_w[3];
-            lds_barrier();
-          }
-          for (uint32_t i = threadIdx.x; i < n2; i += kBlock) {
-            const uint32_t pos = s_pos[i];
-            const TestCell x = cell_of(pos);
-            const bool w0 = g.n_theta > 1 && slice_wins<NARROW>(g, acc, x, -1);  // uniform condition
-            const bool w1 = g.n_theta > 1 && slice_wins<NARROW>(g, acc, x, 1);
-            if (!w0 && !w1) keep(pos, x);
+        for (uint32_t i = 0; i < kPassJobs / 4; ++i) {
+          if (w + 4u * i < n_job) {  // uniform
+            m16[(w + 4u * i) * 64u + lane] = (uint16_t)m[i];
+            cnt += (uint32_t)__builtin_popcount(m[i]);
           }
         }
-        lds_barrier();
+        cnt = wave_sum(cnt);
+        if (lane == 0u) s_w[w] = cnt;
         if (threadIdx.x == 0) s_n = 0u;
         lds_barrier();
-      }
-      for (uint32_t i = 0u; i < kPassJobs / 4 && w + 4u * i < n_job; ++i) {  // uniform: the peaks' masks
-        const uint32_t slot = w + 4u * i;
-        const size_t at = (size_t)(l0 + win + s_ids[p0 + slot]) * 64u + lane;
-        const uint32_t mm = m16[slot * 64u + lane];
-        if (two) ((GLOBAL uint16_t*)gp(e.masks))[at] = (uint16_t)mm;
-        else gp(e.masks)[at] = (uint8_t)mm;
+        // all the jobs' survivors at once where the list holds them, else four jobs at a time
+        const uint32_t step = s_w[0] + s_w[1] + s_w[2] + s_w[3] <= kList ? kPassJobs / 4 : 1u;
+        for (uint32_t i0 = 0u; 4u * i0 < n_job; i0 += step) {               // uniform
+          for (uint32_t i = i0; i < i0 + step && w + 4u * i < n_job; ++i) {  // uniform
+            const uint32_t slot = w + 4u * i;
+            uint32_t mm = m16[slot * 64u + lane];
+            m16[slot * 64u + lane] = 0;
+            const uint32_t c = (uint32_t)__builtin_popcount(mm), incl = wave_incl_scan(c);
+            uint32_t from = 0u;
+            if (lane == 63u) from = atomicAdd(&s_n, incl);
+            uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)from, 63) + incl - c;
+            while (mm) {
+              s_pos[at++] = (slot << 10) | (lane << 4) | (uint32_t)__builtin_ctz(mm);
+              mm &= mm - 1u;
+            }
+          }
+          lds_barrier();
+          const uint32_t n = s_n;  // uniform
+          if (n <= kFew) {
+            const uint32_t half = threadIdx.x >> 5, k = threadIdx.x & 31u;
+            const int kk = (int)min(k, 26u), dt = kk / 9 - 1, dp = kk / 3 % 3 - 1, da = kk % 3 - 1;
+            for (uint32_t b0 = 0u; b0 < n; b0 += 32u) {  // uniform
+              TestCell x[4];
+              bool beaten[4];
+#pragma unroll
+              for (uint32_t q = 0; q < 4; ++q) {
+                x[q] = cell_of(s_pos[min(b0 + half + 8u * q, n - 1u)]);
+                bool in;
+                const uint32_t at = row_window(g, x[q], dt, dp, da, &in);
+                beaten[q] = row_wins(x[q], load_row<NARROW>(g, acc, at), at, kk == 13) && in && k < 27u;
+              }
+#pragma unroll
+              for (uint32_t q = 0; q < 4; ++q) {
+                const uint32_t i = b0 + half + 8u * q;
+                const uint32_t hm = (uint32_t)(__builtin_amdgcn_ballot_w64(beaten[q]) >> (lane & 32u));
+                if (k == 0u && i < n && hm == 0u) keep(s_pos[i], x[q]);
+              }
+            }
+          } else {
+            uint32_t n2 = 0u;
+            for (uint32_t b0 = 0u; b0 < n; b0 += kBlock) {  // uniform
+              const uint32_t i = b0 + threadIdx.x;
+              uint32_t pos = 0u;
+              bool alive = false;
+              if (i < n) {
+                pos = s_pos[i];
+                alive = !slice_wins<NARROW, 0>(g, acc, cell_of(pos));
+              }
+              const uint64_t b = __builtin_amdgcn_ballot_w64(alive);
+              if (lane == 0u) s_w[w] = (uint32_t)__builtin_popcountll(b);
+              lds_barrier();  // every wave has read its entries: the front of the list is free
+              const uint32_t c1 = s_w[0], c2 = c1 + s_w[1], c3 = c2 + s_w[2];
+              if (alive) s_pos[rank_of(b, n2 + (w == 0u ? 0u : w == 1u ? c1 : w == 2u ? c2 : c3))] = pos;
+              n2 += c3 + s_w[3];
+              lds_barrier();
+            }
+            for (uint32_t i = threadIdx.x; i < n2; i += kBlock) {
+              const uint32_t pos = s_pos[i];
+              const TestCell x = cell_of(pos);
+              if (!slice_wins<NARROW, -1>(g, acc, x) && !slice_wins<NARROW, 1>(g, acc, x)) keep(pos, x);
+            }
+          }
+          lds_barrier();
+          if (threadIdx.x == 0) s_n = 0u;
+          lds_barrier();
+        }
+        for (uint32_t i = 0u; i < kPassJobs / 4 && w + 4u * i < n_job; ++i) {  // uniform: the peaks' masks
+          const uint32_t slot = w + 4u * i;
+          const size_t at = (size_t)(l0 + win + s_ids[p0 + slot]) * 64u + lane;
+          const uint32_t mm = m16[slot * 64u + lane];
+          if (two) ((GLOBAL uint16_t*)gp(e.masks))[at] = (uint16_t)mm;
+          else gp(e.masks)[at] = (uint8_t)mm;
+        }
       }
     }
-  }
-  lds_barrier();
-  const uint32_t n = s_np;
-  if (threadIdx.x == 0) {
-    gp(e.group_pk)[grp * (uint32_t)g.j.pk_step] = n;
-    if (n && supers) gatomic_add(e.super_pk + grp / 64u, n);
-  }
-  if (n == 0u || n > seg_cap) {  // uniform
     lds_barrier();
-    continue;
-  }
-  // pad to whole 16-byte reads with cells that rank after every peak's
-  if (threadIdx.x < 4u && n + threadIdx.x < seg_cap) s_pc[n + threadIdx.x] = 0xffffffffu;
-  lds_barrier();
-  const u32x4* s4 = reinterpret_cast<const u32x4*>(s_pc);
-  for (uint32_t i = threadIdx.x; i < n; i += kBlock) {
-    const uint32_t c = s_pc[i];
-    uint32_t r = 0u;
-    for (uint32_t k = 0u; k < (n + 3u) / 4u; ++k) {
-      const u32x4 o = s4[k];
-      r += (o.x < c ? 1u : 0u) + (o.y < c ? 1u : 0u) + (o.z < c ? 1u : 0u) + (o.w < c ? 1u : 0u);
+    const uint32_t n = s_np;
+    if (threadIdx.x == 0) {
+      gp(e.group_pk)[grp * (uint32_t)g.j.pk_step] = n;
+      if (n && supers) gatomic_add(e.super_pk + grp / 64u, n);
     }
-    const u32x2 pk = {c, s_pv[i]};
-    ((GLOBAL u32x2*)gp(e.seg))[(size_t)grp * seg_cap + r] = pk;
-  }
-  lds_barrier();  // the next group clears what this one still reads
+    if (n == 0u || n > seg_cap) {  // uniform
+      lds_barrier();
+      continue;
+    }
+    // pad to whole 16-byte reads with cells that rank after every peak's
+    if (threadIdx.x < 4u && n + threadIdx.x < seg_cap) s_pc[n + threadIdx.x] = 0xffffffffu;
+    lds_barrier();
+    const u32x4* s4 = reinterpret_cast<const u32x4*>(s_pc);
+    for (uint32_t i = threadIdx.x; i < n; i += kBlock) {
+      const uint32_t c = s_pc[i];
+      uint32_t r = 0u;
+      for (uint32_t k = 0u; k < (n + 3u) / 4u; ++k) {
+        const u32x4 o = s4[k];
+        r += (o.x < c ? 1u : 0u) + (o.y < c ? 1u : 0u) + (o.z < c ? 1u : 0u) + (o.w < c ? 1u : 0u);
+      }
+      const u32x2 pk = {c, s_pv[i]};
+      ((GLOBAL u32x2*)gp(e.seg))[(size_t)grp * seg_cap + r] = pk;
+    }
+    lds_barrier();  // the next group clears what this one still reads
   }
 }
 
@@ -1031,9 +1053,8 @@ __global__ __launch_bounds__(kBlock) void k_peak_write(DevGrid g, EvDesc ev0, co
       const uint32_t v = gp((const uint32_t*)e.acc)[c];
       if (!sorted) {  // uniform
         const TestCell x = test_cell(g, c, v);
-#pragma unroll 1
-        for (int dt = -1; dt <= 1; ++dt)
-          if (pk) pk = !slice_wins<NARROW>(g, e.acc, x, dt);
+        pk = pk && !slice_wins<NARROW, 0>(g, e.acc, x) && !slice_wins<NARROW, -1>(g, e.acc, x) &&
+             !slice_wins<NARROW, 1>(g, e.acc, x);
       }
       const uint64_t b = __builtin_amdgcn_ballot_w64(pk);
       const int64_t o = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
