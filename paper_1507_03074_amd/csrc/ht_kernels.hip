@@ -1105,7 +1105,7 @@ constexpr int kWriteStage = 4096;  // peaks of a group staged in LDS by the dens
 
 // ---------------------------------------------------------------------------------------------
 // Peak search of crowded events: an LDS-halo stencil over the whole matrix (one read of it), in
-// place of the candidate pool. A workgroup owns one chunk of kChunkCells B columns of every
+// place of the survivor masks. A workgroup owns one chunk of kChunkCells B columns of every
 // (theta, phi) slab and walks down a segment of S A rows. Wave p holds phi cell p of every theta
 // cell, so its theta neighbours are in its own registers: lane j holds cell b = base + j - 1 of
 // slab (t, p) for each t, where base = kChunkCells * chunk. Lanes 1..62 are tested; lanes 0 and
@@ -1822,11 +1822,12 @@ hipError_t launch_peaks(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, 
                         hipStream_t s)
 {
   // A workgroup per group, so that the hardware deals the uneven ones out as CUs come free (16384
-  // groups of 8x32x2048x2048 cells, four events: 1.24 ms with 2048 workgroups each, 1.16 with all);
-  // batches of many events, which are ordinary ones, kTestGrid over all. For the lists of small
-  // grids at least one per CU over all events. A multiple of the XCDs.
+  // groups of 8x32x2048x2048 cells, four events: 1.24 ms with 2048 workgroups each, 1.16 with all; ten
+  // events, whole batch: 10.37 ms with 819 each, 10.09 with all). Batches of many events on grids of up
+  // to 4096 groups, which are ordinary ones (the paper grid has 2048), share kTestGrid. For the lists
+  // of small grids at least one per CU over all events. A multiple of the XCDs.
   const unsigned least = std::max(kTestBlocks, 256u / (unsigned)n_ev);
-  const unsigned most = n_ev <= 8 ? 16384u : std::max(least, kTestGrid / (unsigned)n_ev);
+  const unsigned most = n_ev <= 8 || n_grp > 4096u ? 16384u : std::max(least, kTestGrid / (unsigned)n_ev);
   const dim3 tg((std::min(std::max(n_grp, least), most) + 7u) & ~7u, n_ev);
   if (g.n_b < 3) hipLaunchKernelGGL(k_peak_test<true>, tg, dim3(kBlock), 0, s, g, ev0, evs);
   else hipLaunchKernelGGL(k_peak_test<false>, tg, dim3(kBlock), 0, s, g, ev0, evs);
