@@ -209,9 +209,9 @@ Tiling choose_tiling(const ht_grid& g)
   // where one pass over the matrix beats a test of every candidate. The survivors are a quarter of
   // them, so unless the caller sets a threshold the stencil starts at twice that, or two and a half
   // times where a pass is long, from 128 MiB on. Whole call, survivors against stencil, in us:
-  // 4x16x1024x1024 at 2 times 113 / 134, at 3 times 155 / 144; 4x16x512x512 at 1 time 40 / 46, at
-  // 2 times 55 / 52; 4x16x64x64 at 2 times 20 / 27; 3x7x501x333 at 2 times 28 / 30, at 3 times
-  // 34 / 32. -1: never
+  // 4x16x1024x1024 at 2.4 times 122 / 137, at 3.7 times 183 / 150; 4x16x512x512 at 2 times 52 / 52,
+  // at 2.9 times 59 / 55; 4x16x256x256 at 2.9 times 37 / 38, at 4.4 times 53 / 40; 4x16x128x128 at
+  // 2.9 times 31 / 33. -1: never
   const int64_t def = ((int64_t)g.n_theta * g.n_phi * g.n_b + 3) / 4;
   const int64_t bytes = 4 * (int64_t)g.n_theta * g.n_phi * g.n_a * g.n_b;
   int64_t dh = def, from = bytes >= ((int64_t)128 << 20) ? def * 5 / 2 : def * 2;
@@ -741,7 +741,7 @@ int launch_batch(const DevGrid& g, const EvDesc* d_ev, int n_ev, int64_t max_hit
   if (pieces > 1) {
     // The batch in `pieces` runs of consecutive events: the fill of run i + 1 (on s) overlaps
     // the peak search of run i (on the side stream, after an event recorded when run i's fill
-    // is done): the fill is bound by HBM writes, the candidate test by memory latency. s waits
+    // is done): the fill is bound by HBM writes, the peak test by memory latency. s waits
     // for the side stream at the end, so the call's completion on s covers everything.
     hipError_t e;
     for (int i = 0; i < pieces; ++i) {
@@ -776,7 +776,7 @@ int launch_batch(const DevGrid& g, const EvDesc* d_ev, int n_ev, int64_t max_hit
   }
   if ((rc = injected_failure("peaks"))) return rc;
   StageTimer t("peaks", s);
-  if (!any_dense && g.lds_fill && few_cells(g, max_hits) && use_lists(g, max_hits, max_hits))
+  if (!any_dense && g.lds_fill && few_cells(g, max_hits) && use_lists(g, n_ev, max_hits, max_hits))
     return check_launch(launch_few_peaks(g, none, d_ev, n_ev, s), "peak launch");
   if (any_bands && (rc = check_launch(launch_peaks(g, none, d_ev, n_ev, g.j.n_groups, s), "peak launch"))) return rc;
   if (any_dense && (rc = check_launch(launch_peaks_dense(g, none, d_ev, n_ev, s), "stencil peak launch")))
@@ -934,7 +934,7 @@ int run_event(const ht_grid* grid, const float* x, const float* y, const float* 
   std::memset(&ev, 0, sizeof(ev));
   carve_event_scratch(p.g, nh, direct, w->dev, &ev, layout);
   ev.dense = dense ? 1 : 0;
-  ev.lists = layout == kPeakBands && (!do_fill || atomic || use_lists(p.g, nh, nh)) ? 1 : 0;
+  ev.lists = layout == kPeakBands && (!do_fill || atomic || use_lists(p.g, 1, nh, nh)) ? 1 : 0;
   use_counters(w, 0, &ev);
   ev.x = x;
   ev.y = y;
@@ -1048,7 +1048,7 @@ int ht_fill_peaks_batch(const ht_grid* grid, const ht_event* events, int32_t n_e
     any_dense = any_dense || dense;
     carve_event_scratch(p.g, ev.n_hits, direct, w->dev + offs[i], &d, dense ? kPeakMask : kPeakBands);
     d.dense = dense ? 1 : 0;
-    d.lists = !dense && (!p.g.lds_fill || use_lists(p.g, max_hits_b, ev.n_hits)) ? 1 : 0;
+    d.lists = !dense && (!p.g.lds_fill || use_lists(p.g, n_events, max_hits_b, ev.n_hits)) ? 1 : 0;
     use_counters(w, i, &d);
     d.x = x ? x + ev.hit_offset : nullptr;
     d.y = y ? y + ev.hit_offset : nullptr;

@@ -1,5 +1,5 @@
 // ht_device.h -- device code shared by the kernel translation units of libht.so: memory
-// helpers, wave and block scans, the candidate pooling of an LDS tile, and the fill kernel
+// helpers, wave and block scans, the survivors of an LDS tile's cells, and the fill kernel
 // template (its row counts are instantiated in separate translation units so that they compile
 // in parallel).
 //

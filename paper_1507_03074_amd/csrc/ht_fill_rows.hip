@@ -1,7 +1,7 @@
 // ht_fill_rows.hip -- the fill kernel instantiated for one A-row count per tile, HT_FILL_ROWS,
 // given on the compiler's command line (the build compiles this file once per row count, in
-// parallel: each instantiates 16 kernel variants of store kind, vector width, candidate
-// emission and record caching).
+// parallel: each instantiates 16 kernel variants of store kind, vector width, survivor masks and
+// list length).
 #include "ht_device.h"
 
 #pragma clang fp contract(off)

@@ -78,7 +78,7 @@ struct DevGrid {
   int32_t dense_w;         // 1: the stencil peak search is available on this grid (0: not)
   int32_t dense_rows;      // A rows per workgroup of the stencil peak search (a multiple of 12)
   int32_t dense_hits;      // events with at least this many hits take the stencil (0: never)
-  JobGeom j;               // jobs of the candidate search (of fill tiles, or of a scanned matrix)
+  JobGeom j;               // jobs of the survivor search (of fill tiles, or of a scanned matrix)
   const float* a2;         // device [n_a]
   const float* phi_cs;     // device [2 * 2 n_phi] (cos, sin)
   const float* th_cs;      // device [2 * (2 n_theta + 1)] (cos, sin)
@@ -103,7 +103,7 @@ struct EvDesc {
   uint32_t* hit_pos;    // [4 n_hits] position of the (hit, cell) in its slab list
   float4* hit_rec;      // [n_hits] (x, r2, k, 0)
   float4* list;         // hit records bucketed by slab: [n_slabs * list_cap] or [4 n_hits]
-  // candidate search (ordinary events): the groups [grp0, grp0 + n_grp) of the event, all of them
+  // survivor search (ordinary events): the groups [grp0, grp0 + n_grp) of the event, all of them
   // except where a caller's fixed scratch holds only a slice at a time
   uint32_t grp0, n_grp;
   uint32_t* group_pk;   // peaks per group of jobs, g.j.pk_step words apart (or [groups of tiles]: stencil)
@@ -117,7 +117,7 @@ struct EvDesc {
   uint32_t clear_n16;   // stencil's group_pk; in 16-byte units
   const int64_t* carry_in;  // peaks of the earlier slices, or NULL
   int64_t* carry_out;       // receives the peaks up to and with this slice, or NULL
-  int32_t dense;        // 1: peaks from the stencil over the matrix (crowded events), not the pool
+  int32_t dense;        // 1: peaks from the stencil over the matrix (crowded events), no masks
   uint8_t* pk_mask;     // 64-bit words of peak bits of a dense event, kChunkCells cells per
                         // (slab, row, chunk) word, stored by the stencil's workgroups
 };
@@ -184,7 +184,7 @@ hipError_t launch_fetch(EvDesc* evs, const EvDesc* host, int n_ev, hipStream_t s
 hipError_t launch_prep(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev,
                        int64_t max_hits, bool direct, hipStream_t s);
 hipError_t launch_fill(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev,
-                       bool emit_candidates, int64_t max_hits, hipStream_t s);
+                       bool emit, int64_t max_hits, hipStream_t s);
 // Survivors of a written matrix (g.j set for a scan), for n_grp groups per event. counters: the
 // scan uses the counter pair (no preparation of the same call does): the lists' lengths in one
 // array, and it clears the other.
@@ -211,9 +211,9 @@ hipError_t launch_fill_atomic(const DevGrid& g, const EvDesc& ev0, const EvDesc*
 hipError_t launch_readout(const DevGrid& g, const ht_peak* peaks, const int64_t* n_found, int64_t cap,
                           ht_track* tracks, double b_min, double db, hipStream_t s);
 
-// Whether the fill of a launch of events of up to max_hits hits makes lists of the survivors of an
-// event of `hits` hits.
-bool use_lists(const DevGrid& g, int64_t max_hits, int64_t hits);
+// Whether the fill of a launch of n_ev events of up to max_hits hits makes lists of the survivors of
+// an event of `hits` hits. (If it does for one, it does for those of fewer hits.)
+bool use_lists(const DevGrid& g, int n_ev, int64_t max_hits, int64_t hits);
 // Whether that fill takes its long-list variant (given g.rows).
 bool long_lists(const DevGrid& g, int64_t max_hits);
 size_t fill_lds_bytes(const DevGrid& g, bool long_l);
@@ -226,7 +226,7 @@ int pointer_kind(const void* ptr);
 int check_accessible(const void* ptr, const char* what);
 // Enqueues one event's stages on s: prep (counting into ev.slab_cnt and clearing
 // ev.slab_cnt_next), then the fill, then the peak search, as do_fill / do_peaks ask; `atomic`
-// takes the global-atomic fill and a candidate scan of the matrix. *counters_used is set once
+// takes the global-atomic fill and a scan of the matrix for survivors. *counters_used is set once
 // a kernel that uses the counter pair is on the stream (the caller then flips to the other
 // array for its next call). `timed` records the stage timers of ht_profile_enable.
 int enqueue_event(const DevGrid& g, const EvDesc& ev, int64_t n_hits, bool direct, bool atomic,
@@ -237,7 +237,7 @@ int validate_grid(const ht_grid* g);
 uint64_t n_cells(const ht_grid& g);
 // Validates the grid, uploads its tables once per device and picks the tiling.
 int make_device_grid(const ht_grid& g, int dev, int n_ev, int64_t max_hits, DevGrid* out);
-// The whole batched pipeline (prep, fill with candidates, peaks) for n_ev events whose
+// The whole batched pipeline (prep, fill with survivors, peaks) for n_ev events whose
 // descriptors are already in device memory.
 // *prep_enqueued is set once the preparation (which counts into and clears the events' counter
 // arrays) is on the stream.

@@ -1741,15 +1741,22 @@ bool long_lists(const DevGrid& g, int64_t max_hits)
   return g.rows <= 8 && g.finite_votes && max_hits * 3 > (int64_t)2 * kBlock * g.n_slabs;
 }
 
-bool use_lists(const DevGrid& g, int64_t max_hits, int64_t hits)
+bool use_lists(const DevGrid& g, int n_ev, int64_t max_hits, int64_t hits)
 {
-  if (long_lists(g, max_hits)) return false;
-  // The survivors expected must fit: on the paper grid 2.7k at 5000 hits, 46k at 14142, 661k at
-  // 40000; about as the cube of the hits per (slab, B) column, times the cells. The lists hold 65k.
   // The long-list fill makes none: with the code for them it spills registers (a 14142-hit event's
   // fill took 68 us, not 55, and its test 23 us, not 24).
-  const double ratio = 4.0 * (double)hits / ((double)g.n_slabs * g.n_b);
-  return ratio * ratio * ratio * (double)g.n_slabs * g.n_a * g.n_b <= 48e6;
+  if (long_lists(g, max_hits)) return false;
+  // Survivors come about as the cube of the hits per (slab, B) column, times the cells: on the paper
+  // grid 2.7k at 5000 hits, 46k at 14142, 661k at 40000. They must fit the lists, 65k. And where a
+  // job has several, the masks' test of a cell per lane is the faster one, once the launch is more
+  // than latency. Lists and masks, in us: seven events of 6585 hits on 4x16x256x256 134 and 85, two
+  // of them 58 and 46, one (18e6) 34 and 31; 16 of 4000 135 and 116; 20 of 2500 on 4x16x128x128 83
+  // and 64; 14 of 1139 on 4x4x130x259 (10e6) 39.5 and 43; one of 8000 on 4x16x512x512 (16e6) 39 and
+  // 42; twelve of 8000 on the paper grid (0.1 per cell) 569 and 619.
+  const double ratio = 4.0 * (double)hits / ((double)g.n_slabs * g.n_b), cube = ratio * ratio * ratio;
+  const double cells = (double)g.n_slabs * g.n_a * g.n_b;
+  if (cube > 0.5 && cube * cells * n_ev > 20e6) return false;
+  return cube * cells <= 48e6;
 }
 
 hipError_t launch_fill(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev,

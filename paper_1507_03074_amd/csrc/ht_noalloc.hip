@@ -151,7 +151,7 @@ extern "C" int ht_fill_peaks_noalloc(const ht_grid* grid, const float* x, const 
   std::memset(&ev, 0, sizeof(ev));
   carve_event_scratch(g, n_hits, direct, base + kEvOff, &ev, sliced ? 0 : layout);
   ev.dense = dense ? 1 : 0;
-  ev.lists = !sliced && !dense && (atomic || use_lists(g, n_hits, n_hits)) ? 1 : 0;
+  ev.lists = !sliced && !dense && (atomic || use_lists(g, 1, n_hits, n_hits)) ? 1 : 0;
   uint32_t* pair = (uint32_t*)base;
   ev.slab_cnt = pair + (g_parity[dev] ? kCounterWords : 0);
   ev.slab_cnt_next = pair + (g_parity[dev] ? 0 : kCounterWords);

@@ -140,7 +140,7 @@ int launch(ht_server* sv, Batch& b)
     // crowded events search their peaks with the stencil (the slot holds both layouts)
     d.dense = (sv->layout & kPeakMask) && dense_peaks(sv->g, r->n) ? 1 : 0;
     if (d.dense) clear_groups(sv->g, &d);
-    d.lists = !d.dense && (!sv->g.lds_fill || use_lists(sv->g, batch_max, r->n)) ? 1 : 0;
+    d.lists = !d.dense && (!sv->g.lds_fill || use_lists(sv->g, (int)b.reqs.size(), batch_max, r->n)) ? 1 : 0;
     any_bands = any_bands || !d.dense;
     any_dense = any_dense || d.dense;
     d.slab_cnt = sl.ctr + (sl.parity ? kCounterWords : 0);

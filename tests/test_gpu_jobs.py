@@ -232,3 +232,32 @@ def test_mask_groups_are_all_searched(B, shape):
             same_peaks(spec, (c, v, n), M, "one event")
     finally:
         B.ht_set_tuning(spec)
+
+
+def test_short_lists_with_masks_only(B):
+    """Batches whose survivors are many in a job and in all are searched from masks, though the fill
+    is the short-list one; with events of few hits, and each event alone, from the lists."""
+    from oracle import oracle
+    rng = np.random.default_rng(17)
+    spec = synth.GridSpec(4, 16, 256, 256, threshold=8)
+    og = oracle.OracleGrid(*spec.as_tuple())
+    evs = []
+    for n in (6585, 300, 5000):
+        ev = synth.make_hits(rng, n // 14, n - 12 * (n // 14))
+        evs.append((ev.x, ev.y, ev.z))
+    want = [oracle.fill(og, *h)[0] for h in evs]
+    B.ht_set_tuning(spec, dense_hits=-1)
+    try:
+        for pick in ([0, 1, 2], [1, 2]):
+            say("events", pick)
+            res = B.fill_peaks_batch(spec, [evs[i] for i in pick])
+            for k, i in enumerate(pick):
+                assert np.array_equal(B.as_u32(res.acc[k]), want[i]), i
+                same_peaks(spec, res.peaks[k], want[i], "event %d" % i)
+        for h, M in zip(evs, want):
+            say("one event of", len(h[0]))
+            acc, c, v, n = B.fill_peaks(spec, *B.hits_to_device(*h))
+            assert np.array_equal(B.as_u32(acc), M)
+            same_peaks(spec, (c, v, n), M, "one event")
+    finally:
+        B.ht_set_tuning(spec)
