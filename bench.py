@@ -157,7 +157,7 @@ def measure_peaks(B, torch, acc_bytes, big_bytes=2 << 30):
 
 
 def bench_batched(B, torch, synth, workload, n_events, reps, capacity, tune_batch=False):
-    """One ht_fill_peaks_batch call (a captured graph) over n_events events of the workload;
+    """One ht_fill_peaks_batch call over n_events events of the workload;
     with tune_batch, the launch shape comes from the autotuner run on another batch of the same
     workload (events n_events .. 2 n_events - 1, kept apart from the timed ones), and the grid's
     previous shape is restored afterwards."""
@@ -187,7 +187,7 @@ def bench_batched(B, torch, synth, workload, n_events, reps, capacity, tune_batc
     B.ht_fill_peaks_batch(spec, events, x, y, z, acc, out, nf)
     torch.cuda.synchronize()
     votes = int(acc.sum(dtype=torch.int64).item())
-    # two untimed batches after the first (which captures the graph), so the timed ones start
+    # two untimed batches after the first (which allocates the scratch), so the timed ones start
     # from a running GPU
     for _ in range(2):
         B.ht_fill_peaks_batch(spec, events, x, y, z, acc, out, nf)
@@ -546,7 +546,7 @@ def ctypes_stream(stream):
 def bench_crowded(B, torch, synth, steps, tuning=None):
     """Stage times on the smallest, median and largest of 40 events of workload 3 (lognormal
     5k-40k hits on the paper grid), at the given launch shape or the library's default. The
-    largest event pools 2.6M candidates, so its peak stage runs the many-candidate test."""
+    largest event has 0.66M survivors, so its peak stage runs the test from masks."""
     spec = synth.WORKLOADS[3].grid
     if tuning:
         B.ht_set_tuning(spec, B.Tuning(*[int(v) for v in tuning.split(",")]))
@@ -576,7 +576,7 @@ def bench_crowded(B, torch, synth, steps, tuning=None):
 
 def bench_crossover(B, torch, synth, steps):
     """The whole fused call (prep, fill, peak search) on served-stream events of 6k-40k hits
-    (workload 3, paper grid), once with every event's peaks from the candidate pool and once
+    (workload 3, paper grid), once with every event's peaks from the fill's survivors and once
     from the stencil over the matrix: where the library's default threshold between the two
     comes from. Peak counts must agree."""
     import os
@@ -644,10 +644,10 @@ def main():
                          "(workload 3) at the --tuning shape or the default; prints one line")
     ap.add_argument("--crossover", action="store_true",
                     help="time the fused call on served-stream events of 6k-40k hits with the "
-                         "candidate pool and with the stencil peak search; prints one line")
+                         "fill's survivors and with the stencil peak search; prints one line")
     ap.add_argument("--only", choices=("batched", "stress", "served"),
                     help="one workload only, for profiles: the batched workload 2 (100 events, "
-                         "one graph launch) or the stress workload 4 (16 events) at the launch "
+                         "one call) or the stress workload 4 (16 events) at the launch "
                          "shape the batch autotuner picks, --steps capped at 10 batches; or the "
                          "served workload 3 at its saturation rate (1200 events); prints one "
                          "line")
