@@ -442,7 +442,7 @@ size_t event_scratch_bytes(const DevGrid& g, int64_t n, bool direct, int peaks)
   }
   if (peaks) b += al(4 * group_words(g, peaks));  // group_pk
   if (peaks & kPeakBands) {
-    b += al(4 * (((size_t)g.j.n_groups + 63) / 64)) + al(g.j.n_jobs);  // super_pk, job_any
+    b += al(4 * kSuperStep * (((size_t)g.j.n_groups + 63) / 64)) + al(g.j.n_jobs);  // super_pk, job_any
     b += al(16 * (size_t)kLists * kListCap);                              // surv
     b += al((size_t)64 * g.j.elem_bytes * g.j.n_jobs);                 // masks
     b += al(8 * (size_t)g.j.seg * g.j.n_groups);                       // seg
@@ -488,7 +488,7 @@ void carve_peak_scratch(const DevGrid& g, char* p, EvDesc* ev, int peaks, uint32
   ev->n_grp = n_grp;
   ev->clear_n16 = 0;
   ev->lists = 0;
-  if (peaks & kPeakBands) ev->super_pk = (uint32_t*)take(4 * (((size_t)n_grp + 63) / 64));
+  if (peaks & kPeakBands) ev->super_pk = (uint32_t*)take(4 * kSuperStep * (((size_t)n_grp + 63) / 64));
   if (peaks) ev->group_pk = (uint32_t*)take(4 * group_words(g, peaks));
   if (peaks & kPeakBands) {
     ev->job_any = (uint8_t*)take(n);

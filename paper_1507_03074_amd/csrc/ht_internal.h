@@ -52,6 +52,7 @@ struct JobGeom {
   uint32_t n_jobs, n_groups;
 };
 constexpr uint32_t kSegMax = 1024;
+constexpr uint32_t kSuperStep = 32;  // words: a cache line each
 // Few peaks: at most this many cells can reach the threshold (each of the lists holds as many).
 constexpr uint32_t kFewCells = 8192;
 static_assert(kFewCells <= kListCap, "no list overflows where so few cells reach the threshold");
@@ -107,7 +108,7 @@ struct EvDesc {
   // except where a caller's fixed scratch holds only a slice at a time
   uint32_t grp0, n_grp;
   uint32_t* group_pk;   // peaks per group of jobs, g.j.pk_step words apart (or [groups of tiles]: stencil)
-  uint32_t* super_pk;   // [n_grp / 64, rounded up] peaks per 64 groups
+  uint32_t* super_pk;   // [n_grp / 64, rounded up] peaks per 64 groups, kSuperStep words apart
   uint8_t* job_any;     // [jobs] 1: the job has survivors (its masks are valid)
   uint8_t* masks;       // [jobs][64 lanes] mask elements; jobs without the flag are not written
   uint2* seg;           // [n_grp][g.j.seg] each group's peaks (cell, votes)

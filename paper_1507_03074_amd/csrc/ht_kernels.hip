@@ -406,7 +406,7 @@ __global__ __launch_bounds__(kBlock) void k_scan(DevGrid g, EvDesc ev0, const Ev
   const uint32_t nb = (uint32_t)g.n_b, units = (uint32_t)g.j.units, P = (uint32_t)g.j.sub;
   for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < e.n_grp; i += gridDim.x * kBlock) {
     gp(e.group_pk)[i * (uint32_t)g.j.pk_step] = 0u;
-    if (i < (e.n_grp + 63u) / 64u) gp(e.super_pk)[i] = 0u;
+    if (i < (e.n_grp + 63u) / 64u) gp(e.super_pk)[i * kSuperStep] = 0u;
   }
   if (counters)  // uniform
     for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < (uint32_t)kCounterWords; i += gridDim.x * kBlock)
@@ -615,7 +615,7 @@ __device__ __forceinline__ void tile_range(const DevGrid& g, int tile, uint32_t*
 // groups whose peaks do not fit it.
 constexpr uint32_t kList = 1024;  // four jobs have at most this many survivors (one per 2 x 2 cells)
 constexpr uint32_t kFew = 64;
-constexpr uint32_t kSuperGroups = 2048;
+constexpr uint32_t kSuperGroups = 8192;
 constexpr uint32_t kTestBlocks = 4 * kLists * 32 / kBlock;
 constexpr uint32_t kTestGrid = 8192;
 constexpr uint32_t kPassJobs = 64;
@@ -674,7 +674,7 @@ __global__ __launch_bounds__(kBlock) void k_peak_test(DevGrid g, EvDesc ev0, con
           const uint32_t hm = (uint32_t)(__builtin_amdgcn_ballot_w64(beaten[q]) >> (lane & 32u));
           if (k == 0u && hm == 0u) {
             const uint32_t o = gatomic_add(e.group_pk + en[q].z * (uint32_t)g.j.pk_step, 1u);
-            if (supers) gatomic_add(e.super_pk + en[q].z / 64u, 1u);
+            if (supers) gatomic_add(e.super_pk + en[q].z / 64u * kSuperStep, 1u);
             const u32x2 pk = {en[q].x, en[q].y};
             if (o < seg_cap) ((GLOBAL u32x2*)gp(e.seg))[(size_t)en[q].z * seg_cap + o] = pk;
           }
@@ -854,7 +854,7 @@ __global__ __launch_bounds__(kBlock) void k_peak_test(DevGrid g, EvDesc ev0, con
     const uint32_t n = s_np;
     if (threadIdx.x == 0) {
       gp(e.group_pk)[grp * (uint32_t)g.j.pk_step] = n;
-      if (n && supers) gatomic_add(e.super_pk + grp / 64u, n);
+      if (n && supers) gatomic_add(e.super_pk + grp / 64u * kSuperStep, n);
     }
     if (n == 0u || n > seg_cap) {  // uniform
       lds_barrier();
@@ -950,9 +950,10 @@ __global__ __launch_bounds__(1024) void k_few_peaks(DevGrid g, EvDesc ev0, const
 // Ordered peak list, one wave per group: its output offset is the sum of the earlier groups'
 // counts (a workgroup's four waves share it: with 2048 groups a wave of its own took 6.2 us, four
 // together 4.7), loaded together with its first 64 peaks, so an ordinary group is one memory
-// round trip. Past kSuperGroups groups the counts are also kept per block of 64 groups (not
-// below: the atomic additions of a test to one cache line take 10 ns each, which cost 9 us on the
-// paper event). Peaks found from the lists are in no order in their segment: each lane ranks its
+// round trip. Past kSuperGroups groups the counts are also kept per block of 64 groups, a cache line
+// each (not below: a test's atomic additions to one cache line take 10 ns each, which cost 9 us on the
+// paper event, and 80 us of a 23k-hit event's test on 7x29x573x923 cells, 3654 groups). Peaks found
+// from the lists are in no order in their segment: each lane ranks its
 // own among the group's. A group with more peaks than its segment holds is listed from its masks
 // in LDS, in cell order (whole job rows: band by band, row by row, strip by strip, then lane and
 // column), up to eight jobs' masks in flight; masks that the lists replaced still hold survivors,
@@ -981,7 +982,7 @@ __global__ __launch_bounds__(kBlock) void k_peak_write(DevGrid g, EvDesc ev0, co
   const uint32_t s0 = e.n_grp > kSuperGroups ? G0 & ~63u : 0u;         // groups before s0: by their blocks
   const uint32_t own = G0 + lane < e.n_grp && lane < kBlock / 64 ? gp(e.group_pk)[(G0 + lane) * ps] : 0u;
   uint32_t part = 0u;
-  for (uint32_t i = threadIdx.x; i < s0 / 64u; i += kBlock) part += gp(e.super_pk)[i];
+  for (uint32_t i = threadIdx.x; i < s0 / 64u; i += kBlock) part += gp(e.super_pk)[i * kSuperStep];
   for (uint32_t i0 = s0; i0 < G0; i0 += 8u * kBlock) {  // uniform; eight loads in flight
     uint32_t x[8];
 #pragma unroll

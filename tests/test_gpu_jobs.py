@@ -261,3 +261,20 @@ def test_short_lists_with_masks_only(B):
             same_peaks(spec, (c, v, n), M, "one event")
     finally:
         B.ht_set_tuning(spec)
+
+
+@pytest.mark.parametrize("n_hits", [9000, 30000])  # survivors from lists, from masks
+def test_counts_per_block_of_groups(B, n_hits):
+    """Past 8192 groups of jobs the ordered write takes its offsets from counts per 64 groups."""
+    import torch
+    from oracle import oracle
+    rng = np.random.default_rng(n_hits)
+    spec = synth.GridSpec(8, 32, 2100, 258, threshold=8)
+    ev = synth.make_hits(rng, n_hits // 14, n_hits - 12 * (n_hits // 14))
+    M, _ = oracle.fill(oracle.OracleGrid(*spec.as_tuple()), ev.x, ev.y, ev.z)
+    x, y, z = B.hits_to_device(ev.x, ev.y, ev.z)
+    for k in range(2):
+        say("hits", n_hits, "call", k)
+        acc, c, v, n = B.fill_peaks(spec, x, y, z)
+        same_peaks(spec, (c, v, n), M, "fill_peaks")
+        same_peaks(spec, B.peaks(spec, acc), M, "peaks of the matrix")
