@@ -296,12 +296,19 @@ static void shape_launch(DevGrid* d, const Tiling& tl, int n_ev, int64_t max_hit
     // 512x512 planes: 54.6 us with eight rows, 64.8 with sixteen, which go to the other fill).
     // Short ones: tiles of 16 KiB, twice the workgroups per CU (paper event, 4 against 8 rows: 62.3
     // and 66.5 us; at 512 and 256 columns the 16 KiB tile is the fastest of three as well), but
-    // four rows, a whole band. Launches of fewer tiles than the chip has CUs take lower ones (250
-    // hits on 4x16x64x64: 17.0 us with 16 rows, 17.8 with 64; a hundred such events: 85 and 64).
+    // four rows, a whole band. Launches of fewer tiles than the chip has CUs take lower ones (a
+    // hundred events of 250 hits on 4x16x64x64: 64 rows, 64 us, 16 rows 85).
+    // Where 16 KiB hold more than eight rows, eight of them are a small tile for a long list, which
+    // large launches pay for more often: whole calls, eight rows and 16 KiB, in us: 30k hits on
+    // 4x16x1024x256 (8192 tiles of eight rows) 73 and 75, 18k on 4x16x256x256 (2048) 40 and 44, forty
+    // events of 4000-8000 on 2x8x200x100 (16000) 109 and 100, 41k hits on 8x27x1604x100 (43k) 288 and
+    // 214, eight events of 15k on 4x16x1024x256 (65k) 449 and 314.
+    int low = rows;
+    while (low > 4 && (int64_t)low * d->n_b * 4 > 16384) low /= 2;
+    const bool many = (int64_t)d->n_slabs * ((d->n_a + 7) / 8) * n_ev > 10000;
     d->rows = std::min(rows, 8);
-    if (!long_lists(*d, max_hits)) {
-      d->rows = rows;
-      while (d->rows > 4 && (int64_t)d->rows * d->n_b * 4 > 16384) d->rows /= 2;
+    if ((low > 8 && many) || !long_lists(*d, max_hits)) {
+      d->rows = low;
       while (d->rows > 8 && (int64_t)d->n_slabs * ((d->n_a + d->rows - 1) / d->rows) * n_ev < 256) d->rows /= 2;
     }
     d->tiles_per_slab = (d->n_a + d->rows - 1) / d->rows;
@@ -351,7 +358,9 @@ DevGrid make_devgrid(const ht_grid& g, const DevTables& t, const Tiling& tl, int
                    std::isfinite((float)((double)g.n_b / ((double)g.b_max - (double)g.b_min))) ? 1 : 0;
   d.dense_w = tl.dense_w;
   d.dense_rows = tl.dense_rows;
-  d.dense_hits = tl.dense_from;
+  // A batch that has the stencil's launches anyway takes it for its events from the reported
+  // threshold on (six events of 3050-15250 hits on 4x16x532x171, both searches: 145 us)
+  d.dense_hits = n_ev > 1 && tl.dense_from > 0 && max_hits >= tl.dense_from ? tl.dense_hits : tl.dense_from;
   d.a2 = t.a2;
   d.phi_cs = t.phi;
   d.th_cs = t.th;

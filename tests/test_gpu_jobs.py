@@ -278,3 +278,23 @@ def test_counts_per_block_of_groups(B, n_hits):
         acc, c, v, n = B.fill_peaks(spec, x, y, z)
         same_peaks(spec, (c, v, n), M, "fill_peaks")
         same_peaks(spec, B.peaks(spec, acc), M, "peaks of the matrix")
+
+
+def test_large_batches_of_narrow_rows_and_mixed_searches(B):
+    """Many tiles of long lists on rows of 256 columns take 16 KiB tiles; a batch with a crowded event
+    searches those of its events with the stencil that reach the reported threshold (2048 hits)."""
+    from oracle import oracle
+    rng = np.random.default_rng(23)
+    spec = synth.GridSpec(4, 8, 256, 256)
+    og = oracle.OracleGrid(*spec.as_tuple())
+    evs = []
+    for n in (8000, 5000, 3000, 300):
+        ev = synth.make_hits(rng, n // 14, n - 12 * (n // 14))
+        evs.append((ev.x, ev.y, ev.z))
+    want = [oracle.fill(og, *h)[0] for h in evs]
+    for pick in ([0, 1, 2, 3] * 4, [2, 3] * 8, [0, 3]):
+        say("events", len(pick))
+        res = B.fill_peaks_batch(spec, [evs[i] for i in pick])
+        for k, i in enumerate(pick):
+            assert np.array_equal(B.as_u32(res.acc[k]), want[i]), (k, i)
+            same_peaks(spec, res.peaks[k], want[i], "event %d" % i)
