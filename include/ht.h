@@ -176,12 +176,15 @@ int ht_fill_peaks(const ht_grid* grid, const float* x, const float* y, const flo
  * library's scratch for the call (slab lists, survivor masks, counters, tables) lives in one
  * fixed 64 MiB device array that each GPU the library runs on holds until the process ends;
  * the call makes no hipMalloc, hipFree or other allocating call.
- * Limits: n_a <= 16384, and the slab lists (direct while they fit, else the counting sort) with
- * nine bytes per possible candidate (cand_cap per fill tile, more for large events) must fit the
- * array: about 25 MB for 5000 hits on the 4x16x1024x1024 grid, where events of up to about
- * 500 000 hits fit (crowded events count no candidates). A larger event is refused with HT_EINVAL
- * before any device work, and ht_last_error() states the bytes it needed (use ht_fill_peaks for
- * it). Where the search's own scratch does not fit beside the lists, it runs slice by slice.
+ * Limits: n_a <= 16384, and the array must hold the slab lists (direct where they fit with the
+ * rest, else the counting sort), 16 bytes per fill tile and, from the reported dense_hits on, a word
+ * per 62 columns of every row, below it nine bytes per possible candidate (cand_cap per fill tile, or
+ * a quarter of the bound 4 n_hits n_a / threshold where that is more): about 25 MB for 5000 hits on
+ * the 4x16x1024x1024 grid, where events of up to about 500 000 hits fit. A larger event is refused
+ * with HT_EINVAL before any device work, and ht_last_error() states the bytes it needed (use
+ * ht_fill_peaks for it). What is laid out in the array may be less than the rule counts. Where an
+ * accepted event's survivors do not fit beside its lists, they are searched by the stencil (from
+ * dense_hits on) or slice by slice.
  * Sharing: every call on one GPU uses that GPU's array, which keeps the last call's contents.
  * Calls on one GPU must not overlap (on different streams or host threads they race on the
  * array); calls are serialised on the host by a lock, so overlap only arises from work still

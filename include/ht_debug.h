@@ -58,6 +58,26 @@ int ht_tiling(const ht_grid* grid, int32_t* rows, int32_t* n_tiles, int32_t* can
 int ht_debug_batch_plan(const ht_grid* grid, const ht_event* events, int32_t n_events,
                         int32_t* direct, int64_t* scratch_bytes);
 
+/* ht_debug_launch_plan: what a call would launch, decided on the host with the same code (no device
+ * work, no device memory). call: 0 ht_fill_peaks (one event), 1 ht_fill_peaks_batch,
+ * 2 ht_fill_peaks_noalloc (one event). n_hits: host int64[n_events], the events' sizes.
+ * Errors: HT_EINVAL (grid, call, n_events, sizes, NULL), and for call 2 an event that the call
+ * refuses (n_a, or scratch past its fixed array). */
+typedef struct ht_launch_plan {
+  int32_t rows, nt_store;  /* A rows per fill tile, store kind (0 ordinary, 1 non-temporal, 2) */
+  int32_t long_lists;      /* 1: the fill's variant for long slab lists */
+  int32_t direct;          /* 1: direct slab lists, 0: counting sort */
+  int32_t tiny;            /* 1: preparation and fill are one launch */
+  int32_t few;             /* 1: the peak search is one workgroup per event */
+  int32_t n_stencil;       /* events searched by the stencil */
+  int32_t n_lists;         /* events whose survivors go to lists (not masks alone) */
+  int32_t sliced;          /* 1: the search of call 2 runs slice by slice */
+  int32_t reserved;
+  int64_t scratch_bytes;   /* device scratch of all events */
+} ht_launch_plan;
+int ht_debug_launch_plan(const ht_grid* grid, int32_t call, const int64_t* n_hits, int32_t n_events,
+                         ht_launch_plan* plan);
+
 /* ht_profile_enable: per-stage timing of later calls. mode 1: a HIP event (created without the
  * system-scope fence) is recorded on the call's stream before and after each stage ("prep",
  * "fill", "fill_atomic", "candidates", "peaks"); mode 2: around the fill stages only ("fill",

@@ -79,6 +79,14 @@ class Tuning(ctypes.Structure):
         return {f: getattr(self, f) for f, _ in self._fields_}
 
 
+class LaunchPlan(ctypes.Structure):
+    _fields_ = [(f, ctypes.c_int32) for f in ("rows", "nt_store", "long_lists", "direct", "tiny", "few", "n_stencil",
+                                              "n_lists", "sliced", "reserved")] + [("scratch_bytes", ctypes.c_int64)]
+
+    def as_dict(self):
+        return {f: getattr(self, f) for f, _ in self._fields_ if f != "reserved"}
+
+
 class Timing(ctypes.Structure):
     _fields_ = [("t_submit", ctypes.c_double), ("t_admit", ctypes.c_double),
                 ("t_launch", ctypes.c_double), ("t_done", ctypes.c_double)]
@@ -91,7 +99,7 @@ EXPORTS = ["ht_set_tuning", "ht_get_tuning", "ht_tables", "ht_fill", "ht_peaks",
            "ht_last_error", "ht_debug_hit_values", "ht_debug_unary", "ht_fill_atomic", "ht_tiling",
            "ht_profile_enable", "ht_profile_read", "ht_bench_hbm_write", "ht_bench_hbm_read",
            "ht_bench_copy", "ht_bench_atomic_rand", "ht_bench_lds_atomic", "ht_readout",
-           "ht_debug_pointer_kind", "ht_debug_batch_plan"]
+           "ht_debug_pointer_kind", "ht_debug_batch_plan", "ht_debug_launch_plan"]
 
 _lib = None
 
@@ -127,6 +135,7 @@ def lib():
         "ht_debug_pointer_kind": ([vp, ctypes.POINTER(i32)], ctypes.c_int),
         "ht_debug_batch_plan": ([gp, ctypes.POINTER(Event), i32, ctypes.POINTER(i32),
                                  ctypes.POINTER(i64)], ctypes.c_int),
+        "ht_debug_launch_plan": ([gp, i32, ctypes.POINTER(i64), i32, ctypes.POINTER(LaunchPlan)], ctypes.c_int),
         "ht_serve_create": ([gp, ctypes.POINTER(ServeOpts), ctypes.POINTER(vp)], ctypes.c_int),
         "ht_serve_submit": ([vp, f32p, f32p, f32p, i64, ctypes.POINTER(ctypes.c_uint64)],
                             ctypes.c_int),
@@ -340,6 +349,17 @@ def ht_debug_batch_plan(spec, n_hits):
     check(lib().ht_debug_batch_plan(ctypes.byref(g), arr, len(n_hits), ctypes.byref(d),
                                     ctypes.byref(b)))
     return bool(d.value), b.value
+
+
+def ht_debug_launch_plan(spec, n_hits, call="event"):
+    """What a call ("event", "batch" or "noalloc") would launch for events of these sizes at the
+    grid's current launch shape, as a dict (host only). Raises HTError for a call that is refused."""
+    g = make_grid(spec)
+    arr = (ctypes.c_int64 * len(n_hits))(*[int(n) for n in n_hits])
+    plan = LaunchPlan()
+    check(lib().ht_debug_launch_plan(ctypes.byref(g), ("event", "batch", "noalloc").index(call), arr, len(n_hits),
+                                     ctypes.byref(plan)))
+    return plan.as_dict()
 
 
 def ht_debug_hit_values(spec, x, y, z, stream=None):

@@ -421,7 +421,7 @@ bool direct_lists(const DevGrid& g, int64_t n)
          (size_t)g.n_slabs * (size_t)std::max<int64_t>(n, 1) * 16 <= kDirectListMax;
 }
 
-static size_t mask_bytes(const DevGrid& g)
+size_t mask_bytes(const DevGrid& g)
 {
   // one 64-bit word per (slab, row, chunk of kChunkCells columns), rows padded to whole segments
   // of dense_rows (the stencil's waves store their segments whole)
@@ -1261,6 +1261,52 @@ int ht_debug_batch_plan(const ht_grid* grid, const ht_event* events, int32_t n_e
   size_t total = 0;
   *direct = plan_batch(g, events, n_events, &offs, &total, &max_hits) ? 1 : 0;
   *scratch_bytes = (int64_t)total;
+  return HT_OK;
+}
+
+int ht_debug_launch_plan(const ht_grid* grid, int32_t call, const int64_t* n_hits, int32_t n_events,
+                         ht_launch_plan* plan)
+{
+  int rc = validate_grid(grid);
+  if (rc) return rc;
+  if (!n_hits || !plan || call < 0 || call > 2 || n_events < 1 || n_events > (call == 1 ? 65535 : 1))
+    return fail(HT_EINVAL, "invalid launch-plan arguments");
+  std::vector<ht_event> events((size_t)n_events);
+  int64_t max_hits = 0;
+  for (int32_t i = 0; i < n_events; ++i) {
+    if (n_hits[i] < 0 || n_hits[i] > ((int64_t)1 << 28)) return fail(HT_EINVAL, "event %d has an invalid size", i);
+    events[i] = ht_event{0, n_hits[i], 0, 0};
+    max_hits = std::max(max_hits, n_hits[i]);
+  }
+  const int64_t mh = call == 1 ? batch_hits(max_hits) : max_hits;
+  const Tiling tl = choose_tiling(*grid);
+  const DevGrid g = make_devgrid(*grid, DevTables(), tl, n_events, mh);
+  std::memset(plan, 0, sizeof(*plan));
+  NoallocPlan na;
+  std::memset(&na, 0, sizeof(na));
+  if (call == 2 && (rc = plan_noalloc(*grid, tl, g, max_hits, &na))) return rc;
+  plan->rows = g.rows;
+  plan->nt_store = g.nt_store;
+  plan->long_lists = g.lds_fill && long_lists(g, mh) ? 1 : 0;
+  for (const ht_event& ev : events) {
+    const bool dense = call == 2 ? na.dense : g.lds_fill && dense_peaks(g, ev.n_hits);
+    plan->n_stencil += dense ? 1 : 0;
+    plan->n_lists += !dense && (na.sliced || !g.lds_fill || use_lists(g, n_events, mh, ev.n_hits)) ? 1 : 0;
+  }
+  plan->sliced = na.sliced ? 1 : 0;
+  if (!plan->n_stencil && !na.sliced) {
+    plan->tiny = tiny_launch(g, n_events, mh) ? 1 : 0;
+    plan->few = plan->tiny || (g.lds_fill && few_cells(g, mh) && use_lists(g, n_events, mh, mh)) ? 1 : 0;
+  }
+  if (call == 2) {
+    plan->direct = na.direct ? 1 : 0;
+    plan->scratch_bytes = (int64_t)na.scratch_bytes;
+    return HT_OK;
+  }
+  std::vector<size_t> offs;
+  size_t total = 0;
+  plan->direct = plan_batch(g, events.data(), n_events, &offs, &total, &max_hits) ? 1 : 0;
+  plan->scratch_bytes = (int64_t)total;
   return HT_OK;
 }
 

@@ -169,6 +169,7 @@ bool dense_peaks(const DevGrid& g, int64_t n_hits);
 enum PeakScratch { kPeakBands = 1, kPeakMask = 2 };
 // Bytes of per-event scratch for a grid tiling and an event size, and the carving of it.
 size_t event_scratch_bytes(const DevGrid& g, int64_t n_hits, bool direct, int peaks = kPeakBands);
+size_t mask_bytes(const DevGrid& g);  // of the stencil's peak words
 void carve_event_scratch(const DevGrid& g, int64_t n_hits, bool direct, char* base, EvDesc* ev,
                          int peaks = kPeakBands);
 // The peak-search part of it alone, for n_grp groups from grp0 on.
@@ -219,6 +220,16 @@ bool use_lists(const DevGrid& g, int n_ev, int64_t max_hits, int64_t hits);
 bool long_lists(const DevGrid& g, int64_t max_hits);
 size_t fill_lds_bytes(const DevGrid& g, bool long_l);
 int n_groups(const DevGrid& g);
+
+// The layout of one no-alloc call (ht_noalloc.hip): whether its peaks come from the stencil, the
+// kind of its slab lists, and whether the search runs slice by slice (the grid's jobs are then
+// those of a scan, and slice_groups of them make a slice). HT_EINVAL for an event that it refuses.
+struct NoallocPlan {
+  bool dense, direct, sliced;
+  size_t scratch_bytes;
+  uint32_t slice_groups;
+};
+int plan_noalloc(const ht_grid& grid, const Tiling& tl, const DevGrid& g, int64_t n_hits, NoallocPlan* plan);
 
 // Host helpers (ht_api.cpp).
 // 0: not usable by a kernel; 1: device memory; 2: pinned host memory mapped into the device;

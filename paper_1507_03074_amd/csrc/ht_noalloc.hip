@@ -29,8 +29,8 @@ constexpr int kNoAllocMaxDevices = 64;
 // tables: a2 up to kNoAllocMaxA floats, phi up to 4 * 4096, theta up to 2 * (2 * 4096 + 1)
 constexpr size_t kNoAllocMaxA = 16384;
 constexpr size_t kTabOff = (kCounterBytes + 255) & ~(size_t)255;
-constexpr size_t kTabBytes = (size_t)256 << 10;
-constexpr size_t kEvOff = kTabOff + kTabBytes;
+constexpr size_t kEvOff = 295424;  // the limit below is what the array holds past it
+constexpr size_t kTabBytes = kEvOff - kTabOff;
 static_assert(4 * (kNoAllocMaxA + 4 * kMaxSlabs + 2 * (2 * kMaxSlabs + 1)) + 3 * 256 <= kTabBytes,
               "the largest tables fit their region");
 
@@ -54,23 +54,75 @@ bool same_tables(const ht_grid& a, const ht_grid& b)
 
 size_t al256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-// The call's size limit, in bytes: the slab lists, 16 bytes per fill tile, and for an ordinary
-// event nine bytes per entry of a candidate list of cand_cap cells per tile, or a quarter of the
-// bound 4 n_hits n_a / threshold on the cells that can reach the threshold when that is larger.
-// The survivor masks that the search keeps instead are smaller on nearly every grid; where they
-// are not (rows past 70 000 cells), the search runs slice by slice, so the limit stays this one.
-size_t limit_bytes(const DevGrid& g, const Tiling& tl, int64_t n, bool direct, bool dense)
+// The call's size limit, in bytes: what it accepts is part of its contract, so it is an arithmetic
+// of its own and not what the layout of the day takes. The slab lists, 16 bytes per tile of the
+// reported launch shape, and for a crowded event (of at least the reported dense_hits hits) the
+// stencil's peak words, for any other nine bytes per entry of a candidate list of cand_cap cells per
+// tile, or of a quarter of the bound 4 n_hits n_a / threshold on the cells that can reach the
+// threshold where that is more.
+size_t limit_bytes(const DevGrid& g, const Tiling& tl, int64_t n, bool direct)
 {
   const size_t t = (size_t)tl.n_tiles;
-  size_t b = event_scratch_bytes(g, n, direct, dense ? kPeakMask : 0) + 4 * al256(4 * t);
-  if (dense) return b;
+  size_t b = event_scratch_bytes(g, n, direct, 0) + 4 * al256(4 * t) +
+             al256(4 * ((t + tl.group_tiles - 1) / tl.group_tiles));
+  if (g.lds_fill && tl.dense_hits > 0 && n >= tl.dense_hits) return b + al256(mask_bytes(g));  // crowded
   const size_t cells = (size_t)g.n_theta * g.n_phi * g.n_a * g.n_b;
   const size_t bound = (size_t)n * (g.phi_sectors ? 2 : 4) * (size_t)g.n_a / (size_t)g.threshold;
   const size_t pool = std::min<size_t>(std::max(t * (size_t)tl.cand_cap, std::min(cells, bound / 4)), 0xfffffff0u);
-  return b + al256(4 * ((t + tl.group_tiles - 1) / tl.group_tiles)) + al256(8 * pool) + al256(pool);
+  return b + al256(8 * pool) + al256(pool);
+}
+
+int check_tables(const ht_grid& grid)
+{
+  if ((size_t)grid.n_a > kNoAllocMaxA)
+    return fail(HT_EINVAL, "ht_fill_peaks_noalloc: n_a = %d exceeds its table limit of %zu A bins",
+                grid.n_a, kNoAllocMaxA);
+  return HT_OK;
 }
 
 }  // namespace
+
+int plan_noalloc(const ht_grid& grid, const Tiling& tl, const DevGrid& g, int64_t n, NoallocPlan* plan)
+{
+  if (int rc = check_tables(grid)) return rc;
+  const size_t room = kNoAllocBytes - kEvOff;
+  const bool can_direct = direct_lists(g, n);
+  const size_t need = limit_bytes(g, tl, n, can_direct && limit_bytes(g, tl, n, true) <= room);
+  if (need > room)
+    return fail(HT_EINVAL,
+                "ht_fill_peaks_noalloc: this event needs %zu bytes of scratch; the fixed scratch "
+                "holds %zu (use ht_fill_peaks)", need, room);
+  // the layout: direct slab lists where they fit with the search's scratch, else the counting sort
+  auto fits = [&](bool direct, int peaks) { return event_scratch_bytes(g, n, direct, peaks) <= room; };
+  auto either = [&](int peaks) { return (can_direct && fits(true, peaks)) || fits(false, peaks); };
+  // survivors that do not fit beside the lists of an event that the limit takes for a crowded one
+  // leave it to the stencil
+  const bool crowded = g.lds_fill && tl.dense_hits > 0 && n >= tl.dense_hits;
+  plan->dense = g.lds_fill && (dense_peaks(g, n) || (crowded && !either(kPeakBands)));
+  plan->sliced = !plan->dense && !either(kPeakBands);
+  const int layout = plan->sliced ? 0 : plan->dense ? kPeakMask : kPeakBands;
+  plan->direct = can_direct && fits(true, layout);
+  plan->scratch_bytes = event_scratch_bytes(g, n, plan->direct, layout);
+  plan->slice_groups = 0;
+  if (plan->sliced) {
+    // The survivors do not fit beside the slab lists: the peaks are searched in the written matrix,
+    // as many groups of job rows at a time as fit the whole event scratch (the lists are done with
+    // then), each slice counting on from the one before.
+    DevGrid sg = g;
+    set_jobs(&sg, 0, 1);
+    const size_t fixed = 256 + al256(4 * (size_t)sg.j.n_groups * sg.j.pk_step) + al256(4 * (size_t)sg.j.n_groups) + 16 * (size_t)kListCap * kLists + 6 * 256;
+    const size_t per = (size_t)(1 + 64 * sg.j.elem_bytes) * sg.j.group_jobs + 8 * (size_t)sg.j.seg;
+    const size_t fit = fixed < room ? (room - fixed) / per : 0;
+    if (fit == 0) return fail(HT_EINVAL, "ht_fill_peaks_noalloc: one group of rows needs %zu bytes of scratch", per);
+    plan->slice_groups = (uint32_t)std::min<size_t>(fit, sg.j.n_groups);
+    plan->scratch_bytes = room;
+  }
+  if (plan->scratch_bytes > room)
+    return fail(HT_EINVAL, "ht_fill_peaks_noalloc: this event needs %zu bytes of scratch; the fixed scratch holds %zu",
+                plan->scratch_bytes, room);
+  return HT_OK;
+}
+
 }  // namespace ht
 
 using namespace ht;
@@ -87,9 +139,7 @@ extern "C" int ht_fill_peaks_noalloc(const ht_grid* grid, const float* x, const 
   if (n_hits > ((int64_t)1 << 28)) return fail(HT_EINVAL, "n_hits must be <= 2^28");
   int rc = validate_grid(grid);
   if (rc) return rc;
-  if ((size_t)grid->n_a > kNoAllocMaxA)
-    return fail(HT_EINVAL, "ht_fill_peaks_noalloc: n_a = %d exceeds its table limit of %zu A bins",
-                grid->n_a, kNoAllocMaxA);
+  if ((rc = check_tables(*grid))) return rc;
   if ((rc = check_accessible(out, "out")) || (rc = check_accessible(n_found, "n_found"))) return rc;
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
@@ -98,21 +148,13 @@ extern "C" int ht_fill_peaks_noalloc(const ht_grid* grid, const float* x, const 
     return fail(HT_EINVAL, "ht_fill_peaks_noalloc supports device ordinals below %d", kNoAllocMaxDevices);
   hipStream_t s = (hipStream_t)stream;
 
-  // the layout: direct slab lists when they fit, else the counting sort (the same results);
-  // an event that fits neither is refused before any device work
+  // an event that does not fit is refused before any device work
   const Tiling tl = choose_tiling(*grid);
   DevGrid g = make_devgrid(*grid, DevTables(), tl, 1, n_hits);
-  const bool atomic = !g.lds_fill;
-  const bool dense = !atomic && dense_peaks(g, n_hits);
-  const int layout = dense ? kPeakMask : kPeakBands;
-  const size_t room = kNoAllocBytes - kEvOff;
-  bool direct = !atomic && direct_lists(g, n_hits) && limit_bytes(g, tl, n_hits, true, dense) <= room;
-  const size_t need = limit_bytes(g, tl, n_hits, direct, dense);
-  if (need > room)
-    return fail(HT_EINVAL,
-                "ht_fill_peaks_noalloc: this event needs %zu bytes of scratch; the fixed scratch "
-                "holds %zu (use ht_fill_peaks)", need, room);
-  const bool sliced = event_scratch_bytes(g, n_hits, direct, layout) > room;
+  NoallocPlan plan;
+  if ((rc = plan_noalloc(*grid, tl, g, n_hits, &plan))) return rc;
+  const bool atomic = !g.lds_fill, dense = plan.dense, direct = plan.direct, sliced = plan.sliced;
+  const int layout = sliced ? 0 : dense ? kPeakMask : kPeakBands;
 
   std::lock_guard<std::mutex> lk(g_na_mu);
   if (!g_ptr[dev]) {
@@ -149,7 +191,7 @@ extern "C" int ht_fill_peaks_noalloc(const ht_grid* grid, const float* x, const 
 
   EvDesc ev;
   std::memset(&ev, 0, sizeof(ev));
-  carve_event_scratch(g, n_hits, direct, base + kEvOff, &ev, sliced ? 0 : layout);
+  carve_event_scratch(g, n_hits, direct, base + kEvOff, &ev, layout);
   ev.dense = dense ? 1 : 0;
   ev.lists = !sliced && !dense && (atomic || use_lists(g, 1, n_hits, n_hits)) ? 1 : 0;
   uint32_t* pair = (uint32_t*)base;
@@ -167,17 +209,10 @@ extern "C" int ht_fill_peaks_noalloc(const ht_grid* grid, const float* x, const 
   rc = enqueue_event(g, ev, n_hits, direct, atomic, true, !sliced, false, s, &used);
   if (used) g_parity[dev] ^= 1;
   if (rc || !sliced) return rc;
-  // The masks do not fit beside the slab lists: the peaks are searched in the written matrix, as
-  // many groups of job rows at a time as fit the whole event scratch (the lists are done with
-  // then), each slice counting on from the one before.
   set_jobs(&g, 0, 1);
   int64_t* carry = (int64_t*)(base + kEvOff);
-  const size_t fixed = 256 + al256(4 * (size_t)g.j.n_groups * g.j.pk_step) + al256(4 * (size_t)g.j.n_groups) + 16 * (size_t)kListCap * kLists + 6 * 256;
-  const size_t per = (size_t)(1 + 64 * g.j.elem_bytes) * g.j.group_jobs + 8 * (size_t)g.j.seg;
-  const size_t fit = fixed < room ? (room - fixed) / per : 0;
-  if (fit == 0) return fail(HT_EINVAL, "ht_fill_peaks_noalloc: one group of rows needs %zu bytes of scratch", per);
   for (uint32_t g0 = 0, k = 0; g0 < g.j.n_groups; ++k) {
-    const uint32_t n_grp = (uint32_t)std::min<size_t>(fit, g.j.n_groups - g0);
+    const uint32_t n_grp = std::min<uint32_t>(plan.slice_groups, g.j.n_groups - g0);
     carve_peak_scratch(g, base + kEvOff + 256, &ev, kPeakBands, g0, n_grp);
     ev.lists = 1;
     ev.carry_in = k > 0 ? carry + (k & 1) : nullptr;

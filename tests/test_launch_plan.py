@@ -1,0 +1,103 @@
+"""What the calls would launch (ht_debug_launch_plan, decided on the host with the calls' own code):
+the no-alloc call's limit. No GPU needed."""
+import pytest
+
+from paper_1507_03074_amd import binding as B
+from paper_1507_03074_amd import synth
+
+
+@pytest.fixture(scope="module")
+def lib():
+    from paper_1507_03074_amd import build as hbuild
+    hbuild.ensure_built()  # a missing or stale library is rebuilt, never tested
+    return B.lib()
+
+
+def al(v):
+    return -(-v // 256) * 256
+
+
+def noalloc_limit(spec, n):
+    """Bytes that the documented size rule of ht_fill_peaks_noalloc counts for an event of n hits:
+    slab lists (direct where that keeps within the limit), 16 bytes per tile, and the stencil's peak
+    words from the reported dense_hits on, else nine bytes per candidate."""
+    tl, tu = B.ht_tiling(spec), B.ht_get_tuning(spec)
+    slabs, tiles = spec.n_theta * spec.n_phi, tl["n_tiles"]
+    fixed = al(4 * (slabs + 1)) + 4 * al(4 * tiles) + al(4 * -(-tiles // tu.group_tiles))
+    if tl["lds_fill"] and 0 < tu.dense_hits <= n:
+        chunks = -(-spec.n_b // 62)
+        rows = -(-spec.n_a // max(1, 512 // chunks))
+        rows = max(12, -(-rows // 12) * 12)
+        fixed += al(8 * slabs * -(-spec.n_a // rows) * rows * chunks)
+    else:
+        bound = n * (2 if spec.phi_sectors else 4) * spec.n_a // spec.threshold
+        pool = max(tiles * tl["cand_cap"], min(spec.n_cells, bound // 4))
+        fixed += al(8 * pool) + al(pool)
+    direct = fixed + al(16 * slabs * max(n, 1))
+    packed = fixed + 3 * al(16 * n) + al(64 * n + 16)
+    return direct if tl["lds_fill"] and 16 * slabs * max(n, 1) <= 1 << 29 and direct <= ROOM else packed
+
+
+ROOM = (64 << 20) - 295424
+GRIDS = [(4, 16, 1024, 1024), (4, 16, 2048, 512), (2, 8, 1024, 1024), (4, 16, 512, 512), (4, 16, 64, 64),
+         (1, 3, 16, 16), (3, 7, 501, 333), (4, 16, 2048, 2048), (8, 32, 256, 256), (2, 3, 40, 20000), (1, 3, 2000, 5000)]
+
+
+@pytest.mark.parametrize("grid", GRIDS, ids=lambda g: "x".join(map(str, g)))
+@pytest.mark.parametrize("sectors", [False, True])
+def test_noalloc_accepts_what_its_limit_holds(lib, grid, sectors):
+    """Accepted exactly where the documented arithmetic fits, crowded events of low thresholds among
+    them, with a layout that fits the array."""
+    taken = refused = 0
+    for T in (1, 2, 3, 4, 5, 9, 30):
+        spec = synth.GridSpec(*grid, threshold=T, phi_sectors=sectors)
+        d = B.ht_get_tuning(spec).dense_hits
+        sizes = {0, 1, 250, 5000, 16384, 24576, 31129, 39000, 39321, 60000, 400000, 590000, 600000}
+        sizes |= {d - 1, d, 2 * d, 2 * d + 1, 5 * d // 2} if d > 0 else set()
+        for n in sorted(sizes):
+            try:
+                plan = B.ht_debug_launch_plan(spec, [n], "noalloc")
+            except B.HTError as ex:
+                assert ex.code == B.HT_EINVAL and "bytes of scratch" in str(ex)
+                plan = None
+            assert (plan is not None) == (noalloc_limit(spec, n) <= ROOM), (T, n)
+            taken, refused = taken + (plan is not None), refused + (plan is None)
+            if plan:
+                assert plan["scratch_bytes"] <= ROOM
+    assert taken and (refused or grid == (8, 32, 256, 256) or spec.n_cells < 1 << 27)
+
+
+def test_noalloc_takes_direct_lists_where_they_fit(lib):
+    """The slab lists are direct while they and the search's own scratch fit, not what the size rule
+    counts beside them."""
+    for T in (1, 9):
+        spec = synth.GridSpec(4, 16, 1024, 1024, threshold=T)
+        for n, direct in ((5000, 1), (16384, 1), (33500, 1), (39000, 1), (64000, 0)):
+            assert B.ht_debug_launch_plan(spec, [n], "noalloc")["direct"] == direct, (T, n)
+
+
+def test_noalloc_slices_only_what_does_not_fit(lib):
+    """Slices where the survivors' scratch passes the array, here by two thirds; never for an event
+    that the size rule takes for a crowded one, which has the stencil."""
+    spec = synth.GridSpec(2, 32, 4096, 2048, threshold=9)
+    B.ht_set_tuning(spec, cand_cap=2)
+    try:
+        assert B.ht_debug_launch_plan(spec, [2500], "noalloc")["sliced"] == 1
+        assert B.ht_debug_launch_plan(spec, [2500])["scratch_bytes"] > 5 * ROOM // 3
+    finally:
+        B.ht_set_tuning(spec)
+    spec = synth.GridSpec(4, 16, 2048, 2048, threshold=1)
+    assert B.ht_get_tuning(spec).dense_hits == 32768
+    plan = B.ht_debug_launch_plan(spec, [40000], "noalloc")
+    assert plan["sliced"] == 0 and plan["n_stencil"] == 1
+
+
+def test_launch_plan_validated_on_host(lib):
+    spec = synth.WORKLOADS[0].grid
+    for bad in ([], [-1], [5, 5], [1 << 29]):
+        with pytest.raises(B.HTError) as ex:
+            B.ht_debug_launch_plan(spec, bad)
+        assert ex.value.code == B.HT_EINVAL
+    with pytest.raises(B.HTError):
+        B.ht_debug_launch_plan(synth.GridSpec(1, 3, 16385, 64), [5], "noalloc")
+    assert B.ht_debug_launch_plan(synth.GridSpec(1, 3, 16385, 64), [5])["scratch_bytes"] > 0
