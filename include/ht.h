@@ -98,12 +98,13 @@ typedef struct ht_peak {
 
 /* Launch shape of the kernels for one grid. Results never depend on it (every shape gives
  * bit-identical matrices and peak lists); only speed does. Zero (or -1 for nt_store) means the
- * library's default for that field. */
+ * library's default for that field, as does the default that ht_get_tuning reports for it: setting
+ * what it returned changes nothing. */
 typedef struct ht_tuning {
   int32_t rows;         /* A rows per fill tile: a power of two <= 64 whose rows x n_b uint32
                            counters fit in 56 KiB of LDS. The default reported is 32 KiB of
-                           them; unless this field is set, launches of short slab lists take
-                           half as many, and small launches fewer */
+                           them; with it, launches of short slab lists take half as many, and
+                           small launches fewer */
   int32_t group_tiles;  /* tiles per workgroup of the ordered writer of crowded events: 16, 32
                            or 64 */
   int32_t cand_cap;     /* a power of two <= 4096. The peak search keeps no per-tile candidate
@@ -111,9 +112,9 @@ typedef struct ht_tuning {
                            ht_fill_peaks_noalloc is stated in */
   int32_t nt_store;     /* store kind of the fill's single write of the matrix: 0 ordinary
                            16-byte stores, 1 non-temporal 16-byte stores, 2 ordinary stores of
-                           4-byte alignment. The default reported is 0; unless this field is set
-                           (-1), launches that write more than the last-level cache holds, and
-                           crowded events, take non-temporal stores */
+                           4-byte alignment. The default reported is 0; with it, launches that
+                           write more than the last-level cache holds, and crowded events, take
+                           non-temporal stores */
   int32_t tiles_per_block; /* fill tiles per workgroup, filled in turn with one LDS tile (the
                               slab's hit records are read once): a power of two <= 64 */
   int32_t dense_hits;   /* crowded events: a fused fill + peak search of an event with at least
@@ -122,7 +123,7 @@ typedef struct ht_tuning {
                            instead of testing the fill's survivors; -1 never. The default
                            reported is n_theta n_phi n_b / 4 hits (16384 on the
                            4x16x1024x1024 grid), where the stencil starts to beat a test of
-                           every candidate; unless this field is set, the library takes it from
+                           every candidate; with it, the library takes the stencil from
                            twice that many hits, or 2.5 times (matrices of 128 MiB or more),
                            where it beats a test of the survivors. The stencil needs LDS
                            fill tiles, at most 4 theta and 16 phi cells (one wave per phi cell

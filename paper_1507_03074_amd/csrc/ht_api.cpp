@@ -174,14 +174,16 @@ Tiling choose_tiling(const ht_grid& g)
       have = true;
     }
   }
+  // A field set to its reported default is as good as unset: setting what ht_get_tuning returned
+  // changes nothing, and a shape pins only what it changes.
   if (have) {
-    if (tu.rows > 0 && t.lds_fill) {
+    if (tu.rows > 0 && tu.rows != t.rows && t.lds_fill) {
       t.rows = tu.rows;
       t.auto_rows = 0;
     }
     if (tu.group_tiles > 0) t.group_tiles = tu.group_tiles;
     if (tu.cand_cap > 0) t.cand_cap = tu.cand_cap;
-    if (tu.nt_store >= 0) {
+    if (tu.nt_store >= 0 && tu.nt_store != t.nt_store) {
       t.nt_store = tu.nt_store;
       t.auto_nt = 0;
     }
@@ -217,9 +219,11 @@ Tiling choose_tiling(const ht_grid& g)
   int64_t dh = def, from = bytes >= ((int64_t)128 << 20) ? def * 5 / 2 : def * 2;
   const int forced_dh = env_int("HT_DENSE_HITS", 0);
   if (forced_dh != 0) dh = from = forced_dh;
-  if (have && tu.dense_hits != 0) dh = from = tu.dense_hits;
-  const bool on = t.dense_w > 0 && dh > 0;
-  t.dense_hits = on ? (int32_t)std::min<int64_t>(dh, 1 << 28) : 0;
+  auto reported = [&](int64_t hits) { return t.dense_w > 0 && hits > 0 ? (int32_t)std::min<int64_t>(hits, 1 << 28) : 0; };
+  const int32_t unset = reported(dh);
+  if (have && tu.dense_hits != 0 && tu.dense_hits != (unset > 0 ? unset : -1)) dh = from = tu.dense_hits;
+  t.dense_hits = reported(dh);
+  const bool on = t.dense_hits > 0;
   t.dense_from = on ? (int32_t)std::min<int64_t>(from, 1 << 28) : 0;
   return t;
 }

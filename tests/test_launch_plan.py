@@ -1,5 +1,5 @@
 """What the calls would launch (ht_debug_launch_plan, decided on the host with the calls' own code):
-the no-alloc call's limit. No GPU needed."""
+the no-alloc call's limit, and launch shapes that are read and set back. No GPU needed."""
 import pytest
 
 from paper_1507_03074_amd import binding as B
@@ -90,6 +90,34 @@ def test_noalloc_slices_only_what_does_not_fit(lib):
     assert B.ht_get_tuning(spec).dense_hits == 32768
     plan = B.ht_debug_launch_plan(spec, [40000], "noalloc")
     assert plan["sliced"] == 0 and plan["n_stencil"] == 1
+
+
+def plans(spec):
+    sizes = (0, 250, 1000, 3000, 5000, 12000, 22000, 41000)
+    one = [B.ht_debug_launch_plan(spec, [n]) for n in sizes]
+    return one + [B.ht_debug_launch_plan(spec, b, "batch") for b in ([250] * 100, [5000, 8000] * 50, list(sizes))]
+
+
+@pytest.mark.parametrize("grid", [(4, 16, 1024, 1024), (4, 16, 256, 256), (3, 7, 501, 333), (8, 32, 512, 512), (4, 16, 64, 64)],
+                         ids=lambda g: "x".join(map(str, g)))
+@pytest.mark.parametrize("fields", [{}, {"rows": 4}, {"nt_store": 1}, {"dense_hits": -1}, {"dense_hits": 900}, {"nt_store": 2, "rows": 2},
+                                    {"tiles_per_block": 4, "group_tiles": 64}], ids=str)
+def test_setting_the_reported_shape_changes_no_launch(lib, grid, fields):
+    """ht_get_tuning, then ht_set_tuning of what it returned: the same launches for every event size,
+    whether fields were set before or not."""
+    spec = synth.GridSpec(*grid, threshold=9)
+    try:
+        B.ht_set_tuning(spec, **fields)
+        before, shape = plans(spec), B.ht_get_tuning(spec)
+        B.ht_set_tuning(spec, shape)
+        assert plans(spec) == before
+        assert B.ht_get_tuning(spec).as_dict() == shape.as_dict()
+        B.ht_set_tuning(spec)
+        unset = plans(spec)
+        B.ht_set_tuning(spec, B.ht_get_tuning(spec))
+        assert plans(spec) == unset
+    finally:
+        B.ht_set_tuning(spec)
 
 
 def test_launch_plan_validated_on_host(lib):
