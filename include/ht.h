@@ -125,7 +125,9 @@ typedef struct ht_tuning {
                            4x16x1024x1024 grid), where the stencil starts to beat a test of
                            every candidate; with it, the library takes the stencil from
                            twice that many hits, or 2.5 times (matrices of 128 MiB or more),
-                           where it beats a test of the survivors. The stencil needs LDS
+                           where it beats a test of the survivors. A batch with such an event
+                           takes it for all its events from the reported number on. The stencil
+                           needs LDS
                            fill tiles, at most 4 theta and 16 phi cells (one wave per phi cell
                            holds every theta cell's row), and theta cell 0's row and the last
                            one's less than 2^31 bytes apart; ht_get_tuning reports -1 where it

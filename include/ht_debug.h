@@ -60,7 +60,8 @@ int ht_debug_batch_plan(const ht_grid* grid, const ht_event* events, int32_t n_e
 
 /* ht_debug_launch_plan: what a call would launch, decided on the host with the same code (no device
  * work, no device memory). call: 0 ht_fill_peaks (one event), 1 ht_fill_peaks_batch,
- * 2 ht_fill_peaks_noalloc (one event). n_hits: host int64[n_events], the events' sizes.
+ * 2 ht_fill_peaks_noalloc (one event), 3 a batch of a request loop. n_hits: host int64[n_events], the
+ * events' sizes; for call 3 first the loop's max_hits, then the batch, as large as max_batch.
  * Errors: HT_EINVAL (grid, call, n_events, sizes, NULL), and for call 2 an event that the call
  * refuses (n_a, or scratch past its fixed array). */
 typedef struct ht_launch_plan {

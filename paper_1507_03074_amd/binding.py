@@ -353,11 +353,12 @@ def ht_debug_batch_plan(spec, n_hits):
 
 def ht_debug_launch_plan(spec, n_hits, call="event"):
     """What a call ("event", "batch" or "noalloc") would launch for events of these sizes at the
-    grid's current launch shape, as a dict (host only). Raises HTError for a call that is refused."""
+    grid's current launch shape, as a dict (host only); "serve": a batch of a request loop, whose
+    max_hits comes first. Raises HTError for a call that is refused."""
     g = make_grid(spec)
     arr = (ctypes.c_int64 * len(n_hits))(*[int(n) for n in n_hits])
     plan = LaunchPlan()
-    check(lib().ht_debug_launch_plan(ctypes.byref(g), ("event", "batch", "noalloc").index(call), arr, len(n_hits),
+    check(lib().ht_debug_launch_plan(ctypes.byref(g), ("event", "batch", "noalloc", "serve").index(call), arr, len(n_hits),
                                      ctypes.byref(plan)))
     return plan.as_dict()
 

@@ -334,6 +334,14 @@ static void shape_launch(DevGrid* d, const Tiling& tl, int n_ev, int64_t max_hit
   }
 }
 
+int32_t stencil_from(const Tiling& tl, int n_ev, int64_t max_hits)
+{
+  // A batch that has the stencil's launches anyway, as one of its events reaches its threshold, takes
+  // it for its events from the reported one on (six events of 3050-15250 hits on 4x16x532x171, both
+  // searches: 145 us)
+  return n_ev > 1 && tl.dense_from > 0 && max_hits >= tl.dense_from ? tl.dense_hits : tl.dense_from;
+}
+
 DevGrid make_devgrid(const ht_grid& g, const DevTables& t, const Tiling& tl, int n_ev, int64_t max_hits)
 {
   DevGrid d;
@@ -362,9 +370,7 @@ DevGrid make_devgrid(const ht_grid& g, const DevTables& t, const Tiling& tl, int
                    std::isfinite((float)((double)g.n_b / ((double)g.b_max - (double)g.b_min))) ? 1 : 0;
   d.dense_w = tl.dense_w;
   d.dense_rows = tl.dense_rows;
-  // A batch that has the stencil's launches anyway takes it for its events from the reported
-  // threshold on (six events of 3050-15250 hits on 4x16x532x171, both searches: 145 us)
-  d.dense_hits = n_ev > 1 && tl.dense_from > 0 && max_hits >= tl.dense_from ? tl.dense_hits : tl.dense_from;
+  d.dense_hits = stencil_from(tl, n_ev, max_hits);
   d.a2 = t.a2;
   d.phi_cs = t.phi;
   d.th_cs = t.th;
@@ -628,13 +634,15 @@ int ensure_ev_staging(Workspace* w, int n_ev, hipStream_t s)
   return HT_OK;
 }
 
-int make_device_grid(const ht_grid& g, int dev, int n_ev, int64_t max_hits, DevGrid* out)
+int make_device_grid(const ht_grid& g, int dev, int n_ev, int64_t max_hits, DevGrid* out, Tiling* tl)
 {
   int rc = validate_grid(&g);
   if (rc) return rc;
   DevTables t;
   if ((rc = get_tables(g, dev, &t))) return rc;
-  *out = make_devgrid(g, t, choose_tiling(g), n_ev, max_hits);
+  const Tiling tiling = choose_tiling(g);
+  if (tl) *tl = tiling;
+  *out = make_devgrid(g, t, tiling, n_ev, max_hits);
   return HT_OK;
 }
 
@@ -724,7 +732,17 @@ int injected_failure(const char* stage)
   return HT_OK;
 }
 
-int launch_batch(const DevGrid& g, const EvDesc* d_ev, int n_ev, int64_t max_hits, bool direct,
+BatchShape batch_shape(const DevGrid& g, int n_ev, int64_t max_hits, bool any_dense, int pieces)
+{
+  BatchShape b;
+  b.prep_hits = max_hits;
+  b.long_l = g.lds_fill && long_lists(g, max_hits);
+  b.tiny = !any_dense && pieces == 1 && tiny_launch(g, n_ev, max_hits);
+  b.few = !any_dense && pieces == 1 && g.lds_fill && few_cells(g, max_hits) && use_lists(g, n_ev, max_hits, max_hits);
+  return b;
+}
+
+int launch_batch(const DevGrid& g, const EvDesc* d_ev, int n_ev, const BatchShape& bs, bool direct,
                  bool any_bands, bool any_dense, hipStream_t s, bool* prep_enqueued, const BatchSplit* split)
 {
   EvDesc none;
@@ -732,7 +750,7 @@ int launch_batch(const DevGrid& g, const EvDesc* d_ev, int n_ev, int64_t max_hit
   int rc;
   *prep_enqueued = false;
   const int pieces = split && g.lds_fill ? std::min(split->pieces, n_ev) : 1;
-  if (!any_dense && pieces == 1 && tiny_launch(g, n_ev, max_hits)) {
+  if (bs.tiny) {
     if ((rc = injected_failure("prep")) || (rc = injected_failure("fill"))) return rc;
     {
       StageTimer t("fill", s);
@@ -746,7 +764,7 @@ int launch_batch(const DevGrid& g, const EvDesc* d_ev, int n_ev, int64_t max_hit
   {
     StageTimer t("prep", s);
     if ((rc = injected_failure("prep")) ||
-        (rc = check_launch(launch_prep(g, none, d_ev, n_ev, max_hits, direct && g.lds_fill, s), "prep launch")))
+        (rc = check_launch(launch_prep(g, none, d_ev, n_ev, bs.prep_hits, direct && g.lds_fill, s), "prep launch")))
       return rc;
     *prep_enqueued = true;
   }
@@ -759,7 +777,7 @@ int launch_batch(const DevGrid& g, const EvDesc* d_ev, int n_ev, int64_t max_hit
     hipError_t e;
     for (int i = 0; i < pieces; ++i) {
       const int e0 = (int)((int64_t)n_ev * i / pieces), e1 = (int)((int64_t)n_ev * (i + 1) / pieces);
-      if ((rc = check_launch(launch_fill(g, none, d_ev + e0, e1 - e0, any_bands, max_hits, s), "fill launch")))
+      if ((rc = check_launch(launch_fill(g, none, d_ev + e0, e1 - e0, any_bands, bs.long_l, s), "fill launch")))
         return rc;
       if ((e = hipEventRecord(split->filled[i], s)) != hipSuccess) return fail_hip(e, "hipEventRecord");
       if ((e = hipStreamWaitEvent(split->side, split->filled[i], 0)) != hipSuccess)
@@ -777,11 +795,11 @@ int launch_batch(const DevGrid& g, const EvDesc* d_ev, int n_ev, int64_t max_hit
   }
   if (g.lds_fill) {
     StageTimer t("fill", s);
-    if ((rc = check_launch(launch_fill(g, none, d_ev, n_ev, any_bands, max_hits, s), "fill launch"))) return rc;
+    if ((rc = check_launch(launch_fill(g, none, d_ev, n_ev, any_bands, bs.long_l, s), "fill launch"))) return rc;
   } else {
     {
       StageTimer t("fill_atomic", s);
-      if ((rc = check_launch(launch_fill_atomic(g, none, d_ev, n_ev, max_hits, s), "fill launch")))
+      if ((rc = check_launch(launch_fill_atomic(g, none, d_ev, n_ev, bs.prep_hits, s), "fill launch")))
         return rc;
     }
     StageTimer t("candidates", s);
@@ -789,8 +807,7 @@ int launch_batch(const DevGrid& g, const EvDesc* d_ev, int n_ev, int64_t max_hit
   }
   if ((rc = injected_failure("peaks"))) return rc;
   StageTimer t("peaks", s);
-  if (!any_dense && g.lds_fill && few_cells(g, max_hits) && use_lists(g, n_ev, max_hits, max_hits))
-    return check_launch(launch_few_peaks(g, none, d_ev, n_ev, s), "peak launch");
+  if (bs.few) return check_launch(launch_few_peaks(g, none, d_ev, n_ev, s), "peak launch");
   if (any_bands && (rc = check_launch(launch_peaks(g, none, d_ev, n_ev, g.j.n_groups, s), "peak launch"))) return rc;
   if (any_dense && (rc = check_launch(launch_peaks_dense(g, none, d_ev, n_ev, s), "stencil peak launch")))
     return rc;
@@ -827,9 +844,9 @@ int check_accessible(const void* ptr, const char* what)
   return HT_OK;
 }
 
-// The event size that a batch's launches are made for: prep grids are sized for a power-of-two
-// bucket of workgroups, so batches of one size share a graph (workgroups past an event's hits
-// return at once).
+// The event size that a captured batch's preparation is made for: a power-of-two bucket of
+// workgroups, so that batches of one size share a graph (workgroups past an event's hits return at
+// once).
 int64_t batch_hits(int64_t max_hits)
 {
   int64_t blocks = 1;
@@ -895,7 +912,7 @@ int enqueue_event(const DevGrid& g, const EvDesc& ev, int64_t nh, bool direct, b
       if ((rc = check_launch(launch_fill_atomic(g, ev, nullptr, 1, nh, s), "fill launch"))) return rc;
     } else {
       HT_STAGE(t, "fill");
-      if ((rc = check_launch(launch_fill(g, ev, nullptr, 1, do_peaks && !ev.dense, nh, s), "fill launch"))) return rc;
+      if ((rc = check_launch(launch_fill(g, ev, nullptr, 1, do_peaks && !ev.dense, long_lists(g, nh), s), "fill launch"))) return rc;
     }
   }
   if (do_peaks) {
@@ -1038,9 +1055,8 @@ int ht_fill_peaks_batch(const ht_grid* grid, const ht_event* events, int32_t n_e
     if (ev.n_hits > 0 && (!x || !y || !z)) return fail(HT_EINVAL, "hit arrays are NULL");
     if (ev.peak_capacity > 0 && !out) return fail(HT_EINVAL, "out is NULL");
   }
-  const int64_t max_hits_b = batch_hits(max_hits);
   Prepared p;
-  if ((rc = prepare(grid, stream, &p, n_events, max_hits_b))) return rc;
+  if ((rc = prepare(grid, stream, &p, n_events, max_hits))) return rc;
   if ((rc = check_accessible(out, "out")) || (rc = check_accessible(n_found, "n_found"))) return rc;
   std::vector<size_t> offs;
   size_t total_scratch = 0;
@@ -1061,7 +1077,7 @@ int ht_fill_peaks_batch(const ht_grid* grid, const ht_event* events, int32_t n_e
     any_dense = any_dense || dense;
     carve_event_scratch(p.g, ev.n_hits, direct, w->dev + offs[i], &d, dense ? kPeakMask : kPeakBands);
     d.dense = dense ? 1 : 0;
-    d.lists = !dense && (!p.g.lds_fill || use_lists(p.g, n_events, max_hits_b, ev.n_hits)) ? 1 : 0;
+    d.lists = !dense && (!p.g.lds_fill || use_lists(p.g, n_events, max_hits, ev.n_hits)) ? 1 : 0;
     use_counters(w, i, &d);
     d.x = x ? x + ev.hit_offset : nullptr;
     d.y = y ? y + ev.hit_offset : nullptr;
@@ -1101,6 +1117,7 @@ int ht_fill_peaks_batch(const ht_grid* grid, const ht_event* events, int32_t n_e
     for (int i = 0; i < kMaxPieces; ++i) split.filled[i] = w->split_ev[i];
     split.done = w->split_ev[kMaxPieces];
   }
+  BatchShape shape = batch_shape(p.g, n_events, max_hits, any_dense, pieces);
   // The descriptors above hold this call's counter arrays. The next call switches to the other
   // arrays only once this call's preparation (which counts into these and clears those) is on
   // the stream; a call that fails before that leaves the counters as they were.
@@ -1108,19 +1125,21 @@ int ht_fill_peaks_batch(const ht_grid* grid, const ht_event* events, int32_t n_e
     if ((e = launch_fetch(w->d_ev, h_ev, n_events, p.s)) != hipSuccess) return fail_hip(e, "descriptor launch");
     if ((e = hipEventRecord(w->ev_read[w->turn], p.s)) != hipSuccess) return fail_hip(e, "hipEventRecord");
     bool prep_enqueued = false;
-    rc = launch_batch(p.g, w->d_ev, n_events, max_hits_b, direct, any_bands, any_dense, p.s, &prep_enqueued,
+    rc = launch_batch(p.g, w->d_ev, n_events, shape, direct, any_bands, any_dense, p.s, &prep_enqueued,
                       pieces > 1 ? &split : nullptr);
     if (prep_enqueued) flip_counters(w, n_events);
     return rc;
   }
   // graph key: everything the captured launches depend on besides the descriptor contents
+  shape.prep_hits = batch_hits(max_hits);
   std::vector<unsigned char> key(sizeof(DevGrid) + 4 * sizeof(int64_t) + 2 * sizeof(void*));
   {
     unsigned char* q = key.data();
     std::memcpy(q, &p.g, sizeof(DevGrid));
     q += sizeof(DevGrid);
-    const int64_t ints[4] = {n_events, max_hits_b, p.dev,
-                             (direct ? 1 : 0) | (any_bands ? 2 : 0) | (any_dense ? 4 : 0) | (pieces << 3)};
+    const int64_t ints[4] = {n_events, shape.prep_hits, p.dev,
+                             (direct ? 1 : 0) | (any_bands ? 2 : 0) | (any_dense ? 4 : 0) | (shape.long_l ? 8 : 0) |
+                                 (shape.tiny ? 16 : 0) | (shape.few ? 32 : 0) | (pieces << 6)};
     std::memcpy(q, ints, sizeof(ints));
     q += sizeof(ints);
     const void* ptrs[2] = {w->d_ev, h_ev};
@@ -1140,7 +1159,7 @@ int ht_fill_peaks_batch(const ht_grid* grid, const ht_event* events, int32_t n_e
     e = launch_fetch(w->d_ev, h_ev, n_events, w->capture);
     bool captured_prep = false;
     int lrc = e == hipSuccess
-                  ? launch_batch(p.g, w->d_ev, n_events, max_hits_b, direct, any_bands, any_dense, w->capture,
+                  ? launch_batch(p.g, w->d_ev, n_events, shape, direct, any_bands, any_dense, w->capture,
                                  &captured_prep, pieces > 1 ? &split : nullptr)
                   : HT_EDEVICE;
     t_capturing = false;
@@ -1260,7 +1279,7 @@ int ht_debug_batch_plan(const ht_grid* grid, const ht_event* events, int32_t n_e
   // the tiling alone decides the layout; the tables (device memory) are not needed
   int64_t max_hits = 0;
   for (int32_t i = 0; i < n_events; ++i) max_hits = std::max(max_hits, events[i].n_hits);
-  const DevGrid g = make_devgrid(*grid, DevTables(), choose_tiling(*grid), n_events, batch_hits(max_hits));
+  const DevGrid g = make_devgrid(*grid, DevTables(), choose_tiling(*grid), n_events, max_hits);
   std::vector<size_t> offs;
   size_t total = 0;
   *direct = plan_batch(g, events, n_events, &offs, &total, &max_hits) ? 1 : 0;
@@ -1273,43 +1292,52 @@ int ht_debug_launch_plan(const ht_grid* grid, int32_t call, const int64_t* n_hit
 {
   int rc = validate_grid(grid);
   if (rc) return rc;
-  if (!n_hits || !plan || call < 0 || call > 2 || n_events < 1 || n_events > (call == 1 ? 65535 : 1))
+  const bool serve = call == 3, batch = call == 1 || serve;
+  if (!n_hits || !plan || call < 0 || call > 3 || n_events < (serve ? 2 : 1) || n_events > (batch ? 65535 : 1))
     return fail(HT_EINVAL, "invalid launch-plan arguments");
   std::vector<ht_event> events((size_t)n_events);
   int64_t max_hits = 0;
   for (int32_t i = 0; i < n_events; ++i) {
     if (n_hits[i] < 0 || n_hits[i] > ((int64_t)1 << 28)) return fail(HT_EINVAL, "event %d has an invalid size", i);
     events[i] = ht_event{0, n_hits[i], 0, 0};
-    max_hits = std::max(max_hits, n_hits[i]);
+    if (!serve || i > 0) max_hits = std::max(max_hits, n_hits[i]);
   }
-  const int64_t mh = call == 1 ? batch_hits(max_hits) : max_hits;
   const Tiling tl = choose_tiling(*grid);
-  const DevGrid g = make_devgrid(*grid, DevTables(), tl, n_events, mh);
+  const int64_t loop_hits = serve ? n_hits[0] : 0;
+  if (serve) events.erase(events.begin());
+  const int n_ev = (int)events.size();
+  DevGrid g = make_devgrid(*grid, DevTables(), tl, n_ev, serve ? loop_hits : max_hits);
+  if (serve) g.dense_hits = stencil_from(tl, n_ev, max_hits);
   std::memset(plan, 0, sizeof(*plan));
   NoallocPlan na;
   std::memset(&na, 0, sizeof(na));
   if (call == 2 && (rc = plan_noalloc(*grid, tl, g, max_hits, &na))) return rc;
   plan->rows = g.rows;
   plan->nt_store = g.nt_store;
-  plan->long_lists = g.lds_fill && long_lists(g, mh) ? 1 : 0;
   for (const ht_event& ev : events) {
     const bool dense = call == 2 ? na.dense : g.lds_fill && dense_peaks(g, ev.n_hits);
     plan->n_stencil += dense ? 1 : 0;
-    plan->n_lists += !dense && (na.sliced || !g.lds_fill || use_lists(g, n_events, mh, ev.n_hits)) ? 1 : 0;
+    plan->n_lists += !dense && (na.sliced || !g.lds_fill || use_lists(g, n_ev, max_hits, ev.n_hits)) ? 1 : 0;
   }
   plan->sliced = na.sliced ? 1 : 0;
-  if (!plan->n_stencil && !na.sliced) {
-    plan->tiny = tiny_launch(g, n_events, mh) ? 1 : 0;
-    plan->few = plan->tiny || (g.lds_fill && few_cells(g, mh) && use_lists(g, n_events, mh, mh)) ? 1 : 0;
-  }
+  const BatchShape b = batch_shape(g, n_ev, max_hits, plan->n_stencil > 0 || na.sliced, 1);
+  plan->long_lists = b.long_l ? 1 : 0;
+  plan->tiny = b.tiny ? 1 : 0;
+  plan->few = b.few || b.tiny ? 1 : 0;
   if (call == 2) {
     plan->direct = na.direct ? 1 : 0;
     plan->scratch_bytes = (int64_t)na.scratch_bytes;
     return HT_OK;
   }
+  if (serve) {
+    plan->direct = direct_lists(g, loop_hits) ? 1 : 0;
+    const int layout = kPeakBands | (tl.dense_from > 0 && loop_hits >= tl.dense_from ? kPeakMask : 0);
+    plan->scratch_bytes = (int64_t)(n_ev * event_scratch_bytes(g, loop_hits, plan->direct != 0, layout));
+    return HT_OK;
+  }
   std::vector<size_t> offs;
   size_t total = 0;
-  plan->direct = plan_batch(g, events.data(), n_events, &offs, &total, &max_hits) ? 1 : 0;
+  plan->direct = plan_batch(g, events.data(), n_ev, &offs, &total, &max_hits) ? 1 : 0;
   plan->scratch_bytes = (int64_t)total;
   return HT_OK;
 }

@@ -155,6 +155,9 @@ inline size_t th_floats(const ht_grid& g) { return 2 * (2 * (size_t)g.n_theta + 
 void host_tables_into(const ht_grid& g, float* a2, float* inv_db, float* phi, float* th);
 // n_ev, max_hits: what the launches it is for hold.
 DevGrid make_devgrid(const ht_grid& g, const DevTables& t, const Tiling& tl, int n_ev, int64_t max_hits);
+// The hits from which the events of a launch of n_ev events of up to max_hits hits take the stencil
+// (DevGrid::dense_hits; 0: none).
+int32_t stencil_from(const Tiling& tl, int n_ev, int64_t max_hits);
 // Sets g.j: the jobs of tiles of `tile_rows` rows, or with 0 those of a matrix that k_scan reads
 // (bands of four rows, or of one in very wide rows). n_ev: events of the launch.
 void set_jobs(DevGrid* g, int tile_rows, int n_ev);
@@ -186,7 +189,7 @@ hipError_t launch_fetch(EvDesc* evs, const EvDesc* host, int n_ev, hipStream_t s
 hipError_t launch_prep(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev,
                        int64_t max_hits, bool direct, hipStream_t s);
 hipError_t launch_fill(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev,
-                       bool emit, int64_t max_hits, hipStream_t s);
+                       bool emit, bool long_l, hipStream_t s);
 // Survivors of a written matrix (g.j set for a scan), for n_grp groups per event. counters: the
 // scan uses the counter pair (no preparation of the same call does): the lists' lengths in one
 // array, and it clears the other.
@@ -248,7 +251,14 @@ int fail_hip(hipError_t e, const char* what);
 int validate_grid(const ht_grid* g);
 uint64_t n_cells(const ht_grid& g);
 // Validates the grid, uploads its tables once per device and picks the tiling.
-int make_device_grid(const ht_grid& g, int dev, int n_ev, int64_t max_hits, DevGrid* out);
+int make_device_grid(const ht_grid& g, int dev, int n_ev, int64_t max_hits, DevGrid* out, Tiling* tl = nullptr);
+// What a batch of n_ev events of up to max_hits hits launches, besides what g says.
+struct BatchShape {
+  int64_t prep_hits;  // that the preparation's grid is made for: at least max_hits
+  bool long_l;        // the fill's variant for long lists
+  bool tiny, few;     // the launches of tiny events, the search of few cells
+};
+BatchShape batch_shape(const DevGrid& g, int n_ev, int64_t max_hits, bool any_dense, int pieces);
 // The whole batched pipeline (prep, fill with survivors, peaks) for n_ev events whose
 // descriptors are already in device memory.
 // *prep_enqueued is set once the preparation (which counts into and clears the events' counter
@@ -264,7 +274,7 @@ struct BatchSplit {
 };
 // any_bands / any_dense: whether some event searches its peaks through the fill's survivors /
 // the stencil (only the kernels needed are launched). split: NULL, or how to overlap.
-int launch_batch(const DevGrid& g, const EvDesc* d_ev, int n_ev, int64_t max_hits, bool direct,
+int launch_batch(const DevGrid& g, const EvDesc* d_ev, int n_ev, const BatchShape& bs, bool direct,
                  bool any_bands, bool any_dense, hipStream_t s, bool* prep_enqueued,
                  const BatchSplit* split = nullptr);
 

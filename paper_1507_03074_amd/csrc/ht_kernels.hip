@@ -1761,9 +1761,8 @@ bool use_lists(const DevGrid& g, int n_ev, int64_t max_hits, int64_t hits)
 }
 
 hipError_t launch_fill(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev,
-                       bool emit, int64_t max_hits, hipStream_t s)
+                       bool emit, bool long_l, hipStream_t s)
 {
-  const bool long_l = long_lists(g, max_hits);
   // store kind 2: 4-byte stores (the dword path), otherwise 16-byte stores where rows allow
   const bool vec = (g.n_b % 4) == 0 && g.nt_store != 2;
   const size_t lds = fill_lds_bytes(g, long_l);

@@ -68,7 +68,8 @@ using namespace ht;
 struct ht_server {
   ht_grid grid;
   ht_serve_opts opts;
-  DevGrid g;
+  Tiling tl;
+  DevGrid g;                    // for the largest batch (the slots' layout)
   int dev = 0;
   uint64_t cells = 0;
   size_t scratch_bytes = 0;
@@ -123,8 +124,10 @@ int launch(ht_server* sv, Batch& b)
 {
   hipStream_t s = sv->streams[b.stream];
   const int64_t mh = sv->opts.max_hits;
-  int64_t max_n = 0, batch_max = 0;
+  int64_t batch_max = 0;
   for (const Request* r : b.reqs) batch_max = std::max(batch_max, r->n);
+  DevGrid g = sv->g;
+  g.dense_hits = stencil_from(sv->tl, (int)b.reqs.size(), batch_max);
   bool any_bands = false, any_dense = false;
   hipError_t e;
   for (size_t i = 0; i < b.reqs.size(); ++i) {
@@ -136,11 +139,11 @@ int launch(ht_server* sv, Batch& b)
       return fail_hip(e, "hipMemcpyAsync(hits)");
     EvDesc& d = sv->h_ev[b.stream][i];
     std::memset(&d, 0, sizeof(d));
-    carve_event_scratch(sv->g, mh, sv->direct, sl.scratch, &d, sv->layout);
+    carve_event_scratch(g, mh, sv->direct, sl.scratch, &d, sv->layout);
     // crowded events search their peaks with the stencil (the slot holds both layouts)
-    d.dense = (sv->layout & kPeakMask) && dense_peaks(sv->g, r->n) ? 1 : 0;
-    if (d.dense) clear_groups(sv->g, &d);
-    d.lists = !d.dense && (!sv->g.lds_fill || use_lists(sv->g, (int)b.reqs.size(), batch_max, r->n)) ? 1 : 0;
+    d.dense = (sv->layout & kPeakMask) && dense_peaks(g, r->n) ? 1 : 0;
+    if (d.dense) clear_groups(g, &d);
+    d.lists = !d.dense && (!g.lds_fill || use_lists(g, (int)b.reqs.size(), batch_max, r->n)) ? 1 : 0;
     any_bands = any_bands || !d.dense;
     any_dense = any_dense || d.dense;
     d.slab_cnt = sl.ctr + (sl.parity ? kCounterWords : 0);
@@ -153,13 +156,13 @@ int launch(ht_server* sv, Batch& b)
     d.out = sl.d_out;  // mapped pinned host memory: the kernels write the peaks to the host
     d.cap = sv->opts.peak_capacity;
     d.n_found = sl.d_nfound;
-    max_n = std::max(max_n, r->n);
   }
   if ((e = launch_fetch(sv->d_ev[b.stream], sv->h_ev[b.stream], (int)b.reqs.size(), s)) != hipSuccess)
     return fail_hip(e, "descriptor launch");
   bool prep_enqueued = false;
-  int rc = launch_batch(sv->g, sv->d_ev[b.stream], (int)b.reqs.size(), max_n, sv->direct, any_bands,
-                        any_dense, s, &prep_enqueued);
+  const BatchShape shape = batch_shape(g, (int)b.reqs.size(), batch_max, any_dense, 1);
+  int rc = launch_batch(g, sv->d_ev[b.stream], (int)b.reqs.size(), shape, sv->direct, any_bands, any_dense, s,
+                        &prep_enqueued);
   // a slot switches counter arrays only once the preparation that counts into this one and
   // clears the other is on the stream
   if (prep_enqueued)
@@ -264,13 +267,13 @@ int ht_serve_create(const ht_grid* grid, const ht_serve_opts* opts, ht_server** 
   sv->grid = *grid;
   sv->opts = *opts;
   sv->dev = opts->device;
-  if ((rc = make_device_grid(*grid, sv->dev, opts->max_batch, opts->max_hits, &sv->g))) {
+  if ((rc = make_device_grid(*grid, sv->dev, opts->max_batch, opts->max_hits, &sv->g, &sv->tl))) {
     delete sv;
     return rc;
   }
   sv->cells = n_cells(*grid);
   sv->direct = direct_lists(sv->g, opts->max_hits);
-  sv->layout = kPeakBands | (dense_peaks(sv->g, opts->max_hits) ? kPeakMask : 0);
+  sv->layout = kPeakBands | (sv->tl.dense_from > 0 && opts->max_hits >= sv->tl.dense_from ? kPeakMask : 0);
   sv->scratch_bytes = event_scratch_bytes(sv->g, opts->max_hits, sv->direct, sv->layout);
   const size_t slot_bytes = al(4 * sv->cells) + al(sv->scratch_bytes) + al(12 * (size_t)opts->max_hits);
   const int64_t n_slots = std::min<int64_t>(opts->hbm_budget_bytes / (int64_t)slot_bytes, 4096);

@@ -79,3 +79,51 @@ def test_noalloc_layouts(B):
     assert B.ht_debug_launch_plan(spec, [40000], "noalloc")["n_stencil"] == 1
     assert B.ht_debug_launch_plan(spec, [40000])["n_stencil"] == 0
     assert noalloc_equals_fill_peaks(B, spec, hits(4, 40000)) > 1000
+
+
+def oracle_run(spec, ev):
+    from oracle import oracle
+    g = oracle.OracleGrid(*spec.as_tuple())
+    M, _ = oracle.fill(g, *ev)
+    return (M, *oracle.peaks(g, M))
+
+
+@pytest.mark.parametrize("graph", ["0", "1"])
+def test_batches_around_the_stencil_threshold(B, monkeypatch, graph):
+    """The default launches of batches whose largest event lies below and at twice the reported
+    dense_hits (8192 on 4x16x256x256), one graph bucket of workgroups; replayed."""
+    spec = synth.GridSpec(4, 16, 256, 256, threshold=8)
+    monkeypatch.setenv("HT_BATCH_GRAPH", graph)
+    batches = ([6585] * 3 + [300], [4500, 4200, 300], [8191, 5000, 300], [8192, 5000, 4095, 300])
+    want = {}
+    for _ in range(2):
+        for sizes in batches:
+            say("graph", graph, "sizes", sizes)
+            evs = [hits(10 + i, n) for i, n in enumerate(sizes)]
+            res = B.fill_peaks_batch(spec, evs)
+            for i, n in enumerate(sizes):
+                if (i, n) not in want:
+                    want[i, n] = oracle_run(spec, evs[i])
+                M, c, v, k = want[i, n]
+                assert np.array_equal(B.as_u32(res.acc[i]), M), (sizes, i)
+                got = res.peaks[i]
+                assert got[2] == k and np.array_equal(got[0], c) and np.array_equal(got[1], v), (sizes, i)
+
+
+def test_request_loop_with_few_crowded_events(B):
+    """A loop made for crowded events: batches without one, with one, and single events."""
+    import time
+    spec = synth.GridSpec(4, 16, 256, 256, threshold=8)
+    sizes = [5000] * 3 + [9000, 5000, 300, 4096] + [4100]
+    evs = [hits(20 + i, n) for i, n in enumerate(sizes)]
+    with B.Server(spec, 2 << 30, peak_capacity=1 << 16, max_hits=9000, max_batch=4, n_streams=2, queue_depth=16) as srv:
+        for group in (range(0, 3), range(3, 7), range(7, 8)):
+            say("served", [sizes[i] for i in group])
+            tickets = [srv.submit(*evs[i]) for i in group]
+            for i, t in zip(group, tickets):
+                deadline = time.time() + 60
+                while (r := srv.poll(t)) is None:
+                    assert time.time() < deadline
+                    time.sleep(1e-4)
+                M, c, v, k = oracle_run(spec, evs[i])
+                assert r[2] == k and np.array_equal(r[0], c) and np.array_equal(r[1], v), i

@@ -1,5 +1,6 @@
 """What the calls would launch (ht_debug_launch_plan, decided on the host with the calls' own code):
-the no-alloc call's limit, and launch shapes that are read and set back. No GPU needed."""
+the no-alloc call's limit, launch shapes that are read and set back, and batches whose launches are
+chosen by their own events. No GPU needed."""
 import pytest
 
 from paper_1507_03074_amd import binding as B
@@ -118,6 +119,34 @@ def test_setting_the_reported_shape_changes_no_launch(lib, grid, fields):
         assert plans(spec) == unset
     finally:
         B.ht_set_tuning(spec)
+
+
+def test_batches_are_searched_by_their_own_largest_event(lib):
+    """The stencil's threshold, long or short lists and the tile height of a batch go by its largest
+    event, not by a rounded number of hits; with one event from the stencil's threshold on (2.5 times
+    the reported 16384, twice the reported 4096), all from the reported one on take it."""
+    paper, small = synth.GridSpec(4, 16, 1024, 1024, threshold=9), synth.GridSpec(4, 16, 256, 256, threshold=8)
+
+    def plan(spec, sizes, call="batch"):
+        return B.ht_debug_launch_plan(spec, sizes, call)
+    assert plan(paper, [33000, 30000, 20000, 5000])["n_stencil"] == 0
+    assert plan(paper, [40959, 30000, 20000, 5000])["n_stencil"] == 0
+    assert plan(paper, [40960, 30000, 16384, 16383])["n_stencil"] == 3
+    assert plan(small, [4500, 4200, 4100, 300])["n_stencil"] == 0
+    p = plan(small, [6585] * 7)
+    assert p["n_stencil"] == 0 and p["n_lists"] == 0 and not p["long_lists"]  # masks of the short-list fill
+    assert plan(small, [8191] * 7)["n_stencil"] == 0 and plan(small, [8192] + [4096] * 6)["n_stencil"] == 7
+    for n in (8193, 9000, 10922):
+        p = plan(paper, [n] * 8)
+        assert not p["long_lists"] and p["rows"] == plan(paper, [n])["rows"] == 4, n
+    assert plan(paper, [10923] * 8)["long_lists"]
+    for spec, sizes in ((paper, [9000] * 8), (small, [3000] * 20), (paper, [42000, 20000])):
+        assert plan(spec, sizes) == plan(spec, sizes[::-1])
+    # a request loop's batches, whatever the largest event that it may get
+    for max_hits, want in ((40000, 0), (41000, 0), (60000, 0)):
+        assert plan(paper, [max_hits] + [20000] * 8, "serve")["n_stencil"] == want, max_hits
+    assert plan(paper, [60000] + [20000] * 7 + [45000], "serve")["n_stencil"] == 8
+    assert plan(paper, [60000, 20000], "serve")["n_stencil"] == 0
 
 
 def test_launch_plan_validated_on_host(lib):
