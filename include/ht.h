@@ -123,15 +123,15 @@ typedef struct ht_tuning {
                            instead of testing the fill's survivors; -1 never. The default
                            reported is n_theta n_phi n_b / 4 hits (16384 on the
                            4x16x1024x1024 grid), where the stencil starts to beat a test of
-                           every candidate; with it, the library takes the stencil from
-                           twice that many hits, or 2.5 times (matrices of 128 MiB or more),
-                           where it beats a test of the survivors. A batch with such an event
-                           takes it for all its events from the reported number on. The stencil
-                           needs LDS
-                           fill tiles, at most 4 theta and 16 phi cells (one wave per phi cell
-                           holds every theta cell's row), and theta cell 0's row and the last
-                           one's less than 2^31 bytes apart; ht_get_tuning reports -1 where it
-                           is unavailable. */
+                           every candidate; with it, the library takes the stencil where it
+                           beats a test of the survivors: from twice that many hits, or 2.5
+                           times (matrices of 128 MiB or more), at thresholds of nine votes and
+                           more, from fewer below, at least the reported number. A batch with
+                           such an event takes it for all its events from the reported number
+                           on. The stencil needs LDS fill tiles, at most 4 theta and 16 phi
+                           cells (one wave per phi cell holds every theta cell's row), and theta
+                           cell 0's row and the last one's less than 2^31 bytes apart;
+                           ht_get_tuning reports -1 where it is unavailable. */
 } ht_tuning;
 
 /* ht_set_tuning: use `tuning` for every later call on grids with these dimensions and ranges

@@ -1756,6 +1756,10 @@ bool use_lists(const DevGrid& g, int n_ev, int64_t max_hits, int64_t hits)
   // 42; twelve of 8000 on the paper grid (0.1 per cell) 569 and 619.
   const double ratio = 4.0 * (double)hits / ((double)g.n_slabs * g.n_b), cube = ratio * ratio * ratio;
   const double cells = (double)g.n_slabs * g.n_a * g.n_b;
+  // At a threshold of one vote most cells of a vote survive. Lists and masks, in us: 4x16x256x256, 32
+  // hits (B 32768) 53 and 40, eight (8192) 25 and 28; 4x16x128x128, 32 hits (16384) 42 and 37, 250 (128000)
+  // 59 and 46; 4x16x512x512, 16 hits (32768) 34 and 36, 32 hits 62 and 50.
+  if (g.threshold == 1 && (double)hits * (g.phi_sectors ? 2 : 4) * g.n_a * n_ev > 30e3) return false;
   if (cube > 0.5 && cube * cells * n_ev > 20e6) return false;
   return cube * cells <= 48e6;
 }

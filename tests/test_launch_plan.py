@@ -149,6 +149,30 @@ def test_batches_are_searched_by_their_own_largest_event(lib):
     assert plan(paper, [60000, 20000], "serve")["n_stencil"] == 0
 
 
+def test_low_thresholds_are_left_to_the_stencil_earlier(lib):
+    """The hits from which the stencil takes an event, by threshold: the reported number up to four
+    votes, 2 or 2.5 times it from eight or nine on; one vote per cell also keeps survivors off the
+    lists."""
+    for grid, d, steps in (((4, 16, 1024, 1024), 16384, {1: 1, 3: 1, 4: 1, 5: 4 / 3, 7: 2, 8: 7 / 3, 9: 2.5, 100: 2.5}),
+                           ((4, 16, 256, 256), 4096, {1: 1, 4: 1, 6: 1, 7: 1.5, 8: 2, 9: 2, 100: 2}),
+                           ((1, 3, 256, 256), 192, {1: 1, 6: 1, 8: 2})):
+        for T, f in steps.items():
+            spec = synth.GridSpec(*grid, threshold=T)
+            assert B.ht_get_tuning(spec).dense_hits == d
+            n = int(d * f)
+            assert B.ht_debug_launch_plan(spec, [n - 1])["n_stencil"] == 0, (grid, T)
+            assert B.ht_debug_launch_plan(spec, [n])["n_stencil"] == 1, (grid, T)
+            B.ht_set_tuning(spec, dense_hits=d + 5)
+            try:
+                assert [B.ht_debug_launch_plan(spec, [k])["n_stencil"] for k in (d + 4, d + 5)] == [0, 1]
+            finally:
+                B.ht_set_tuning(spec)
+    spec = synth.GridSpec(4, 16, 256, 256, threshold=1)
+    assert [B.ht_debug_launch_plan(spec, [n])["n_lists"] for n in (8, 29, 30, 250)] == [1, 1, 0, 0]
+    assert B.ht_debug_launch_plan(spec, [8] * 4, "batch")["n_lists"] == 0
+    assert B.ht_debug_launch_plan(synth.GridSpec(4, 16, 256, 256, threshold=2), [250])["n_lists"] == 1
+
+
 def test_launch_plan_validated_on_host(lib):
     spec = synth.WORKLOADS[0].grid
     for bad in ([], [-1], [5, 5], [1 << 29]):
