@@ -55,6 +55,7 @@ constexpr uint32_t kSegMax = 1024;
 constexpr uint32_t kSuperStep = 32;  // words: a cache line each
 // Few peaks: at most this many cells can reach the threshold (each of the lists holds as many).
 constexpr uint32_t kFewCells = 8192;
+constexpr int64_t kFewHits = 65535;  // and hits
 static_assert(kFewCells <= kListCap, "no list overflows where so few cells reach the threshold");
 constexpr int kTinyHits = 1024;  // of an event that takes two launches (tiny_launch)
 

@@ -886,7 +886,8 @@ template <bool NARROW>
 __global__ __launch_bounds__(1024) void k_few_peaks(DevGrid g, EvDesc ev0, const EvDesc* evs)
 {
   __shared__ __align__(16) uint32_t s_c[kFewCells + 4];
-  __shared__ uint16_t s_v[kFewCells];  // votes: at most kTinyHits
+  __shared__ uint16_t s_v[kFewCells];  // votes: at most one per hit
+  static_assert(kFewHits <= 0xffff, "the counts of an event with few cells have 16 bits");
   __shared__ uint32_t s_n;
   EvDesc e = load_ev(ev0, evs);
   const bool a8 = ((uintptr_t)e.out & 7u) == 0;
@@ -1782,8 +1783,13 @@ static size_t tiny_lds_bytes(const DevGrid& g)
 bool few_cells(const DevGrid& g, int64_t max_hits)
 {
   // A hit votes once per A row and cell, so hits * cells * n_a / threshold cells reach the threshold
-  // at most. (The counts have 16 bits in the kernel.)
-  return max_hits <= 65535 && max_hits * (g.phi_sectors ? 2 : 4) * g.n_a / (int64_t)g.threshold <= kFewCells;
+  // at most, and in ordinary events far fewer, unless one or two votes are enough: then most of them
+  // do, more than one workgroup tests in the time of two launches. One workgroup and the general
+  // search from lists, in us: T 1, 4x16x64x64, one hit (bound 256) 12 and 15, two 19 and 17, 32 (8192)
+  // 59 and 18; two hits on 4x16x1024x1024 (8192) 179 and 51; T 2, 4x16x64x64, 32 hits (4096) 15 and
+  // 16, 64 (8192) 28 and 17; T 3, 64 hits (5461) 15.4 and 16.6; T 4, 128 (8192) 16.5 and 17.0.
+  const int64_t limit = g.threshold == 1 ? 256 : g.threshold == 2 ? kFewCells / 2 : kFewCells;
+  return max_hits <= kFewHits && max_hits * (g.phi_sectors ? 2 : 4) * g.n_a / (int64_t)g.threshold <= limit;
 }
 
 bool tiny_launch(const DevGrid& g, int n_ev, int64_t max_hits)

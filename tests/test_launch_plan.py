@@ -173,6 +173,18 @@ def test_low_thresholds_are_left_to_the_stencil_earlier(lib):
     assert B.ht_debug_launch_plan(synth.GridSpec(4, 16, 256, 256, threshold=2), [250])["n_lists"] == 1
 
 
+def test_one_workgroup_searches_few_cells_only(lib):
+    """The one-workgroup search takes events that leave at most 8192 cells at the threshold, 4096 at
+    two votes and 256 at one."""
+    for (grid, T), sizes in ((((4, 16, 64, 64), 1), {1: 1, 2: 0, 32: 0}), (((4, 16, 64, 64), 2), {32: 1, 33: 0, 64: 0}),
+                             (((4, 16, 64, 64), 3), {96: 1, 97: 0}), (((4, 16, 64, 64), 8), {250: 1, 256: 1, 257: 0}),
+                             (((4, 16, 1024, 1024), 1), {1: 0, 2: 0}), (((2, 4, 16, 14336), 1), {4: 1, 5: 0, 128: 0})):
+        for n, few in sizes.items():
+            spec = synth.GridSpec(*grid, threshold=T)
+            for plan in (B.ht_debug_launch_plan(spec, [n]), B.ht_debug_launch_plan(spec, [n] * 3, "batch")):
+                assert plan["few"] == few and plan["tiny"] <= few, (grid, T, n)
+
+
 def test_launch_plan_validated_on_host(lib):
     spec = synth.WORKLOADS[0].grid
     for bad in ([], [-1], [5, 5], [1 << 29]):
