@@ -210,21 +210,21 @@ Tiling choose_tiling(const ht_grid& g)
   // The reported default, n_slabs n_b / 4 hits (a quarter of a hit per (theta, phi, B) cell), is
   // where one pass over the matrix beats a test of every candidate. The survivors are a quarter of
   // them, so unless the caller sets a threshold the stencil starts later: at twice that for peaks of
-  // eight votes or more, 2.5 times (nine votes) in matrices of 128 MiB or more, where a pass is long.
+  // seven votes or more, 2.5 times (nine votes) in matrices of 128 MiB or more, where a pass is long.
   // Peaks of fewer votes have many more survivors, and the stencil's time does not depend on them.
   // Whole calls, survivors against stencil, in us, by the threshold T and multiples of the default:
   // 4x16x1024x1024 T 9: x2 104 / 129, x2.5 127 / 136; T 8: x2 111 / 130, x2.5 145 / 136; T 7: x1.5
   // 108 / 129, x2 122 / 130, x2.5 187 / 137; T 6: x1.5 118 / 130, x2 143 / 131; T 5: x1.05 116 / 130,
   // x1.5 139 / 130; T 4: x1.05 131 / 131; T 3: x1.1 210 / 131. 4x16x512x512 T 8: x2 52 / 52, x2.5
-  // 64 / 54; T 7: x1.5 51 / 51, x2.5 67 / 54; T 5: x1.05 54 / 50, x1.5 65 / 53. 4x16x256x256 T 8: x2
-  // 34 / 42, x2.5 48 / 44; T 6: x1.5 42 / 42, x2 49 / 44. At x2 and T 8 on 2x8x512x512 30 / 34,
+  // 64 / 54; T 7: x2 54 / 53, x2.5 67 / 54; T 5: x1.05 54 / 50, x1.5 65 / 53. 4x16x256x256 T 8: x2
+  // 34 / 42, x2.5 48 / 44; T 7: x2 36 / 43; T 6: x1.5 42 / 42, x2 49 / 44; T 5, x1.1 62 / 42. At x2 and T 8 on 2x8x512x512 30 / 34,
   // 3x7x501x333 31 / 33, 3x12x900x200 42 / 41, 2x16x300x900 36 / 45, 1x3x256x256 22 / 23, sectors
   // 4x4x1024x1024 38 / 42; sixteen events of 4x16x256x256 160 / 154, 4x16x128x128 68 / 67. -1: never
   const int64_t def = ((int64_t)g.n_theta * g.n_phi * g.n_b + 3) / 4;
   const int64_t bytes = 4 * (int64_t)g.n_theta * g.n_phi * g.n_a * g.n_b;
   const int64_t T = std::min<int64_t>(g.threshold, 16);
   int64_t dh = def, from = bytes >= ((int64_t)128 << 20) ? std::min(def * (T - 1) / 3, def * 5 / 2)
-                                                         : std::min(def * (T - 4) / 2, def * 2);
+                                                         : std::min(def * (T - 3) / 2, def * 2);
   from = std::max(from, def);
   const int forced_dh = env_int("HT_DENSE_HITS", 0);
   if (forced_dh != 0) dh = from = forced_dh;

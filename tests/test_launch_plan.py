@@ -151,11 +151,11 @@ def test_batches_are_searched_by_their_own_largest_event(lib):
 
 def test_low_thresholds_are_left_to_the_stencil_earlier(lib):
     """The hits from which the stencil takes an event, by threshold: the reported number up to four
-    votes, 2 or 2.5 times it from eight or nine on; one vote per cell also keeps survivors off the
+    votes, 2 or 2.5 times it from seven or nine on; one vote per cell also keeps survivors off the
     lists."""
     for grid, d, steps in (((4, 16, 1024, 1024), 16384, {1: 1, 3: 1, 4: 1, 5: 4 / 3, 7: 2, 8: 7 / 3, 9: 2.5, 100: 2.5}),
-                           ((4, 16, 256, 256), 4096, {1: 1, 4: 1, 6: 1, 7: 1.5, 8: 2, 9: 2, 100: 2}),
-                           ((1, 3, 256, 256), 192, {1: 1, 6: 1, 8: 2})):
+                           ((4, 16, 256, 256), 4096, {1: 1, 4: 1, 5: 1, 6: 1.5, 7: 2, 8: 2, 100: 2}),
+                           ((1, 3, 256, 256), 192, {1: 1, 5: 1, 8: 2})):
         for T, f in steps.items():
             spec = synth.GridSpec(*grid, threshold=T)
             assert B.ht_get_tuning(spec).dense_hits == d
