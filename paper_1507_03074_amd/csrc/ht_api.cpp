@@ -320,14 +320,14 @@ static void shape_launch(DevGrid* d, const Tiling& tl, int n_ev, int64_t max_hit
     while (low > 4 && (int64_t)low * d->n_b * 4 > 16384) low /= 2;
     const bool many = (int64_t)d->n_slabs * ((d->n_a + 7) / 8) * n_ev > 10000;
     d->rows = std::min(rows, 8);
-    if ((low > 8 && many) || !long_lists(*d, max_hits)) {
+    if ((low > 8 && many) || !long_lists(*d, n_ev, max_hits)) {
       d->rows = low;
       while (d->rows > 8 && (int64_t)d->n_slabs * ((d->n_a + d->rows - 1) / d->rows) * n_ev < 256) d->rows /= 2;
     }
     d->tiles_per_slab = (d->n_a + d->rows - 1) / d->rows;
     d->n_tiles = d->n_slabs * d->tiles_per_slab;
   }
-  const bool long_l = tl.lds_fill && long_lists(*d, max_hits);
+  const bool long_l = tl.lds_fill && long_lists(*d, n_ev, max_hits);
   if (tl.auto_nt) {
     // Non-temporal stores where the launch writes more than the 256 MiB last-level cache holds (100
     // paper events: 4.5 and 5.3 ms), or the fill is not what waits for its stores: long lists and
@@ -351,7 +351,7 @@ int32_t stencil_from(const Tiling& tl, int n_ev, int64_t max_hits)
   return n_ev > 1 && tl.dense_from > 0 && max_hits >= tl.dense_from ? tl.dense_hits : tl.dense_from;
 }
 
-DevGrid make_devgrid(const ht_grid& g, const DevTables& t, const Tiling& tl, int n_ev, int64_t max_hits)
+DevGrid make_devgrid(const ht_grid& g, const DevTables& t, const Tiling& tl, int n_ev, int64_t max_hits, bool search)
 {
   DevGrid d;
   std::memset(&d, 0, sizeof(d));  // padding too: the bytes key the graph cache
@@ -377,6 +377,7 @@ DevGrid make_devgrid(const ht_grid& g, const DevTables& t, const Tiling& tl, int
   // finite and not 0, so B is no NaN; and neither is (B - b_min) inv_db while inv_db is finite
   d.finite_votes = std::max(std::fabs((double)g.a_min), std::fabs((double)g.a_max)) <= std::ldexp(1.0, 59) &&
                    std::isfinite((float)((double)g.n_b / ((double)g.b_max - (double)g.b_min))) ? 1 : 0;
+  d.search = search ? 1 : 0;
   d.dense_w = tl.dense_w;
   d.dense_rows = tl.dense_rows;
   d.dense_hits = stencil_from(tl, n_ev, max_hits);
@@ -643,7 +644,7 @@ int ensure_ev_staging(Workspace* w, int n_ev, hipStream_t s)
   return HT_OK;
 }
 
-int make_device_grid(const ht_grid& g, int dev, int n_ev, int64_t max_hits, DevGrid* out, Tiling* tl)
+int make_device_grid(const ht_grid& g, int dev, int n_ev, int64_t max_hits, DevGrid* out, Tiling* tl, bool search)
 {
   int rc = validate_grid(&g);
   if (rc) return rc;
@@ -651,7 +652,7 @@ int make_device_grid(const ht_grid& g, int dev, int n_ev, int64_t max_hits, DevG
   if ((rc = get_tables(g, dev, &t))) return rc;
   const Tiling tiling = choose_tiling(g);
   if (tl) *tl = tiling;
-  *out = make_devgrid(g, t, tiling, n_ev, max_hits);
+  *out = make_devgrid(g, t, tiling, n_ev, max_hits, search);
   return HT_OK;
 }
 
@@ -713,13 +714,13 @@ struct Prepared {
   hipStream_t s;
 };
 
-int prepare(const ht_grid* grid, void* stream, Prepared* p, int n_ev, int64_t max_hits)
+int prepare(const ht_grid* grid, void* stream, Prepared* p, int n_ev, int64_t max_hits, bool search = true)
 {
   int rc = validate_grid(grid);
   if (rc) return rc;
   hipError_t e = hipGetDevice(&p->dev);
   if (e != hipSuccess) return fail_hip(e, "hipGetDevice");
-  if ((rc = make_device_grid(*grid, p->dev, n_ev, max_hits, &p->g))) return rc;
+  if ((rc = make_device_grid(*grid, p->dev, n_ev, max_hits, &p->g, nullptr, search))) return rc;
   p->s = (hipStream_t)stream;
   return HT_OK;
 }
@@ -745,7 +746,7 @@ BatchShape batch_shape(const DevGrid& g, int n_ev, int64_t max_hits, bool any_de
 {
   BatchShape b;
   b.prep_hits = max_hits;
-  b.long_l = g.lds_fill && long_lists(g, max_hits);
+  b.long_l = g.lds_fill && long_lists(g, n_ev, max_hits);
   b.tiny = !any_dense && pieces == 1 && tiny_launch(g, n_ev, max_hits);
   b.few = !any_dense && pieces == 1 && g.lds_fill && few_cells(g, max_hits) && use_lists(g, n_ev, max_hits, max_hits);
   return b;
@@ -921,7 +922,7 @@ int enqueue_event(const DevGrid& g, const EvDesc& ev, int64_t nh, bool direct, b
       if ((rc = check_launch(launch_fill_atomic(g, ev, nullptr, 1, nh, s), "fill launch"))) return rc;
     } else {
       HT_STAGE(t, "fill");
-      if ((rc = check_launch(launch_fill(g, ev, nullptr, 1, do_peaks && !ev.dense, long_lists(g, nh), s), "fill launch"))) return rc;
+      if ((rc = check_launch(launch_fill(g, ev, nullptr, 1, do_peaks && !ev.dense, long_lists(g, 1, nh), s), "fill launch"))) return rc;
     }
   }
   if (do_peaks) {
@@ -955,7 +956,7 @@ int run_event(const ht_grid* grid, const float* x, const float* y, const float* 
     return fail(HT_EINVAL, "peak output arguments are invalid");
   if (n > ((int64_t)1 << 28)) return fail(HT_EINVAL, "n_hits must be <= 2^28");
   Prepared p;
-  int rc = prepare(grid, stream, &p, 1, do_fill ? n : 0);
+  int rc = prepare(grid, stream, &p, 1, do_fill ? n : 0, do_peaks);
   if (rc) return rc;
   if (do_peaks && ((rc = check_accessible(out, "out")) || (rc = check_accessible(n_found, "n_found"))))
     return rc;

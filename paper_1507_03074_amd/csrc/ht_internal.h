@@ -76,6 +76,7 @@ struct DevGrid {
   int32_t fill_tiles;      // fill tiles per workgroup (filled in turn)
   int32_t phi_sectors;     // 1: phi cells are independent sectors (no phi widening or neighbours)
   int32_t packed_lists;    // 1: always the counting-sort (packed) slab lists, never direct ones
+  int32_t search;          // 1: the launch searches the fill's survivors (0: a fill alone)
   int32_t finite_votes;    // 1: no vote of a hit with finite 1/(2y) is NaN (bounded A, finite inv_db)
   int32_t dense_w;         // 1: the stencil peak search is available on this grid (0: not)
   int32_t dense_rows;      // A rows per workgroup of the stencil peak search (a multiple of 12)
@@ -154,8 +155,9 @@ inline size_t th_floats(const ht_grid& g) { return 2 * (2 * (size_t)g.n_theta + 
 // The tables computed on the host in double and rounded once to float, into caller arrays of
 // the sizes above.
 void host_tables_into(const ht_grid& g, float* a2, float* inv_db, float* phi, float* th);
-// n_ev, max_hits: what the launches it is for hold.
-DevGrid make_devgrid(const ht_grid& g, const DevTables& t, const Tiling& tl, int n_ev, int64_t max_hits);
+// n_ev, max_hits: what the launches it is for hold; search: whether they search for peaks.
+DevGrid make_devgrid(const ht_grid& g, const DevTables& t, const Tiling& tl, int n_ev, int64_t max_hits,
+                     bool search = true);
 // The hits from which the events of a launch of n_ev events of up to max_hits hits take the stencil
 // (DevGrid::dense_hits; 0: none).
 int32_t stencil_from(const Tiling& tl, int n_ev, int64_t max_hits);
@@ -221,7 +223,7 @@ hipError_t launch_readout(const DevGrid& g, const ht_peak* peaks, const int64_t*
 // an event of `hits` hits. (If it does for one, it does for those of fewer hits.)
 bool use_lists(const DevGrid& g, int n_ev, int64_t max_hits, int64_t hits);
 // Whether that fill takes its long-list variant (given g.rows).
-bool long_lists(const DevGrid& g, int64_t max_hits);
+bool long_lists(const DevGrid& g, int n_ev, int64_t max_hits);
 size_t fill_lds_bytes(const DevGrid& g, bool long_l);
 int n_groups(const DevGrid& g);
 
@@ -252,7 +254,8 @@ int fail_hip(hipError_t e, const char* what);
 int validate_grid(const ht_grid* g);
 uint64_t n_cells(const ht_grid& g);
 // Validates the grid, uploads its tables once per device and picks the tiling.
-int make_device_grid(const ht_grid& g, int dev, int n_ev, int64_t max_hits, DevGrid* out, Tiling* tl = nullptr);
+int make_device_grid(const ht_grid& g, int dev, int n_ev, int64_t max_hits, DevGrid* out, Tiling* tl = nullptr,
+                     bool search = true);
 // What a batch of n_ev events of up to max_hits hits launches, besides what g says.
 struct BatchShape {
   int64_t prep_hits;  // that the preparation's grid is made for: at least max_hits

@@ -30,6 +30,7 @@
 // Every floating-point step of the bin rule is one binary32 operation, rounded to nearest even,
 // in the documented order: contraction is off for this file, sqrtf and the division are the
 // correctly rounded forms.
+#include <cmath>
 #include <cstdlib>
 
 #include "ht_device.h"
@@ -1735,19 +1736,40 @@ hipError_t launch_prep(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, i
   return hipGetLastError();
 }
 
-bool long_lists(const DevGrid& g, int64_t max_hits)
+// A measure of the survivors of an event at a threshold of nine votes or so: the cube of its hits per
+// (slab, B) column, times the cells.
+static double survivor_measure(const DevGrid& g, int64_t hits, double* per_cell)
+{
+  const double ratio = 4.0 * (double)hits / ((double)g.n_slabs * g.n_b);
+  *per_cell = ratio * ratio * ratio;
+  return *per_cell * (double)g.n_slabs * g.n_a * g.n_b;
+}
+
+bool long_lists(const DevGrid& g, int n_ev, int64_t max_hits)
 {
   // more than two records per thread of the short-list fill expected per slab (a hit has at most
   // four cells, about three on average), in tiles narrow enough for it to matter; and votes that
   // are never NaN, which the long-list fill cannot tell from bin 0
-  return g.rows <= 8 && g.finite_votes && max_hits * 3 > (int64_t)2 * kBlock * g.n_slabs;
+  const int64_t longest = (int64_t)2 * kBlock * g.n_slabs;
+  if (g.rows > 8 || !g.finite_votes || max_hits * 3 <= longest) return false;
+  if (!g.search || dense_peaks(g, max_hits)) return true;
+  // Lists of up to six times that whose events leave few survivors (more at low thresholds) stay with
+  // the short-list fill: it lists the survivors, and their test takes half the time of the masks'.
+  // Short and long, whole calls in us: 2700 hits on 2x4x256x9000 27.8 and 34.7, 5461 (5e5) 30.9 and
+  // 34.7; 2048 on 1x3x2000x5000 (5e6) 34 and 47; 2785 on sectors 4x4x1024x1024 (5e6) 29.5 and 33.8;
+  // 5461 on 2x4x256x2500 (7e6) 25.4 and 26.1, 10922 (53e6, eight times as long) 31.4 and 29.0; 11141 on
+  // 4x16x1024x1024 (21e6) 65 and 69, 13107 (34e6) 76 and 72; T 3, 2048 on 2x4x256x9000 (3e4) 31 and 39,
+  // 5461 58 and 45; T 2, 2048 65 and 47.
+  double per_cell;
+  const double low = std::max(1.0, 9.0 / g.threshold);
+  return max_hits * 3 > 6 * longest || survivor_measure(g, max_hits, &per_cell) * n_ev * std::pow(low, 5) > 12e6;
 }
 
 bool use_lists(const DevGrid& g, int n_ev, int64_t max_hits, int64_t hits)
 {
   // The long-list fill makes none: with the code for them it spills registers (a 14142-hit event's
   // fill took 68 us, not 55, and its test 23 us, not 24).
-  if (long_lists(g, max_hits)) return false;
+  if (long_lists(g, n_ev, max_hits)) return false;
   // Survivors come about as the cube of the hits per (slab, B) column, times the cells: on the paper
   // grid 2.7k at 5000 hits, 46k at 14142, 661k at 40000. They must fit the lists, 65k. And where a
   // job has several, the masks' test of a cell per lane is the faster one, once the launch is more
@@ -1755,14 +1777,14 @@ bool use_lists(const DevGrid& g, int n_ev, int64_t max_hits, int64_t hits)
   // of them 58 and 46, one (18e6) 34 and 31; 16 of 4000 135 and 116; 20 of 2500 on 4x16x128x128 83
   // and 64; 14 of 1139 on 4x4x130x259 (10e6) 39.5 and 43; one of 8000 on 4x16x512x512 (16e6) 39 and
   // 42; twelve of 8000 on the paper grid (0.1 per cell) 569 and 619.
-  const double ratio = 4.0 * (double)hits / ((double)g.n_slabs * g.n_b), cube = ratio * ratio * ratio;
-  const double cells = (double)g.n_slabs * g.n_a * g.n_b;
+  double cube;
+  const double measure = survivor_measure(g, hits, &cube);
   // At a threshold of one vote most cells of a vote survive. Lists and masks, in us: 4x16x256x256, 32
   // hits (B 32768) 53 and 40, eight (8192) 25 and 28; 4x16x128x128, 32 hits (16384) 42 and 37, 250 (128000)
   // 59 and 46; 4x16x512x512, 16 hits (32768) 34 and 36, 32 hits 62 and 50.
   if (g.threshold == 1 && (double)hits * (g.phi_sectors ? 2 : 4) * g.n_a * n_ev > 30e3) return false;
-  if (cube > 0.5 && cube * cells * n_ev > 20e6) return false;
-  return cube * cells <= 48e6;
+  if (cube > 0.5 && measure * n_ev > 20e6) return false;
+  return measure <= 48e6;
 }
 
 hipError_t launch_fill(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev,

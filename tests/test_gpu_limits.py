@@ -127,3 +127,23 @@ def test_request_loop_with_few_crowded_events(B):
                     time.sleep(1e-4)
                 M, c, v, k = oracle_run(spec, evs[i])
                 assert r[2] == k and np.array_equal(r[0], c) and np.array_equal(r[1], v), i
+
+
+@pytest.mark.parametrize("grid,threshold,sizes", [((2, 4, 40, 2500), 4, (1300, 1400, 2700, 8192, 8193)),
+                                                  ((1, 3, 50, 333), 9, (512, 513, 1500)),
+                                                  ((1, 3, 33, 14000), 3, (600, 2048, 2049))],
+                         ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_moderately_long_slab_lists(B, grid, threshold, sizes):
+    """Slab lists of one to six times the short-list fill's 512 records in registers, and more: either
+    fill, single events and batches."""
+    spec = synth.GridSpec(*grid, threshold=threshold)
+    evs = [hits(30, n) for n in sizes]
+    want = [oracle_run(spec, ev) for ev in evs]
+    for n, ev, (M, c, v, k) in zip(sizes, evs, want):
+        say(grid, "hits", n, "long", B.ht_debug_launch_plan(spec, [n])["long_lists"])
+        acc, gc, gv, gk = B.fill_peaks(spec, *B.hits_to_device(*ev))
+        assert np.array_equal(B.as_u32(acc), M) and gk == k and np.array_equal(gc, c) and np.array_equal(gv, v), n
+    res = B.fill_peaks_batch(spec, evs)
+    for i, (M, c, v, k) in enumerate(want):
+        assert np.array_equal(B.as_u32(res.acc[i]), M), i
+        assert res.peaks[i][2] == k and np.array_equal(res.peaks[i][0], c) and np.array_equal(res.peaks[i][1], v), i

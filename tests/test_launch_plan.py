@@ -185,6 +185,22 @@ def test_one_workgroup_searches_few_cells_only(lib):
                 assert plan["few"] == few and plan["tiny"] <= few, (grid, T, n)
 
 
+def test_long_slab_lists_with_few_survivors_keep_the_survivor_lists(lib):
+    """Events of a few slabs, of more than 512 records each, but with few survivors: the short-list fill
+    and the search from lists, as for shorter ones; the long-list fill where survivors are many, at low
+    thresholds sooner, and past six times that length."""
+    for grid, T, sectors, sizes in (((2, 4, 256, 9000), 9, False, {1300: 0, 1392: 0, 2700: 0, 7200: 0, 8192: 0, 8193: 1}),
+                                    ((2, 4, 256, 9000), 3, False, {1392: 0, 2048: 0, 3413: 1}),
+                                    ((1, 3, 2000, 5000), 9, False, {522: 0, 2048: 0, 3000: 1}),
+                                    ((4, 4, 1024, 1024), 9, True, {2785: 0, 3276: 0, 4000: 1, 5000: 1}),
+                                    ((4, 16, 1024, 1024), 9, False, {10922: 0, 10923: 1, 14142: 1}),
+                                    ((2, 4, 256, 9000), 1, False, {1300: 0, 1392: 1})):
+        for n, long_l in sizes.items():
+            spec = synth.GridSpec(*grid, threshold=T, phi_sectors=sectors)
+            plan = B.ht_debug_launch_plan(spec, [n])
+            assert plan["long_lists"] == long_l and plan["n_lists"] == (0 if long_l or T == 1 else 1), (grid, T, n)
+
+
 def test_launch_plan_validated_on_host(lib):
     spec = synth.WORKLOADS[0].grid
     for bad in ([], [-1], [5, 5], [1 << 29]):
