@@ -456,6 +456,24 @@ static size_t group_words(const DevGrid& g, int peaks)
   return std::max<size_t>((peaks & kPeakBands) ? (size_t)g.j.n_groups * g.j.pk_step : 0, (peaks & kPeakMask) ? (size_t)n_groups(g) : 0);
 }
 
+// Entries of a survivor list of an event of up to n hits (below 0: unknown). Of few cells all fit the
+// one list. Else the lists hold one in 32 of the matrix's cells in all, or a quarter of those that can
+// reach the threshold where that is more, and none more than can; past that, and past kListCap a
+// list, the search works from the masks.
+static uint32_t surv_cap(const DevGrid& g, int64_t n, int peaks)
+{
+  const int64_t cells = (int64_t)g.n_slabs * g.n_a * g.n_b;
+  const int64_t bound = n < 0 ? cells : std::min(cells, cells_bound(g, n));
+  if (peaks & kPeakFew) return (uint32_t)std::max<int64_t>(1, std::min<int64_t>(bound, kFewCells));
+  const int64_t share = std::max(cells / 32, bound / 4) / kLists;
+  return (uint32_t)std::max<int64_t>(8, std::min<int64_t>(std::min(bound, share), kListCap));
+}
+
+size_t surv_bytes(const DevGrid& g, int64_t n, int peaks)
+{
+  return al(16 * (size_t)(peaks & kPeakFew ? 1 : kLists) * surv_cap(g, n, peaks));
+}
+
 size_t event_scratch_bytes(const DevGrid& g, int64_t n, bool direct, int peaks)
 {
   const size_t nn = (size_t)std::max<int64_t>(n, 0);
@@ -469,13 +487,12 @@ size_t event_scratch_bytes(const DevGrid& g, int64_t n, bool direct, int peaks)
     b += al(16 * nn);                         // hit_rec
     b += al(64 * nn + 16);                    // list (+1 record of slack for the fill)
   }
-  if (peaks) b += al(4 * group_words(g, peaks));  // group_pk
+  if (peaks & (kPeakBands | kPeakMask)) b += al(4 * group_words(g, peaks));  // group_pk
   if (peaks & kPeakBands) {
-    b += al(4 * kSuperStep * (((size_t)g.j.n_groups + 63) / 64)) + al(g.j.n_jobs);  // super_pk, job_any
-    b += al(16 * (size_t)kLists * kListCap);                              // surv
-    b += al((size_t)64 * g.j.elem_bytes * g.j.n_jobs);                 // masks
-    b += al(8 * (size_t)g.j.seg * g.j.n_groups);                       // seg
+    b += al(4 * kSuperStep * (((size_t)g.j.n_groups + 63) / 64));  // super_pk
+    b += al(8 * (size_t)g.j.seg * g.j.n_groups);                   // seg
   }
+  if (peaks & (kPeakBands | kPeakFew)) b += al(g.j.n_jobs) + al((size_t)64 * g.j.elem_bytes * g.j.n_jobs) + surv_bytes(g, n, peaks);
   if (peaks & kPeakMask) b += al(mask_bytes(g));  // pk_mask
   return b;
 }
@@ -502,10 +519,10 @@ void carve_event_scratch(const DevGrid& g, int64_t n, bool direct, char* p, EvDe
     ev->hit_rec = (float4*)take(16 * nn);
     ev->list = (float4*)take(64 * nn + 16);
   }
-  carve_peak_scratch(g, p, ev, peaks, 0, g.j.n_groups);
+  carve_peak_scratch(g, n, p, ev, peaks, 0, g.j.n_groups);
 }
 
-void carve_peak_scratch(const DevGrid& g, char* p, EvDesc* ev, int peaks, uint32_t grp0, uint32_t n_grp)
+void carve_peak_scratch(const DevGrid& g, int64_t n_hits, char* p, EvDesc* ev, int peaks, uint32_t grp0, uint32_t n_grp)
 {
   auto take = [&p](size_t bytes) {
     char* r = p;
@@ -518,14 +535,17 @@ void carve_peak_scratch(const DevGrid& g, char* p, EvDesc* ev, int peaks, uint32
   ev->clear_n16 = 0;
   ev->lists = 0;
   if (peaks & kPeakBands) ev->super_pk = (uint32_t*)take(4 * kSuperStep * (((size_t)n_grp + 63) / 64));
-  if (peaks) ev->group_pk = (uint32_t*)take(4 * group_words(g, peaks));
-  if (peaks & kPeakBands) {
+  if (peaks & (kPeakBands | kPeakMask)) ev->group_pk = (uint32_t*)take(4 * group_words(g, peaks));
+  if (peaks & (kPeakBands | kPeakFew)) {
     ev->job_any = (uint8_t*)take(n);
     ev->masks = (uint8_t*)take((size_t)64 * g.j.elem_bytes * n);
+    ev->surv = (uint4*)take(surv_bytes(g, n_hits, peaks));
+    ev->lists = (peaks & kPeakFew ? 0u : (kLists - 1u) << kListShift) | surv_cap(g, n_hits, peaks);
+  }
+  if (peaks & kPeakBands) {
     ev->clear = ev->super_pk;
     ev->clear_n16 = (uint32_t)((ev->masks - (uint8_t*)ev->super_pk) / 16);
     ev->seg = (uint2*)take(8 * (size_t)g.j.seg * n_grp);
-    ev->surv = (uint4*)take(16 * (size_t)kLists * kListCap);
   }
   if (peaks & kPeakMask) ev->pk_mask = (uint8_t*)take(mask_bytes(g));
   if (peaks == kPeakMask) clear_groups(g, ev);
@@ -742,13 +762,24 @@ int injected_failure(const char* stage)
   return HT_OK;
 }
 
+size_t slot_scratch_bytes(const DevGrid& g, const Tiling& tl, int max_batch, int64_t max_hits, int* layout)
+{
+  const bool direct = direct_lists(g, max_hits), crowded = tl.dense_from > 0 && max_hits >= tl.dense_from;
+  if (!crowded && batch_shape(g, max_batch, max_hits, false, 1).few) {  // and so are smaller batches
+    *layout = kPeakFew;
+    return event_scratch_bytes(g, max_hits, direct, kPeakFew);
+  }
+  *layout = kPeakBands | (crowded ? kPeakMask : 0);
+  return std::max(event_scratch_bytes(g, max_hits, direct, *layout), event_scratch_bytes(g, max_hits, direct, kPeakFew));
+}
+
 BatchShape batch_shape(const DevGrid& g, int n_ev, int64_t max_hits, bool any_dense, int pieces)
 {
   BatchShape b;
   b.prep_hits = max_hits;
   b.long_l = g.lds_fill && long_lists(g, n_ev, max_hits);
   b.tiny = !any_dense && pieces == 1 && tiny_launch(g, n_ev, max_hits);
-  b.few = !any_dense && pieces == 1 && g.lds_fill && few_cells(g, max_hits) && use_lists(g, n_ev, max_hits, max_hits);
+  b.few = b.tiny || (!any_dense && pieces == 1 && g.lds_fill && few_cells(g, max_hits) && use_lists(g, n_ev, max_hits, max_hits));
   return b;
 }
 
@@ -868,10 +899,10 @@ int64_t batch_hits(int64_t max_hits)
 // their scratch totals at most 8 GiB, else the counting sort for all (the 16-event batch of
 // 105600-hit events on the 8x32x2048x2048 grid takes the counting sort). Returns whether the
 // lists are direct; offs[i] is event i's scratch offset, *total the bytes of all of them.
-bool plan_batch(const DevGrid& g, const ht_event* events, int n_events, std::vector<size_t>* offs,
-                size_t* total, int64_t* max_hits)
+bool plan_batch(const DevGrid& g, const ht_event* events, int n_events, bool few, std::vector<size_t>* offs,
+                size_t* total)
 {
-  auto layout = [&g](int64_t n) { return dense_peaks(g, n) ? kPeakMask : kPeakBands; };
+  auto layout = [&g, few](int64_t n) { return dense_peaks(g, n) ? kPeakMask : few ? kPeakFew : kPeakBands; };
   bool direct = g.lds_fill != 0;
   size_t direct_bytes = 0;
   for (int i = 0; i < n_events; ++i) {
@@ -881,9 +912,7 @@ bool plan_batch(const DevGrid& g, const ht_event* events, int n_events, std::vec
   if (direct_bytes > kBatchDirectMax) direct = false;
   offs->assign((size_t)n_events, 0);
   *total = 0;
-  *max_hits = 0;
   for (int i = 0; i < n_events; ++i) {
-    *max_hits = std::max(*max_hits, events[i].n_hits);
     (*offs)[i] = *total;
     *total += event_scratch_bytes(g, events[i].n_hits, direct, layout(events[i].n_hits));
   }
@@ -897,7 +926,8 @@ int enqueue_event(const DevGrid& g, const EvDesc& ev, int64_t nh, bool direct, b
 #define HT_STAGE(var, name) StageTimer var(timed ? name : nullptr, s)
   int rc;
   *counters_used = false;
-  if (do_fill && do_peaks && !atomic && !ev.dense && tiny_launch(g, 1, nh)) {
+  const bool few = do_fill && do_peaks && ev.lists != 0 && ev.lists >> kListShift == 0;
+  if (few && tiny_launch(g, 1, nh)) {
     if ((rc = injected_failure("prep")) || (rc = injected_failure("fill"))) return rc;
     {
       HT_STAGE(t, "fill");
@@ -935,7 +965,7 @@ int enqueue_event(const DevGrid& g, const EvDesc& ev, int64_t nh, bool direct, b
     HT_STAGE(t, "peaks");
     if (ev.dense) {
       if ((rc = check_launch(launch_peaks_dense(g, ev, nullptr, 1, s), "stencil peak launch"))) return rc;
-    } else if (do_fill && !atomic && ev.lists && few_cells(g, nh)) {
+    } else if (few) {
       if ((rc = check_launch(launch_few_peaks(g, ev, nullptr, 1, s), "peak launch"))) return rc;
     } else if ((rc = check_launch(launch_peaks(g, ev, nullptr, 1, ev.n_grp, s), "peak launch"))) {
       return rc;
@@ -965,16 +995,18 @@ int run_event(const ht_grid* grid, const float* x, const float* y, const float* 
   const bool direct = !atomic && direct_lists(p.g, nh);
   // crowded events of the fused call: peaks from the stencil over the written matrix
   const bool dense = do_fill && do_peaks && !atomic && dense_peaks(p.g, nh);
-  const int layout = !do_peaks ? 0 : dense ? kPeakMask : kPeakBands;
+  const bool few = do_fill && do_peaks && !atomic && batch_shape(p.g, 1, nh, dense, 1).few;
+  const int layout = !do_peaks ? 0 : dense ? kPeakMask : few ? kPeakFew : kPeakBands;
+  const int64_t hits = do_fill ? nh : -1;  // for the scratch
   if (do_peaks && (!do_fill || atomic)) set_jobs(&p.g, 0, 1);  // the survivors come from a scan
   Workspace* w;
-  if ((rc = get_workspace(p.dev, p.s, event_scratch_bytes(p.g, nh, direct, layout), &w))) return rc;
+  if ((rc = get_workspace(p.dev, p.s, event_scratch_bytes(p.g, hits, direct, layout), &w))) return rc;
   if ((rc = ensure_counters(w, 1, p.s))) return rc;
   EvDesc ev;
   std::memset(&ev, 0, sizeof(ev));
-  carve_event_scratch(p.g, nh, direct, w->dev, &ev, layout);
+  carve_event_scratch(p.g, hits, direct, w->dev, &ev, layout);
   ev.dense = dense ? 1 : 0;
-  ev.lists = layout == kPeakBands && (!do_fill || atomic || use_lists(p.g, 1, nh, nh)) ? 1 : 0;
+  if (layout == kPeakBands && do_fill && !atomic && !use_lists(p.g, 1, nh, nh)) ev.lists = 0;
   use_counters(w, 0, &ev);
   ev.x = x;
   ev.y = y;
@@ -1068,26 +1100,32 @@ int ht_fill_peaks_batch(const ht_grid* grid, const ht_event* events, int32_t n_e
   Prepared p;
   if ((rc = prepare(grid, stream, &p, n_events, max_hits))) return rc;
   if ((rc = check_accessible(out, "out")) || (rc = check_accessible(n_found, "n_found"))) return rc;
+  // overlap of the peak searches with the fills of later events: the batch in `pieces` runs
+  const int pieces = std::max(1, std::min(std::min(env_int("HT_BATCH_PIECES", 1), kMaxPieces), (int)n_events));
+  bool any_bands = false, any_dense = false;
+  for (int32_t i = 0; i < n_events; ++i) {
+    const bool dense = p.g.lds_fill && dense_peaks(p.g, events[i].n_hits);
+    any_bands = any_bands || !dense;
+    any_dense = any_dense || dense;
+  }
+  BatchShape shape = batch_shape(p.g, n_events, max_hits, any_dense, pieces);
   std::vector<size_t> offs;
   size_t total_scratch = 0;
-  const bool direct = plan_batch(p.g, events, n_events, &offs, &total_scratch, &max_hits);
+  const bool direct = plan_batch(p.g, events, n_events, shape.few, &offs, &total_scratch);
   Workspace* w;
   if ((rc = get_workspace(p.dev, p.s, total_scratch, &w))) return rc;
   if ((rc = ensure_ev_staging(w, n_events, p.s))) return rc;
   if ((rc = ensure_counters(w, n_events, p.s))) return rc;
   EvDesc* const h_ev = w->h_ev[w->turn];
   const uint64_t cells = n_cells(*grid);
-  bool any_bands = false, any_dense = false;
   for (int32_t i = 0; i < n_events; ++i) {
     const ht_event& ev = events[i];
     EvDesc& d = h_ev[i];
     std::memset(&d, 0, sizeof(d));
     const bool dense = p.g.lds_fill && dense_peaks(p.g, ev.n_hits);
-    any_bands = any_bands || !dense;
-    any_dense = any_dense || dense;
-    carve_event_scratch(p.g, ev.n_hits, direct, w->dev + offs[i], &d, dense ? kPeakMask : kPeakBands);
+    carve_event_scratch(p.g, ev.n_hits, direct, w->dev + offs[i], &d, dense ? kPeakMask : shape.few ? kPeakFew : kPeakBands);
     d.dense = dense ? 1 : 0;
-    d.lists = !dense && (!p.g.lds_fill || use_lists(p.g, n_events, max_hits, ev.n_hits)) ? 1 : 0;
+    if (!shape.few && p.g.lds_fill && !use_lists(p.g, n_events, max_hits, ev.n_hits)) d.lists = 0;
     use_counters(w, i, &d);
     d.x = x ? x + ev.hit_offset : nullptr;
     d.y = y ? y + ev.hit_offset : nullptr;
@@ -1099,8 +1137,6 @@ int ht_fill_peaks_batch(const ht_grid* grid, const ht_event* events, int32_t n_e
     d.n_found = n_found + i;
   }
   hipError_t e;
-  // overlap of the peak searches with the fills of later events: the batch in `pieces` runs
-  const int pieces = std::max(1, std::min(std::min(env_int("HT_BATCH_PIECES", 1), kMaxPieces), (int)n_events));
   BatchSplit split;
   std::memset(&split, 0, sizeof(split));
   split.pieces = pieces;
@@ -1127,7 +1163,6 @@ int ht_fill_peaks_batch(const ht_grid* grid, const ht_event* events, int32_t n_e
     for (int i = 0; i < kMaxPieces; ++i) split.filled[i] = w->split_ev[i];
     split.done = w->split_ev[kMaxPieces];
   }
-  BatchShape shape = batch_shape(p.g, n_events, max_hits, any_dense, pieces);
   // The descriptors above hold this call's counter arrays. The next call switches to the other
   // arrays only once this call's preparation (which counts into these and clears those) is on
   // the stream; a call that fails before that leaves the counters as they were.
@@ -1290,9 +1325,11 @@ int ht_debug_batch_plan(const ht_grid* grid, const ht_event* events, int32_t n_e
   int64_t max_hits = 0;
   for (int32_t i = 0; i < n_events; ++i) max_hits = std::max(max_hits, events[i].n_hits);
   const DevGrid g = make_devgrid(*grid, DevTables(), choose_tiling(*grid), n_events, max_hits);
+  bool any_dense = false;
+  for (int32_t i = 0; i < n_events; ++i) any_dense = any_dense || (g.lds_fill && dense_peaks(g, events[i].n_hits));
   std::vector<size_t> offs;
   size_t total = 0;
-  *direct = plan_batch(g, events, n_events, &offs, &total, &max_hits) ? 1 : 0;
+  *direct = plan_batch(g, events, n_events, batch_shape(g, n_events, max_hits, any_dense, 1).few, &offs, &total) ? 1 : 0;
   *scratch_bytes = (int64_t)total;
   return HT_OK;
 }
@@ -1327,13 +1364,15 @@ int ht_debug_launch_plan(const ht_grid* grid, int32_t call, const int64_t* n_hit
   for (const ht_event& ev : events) {
     const bool dense = call == 2 ? na.dense : g.lds_fill && dense_peaks(g, ev.n_hits);
     plan->n_stencil += dense ? 1 : 0;
-    plan->n_lists += !dense && (na.sliced || !g.lds_fill || use_lists(g, n_ev, max_hits, ev.n_hits)) ? 1 : 0;
   }
   plan->sliced = na.sliced ? 1 : 0;
   const BatchShape b = batch_shape(g, n_ev, max_hits, plan->n_stencil > 0 || na.sliced, 1);
+  for (const ht_event& ev : events)
+    if (na.sliced || b.few || !g.lds_fill || use_lists(g, n_ev, max_hits, ev.n_hits))
+      plan->n_lists += call == 2 ? !na.dense : !(g.lds_fill && dense_peaks(g, ev.n_hits));
   plan->long_lists = b.long_l ? 1 : 0;
   plan->tiny = b.tiny ? 1 : 0;
-  plan->few = b.few || b.tiny ? 1 : 0;
+  plan->few = b.few ? 1 : 0;
   if (call == 2) {
     plan->direct = na.direct ? 1 : 0;
     plan->scratch_bytes = (int64_t)na.scratch_bytes;
@@ -1341,13 +1380,13 @@ int ht_debug_launch_plan(const ht_grid* grid, int32_t call, const int64_t* n_hit
   }
   if (serve) {
     plan->direct = direct_lists(g, loop_hits) ? 1 : 0;
-    const int layout = kPeakBands | (tl.dense_from > 0 && loop_hits >= tl.dense_from ? kPeakMask : 0);
-    plan->scratch_bytes = (int64_t)(n_ev * event_scratch_bytes(g, loop_hits, plan->direct != 0, layout));
+    int layout;
+    plan->scratch_bytes = (int64_t)n_ev * (int64_t)slot_scratch_bytes(g, tl, n_ev, loop_hits, &layout);
     return HT_OK;
   }
   std::vector<size_t> offs;
   size_t total = 0;
-  plan->direct = plan_batch(g, events.data(), n_ev, &offs, &total, &max_hits) ? 1 : 0;
+  plan->direct = plan_batch(g, events.data(), n_ev, b.few, &offs, &total) ? 1 : 0;
   plan->scratch_bytes = (int64_t)total;
   return HT_OK;
 }

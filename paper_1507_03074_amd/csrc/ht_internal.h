@@ -18,13 +18,16 @@ constexpr int kMaxSlabs = 4096;
 // separate clearing launch. They live in memory of their own, cleared once when allocated.
 // Each array holds kMaxSlabs slab counters, then the lengths of the survivor lists (from kListLens
 // on) and a word that is set when a survivor did not fit its list (kListOver). An event's survivors
-// (cell, votes, group of jobs) go to kLists lists of kListCap entries each, its jobs taking the
-// lists in turn. One list would do but for its counter: atomic additions to one cache line take
+// (cell, votes, group of jobs) go to kLists lists of up to kListCap entries each, chosen by
+// a hash of the job. One list would do but for its counter: atomic additions to one cache line take
 // 10 ns each, and an event of 10k hits has 5000 jobs with survivors; the lists' lengths are a
-// cache line (kListLine words) apart. An event with more survivors is tested group by group.
+// cache line (kListLine words) apart. An event with more survivors is tested group by group. An event
+// of few cells (few_cells) has one list that holds them all.
 constexpr uint32_t kLists = 8;
 constexpr uint32_t kListCap = 8192;
 constexpr uint32_t kListLine = 32;
+constexpr uint32_t kListShift = 28;  // of EvDesc::lists
+constexpr uint32_t kListEntries = (1u << kListShift) - 1u;
 constexpr int kListLens = kMaxSlabs;
 constexpr int kListOver = kListLens + (int)(kLists * kListLine);
 constexpr int kCounterWords = kListOver + (int)kListLine;
@@ -53,10 +56,9 @@ struct JobGeom {
 };
 constexpr uint32_t kSegMax = 1024;
 constexpr uint32_t kSuperStep = 32;  // words: a cache line each
-// Few peaks: at most this many cells can reach the threshold (each of the lists holds as many).
+// Few peaks: at most this many cells can reach the threshold.
 constexpr uint32_t kFewCells = 8192;
 constexpr int64_t kFewHits = 65535;  // and hits
-static_assert(kFewCells <= kListCap, "no list overflows where so few cells reach the threshold");
 constexpr int kTinyHits = 1024;  // of an event that takes two launches (tiny_launch)
 
 // Grid constants and tables as the kernels see them (passed by value as a kernel argument).
@@ -114,8 +116,10 @@ struct EvDesc {
   uint8_t* job_any;     // [jobs] 1: the job has survivors (its masks are valid)
   uint8_t* masks;       // [jobs][64 lanes] mask elements; jobs without the flag are not written
   uint2* seg;           // [n_grp][g.j.seg] each group's peaks (cell, votes)
-  uint4* surv;          // [kLists][kListCap] survivors (cell, votes, group, 0) in no order
-  uint32_t lists;       // 0: no lists are made (crowded slabs)
+  uint4* surv;          // [lists][entries] survivors (cell, votes, group, 0) in no order
+  uint32_t lists;       // their number - 1 << kListShift | entries of one; 0: none are made (crowded
+                        // slabs). One word, as every scalar register counts in the fill, which
+                        // stores the masks also of an event of few cells: no search reads them
   void* clear;          // what the preparation clears: super_pk, group_pk and job_any, or the
   uint32_t clear_n16;   // stencil's group_pk; in 16-byte units
   const int64_t* carry_in;  // peaks of the earlier slices, or NULL
@@ -171,15 +175,18 @@ bool direct_lists(const DevGrid& g, int64_t n_hits);
 // over the matrix (crowded events) instead of testing the fill's survivors.
 bool dense_peaks(const DevGrid& g, int64_t n_hits);
 // What an event's peak-search scratch holds: the survivors' masks, the stencil's peak words, or
-// both (request-loop slots, which serve events of either kind), or neither.
-enum PeakScratch { kPeakBands = 1, kPeakMask = 2 };
-// Bytes of per-event scratch for a grid tiling and an event size, and the carving of it.
+// both (request-loop slots, which serve events of either kind), the one list of an event of few cells
+// (and room for masks), or nothing.
+enum PeakScratch { kPeakBands = 1, kPeakMask = 2, kPeakFew = 4 };
+// Bytes of per-event scratch for a grid tiling and an event size (below 0: no hits, but a matrix of
+// any counts), and the carving of it.
 size_t event_scratch_bytes(const DevGrid& g, int64_t n_hits, bool direct, int peaks = kPeakBands);
 size_t mask_bytes(const DevGrid& g);  // of the stencil's peak words
 void carve_event_scratch(const DevGrid& g, int64_t n_hits, bool direct, char* base, EvDesc* ev,
                          int peaks = kPeakBands);
 // The peak-search part of it alone, for n_grp groups from grp0 on.
-void carve_peak_scratch(const DevGrid& g, char* base, EvDesc* ev, int peaks, uint32_t grp0, uint32_t n_grp);
+void carve_peak_scratch(const DevGrid& g, int64_t n_hits, char* base, EvDesc* ev, int peaks, uint32_t grp0, uint32_t n_grp);
+size_t surv_bytes(const DevGrid& g, int64_t n_hits, int peaks);  // of the survivor lists
 
 // The preparation clears the stencil's peak counts (an event of a layout with both searches).
 void clear_groups(const DevGrid& g, EvDesc* ev);
@@ -203,8 +210,9 @@ hipError_t launch_peaks(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, 
 // Stencil peak search and ordered write of the events marked dense (others are skipped).
 hipError_t launch_peaks_dense(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev,
                               hipStream_t s);
-// Peak search of filled events with survivor lists whose grid and hits leave at most kFewCells cells
-// at the threshold (few_cells): one launch.
+// Peak search of filled events whose survivors are in one list (kPeakFew), as their grid and hits
+// leave at most kFewCells cells at the threshold (few_cells): one launch.
+int64_t cells_bound(const DevGrid& g, int64_t hits);  // cells that can reach the threshold
 bool few_cells(const DevGrid& g, int64_t max_hits);
 hipError_t launch_few_peaks(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, int n_ev, hipStream_t s);
 // Launches of tiny events (g.j set for fill tiles, few cells): whether these are, and their fill with
@@ -232,6 +240,7 @@ int n_groups(const DevGrid& g);
 // those of a scan, and slice_groups of them make a slice). HT_EINVAL for an event that it refuses.
 struct NoallocPlan {
   bool dense, direct, sliced;
+  int layout;
   size_t scratch_bytes;
   uint32_t slice_groups;
 };
@@ -260,9 +269,13 @@ int make_device_grid(const ht_grid& g, int dev, int n_ev, int64_t max_hits, DevG
 struct BatchShape {
   int64_t prep_hits;  // that the preparation's grid is made for: at least max_hits
   bool long_l;        // the fill's variant for long lists
-  bool tiny, few;     // the launches of tiny events, the search of few cells
+  bool few;           // the search of few cells: the ordinary events have the layout kPeakFew
+  bool tiny;          // and the launches of tiny events
 };
 BatchShape batch_shape(const DevGrid& g, int n_ev, int64_t max_hits, bool any_dense, int pieces);
+// Scratch of one slot of a request loop (g made for batches of max_batch events of max_hits hits), and
+// the layout of those of its batches that are not of few cells, whose slots are carved as kPeakFew.
+size_t slot_scratch_bytes(const DevGrid& g, const Tiling& tl, int max_batch, int64_t max_hits, int* layout);
 // The whole batched pipeline (prep, fill with survivors, peaks) for n_ev events whose
 // descriptors are already in device memory.
 // *prep_enqueued is set once the preparation (which counts into and clears the events' counter

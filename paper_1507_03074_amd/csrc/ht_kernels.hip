@@ -642,10 +642,11 @@ __global__ __launch_bounds__(kBlock) void k_peak_test(DevGrid g, EvDesc ev0, con
     // in flight (half waves past a multiple of kLists of them take none)
     const uint32_t hw = blockIdx.x * (kBlock / 32) + (threadIdx.x >> 5), k = threadIdx.x & 31u;
     const uint32_t l = hw % kLists, step = gridDim.x * (kBlock / 32) / kLists;
-    const GLOBAL u32x4* const list = (const GLOBAL u32x4*)gp((const uint4*)e.surv) + l * kListCap;
+    const uint32_t cap = e.lists & kListEntries;
+    const GLOBAL u32x4* const list = (const GLOBAL u32x4*)gp((const uint4*)e.surv) + l * cap;
     // the first entry is loaded before the list's length is known: one round trip for both
     u32x4 en[4];
-    en[0] = list[min(hw / kLists, kListCap - 1u)];
+    en[0] = list[min(hw / kLists, cap - 1u)];
     const uint32_t n = gp((const uint32_t*)e.slab_cnt)[kListLens + l * kListLine];
     if (gp((const uint32_t*)e.slab_cnt)[kListOver] == 0u) {  // uniform over the grid
       const int kk = (int)min(k, 26u), dt = kk / 9 - 1, dp = kk / 3 % 3 - 1, da = kk % 3 - 1;
@@ -657,7 +658,7 @@ __global__ __launch_bounds__(kBlock) void k_peak_test(DevGrid g, EvDesc ev0, con
 #pragma unroll
         for (uint32_t q = 0; q < 4; ++q) {
           const uint32_t i = i0 + q * step;
-          if (i < n_max && i != i_wave) en[q] = list[min(i, kListCap - 1u)];
+          if (i < n_max && i != i_wave) en[q] = list[min(i, cap - 1u)];
         }
 #pragma unroll
         for (uint32_t q = 0; q < 4; ++q) {
@@ -893,29 +894,25 @@ __global__ __launch_bounds__(1024) void k_few_peaks(DevGrid g, EvDesc ev0, const
   EvDesc e = load_ev(ev0, evs);
   const bool a8 = ((uintptr_t)e.out & 7u) == 0;
   const uint32_t lane = threadIdx.x & 63u, hw = threadIdx.x >> 5, k = threadIdx.x & 31u;
-  constexpr uint32_t kStep = 1024 / 32 / kLists;  // half waves per list
-  const uint32_t l = hw % kLists;
-  const GLOBAL u32x4* const list = (const GLOBAL u32x4*)gp((const uint4*)e.surv) + l * kListCap;
+  constexpr uint32_t kStep = 1024 / 32;  // half waves
+  const GLOBAL u32x4* const list = (const GLOBAL u32x4*)gp((const uint4*)e.surv);
+  const uint32_t last = (e.lists & kListEntries) - 1u;
   if (threadIdx.x == 0) s_n = 0u;
   u32x4 en[4];
 #pragma unroll
-  for (uint32_t q = 0; q < 4; ++q) en[q] = list[hw / kLists + q * kStep];  // before their number is known
-  const uint32_t n = gp((const uint32_t*)e.slab_cnt)[kListLens + l * kListLine];
+  for (uint32_t q = 0; q < 4; ++q) en[q] = list[min(hw + q * kStep, last)];  // before their number is known
+  const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)gp((const uint32_t*)e.slab_cnt)[kListLens]);
   const int kk = (int)min(k, 26u), dt = kk / 9 - 1, dp = kk / 3 % 3 - 1, da = kk % 3 - 1;
-  const uint32_t n_max = max((uint32_t)__builtin_amdgcn_readlane((int)n, 0), (uint32_t)__builtin_amdgcn_readlane((int)n, 32));
-  const uint32_t i_wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(hw / kLists));  // the same in both halves
   lds_barrier();
-  for (uint32_t i0 = i_wave; i0 < n_max; i0 += 4u * kStep) {  // wave-uniform
+  for (uint32_t i0 = 0u; i0 < n; i0 += 4u * kStep) {  // uniform
     bool beaten[4];
 #pragma unroll
-    for (uint32_t q = 0; q < 4; ++q) {
-      const uint32_t i = i0 + q * kStep;
-      if (i0 != i_wave && i < n_max) en[q] = list[min(i, kListCap - 1u)];
-    }
+    for (uint32_t q = 0; q < 4; ++q)
+      if (i0 > 0u) en[q] = list[min(i0 + hw + q * kStep, last)];
 #pragma unroll
     for (uint32_t q = 0; q < 4; ++q) {
       beaten[q] = true;
-      if (i0 + q * kStep < n) {
+      if (i0 + hw + q * kStep < n) {
         const TestCell x = test_cell(g, en[q].x, en[q].y);
         bool in;
         const uint32_t at = row_window(g, x, dt, dp, da, &in);
@@ -1802,16 +1799,21 @@ static size_t tiny_lds_bytes(const DevGrid& g)
   return fill_lds_bytes(g, false) + (size_t)(4 * g.n_phi + 2 * (2 * g.n_theta + 1)) * sizeof(float);
 }
 
+int64_t cells_bound(const DevGrid& g, int64_t hits)
+{
+  // a hit votes once per A row in each of its (theta, phi) cells
+  return hits * (g.phi_sectors ? 2 : 4) * g.n_a / (int64_t)g.threshold;
+}
+
 bool few_cells(const DevGrid& g, int64_t max_hits)
 {
-  // A hit votes once per A row and cell, so hits * cells * n_a / threshold cells reach the threshold
-  // at most, and in ordinary events far fewer, unless one or two votes are enough: then most of them
+  // Of the cells that can reach the threshold far fewer do in ordinary events, unless one or two votes are enough: then most of them
   // do, more than one workgroup tests in the time of two launches. One workgroup and the general
   // search from lists, in us: T 1, 4x16x64x64, one hit (bound 256) 12 and 15, two 19 and 17, 32 (8192)
   // 59 and 18; two hits on 4x16x1024x1024 (8192) 179 and 51; T 2, 4x16x64x64, 32 hits (4096) 15 and
   // 16, 64 (8192) 28 and 17; T 3, 64 hits (5461) 15.4 and 16.6; T 4, 128 (8192) 16.5 and 17.0.
   const int64_t limit = g.threshold == 1 ? 256 : g.threshold == 2 ? kFewCells / 2 : kFewCells;
-  return max_hits <= kFewHits && max_hits * (g.phi_sectors ? 2 : 4) * g.n_a / (int64_t)g.threshold <= limit;
+  return max_hits <= kFewHits && cells_bound(g, max_hits) <= limit;
 }
 
 bool tiny_launch(const DevGrid& g, int n_ev, int64_t max_hits)

@@ -99,8 +99,10 @@ int plan_noalloc(const ht_grid& grid, const Tiling& tl, const DevGrid& g, int64_
   // leave it to the stencil
   const bool crowded = g.lds_fill && tl.dense_hits > 0 && n >= tl.dense_hits;
   plan->dense = g.lds_fill && (dense_peaks(g, n) || (crowded && !either(kPeakBands)));
-  plan->sliced = !plan->dense && !either(kPeakBands);
-  const int layout = plan->sliced ? 0 : plan->dense ? kPeakMask : kPeakBands;
+  const int search = batch_shape(g, 1, n, plan->dense, 1).few ? kPeakFew : kPeakBands;
+  plan->sliced = !plan->dense && !either(search);
+  const int layout = plan->sliced ? 0 : plan->dense ? kPeakMask : search;
+  plan->layout = layout;
   plan->direct = can_direct && fits(true, layout);
   plan->scratch_bytes = event_scratch_bytes(g, n, plan->direct, layout);
   plan->slice_groups = 0;
@@ -110,7 +112,7 @@ int plan_noalloc(const ht_grid& grid, const Tiling& tl, const DevGrid& g, int64_
     // then), each slice counting on from the one before.
     DevGrid sg = g;
     set_jobs(&sg, 0, 1);
-    const size_t fixed = 256 + al256(4 * (size_t)sg.j.n_groups * sg.j.pk_step) + al256(4 * (size_t)sg.j.n_groups) + 16 * (size_t)kListCap * kLists + 6 * 256;
+    const size_t fixed = 256 + al256(4 * (size_t)sg.j.n_groups * sg.j.pk_step) + al256(4 * (size_t)sg.j.n_groups) + surv_bytes(sg, n, kPeakBands) + 6 * 256;
     const size_t per = (size_t)(1 + 64 * sg.j.elem_bytes) * sg.j.group_jobs + 8 * (size_t)sg.j.seg;
     const size_t fit = fixed < room ? (room - fixed) / per : 0;
     if (fit == 0) return fail(HT_EINVAL, "ht_fill_peaks_noalloc: one group of rows needs %zu bytes of scratch", per);
@@ -154,7 +156,6 @@ extern "C" int ht_fill_peaks_noalloc(const ht_grid* grid, const float* x, const 
   NoallocPlan plan;
   if ((rc = plan_noalloc(*grid, tl, g, n_hits, &plan))) return rc;
   const bool atomic = !g.lds_fill, dense = plan.dense, direct = plan.direct, sliced = plan.sliced;
-  const int layout = sliced ? 0 : dense ? kPeakMask : kPeakBands;
 
   std::lock_guard<std::mutex> lk(g_na_mu);
   if (!g_ptr[dev]) {
@@ -191,9 +192,9 @@ extern "C" int ht_fill_peaks_noalloc(const ht_grid* grid, const float* x, const 
 
   EvDesc ev;
   std::memset(&ev, 0, sizeof(ev));
-  carve_event_scratch(g, n_hits, direct, base + kEvOff, &ev, layout);
+  carve_event_scratch(g, n_hits, direct, base + kEvOff, &ev, plan.layout);
   ev.dense = dense ? 1 : 0;
-  ev.lists = !sliced && !dense && (atomic || use_lists(g, 1, n_hits, n_hits)) ? 1 : 0;
+  if (plan.layout == kPeakBands && !atomic && !use_lists(g, 1, n_hits, n_hits)) ev.lists = 0;
   uint32_t* pair = (uint32_t*)base;
   ev.slab_cnt = pair + (g_parity[dev] ? kCounterWords : 0);
   ev.slab_cnt_next = pair + (g_parity[dev] ? 0 : kCounterWords);
@@ -213,8 +214,7 @@ extern "C" int ht_fill_peaks_noalloc(const ht_grid* grid, const float* x, const 
   int64_t* carry = (int64_t*)(base + kEvOff);
   for (uint32_t g0 = 0, k = 0; g0 < g.j.n_groups; ++k) {
     const uint32_t n_grp = std::min<uint32_t>(plan.slice_groups, g.j.n_groups - g0);
-    carve_peak_scratch(g, base + kEvOff + 256, &ev, kPeakBands, g0, n_grp);
-    ev.lists = 1;
+    carve_peak_scratch(g, n_hits, base + kEvOff + 256, &ev, kPeakBands, g0, n_grp);
     ev.carry_in = k > 0 ? carry + (k & 1) : nullptr;
     ev.carry_out = carry + ((k + 1) & 1);
     ev.slab_cnt = pair + (g_parity[dev] ? kCounterWords : 0);

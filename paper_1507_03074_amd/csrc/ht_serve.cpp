@@ -74,7 +74,7 @@ struct ht_server {
   uint64_t cells = 0;
   size_t scratch_bytes = 0;
   bool direct = false;
-  int layout = kPeakBands;       // slots hold survivor masks, and peak words when events can be crowded
+  int layout = kPeakBands;       // of the slots: survivor masks, and peak words when events can be crowded
   char* arena = nullptr;        // device: all slots
   uint32_t* ctr = nullptr;      // device: slab counters of all slots
   char* host_out = nullptr;     // pinned: per-slot peak lists and counts
@@ -129,6 +129,9 @@ int launch(ht_server* sv, Batch& b)
   DevGrid g = sv->g;
   g.dense_hits = stencil_from(sv->tl, (int)b.reqs.size(), batch_max);
   bool any_bands = false, any_dense = false;
+  auto stencil = [&](const Request* r) { return (sv->layout & kPeakMask) && dense_peaks(g, r->n); };
+  for (const Request* r : b.reqs) (stencil(r) ? any_dense : any_bands) = true;
+  const BatchShape shape = batch_shape(g, (int)b.reqs.size(), batch_max, any_dense, 1);
   hipError_t e;
   for (size_t i = 0; i < b.reqs.size(); ++i) {
     Request* r = b.reqs[i];
@@ -139,13 +142,12 @@ int launch(ht_server* sv, Batch& b)
       return fail_hip(e, "hipMemcpyAsync(hits)");
     EvDesc& d = sv->h_ev[b.stream][i];
     std::memset(&d, 0, sizeof(d));
-    carve_event_scratch(g, mh, sv->direct, sl.scratch, &d, sv->layout);
-    // crowded events search their peaks with the stencil (the slot holds both layouts)
-    d.dense = (sv->layout & kPeakMask) && dense_peaks(g, r->n) ? 1 : 0;
+    // a slot is carved for the batch: one list of few cells, or all that its events may need
+    if (shape.few) carve_event_scratch(g, r->n, sv->direct, sl.scratch, &d, kPeakFew);
+    else carve_event_scratch(g, mh, sv->direct, sl.scratch, &d, sv->layout);
+    d.dense = stencil(r) ? 1 : 0;
     if (d.dense) clear_groups(g, &d);
-    d.lists = !d.dense && (!g.lds_fill || use_lists(g, (int)b.reqs.size(), batch_max, r->n)) ? 1 : 0;
-    any_bands = any_bands || !d.dense;
-    any_dense = any_dense || d.dense;
+    if (d.dense || (!shape.few && g.lds_fill && !use_lists(g, (int)b.reqs.size(), batch_max, r->n))) d.lists = 0;
     d.slab_cnt = sl.ctr + (sl.parity ? kCounterWords : 0);
     d.slab_cnt_next = sl.ctr + (sl.parity ? 0 : kCounterWords);
     d.x = sl.hits;
@@ -160,7 +162,6 @@ int launch(ht_server* sv, Batch& b)
   if ((e = launch_fetch(sv->d_ev[b.stream], sv->h_ev[b.stream], (int)b.reqs.size(), s)) != hipSuccess)
     return fail_hip(e, "descriptor launch");
   bool prep_enqueued = false;
-  const BatchShape shape = batch_shape(g, (int)b.reqs.size(), batch_max, any_dense, 1);
   int rc = launch_batch(g, sv->d_ev[b.stream], (int)b.reqs.size(), shape, sv->direct, any_bands, any_dense, s,
                         &prep_enqueued);
   // a slot switches counter arrays only once the preparation that counts into this one and
@@ -273,8 +274,7 @@ int ht_serve_create(const ht_grid* grid, const ht_serve_opts* opts, ht_server** 
   }
   sv->cells = n_cells(*grid);
   sv->direct = direct_lists(sv->g, opts->max_hits);
-  sv->layout = kPeakBands | (sv->tl.dense_from > 0 && opts->max_hits >= sv->tl.dense_from ? kPeakMask : 0);
-  sv->scratch_bytes = event_scratch_bytes(sv->g, opts->max_hits, sv->direct, sv->layout);
+  sv->scratch_bytes = slot_scratch_bytes(sv->g, sv->tl, opts->max_batch, opts->max_hits, &sv->layout);
   const size_t slot_bytes = al(4 * sv->cells) + al(sv->scratch_bytes) + al(12 * (size_t)opts->max_hits);
   const int64_t n_slots = std::min<int64_t>(opts->hbm_budget_bytes / (int64_t)slot_bytes, 4096);
   if (n_slots < 1) {

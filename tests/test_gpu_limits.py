@@ -147,3 +147,52 @@ def test_moderately_long_slab_lists(B, grid, threshold, sizes):
     for i, (M, c, v, k) in enumerate(want):
         assert np.array_equal(B.as_u32(res.acc[i]), M), i
         assert res.peaks[i][2] == k and np.array_equal(res.peaks[i][0], c) and np.array_equal(res.peaks[i][1], v), i
+
+
+@pytest.mark.parametrize("shape,threshold,sizes", [((1, 3, 16, 16), 2, (0, 1, 40, 400)), ((1, 3, 64, 256), 2, (300, 700)),
+                                                   ((2, 3, 300, 33), 3, (200, 2000)), ((4, 16, 64, 64), 2, (30, 33, 900)),
+                                                   ((1, 4, 20, 1), 1, (1, 3, 4, 60)), ((2, 3, 64, 64), 32, (255, 1024, 1025))])
+def test_survivor_lists_of_every_size(B, monkeypatch, shape, threshold, sizes):
+    """Lists as short as their event: one that holds every survivor of few cells, eight that overflow,
+    and events of either kind in one batch and one request loop."""
+    import time
+    spec = synth.GridSpec(*shape, threshold=threshold)
+    evs = []
+    for n in sizes:
+        ev = synth.make_hits(np.random.default_rng([40, n]), n // 14, n - 12 * (n // 14))
+        x, y, z = (np.asarray(a[:n], np.float32).copy() for a in (ev.x, ev.y, ev.z))
+        if n > 20:  # many hits alike: large counts
+            x[n // 2:], y[n // 2:], z[n // 2:] = x[0], y[0], z[0]
+        evs.append((x, y, z))
+    want = [oracle_run(spec, ev) for ev in evs]
+
+    def same(i, got, tag):
+        M, c, v, k = want[i]
+        assert got[2] == k and np.array_equal(got[0], c) and np.array_equal(got[1], v), (tag, sizes[i])
+    B.ht_set_tuning(spec, dense_hits=-1)
+    try:
+        for i, ev in enumerate(evs):
+            say(shape, "hits", sizes[i], B.ht_debug_launch_plan(spec, [sizes[i]]))
+            acc, *got = B.fill_peaks(spec, *B.hits_to_device(*ev))
+            assert np.array_equal(B.as_u32(acc), want[i][0]), sizes[i]
+            same(i, got, "event")
+            noalloc_equals_fill_peaks(B, spec, ev)
+            same(i, B.peaks(spec, acc), "matrix")
+        for k in range(4):
+            monkeypatch.setenv("HT_BATCH_GRAPH", str(k % 2))
+            for pick in ([i for i in range(len(evs))], [0, 0, 1]):
+                res = B.fill_peaks_batch(spec, [evs[i] for i in pick])
+                for j, i in enumerate(pick):
+                    assert np.array_equal(B.as_u32(res.acc[j]), want[i][0])
+                    same(i, res.peaks[j], "batch")
+        with B.Server(spec, 64 << 20, peak_capacity=1 << 14, max_hits=max(sizes), max_batch=3, n_streams=2, queue_depth=16) as srv:
+            for k in range(3):
+                tickets = [(i, srv.submit(*evs[i])) for i in range(len(evs))]
+                for i, t in tickets:
+                    deadline = time.time() + 60
+                    while (r := srv.poll(t)) is None:
+                        assert time.time() < deadline
+                        time.sleep(1e-4)
+                    same(i, r, "served")
+    finally:
+        B.ht_set_tuning(spec)

@@ -201,6 +201,21 @@ def test_long_slab_lists_with_few_survivors_keep_the_survivor_lists(lib):
             assert plan["long_lists"] == long_l and plan["n_lists"] == (0 if long_l or T == 1 else 1), (grid, T, n)
 
 
+def test_small_events_take_little_scratch(lib):
+    """The survivor lists are as long as the event may need: the scratch of small events is mostly
+    their slab lists, and large batches of them keep direct lists."""
+    G = synth.GridSpec
+    for grid, T, n, most in (((1, 3, 16, 16), 3, 40, 5 << 10), ((1, 3, 16, 16), 2, 400, 24 << 10), ((4, 16, 64, 64), 8, 250, 420 << 10),
+                             ((4, 16, 64, 64), 8, 1000, 1200 << 10), ((4, 16, 1024, 1024), 9, 5000, 24 << 20)):
+        spec = G(*grid, threshold=T)
+        for call, sizes in (("event", [n]), ("batch", [n] * 50), ("serve", [n] * 9)):
+            events = len(sizes) - (call == "serve")
+            assert B.ht_debug_launch_plan(spec, sizes, call)["scratch_bytes"] <= events * (most + (12 << 10)), (grid, call)
+    plan = B.ht_debug_launch_plan(G(1, 3, 16, 16, threshold=3), [40] * 65535, "batch")
+    assert plan["direct"] and plan["scratch_bytes"] < 1 << 29
+    assert B.ht_debug_launch_plan(G(4, 16, 64, 64, threshold=8), [250] * 20000, "batch")["direct"]
+
+
 def test_launch_plan_validated_on_host(lib):
     spec = synth.WORKLOADS[0].grid
     for bad in ([], [-1], [5, 5], [1 << 29]):
