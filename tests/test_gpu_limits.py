@@ -196,3 +196,57 @@ def test_survivor_lists_of_every_size(B, monkeypatch, shape, threshold, sizes):
                     same(i, r, "served")
     finally:
         B.ht_set_tuning(spec)
+
+
+def fused_equals_oracle(B, spec, ev, want=None):
+    M, c, v, k = want or oracle_run(spec, ev)
+    acc, gc, gv, gk = B.fill_peaks(spec, *B.hits_to_device(*ev))
+    assert np.array_equal(B.as_u32(acc), M) and gk == k and np.array_equal(gc, c) and np.array_equal(gv, v)
+    return M, k
+
+
+def test_default_search_around_the_stencil_threshold(B):
+    """The largest event that the paper grid searches from its survivors by default and the smallest
+    that takes the stencil (40960 hits: 2.5 times the reported dense_hits)."""
+    spec = synth.GridSpec(4, 16, 1024, 1024, threshold=9)
+    x, y, z = hits(50, 40960)
+    for n, stencil in ((40959, 0), (40960, 1)):
+        assert B.ht_debug_launch_plan(spec, [n])["n_stencil"] == stencil
+        say("paper grid, hits", n, "stencil", stencil)
+        assert fused_equals_oracle(B, spec, (x[:n], y[:n], z[:n]))[1] > 100000
+
+
+def test_fused_call_overflows_its_survivor_lists(B):
+    """More survivors than the lists hold: those of every job of 4 rows and 256 columns, counted here,
+    against a quarter of the votes' bound. The search falls back to the masks."""
+    from oracle import oracle
+    spec = synth.GridSpec(2, 3, 16, 1024, threshold=1, a_min=-20000.0, a_max=20000.0, b_min=-20000.0, b_max=20000.0)
+    n = 300
+    ev = synth.uniform_hits(np.random.default_rng(n), n, 1000.0, 2500.0)
+    plan = B.ht_debug_launch_plan(spec, [n])
+    assert plan["rows"] == 4 and plan["n_lists"] == 1 and not plan["few"] and not plan["long_lists"]
+    M, _ = fused_equals_oracle(B, spec, ev)
+    job = oracle.OracleGrid(*synth.GridSpec(1, 1, 4, 256, threshold=1, phi_sectors=True).as_tuple())
+    blocks = M.reshape(6, 4, 4, 4, 256).swapaxes(2, 3).reshape(-1, 1, 1, 4, 256)
+    survivors = sum(oracle.peaks(job, np.ascontiguousarray(b))[2] for b in blocks)
+    say("survivors", survivors)
+    assert survivors > n * 4 * spec.n_a // 4 > spec.n_cells // 32
+    res = B.fill_peaks_batch(spec, [ev, ev])
+    for got in res.peaks:
+        assert got[2] == oracle_run(spec, ev)[3]
+
+
+def test_fused_call_overflows_its_groups_segments(B):
+    """One sector of one theta cell, where a peak is a maximum of its own plane: more peaks in a group
+    of jobs than its segment holds (one per 64 cells), from survivor lists and from masks."""
+    spec = synth.GridSpec(1, 1, 128, 256, threshold=2, phi_sectors=True)
+    B.ht_set_tuning(spec, dense_hits=-1)
+    try:
+        for n, lists in ((170, 1), (700, 0)):
+            ev = synth.uniform_hits(np.random.default_rng(n), n, 1000.0, 2500.0)
+            assert B.ht_debug_launch_plan(spec, [n])["n_lists"] == lists
+            _, k = fused_equals_oracle(B, spec, ev)
+            say("hits", n, "peaks", k)
+            assert k > 2 * spec.n_cells // 64
+    finally:
+        B.ht_set_tuning(spec)
