@@ -137,7 +137,7 @@ constexpr int kChunkCells = 62;
 struct Tiling {
   int32_t rows, tiles_per_slab, n_tiles, lds_fill, group_tiles, nt_store, fill_tiles;
   int32_t auto_rows, auto_nt;  // 1: not set by the caller, so each launch may take its own
-  int32_t cand_cap;  // reported and accepted only: the survivors of the fill take no pool entries
+  int32_t cand_cap;  // of the no-alloc call's limit only: no search keeps a candidate list
   int32_t packed_lists;
   int32_t dense_w, dense_rows;  // stencil peak search (DevGrid fields of these names)
   int32_t dense_hits;           // hits from which it is used: as reported,

@@ -880,10 +880,11 @@ __global__ __launch_bounds__(kBlock) void k_peak_test(DevGrid g, EvDesc ev0, con
   }
 }
 
-// Peaks of an event of which at most kFewCells cells reach the threshold, one workgroup: its
-// survivors half a wave each, one lane per neighbour row, four in flight; the peaks wait in LDS,
-// and each is written at its rank. Bound by its three memory round trips (the lists, the rows, the
-// stores), where the test and the ordered write are two launches of two each.
+// Peaks of an event of few cells (few_cells), whose one list holds all survivors, by one workgroup:
+// half a wave each, one lane per neighbour row, four in flight; the peaks wait in LDS, and each is
+// written at its rank. Bound by its three memory round trips (the list, the rows, the stores), where
+// the test and the ordered write are two launches of two each. (One list, not eight: 100 events of 250
+// hits 5.3 us before, 4.6 now, and the fill's reservations are too few to queue at its counter.)
 template <bool NARROW>
 __global__ __launch_bounds__(1024) void k_few_peaks(DevGrid g, EvDesc ev0, const EvDesc* evs)
 {
@@ -1863,10 +1864,14 @@ hipError_t launch_peaks(const DevGrid& g, const EvDesc& ev0, const EvDesc* evs, 
                         hipStream_t s)
 {
   // A workgroup per group, so that the hardware deals the uneven ones out as CUs come free (16384
-  // groups of 8x32x2048x2048 cells, four events: 1.24 ms with 2048 workgroups each, 1.16 with all; ten
-  // events, whole batch: 10.37 ms with 819 each, 10.09 with all). Batches of many events on grids of up
-  // to 4096 groups, which are ordinary ones (the paper grid has 2048), share kTestGrid. For the lists
-  // of small grids at least one per CU over all events. A multiple of the XCDs.
+  // groups of 8x32x2048x2048 cells, four events: 1.24 ms with 2048 workgroups each, 1.16 with all).
+  // Batches of more than eight events on grids of up to 4096 groups share kTestGrid, within 5% either
+  // way of a workgroup per group: thirty events of 2000 hits on the paper grid (2048 groups) 1383 us
+  // and 1418 with all, nine of 10000 on 8x32x1024x1024 (4096) 1639 and 1665, 100 of 6585 on
+  // 4x16x256x256 (128) 727 and 762; but 100 of 5000 on 4x16x512x512 (512) 1918 and 1837, sixteen of
+  // 22000 on the paper grid 1227 and 1209. Past them all groups win where they are crowded (nine events
+  // of 105600 hits on 8x32x2048x2048, 8192 groups, 9298 and 9037 us; of 20000 hits 6947 and 6991). For
+  // the lists of small grids at least one per CU over all events. A multiple of the XCDs.
   const unsigned least = std::max(kTestBlocks, 256u / (unsigned)n_ev);
   const unsigned most = n_ev <= 8 || n_grp > 4096u ? 16384u : std::max(least, kTestGrid / (unsigned)n_ev);
   const dim3 tg((std::min(std::max(n_grp, least), most) + 7u) & ~7u, n_ev);

@@ -4,7 +4,8 @@ For one grid and a few representative events it times candidate shapes (A rows p
 fill tiles per workgroup, store kind of the matrix write, tiles per peak workgroup), keeps only
 candidates whose vote
 matrices and peak lists are bit-identical to those of the default shape, and applies the
-fastest. Results are cached in a JSON file keyed by GPU architecture and grid.
+fastest. A field at the reported default is left to the library, which chooses it launch by launch:
+a shape pins what it changes. Results are cached in a JSON file keyed by GPU architecture and grid.
 """
 from __future__ import annotations
 
