@@ -539,13 +539,15 @@ void carve_peak_scratch(const DevGrid& g, int64_t n_hits, char* p, EvDesc* ev, i
   if (peaks & (kPeakBands | kPeakFew)) {
     ev->job_any = (uint8_t*)take(n);
     ev->masks = (uint8_t*)take((size_t)64 * g.j.elem_bytes * n);
-    ev->surv = (uint4*)take(surv_bytes(g, n_hits, peaks));
-    ev->lists = (peaks & kPeakFew ? 0u : (kLists - 1u) << kListShift) | surv_cap(g, n_hits, peaks);
   }
   if (peaks & kPeakBands) {
     ev->clear = ev->super_pk;
     ev->clear_n16 = (uint32_t)((ev->masks - (uint8_t*)ev->super_pk) / 16);
     ev->seg = (uint2*)take(8 * (size_t)g.j.seg * n_grp);
+  }
+  if (peaks & (kPeakBands | kPeakFew)) {
+    ev->surv = (uint4*)take(surv_bytes(g, n_hits, peaks));
+    ev->lists = (peaks & kPeakFew ? 0u : (kLists - 1u) << kListShift) | surv_cap(g, n_hits, peaks);
   }
   if (peaks & kPeakMask) ev->pk_mask = (uint8_t*)take(mask_bytes(g));
   if (peaks == kPeakMask) clear_groups(g, ev);
